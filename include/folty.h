@@ -139,16 +139,14 @@ typedef struct {
  * scratch and one scan.  Batched plans and the server ignore it. */
 #define FOLTY_QUERY_SMALLER_SIDE 2u
 
-/* Query flag: filter in one enumeration pass that writes surviving triangles
- * into per-item slots sized for every static triangle (12 bytes of workspace per
- * triangle; the graph's per-item triangle offsets are made first if missing,
- * one enumeration pass, kept with the graph).  Without it a query counts
- * survivors in one pass and enumerates the items that have any a second time,
- * unless an earlier query on the graph found that second pass re-enumerating
- * half of the items or triangles (a wide window): then queries of at least an
- * eighth of that window filter in one pass by themselves.  Results are
- * identical either way.  Single and vertex queries (plans always use the
- * slots; exists-exists-exists queries follow the graph's switch). */
+/* Query flag: test triangles once.  Without it the filter tests the two known
+ * edges of a closing probe first and the whole triangle after (two passes),
+ * unless an earlier query on the graph kept at least one triangle in 64 (a wide
+ * window): then queries of at least an eighth of that window look every probe up
+ * and test whole triangles only, by themselves.  Results are identical either
+ * way.  The graph's triangles are counted first if they have not been.  Single and
+ * vertex queries (plans always use two passes; exists-exists-exists queries
+ * follow the graph's switch). */
 #define FOLTY_QUERY_ONE_PASS 4u
 
 /* Sizes and timings of a graph's index (folty_graph_stats) or of one query
@@ -167,26 +165,25 @@ typedef struct {
     int64_t max_multiplicity; /* sigma_max: longest list E_{x,y} */
     int64_t peel_rounds;      /* rounds of the min-degree peeling within a level: the levels peel
                                  at once, so this is the most rounds any one level needs */
-    int64_t closing_probes;   /* membership probes of the enumeration: sum over oriented edges
-                                 (u,v) of min(|N+(u)|, |N+(v)|) */
+    int64_t closing_probes;   /* closing probes of the enumeration: sum over oriented edges (u,v)
+                                 of min(|N+(v)|, |members of N+(u) past v|) */
     int64_t enum_items;       /* work items the enumeration is split into */
     int64_t batch_size;       /* server: requests that shared this request's pass */
     /* query only */
-    int64_t tests;            /* temporal tests: sum over (triangle, list E_{a,b} with both
-                                 closing lists non-empty) of |E_{a,b}| */
+    int64_t tests;            /* temporal tests: sum over (triangle the filter kept, list E_{a,b}
+                                 whose closing lists can follow it in time) of |E_{a,b}| */
     int64_t n_pairs;          /* solution pairs */
     int64_t n_certificates;   /* |Sol| */
     double build_ms;          /* device time of folty_build_index */
-    double wedge_ms;          /* device time of the counting enumeration pass alone: wedges,
-                                 closing probes and the time-range filter of each triangle */
-    double temporal_ms;       /* device time of the survivor scans, the emitting pass over the
-                                 items with survivors, and the temporal tests */
+    double wedge_ms;          /* device time of the enumeration alone: wedges, closing probes
+                                 and the time-range filter of each triangle */
+    double temporal_ms;       /* device time of the temporal tests of the kept triangles */
     double threshold_ms;      /* device time of threshold, pair reduction and compaction */
     double query_ms;          /* device time of the whole query */
     double latency_ms;        /* server: submit to result ready on the host */
     double queue_ms;          /* server: submit to start of its pass */
-    int64_t filter_passes;    /* query: enumeration passes of its filter (1, or 2 when the
-                                 survivors are written by a second pass; 0 without items) */
+    int64_t filter_passes;    /* query: passes of its filter (2: known edges, then triangles; 1:
+                                 triangles alone; 0 without closing probes) */
     int64_t core_sweeps;      /* h-index sweeps that settled the core numbers */
 } folty_stats;
 
@@ -233,17 +230,16 @@ int folty_build_index(folty_graph *g, const folty_build_opts *opts);
  * receives a result holding the sorted solution pairs; per-edge counts are
  * fetched on demand by folty_result_counts.
  *
- * The filter of a query normally enumerates the graph's triangles twice: once to
- * count survivors, then again over the work items that have any.  After a query
- * (of any kind) whose second enumeration covered at least half of the items or
- * half of the triangles, the library keeps the per-item triangle offsets (from
- * the counts of its first pass), when 12 bytes per triangle fit in a quarter of
- * the free device memory.  Later queries on the graph whose delta is at least an
- * eighth of that query's then filter in one pass, with 12 bytes per triangle of
- * survivor slots in their workspace (FOLTY_QUERY_ONE_PASS asks for that on any
- * query).  The choice depends only on the graph and the queries run before.
+ * The filter of a query enumerates the graph's triangles once and appends those
+ * that can have a run to chunks in the workspace (12 bytes each).  When the chunks
+ * do not suffice (they start at an eighth of what every triangle would take, at
+ * least 50 MB) they grow to what the pass needed and it is repeated.  After a
+ * query that kept at least one triangle in 64, later queries on the graph whose
+ * delta is at least an eighth of that query's test whole triangles only
+ * (FOLTY_QUERY_ONE_PASS asks for that on any query).  The choice depends only on
+ * the graph and the queries run before.
  *
- * The temporal tests of surviving triangles with up to 64 tests run 64
+ * The temporal tests of the kept triangles with up to 64 tests run 64
  * triangles to a wavefront, one test per lane; a triangle with more is listed
  * and its tests run in pieces of 4, one piece per thread.  The list holds at
  * most 2^22 triangles (16 bytes each; the environment variable FOLTY_MAX_HEAVY

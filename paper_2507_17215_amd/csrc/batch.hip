@@ -9,16 +9,17 @@
 // delta of the job.  theta and the universe only enter the threshold step.
 //
 // One plan runs, whatever the number of queries and graphs:
-//   filter   one grid over the enumeration items of all graphs (wave per
-//            item); up to two jobs of a graph share each enumeration
-//   scan     one exclusive scan over all items' test counts
-//   temporal one persistent grid over all surviving tests of all jobs
+//   filter   one grid over the enumeration items of all graphs (wave per item):
+//            each graph is enumerated once for all its jobs, keeping triangles by
+//            their edges' time ranges at the largest delta
+//   temporal one grid over the chunks of kept triangles: a triangle's records are
+//            read once and tested for each job of its graph; then the pieces of
+//            triangles with many tests
 //   threshold one grid over the edges of all jobs: running sum over the levels
 //            and every query of the job at its level, each edge read once
-//   pairs    one grid over all queries' pair slots
 //   sort     one radix sort of (query, u, v) keys
-// The launches from filter to pairs are captured once in a hipGraph and
-// replayed.  The temporal kernel's chunk size and grid are picked by timing a
+// The launches from filter to threshold are captured once in a hipGraph and
+// replayed.  The temporal kernels' piece size and grid are picked by timing a
 // few candidates on the plan's own work and remembered per workload size.
 #include <algorithm>
 #include <cstring>
@@ -36,19 +37,15 @@ namespace folty {
 namespace {
 
 struct JobDev {
-    // filter and temporal tests
-    const int64_t *tri_base, *ts;
+    // temporal tests
+    const int64_t *ts;
     const EdgeRec *rec;
     int32_t variant;
-    int64_t dq; // range slack of the job's largest delta
+    uint32_t dq; // run slack of the job's largest delta
     const int64_t *lv;
     int32_t nl, nls, m;
     uint32_t *hist;  // hist_words(m, nls) counters, tiled (see hist_at)
     unsigned long long *tmask; // per tile of 64 edges: which edges have a non-zero counter
-    int32_t *sv;
-    int64_t *sw;
-    int32_t *su;
-    int64_t *wu; // this job's slice of the concatenated per-item test counts
     // threshold step: the graph's static edge table and degrees, and the job's
     // queries: positions [q0, q1) of the plan's query list (job order, each job's by level)
     const int32_t *sid, *smid, *slo, *shi, *deg, *tcnt;
@@ -78,107 +75,155 @@ __device__ inline int32_t owner_of(const int64_t *__restrict__ base, int32_t n, 
     return lo;
 }
 
-// up to two jobs (predicate codes) of one graph share one enumeration
+// a graph of the plan and its jobs
 struct GroupDev {
-    const EnumItem *item;
-    const int4 *seg;
-    const int32_t *oadj, *tri;
-    const int64_t *tri_base;
-    const EdgeRec *rec;
+    EnumGraph g;
+    const int32_t *tri; // cached triangles, or null
+    int64_t T;          // their number
     const uint2 *rng;
-    int32_t nj;
-    int32_t job[2];
+    int32_t dq;          // range slack of the jobs' largest delta
+    uint32_t predicates; // the jobs' predicates together
+    int32_t j0, j1;     // its jobs: positions in the plan's list of jobs by graph
 };
 
-// NJ jobs per group: the groups of two come first in the plan's group list,
-// so each instantiation covers one contiguous range of group items
-template <int NJ>
-__global__ __launch_bounds__(BLK) __attribute__((amdgpu_waves_per_eu(4))) void k_multi_filter(const GroupDev *__restrict__ groups, int32_t ngr,
-                                                      const int64_t *__restrict__ group_item_base, int64_t g0,
-                                                      int64_t g1, const JobDev *__restrict__ jobs) {
+// Wavefront per unit: an enumeration item of its group, or 64 cached triangles.
+__global__ __launch_bounds__(BLK) __attribute__((amdgpu_waves_per_eu(4))) void k_multi_filter(
+    const GroupDev *__restrict__ groups, int32_t ngr, const int64_t *__restrict__ unit_base, int64_t units,
+    CandBuf out) {
     __shared__ EnumLds lds[WPB];
     const int w = wave_id();
-    for (int64_t g = g0 + (int64_t)blockIdx.x * WPB + w; g < g1; g += (int64_t)gridDim.x * WPB) {
-        const int32_t gi = owner_of(group_item_base, ngr, g);
-        const GroupDev &G = groups[gi];
-        const int64_t it = g - group_item_base[gi];
-        using Sink = std::conditional_t<NJ == 2, PairFilterSink, FilterSink<-1, FILTER_BOTH> >;
-        Sink sink;
-        sink.base = global_ptr(G.tri_base);
-        sink.rec = global_ptr(G.rec);
-        sink.rng = global_ptr(G.rng);
-        if constexpr (NJ == 2) {
-            for (int jj = 0; jj < 2; jj++) {
-                const JobDev &J = jobs[G.job[jj]];
-                sink.f[jj] = JobFilter{J.dq, J.variant, global_ptr(J.sv), global_ptr(J.sw), global_ptr(J.su),
-                                       global_ptr(J.wu)};
-            }
-        } else {
-            const JobDev &J = jobs[G.job[0]];
-            sink.dq = J.dq;
-            sink.variant = J.variant;
-            sink.sv = global_ptr(J.sv);
-            sink.sw = global_ptr(J.sw);
-            sink.su = global_ptr(J.su);
-            sink.wu = global_ptr(J.wu);
+    FilterSink<-1, FILTER_NARROW> sink{};
+    sink.out = out;
+    int32_t last = -1;
+    EnumGraph E{};
+    const int32_t *tri = nullptr;
+    int64_t T = 0;
+    for (int64_t x = (int64_t)blockIdx.x * WPB + w; x < units; x += (int64_t)gridDim.x * WPB) {
+        const int32_t gi = owner_of(unit_base, ngr, x);
+        if (gi != last) {
+            const GroupDev &G = groups[gi];
+            sink.app.close(out); // a chunk holds triangles of one group
+            sink.app.group = gi;
+            sink.rng = global_ptr(G.rng);
+            sink.dq = G.dq;
+            sink.predicates = G.predicates;
+            E = EnumGraph{global_ptr(G.g.item),  global_ptr(G.g.oadj),  global_ptr(G.g.seg), global_ptr(G.g.srng),
+                          global_ptr(G.g.owner), global_ptr(G.g.ooff), G.g.exact};
+            tri = global_ptr(G.tri);
+            T = G.T;
+            last = gi;
         }
-        const int32_t *tri = global_ptr(G.tri);
-        if (tri) cached_item(sink.base, tri, it, sink);
-        else {
-            const int32_t *oadj = global_ptr(G.oadj);
-            const int4 *seg = global_ptr(G.seg);
-            const EnumItem item = global_ptr(G.item)[it];
-            enum_item(item, stage_ahead(item, oadj, seg), oadj, seg, it, sink, lds[w]);
+        const int64_t it = x - unit_base[gi];
+        if (tri) {
+            cached_triangles(tri, T, it, T, sink); // this unit's 64 alone
+        } else {
+            const EnumItem item = E.item[it];
+            enum_item(item, stage_ahead<true>(item, E), E, it, sink, lds[w]);
         }
     }
+    sink.finish();
 }
 
-__global__ __launch_bounds__(BLK) void k_multi_temporal(const JobDev *__restrict__ jobs, int32_t nj,
-                                                        const int64_t *__restrict__ job_item_base, int64_t items,
-                                                        const int64_t *__restrict__ wbase, int ipt) {
-    const int64_t total = wbase[items];
-    const int64_t nchunks = (total + ipt - 1) / ipt;
-    const int64_t stride = (int64_t)gridDim.x * blockDim.x;
-    for (int64_t c = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; c < nchunks; c += stride) {
-        int64_t k = c * ipt;
-        const int64_t k1 = k + ipt < total ? k + ipt : total;
-        while (k < k1) {
-            const int64_t k_start = k;
-            // the global item whose tests contain k, its job, the survivor
-            int64_t a = 0, b = items;
-            while (a < b) {
-                int64_t mid = (a + b) >> 1;
-                if (wbase[mid + 1] <= k) a = mid + 1;
-                else b = mid;
-            }
-            const int64_t g = a;
-            const int32_t j = owner_of(job_item_base, nj, g);
-            const JobDev &J = jobs[j];
-            const int64_t it = g - job_item_base[j];
-            const int32_t *sv = global_ptr(J.sv);
-            const int64_t *sw = global_ptr(J.sw);
-            int64_t r = k - wbase[g];
-            const int64_t s0 = global_ptr(J.tri_base)[it];
-            const int32_t ns = global_ptr(J.su)[it];
-            if (ns <= 0) break; // cannot happen when the offsets are consistent
-            int32_t lo = 0, hi = ns - 1;
-            while (lo < hi) {
-                int32_t mid = (lo + hi + 1) >> 1;
-                if (sw[s0 + mid] <= r) lo = mid;
-                else hi = mid - 1;
-            }
-            r -= sw[s0 + lo];
-            PoolOp op{global_ptr(J.lv), J.nl, J.nls, global_ptr(J.hist), global_ptr(J.tmask)};
-            const EdgeRec *rec = global_ptr(J.rec);
-            const int64_t *ts = global_ptr(J.ts);
-            for (int32_t s = lo; s < ns && k < k1; s++) {
-                const int64_t p = s0 + s;
-                TriLists L = load_lists(rec, sv[3 * p], sv[3 * p + 1], sv[3 * p + 2]);
-                chunk_runs_rt(J.variant, L, run_slack(J.dq), ts, r, k, k1, op);
-                r = 0;
-            }
-            if (k == k_start) break; // every survivor has tests, so this never triggers
+// a job's tests of one triangle
+struct JobRunner {
+    int32_t variant;
+    uint32_t dq;
+    const int64_t *ts;
+    PoolOp op;
+    using Surv = TriLists;
+    __device__ explicit JobRunner(const JobDev &J)
+        : variant(J.variant), dq(J.dq), ts(global_ptr(J.ts)),
+          op{global_ptr(J.lv), J.nl, J.nls, global_ptr(J.hist), global_ptr(J.tmask)} {}
+    __device__ inline void run(const TriLists &L, int64_t, int64_t r, int64_t k1) {
+        int64_t k = r;
+        chunk_runs_rt(variant, L, dq, ts, r, k, k1, op);
+    }
+};
+
+// The tests of every job on one chunk of kept triangles per wavefront, scheduled
+// as a single query's (k_tests_light).  Heavy entries carry their job above the
+// slot.
+constexpr int HEAVY_JOB = 40; // slots are below 2^40
+__global__ __launch_bounds__(BLK) void k_plan_light(CandBuf B, const GroupDev *__restrict__ groups,
+                                                    const int32_t *__restrict__ gjobs, const JobDev *__restrict__ jobs,
+                                                    Heavy *__restrict__ heavy, unsigned long long *__restrict__ counter,
+                                                    int64_t cap, int piece, unsigned long long *__restrict__ tests) {
+    __shared__ FlatLds<false> flds[WPB];
+    const int w = wave_id();
+    const int lane = lane_id();
+    FlatLds<false> &F = flds[w];
+    __shared__ Chunks C;
+    C.load(B);
+    bool full = false;
+    int64_t mine = 0;
+    for (int32_t g = (int32_t)blockIdx.x * WPB + w; g < C.total; g += (int32_t)gridDim.x * WPB) {
+        const int32_t chunk = __builtin_amdgcn_readfirstlane(C.at(B, g));
+        const GroupDev &G = groups[__builtin_amdgcn_readfirstlane(B.tag[chunk])];
+        const int64_t slot = (int64_t)chunk * 64 + lane;
+        const bool on = lane < B.cnt[chunk];
+        TriLists L{};
+        if (on) L = load_lists(global_ptr(jobs[gjobs[G.j0]].rec), B.sv[3 * slot], B.sv[3 * slot + 1], B.sv[3 * slot + 2]);
+        const Span *sp[6] = {&L.d01, &L.d10, &L.d02, &L.d20, &L.d12, &L.d21};
+#pragma unroll
+        for (int k = 0; k < 6; k++) {
+            F.ls[k][lane] = sp[k]->s;
+            F.ln[k][lane] = sp[k]->n;
         }
+        for (int32_t jj = G.j0; jj < G.j1; jj++) {
+            const int32_t j = __builtin_amdgcn_readfirstlane(gjobs[jj]);
+            JobRunner R(jobs[j]);
+            const uint32_t live = on && edges_meet(L, R.dq) ? tri_live_rt(R.variant, L, R.dq) : 0u;
+            int64_t wk = 0;
+#pragma unroll
+            for (int k = 0; k < 6; k++) wk += (live >> k & 1u) ? sp[k]->n : 0;
+            const int64_t np = wk > LIGHT_TESTS ? (wk + piece - 1) / piece : 0;
+            mine += wk;
+            defer_heavy(R, L, slot | (int64_t)j << HEAVY_JOB, wk, np, heavy, counter, cap, full);
+            const int32_t incl = wave_scan(np ? 0 : (int32_t)wk);
+            const int32_t total = __builtin_amdgcn_readlane(incl, 63);
+            if (total == 0) continue;
+            F.incl[lane] = incl;
+            F.live[lane] = np ? 0u : live;
+            wave_sync();
+            const RunLists ids = run_list_ids(R.variant);
+            for (int32_t t = lane; t < total; t += 64) {
+                int a = 0, b = 63;
+                while (a < b) {
+                    const int mid = (a + b) >> 1;
+                    if (F.incl[mid] > t) b = mid;
+                    else a = mid + 1;
+                }
+                flat_run_rt(F, ids, a, t - (a ? F.incl[a - 1] : 0), R.ts, R.op);
+            }
+            wave_sync(); // the next job or chunk rewrites the LDS
+        }
+    }
+    for (int o = 32; o > 0; o >>= 1) mine += __shfl_xor(mine, o);
+    if (lane == 0 && mine) atomicAdd(tests, (unsigned long long)mine);
+}
+
+__global__ __launch_bounds__(BLK) void k_plan_pieces(CandBuf B, const JobDev *__restrict__ jobs,
+                                                     const Heavy *__restrict__ heavy,
+                                                     const unsigned long long *__restrict__ counter, int64_t cap,
+                                                     int piece) {
+    const unsigned long long c = *counter;
+    const int64_t ne = (int64_t)(c >> HEAVY_SHIFT) < cap ? (int64_t)(c >> HEAVY_SHIFT) : cap;
+    const int64_t np = (int64_t)(c & PIECE_MASK);
+    if (ne <= 0) return;
+    for (int64_t p = (int64_t)blockIdx.x * BLK + threadIdx.x; p < np; p += (int64_t)gridDim.x * BLK) {
+        // the last entry whose first piece is <= p (entry 0 starts at piece 0)
+        int64_t a = 0, b = ne - 1;
+        while (a < b) {
+            const int64_t mid = (a + b + 1) >> 1;
+            if (heavy[mid].first <= p) a = mid;
+            else b = mid - 1;
+        }
+        const Heavy h = heavy[a];
+        const int64_t slot = h.slot & (((int64_t)1 << HEAVY_JOB) - 1);
+        const JobDev &J = jobs[h.slot >> HEAVY_JOB];
+        const int64_t k0 = (p - h.first) * piece;
+        JobRunner R(J);
+        R.run(load_lists(global_ptr(J.rec), B.sv[3 * slot], B.sv[3 * slot + 1], B.sv[3 * slot + 2]), slot, k0, k0 + piece);
     }
 }
 
@@ -421,19 +466,20 @@ struct Plan {
     };
     std::vector<Job> jobs;
     std::vector<int32_t> qjob, qlevel;
-    std::vector<int64_t> job_item_base, job_w_base, group_item_base;
-    int32_t ngroups = 0, npairs = 0; // groups; the first npairs hold two jobs
-    int64_t gitems = 0;
-    int64_t items = 0, total_w = 0, rec_cap = 0;
+    std::vector<int64_t> job_w_base, unit_base;
+    int32_t ngroups = 0;
+    int64_t items = 0, units = 0, total_w = 0, rec_cap = 0; // items: over the jobs; units: over the groups
     int nbits = 0;
+    CandBuf cand{};
+    int64_t chunks = 0, heavy_cap = 1;
     // device memory
-    DevBuf d_jobs, d_job_item_base, d_job_w_base, d_queries, d_groups, d_group_item_base;
-    std::vector<DevBuf> hist, tmask, lv, sv, sw, su;
+    DevBuf d_jobs, d_job_w_base, d_queries, d_groups, d_gjobs, d_unit_base;
+    std::vector<DevBuf> hist, tmask, lv;
+    DevBuf sv, svn, tag, heavy, scal;
     bool dirty = true; // some histogram may hold counts (fresh, tuned, or a run did not finish)
-    DevBuf wu, wbase, nrec, keys, vals, keys2, vals2, cub;
-    size_t scan_bytes = 0;
+    DevBuf nrec, keys, vals, keys2, vals2;
     // launch shape and capture
-    int ipt = 1, tblocks = 4096;
+    int ipt = 4, tblocks = 8192; // tests per piece, blocks of the temporal kernel
     bool tuned = false;
     int tune_source = 0; // 0: default shape, 1: timed by this plan, 2: from the tuning table
     bool eager = false; // capture refused: launch directly
@@ -458,23 +504,22 @@ Plan::~Plan() {
         hist.clear();
         tmask.clear();
         lv.clear();
-        sv.clear();
-        sw.clear();
-        su.clear();
+        sv.release();
+        svn.release();
+        tag.release();
+        heavy.release();
+        scal.release();
         d_jobs.release();
-        d_job_item_base.release();
         d_groups.release();
-        d_group_item_base.release();
+        d_gjobs.release();
+        d_unit_base.release();
         d_job_w_base.release();
         d_queries.release();
-        wu.release();
-        wbase.release();
         nrec.release();
         keys.release();
         vals.release();
         keys2.release();
         vals2.release();
-        cub.release();
         (void)hipStreamSynchronize(stream);
         dev_forget_stream(stream);
         (void)hipStreamDestroy(stream);
@@ -492,35 +537,35 @@ static void clear_hist(Plan &P, int j, hipStream_t s) {
     FOLTY_LAUNCHED();
 }
 
+// the tests of the kept triangles: pieces of ipt tests, up to `blocks` blocks
+static void enqueue_tests(Plan &P, int ipt, int blocks, hipStream_t s) {
+    if (P.chunks <= 0) return;
+    unsigned long long *scal = P.scal.as<unsigned long long>();
+    const unsigned lb = (unsigned)std::max<int64_t>(1, std::min<int64_t>((P.chunks + WPB - 1) / WPB, blocks));
+    k_plan_light<<<lb, BLK, 0, s>>>(P.cand, P.d_groups.as<GroupDev>(), P.d_gjobs.as<int32_t>(), P.d_jobs.as<JobDev>(),
+                                    P.heavy.as<Heavy>(), scal + SCAL_HEAVY, P.heavy_cap, ipt, scal + SCAL_TESTS);
+    const unsigned pb = (unsigned)std::max<int64_t>(1, std::min<int64_t>(P.chunks * 16, PIECE_BLOCKS));
+    k_plan_pieces<<<pb, BLK, 0, s>>>(P.cand, P.d_jobs.as<JobDev>(), P.heavy.as<Heavy>(), scal + SCAL_HEAVY,
+                                     P.heavy_cap, ipt);
+    FOLTY_LAUNCHED();
+}
+
 static void enqueue_compute(Plan &P, hipStream_t s) {
     const int nj = (int)P.jobs.size();
     // clear what accumulates: the histograms of jobs whose threshold step does
-    // not leave them cleared, the record count, the test total
+    // not leave them cleared, the record count, the scalars
     for (int j = 0; j < nj; j++)
         if (!P.jobs[j].reset) clear_hist(P, j, s);
     k_fill<int32_t><<<1, 1, 0, s>>>(P.nrec.as<int32_t>(), 0, 1);
-    k_fill<int64_t><<<1, 1, 0, s>>>(P.wu.as<int64_t>() + P.items, (int64_t)0, 1);
+    k_fill<unsigned long long><<<1, BLK, 0, s>>>(P.scal.as<unsigned long long>(), 0ull, SCAL_WORDS);
     FOLTY_LAUNCHED();
-    // groups of two jobs, then groups of one
-    const int64_t gsplit = P.group_item_base[P.npairs];
-    if (gsplit > 0) {
-        unsigned g = (unsigned)std::max<int64_t>(1, std::min<int64_t>((gsplit + WPB - 1) / WPB, ENUM_BLOCKS));
-        k_multi_filter<2><<<g, BLK, 0, s>>>(P.d_groups.as<GroupDev>(), P.ngroups, P.d_group_item_base.as<int64_t>(),
-                                            0, gsplit, P.d_jobs.as<JobDev>());
+    if (P.units > 0) {
+        const unsigned g = (unsigned)std::max<int64_t>(1, std::min<int64_t>((P.units + WPB - 1) / WPB, ENUM_BLOCKS));
+        k_multi_filter<<<g, BLK, 0, s>>>(P.d_groups.as<GroupDev>(), P.ngroups, P.d_unit_base.as<int64_t>(), P.units,
+                                         P.cand);
         FOLTY_LAUNCHED();
     }
-    if (P.gitems > gsplit) {
-        unsigned g = (unsigned)std::max<int64_t>(1, std::min<int64_t>((P.gitems - gsplit + WPB - 1) / WPB, ENUM_BLOCKS));
-        k_multi_filter<1><<<g, BLK, 0, s>>>(P.d_groups.as<GroupDev>(), P.ngroups, P.d_group_item_base.as<int64_t>(),
-                                            gsplit, P.gitems, P.d_jobs.as<JobDev>());
-        FOLTY_LAUNCHED();
-    }
-    exclusive_scan_i64(P.cub.p, P.scan_bytes, P.wu.as<int64_t>(), P.wbase.as<int64_t>(), P.items + 1, s);
-    if (P.items > 0) {
-        k_multi_temporal<<<P.tblocks, BLK, 0, s>>>(P.d_jobs.as<JobDev>(), nj, P.d_job_item_base.as<int64_t>(), P.items,
-                                                   P.wbase.as<int64_t>(), P.ipt);
-        FOLTY_LAUNCHED();
-    }
+    enqueue_tests(P, P.ipt, P.tblocks, s);
     if (P.total_w > 0) {
         k_job_threshold<<<grid_for(P.total_w, BLK, 8192), BLK, 0, s>>>(
             P.d_jobs.as<JobDev>(), nj, P.d_job_w_base.as<int64_t>(), P.total_w, P.d_queries.as<QueryDev>(),
@@ -536,7 +581,7 @@ static void tune(Plan &P) {
     const int nj = (int)P.jobs.size();
     hipStream_t s = P.stream;
     int64_t tests = 0;
-    FOLTY_HIP(hipMemcpyAsync(&tests, P.wbase.as<int64_t>() + P.items, 8, hipMemcpyDeviceToHost, s));
+    FOLTY_HIP(hipMemcpyAsync(&tests, P.scal.as<int64_t>() + SCAL_TESTS, 8, hipMemcpyDeviceToHost, s));
     FOLTY_HIP(hipStreamSynchronize(s));
     P.last_tests = tests;
     const std::pair<int, int> bucket{log2_ceil(tests), log2_ceil(P.total_w)};
@@ -557,17 +602,17 @@ static void tune(Plan &P) {
         P.tuned = true;
         return;
     }
-    const int ipts[] = {1, 2, 4, 8, 16};
-    const int blocks[] = {1024, 2048, 4096, 8192};
+    const int ipts[] = {2, 4, 8, 16};
+    const int blocks[] = {2048, 4096, 8192, 16384};
     double best = 1e30;
     int bi = P.ipt, bb = P.tblocks;
     for (int ip : ipts)
         for (int bl : blocks) {
             for (int j = 0; j < nj; j++) clear_hist(P, j, s);
+            k_fill<unsigned long long><<<1, BLK, 0, s>>>(P.scal.as<unsigned long long>() + SCAL_TESTS, 0ull,
+                                                         SCAL_HEAVY + 1 - SCAL_TESTS); // the filter's chunks stay
             FOLTY_HIP(hipEventRecord(P.ev[1], s));
-            k_multi_temporal<<<bl, BLK, 0, s>>>(P.d_jobs.as<JobDev>(), nj, P.d_job_item_base.as<int64_t>(), P.items,
-                                                P.wbase.as<int64_t>(), ip);
-            FOLTY_LAUNCHED();
+            enqueue_tests(P, ip, bl, s);
             FOLTY_HIP(hipEventRecord(P.ev[2], s));
             FOLTY_HIP(hipEventSynchronize(P.ev[2]));
             double ms = ev_ms2(P.ev[1], P.ev[2]);
@@ -588,10 +633,15 @@ static void tune(Plan &P) {
 }
 
 // Device bytes plan_create and plan_run take for these queries on one graph
-// (the buffers of each job, one per predicate code: window histogram, touched
-// mask, survivor slots; the certificate records of every query, their sorted
+// (the buffers of each job, one per predicate code: window histogram and touched
+// mask; the chunks of kept triangles; the certificate records of every query, their sorted
 // copies and the sort's scratch; per-edge counts handed back), so that a
 // server can admit a batch by what its plan will hold.
+static int64_t plan_chunks(const Index &ix, int64_t T) {
+    return most_chunks(T, std::min<int64_t>((int64_t)ENUM_BLOCKS * WPB, std::max<int64_t>(ix.NI, (T + 63) / 64))) +
+           MAX_REGIONS;
+}
+
 int64_t plan_footprint(const Graph *g, const folty_query *qs, int nq) {
     const Index &ix = g->ix;
     std::map<int, std::vector<int64_t>> lv; // predicate code -> windows
@@ -607,15 +657,14 @@ int64_t plan_footprint(const Graph *g, const folty_query *qs, int nq) {
         std::sort(d.begin(), d.end());
         d.erase(std::unique(d.begin(), d.end()), d.end());
         b += 4 * hist_words(ix.m, padded_levels(d.size())) + 8 * ((int64_t)ix.m / 64 + 1) + 8 * (int64_t)d.size();
-        b += 20 * T + 4 * (int64_t)ix.NI + 16 * ((int64_t)ix.NI + 1);
     }
-    // library scratch: the scan over the jobs' items and the sort of up to
-    // 2 S certificate records per query (sizes only)
-    const int64_t items = (int64_t)lv.size() * ((int64_t)ix.NI + 1);
+    // the chunks of kept triangles (all jobs share them) and the heavy list
+    const int64_t chunks = plan_chunks(ix, T);
+    b += (CHUNK_BYTES + 4) * chunks + (int64_t)sizeof(Heavy) * heavy_slots(64 * chunks) + (int64_t)SCAL_BYTES;
+    // library scratch: the sort of up to 2 S certificate records per query (sizes only)
     const int64_t recs = std::min<int64_t>((int64_t)nq * 2 * (int64_t)ix.S, INT32_MAX); // the sort's limit
     const int kb = bit_length((uint64_t)std::max(1, nq)) + 2 * bit_length((uint64_t)ix.n);
-    b += (int64_t)std::max(exclusive_scan_i64(nullptr, 0, nullptr, nullptr, items + 1, nullptr),
-                           sort_pairs_u64_u32(nullptr, 0, nullptr, nullptr, nullptr, nullptr, recs, kb, nullptr));
+    b += (int64_t)sort_pairs_u64_u32(nullptr, 0, nullptr, nullptr, nullptr, nullptr, recs, kb, nullptr);
     return b + (1 << 20);
 }
 
@@ -638,8 +687,8 @@ Plan *plan_create(Graph *const *gs, int ng, const folty_query *qs, const int32_t
     for (auto &e : P->ev) FOLTY_HIP(hipEventCreate(&e));
     hipStream_t s = P->stream;
     StreamScope sc(s);
-    // the graphs' own streams may still hold work; the one-pass filter writes
-    // survivors into per-item triangle slots
+    // the graphs' own streams may still hold work; the triangles bound the
+    // filter's output
     for (int i = 0; i < ng; i++) {
         FOLTY_HIP(hipStreamSynchronize(gs[i]->stream));
         ensure_triangles(gs[i]);
@@ -681,18 +730,13 @@ Plan *plan_create(Graph *const *gs, int ng, const folty_query *qs, const int32_t
     P->hist.resize(nj);
     P->tmask.resize(nj);
     P->lv.resize(nj);
-    P->sv.resize(nj);
-    P->sw.resize(nj);
-    P->su.resize(nj);
     std::vector<JobDev> jd(nj);
-    P->job_item_base.assign(nj + 1, 0);
     P->job_w_base.assign(nj + 1, 0);
     for (int j = 0; j < nj; j++) {
-        P->job_item_base[j + 1] = P->job_item_base[j] + P->graphs[P->jobs[j].graph]->ix.NI;
+        P->items += P->graphs[P->jobs[j].graph]->ix.NI;
         // each job's edges start on a wavefront boundary
         P->job_w_base[j + 1] = P->job_w_base[j] + (((int64_t)P->graphs[P->jobs[j].graph]->ix.m + 63) & ~63ll);
     }
-    P->items = P->job_item_base[nj];
     P->total_w = P->job_w_base[nj];
     // the plan's queries grouped by job, each job's by level
     std::vector<int32_t> jq(nq);
@@ -705,8 +749,6 @@ Plan *plan_create(Graph *const *gs, int ng, const folty_query *qs, const int32_t
     std::vector<int32_t> jq0(nj, 0), jq1(nj, 0);
     for (int i = nq - 1; i >= 0; i--) jq0[P->qjob[jq[i]]] = i;
     for (int i = 0; i < nq; i++) jq1[P->qjob[jq[i]]] = i + 1;
-    P->wu.ensure(8 * ((size_t)P->items + 1));
-    P->wbase.ensure(8 * ((size_t)P->items + 1));
     for (int j = 0; j < nj; j++) {
         const Index &ix = P->graphs[P->jobs[j].graph]->ix;
         const auto &lvs = P->jobs[j].levels;
@@ -714,25 +756,17 @@ Plan *plan_create(Graph *const *gs, int ng, const folty_query *qs, const int32_t
         P->tmask[j].ensure(8 * (((size_t)ix.m + 63) / 64) + 8);
         P->lv[j].ensure(8 * lvs.size());
         FOLTY_HIP(hipMemcpyAsync(P->lv[j].p, lvs.data(), 8 * lvs.size(), hipMemcpyHostToDevice, s));
-        P->sv[j].ensure(12 * (size_t)ix.T + 12);
-        P->sw[j].ensure(8 * (size_t)ix.T + 8);
-        P->su[j].ensure(4 * (size_t)ix.NI + 4);
         JobDev &d = jd[j];
-        d.tri_base = ix.tri_base.as<int64_t>();
         d.ts = ix.ts.as<int64_t>();
         d.rec = ix.rec.as<EdgeRec>();
         d.variant = P->jobs[j].variant;
-        d.dq = range_slack(lvs.back(), ix.tshift);
+        d.dq = run_slack(range_slack(lvs.back(), ix.tshift));
         d.lv = P->lv[j].as<int64_t>();
         d.nl = (int32_t)lvs.size();
         d.nls = padded_levels(lvs.size());
         d.m = ix.m;
         d.hist = P->hist[j].as<uint32_t>();
         d.tmask = P->tmask[j].as<unsigned long long>();
-        d.sv = P->sv[j].as<int32_t>();
-        d.sw = P->sw[j].as<int64_t>();
-        d.su = P->su[j].as<int32_t>();
-        d.wu = P->wu.as<int64_t>() + P->job_item_base[j];
         d.sid = ix.sid.as<int32_t>();
         d.smid = ix.smid.as<int32_t>();
         d.slo = ix.slo.as<int32_t>();
@@ -749,40 +783,56 @@ Plan *plan_create(Graph *const *gs, int ng, const folty_query *qs, const int32_t
         d.reset = !d.keep_prefix && !oneshot;
         P->jobs[j].reset = d.reset != 0;
     }
-    // groups: the jobs of each graph, two at a time, share one enumeration
-    std::vector<GroupDev> gd, singles;
+    // groups: a graph with its jobs, which share one enumeration
+    std::vector<GroupDev> gd;
+    std::vector<int32_t> gjobs;
+    P->unit_base.assign(1, 0);
     for (int gi = 0; gi < ng; gi++) {
-        std::vector<int> js;
-        for (int j = 0; j < nj; j++)
-            if (P->jobs[j].graph == gi) js.push_back(j);
-        for (size_t k = 0; k < js.size(); k += 2) {
-            const Index &ix = P->graphs[gi]->ix;
-            GroupDev G{};
-            G.item = ix.item.as<EnumItem>();
-            G.seg = ix.seg.as<int4>();
-            G.oadj = ix.oadj.as<int32_t>();
-            G.tri = ix.tri_cached ? ix.tri.as<int32_t>() : nullptr;
-            G.tri_base = ix.tri_base.as<int64_t>();
-            G.rec = ix.rec.as<EdgeRec>();
-            G.rng = ix.erng.as<uint2>();
-            G.nj = k + 1 < js.size() ? 2 : 1;
-            G.job[0] = js[k];
-            G.job[1] = G.nj == 2 ? js[k + 1] : js[k];
-            (G.nj == 2 ? gd : singles).push_back(G);
+        const Index &ix = P->graphs[gi]->ix;
+        GroupDev G{};
+        G.j0 = (int32_t)gjobs.size();
+        int64_t dmax = 0;
+        for (int j = 0; j < nj; j++) {
+            if (P->jobs[j].graph != gi) continue;
+            gjobs.push_back(j);
+            dmax = std::max(dmax, P->jobs[j].levels.back());
+            G.predicates |= 1u << P->jobs[j].variant;
         }
+        G.j1 = (int32_t)gjobs.size();
+        const int64_t T = ix.T.load();
+        if (G.j0 == G.j1 || ix.NI == 0 || T == 0) continue; // no query, or nothing to find
+        G.g = enum_graph(ix);
+        G.tri = ix.tri_cached ? ix.tri.as<int32_t>() : nullptr;
+        G.T = T;
+        G.rng = ix.erng.as<uint2>();
+        G.dq = rng_slack(dmax, ix.rshift);
+        gd.push_back(G);
+        P->unit_base.push_back(P->unit_base.back() + (G.tri ? (T + 63) / 64 : ix.NI));
+        P->chunks += plan_chunks(ix, T);
     }
-    P->npairs = (int32_t)gd.size();
-    gd.insert(gd.end(), singles.begin(), singles.end());
     P->ngroups = (int32_t)gd.size();
-    P->group_item_base.assign(gd.size() + 1, 0);
-    for (size_t k = 0; k < gd.size(); k++)
-        P->group_item_base[k + 1] = P->group_item_base[k] + P->graphs[P->jobs[gd[k].job[0]].graph]->ix.NI;
-    P->gitems = P->group_item_base[gd.size()];
+    P->units = P->unit_base.back();
+    P->heavy_cap = heavy_slots(64 * P->chunks);
+    // every triangle of every graph fits, so nothing is ever dropped
+    P->cand.regions = MAX_REGIONS;
+    P->cand.per_region = (int32_t)((P->chunks + MAX_REGIONS - 1) / MAX_REGIONS);
+    const size_t total = (size_t)MAX_REGIONS * (size_t)P->cand.per_region;
+    P->sv.ensure((CHUNK_BYTES - 4) * total);
+    P->svn.ensure(4 * total);
+    P->tag.ensure(4 * total);
+    P->heavy.ensure(sizeof(Heavy) * (size_t)P->heavy_cap);
+    P->scal.ensure(SCAL_BYTES);
+    P->cand.sv = P->sv.as<int32_t>();
+    P->cand.cnt = P->svn.as<int32_t>();
+    P->cand.tag = P->tag.as<int32_t>();
+    P->cand.ctr = reinterpret_cast<uint32_t *>(P->scal.as<unsigned long long>() + SCAL_REGIONS);
+    P->cand.dropped = reinterpret_cast<uint32_t *>(P->scal.as<unsigned long long>() + SCAL_DROPPED);
     P->d_groups.ensure(sizeof(GroupDev) * std::max<size_t>(1, gd.size()));
-    P->d_group_item_base.ensure(8 * (gd.size() + 1));
+    P->d_gjobs.ensure(4 * std::max<size_t>(1, gjobs.size()));
+    P->d_unit_base.ensure(8 * P->unit_base.size());
     if (!gd.empty()) FOLTY_HIP(hipMemcpyAsync(P->d_groups.p, gd.data(), sizeof(GroupDev) * gd.size(), hipMemcpyHostToDevice, s));
-    FOLTY_HIP(hipMemcpyAsync(P->d_group_item_base.p, P->group_item_base.data(), 8 * (gd.size() + 1),
-                             hipMemcpyHostToDevice, s));
+    if (!gjobs.empty()) FOLTY_HIP(hipMemcpyAsync(P->d_gjobs.p, gjobs.data(), 4 * gjobs.size(), hipMemcpyHostToDevice, s));
+    FOLTY_HIP(hipMemcpyAsync(P->d_unit_base.p, P->unit_base.data(), 8 * P->unit_base.size(), hipMemcpyHostToDevice, s));
     // queries, in job order
     std::vector<QueryDev> qd(nq);
     int64_t cap = 0;
@@ -809,11 +859,9 @@ Plan *plan_create(Graph *const *gs, int ng, const folty_query *qs, const int32_t
     if (bit_length((uint64_t)std::max(1, nq)) + 2 * P->nbits > 64)
         fail(FOLTY_EOVERFLOW, "too many queries for one plan at this graph size");
     P->d_jobs.ensure(sizeof(JobDev) * (size_t)std::max(1, nj));
-    P->d_job_item_base.ensure(8 * ((size_t)nj + 1));
     P->d_job_w_base.ensure(8 * ((size_t)nj + 1));
     P->d_queries.ensure(sizeof(QueryDev) * (size_t)std::max(1, nq));
     if (nj) FOLTY_HIP(hipMemcpyAsync(P->d_jobs.p, jd.data(), sizeof(JobDev) * nj, hipMemcpyHostToDevice, s));
-    FOLTY_HIP(hipMemcpyAsync(P->d_job_item_base.p, P->job_item_base.data(), 8 * (nj + 1), hipMemcpyHostToDevice, s));
     FOLTY_HIP(hipMemcpyAsync(P->d_job_w_base.p, P->job_w_base.data(), 8 * (nj + 1), hipMemcpyHostToDevice, s));
     if (nq) {
         FOLTY_HIP(hipMemcpyAsync(P->d_queries.p, qd.data(), sizeof(QueryDev) * nq, hipMemcpyHostToDevice, s));
@@ -821,8 +869,6 @@ Plan *plan_create(Graph *const *gs, int ng, const folty_query *qs, const int32_t
     P->nrec.ensure(4);
     P->keys.ensure(8 * (size_t)P->rec_cap + 8);
     P->vals.ensure(4 * (size_t)P->rec_cap + 4);
-    P->scan_bytes = exclusive_scan_i64(nullptr, 0, P->wu.as<int64_t>(), P->wbase.as<int64_t>(), P->items + 1, s);
-    P->cub.ensure(P->scan_bytes);
     FOLTY_HIP(hipStreamSynchronize(s));
     return P.release();
 }
@@ -939,7 +985,7 @@ void plan_run(Plan *P, Result **outs) {
         Result *r = res[q].get();
         const Graph *g = P->graphs[P->qgraph[q]];
         fill_stats_from_index(g->ix, &r->stats);
-        r->stats.filter_passes = 1; // plans filter once, into per-item triangle slots
+        r->stats.filter_passes = 1; // plans enumerate once for all their queries
         r->stats.n_pairs = (int64_t)r->u.size();
         r->stats.n_certificates = r->n_certificates;
         r->stats.query_ms = P->last_ms / std::max(1, nq);

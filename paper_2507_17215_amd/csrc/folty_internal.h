@@ -57,6 +57,7 @@ void dev_free(void *p, size_t bytes);
 size_t dev_trim();   // give every cached block back to the driver; returns bytes
 size_t dev_trim_to(size_t keep); // give back cached blocks, largest first, until at most keep bytes stay
 size_t dev_cached(); // bytes held in the cache
+int64_t arena_left(); // bytes the thread's ArenaScope has left, or -1 without one
 void dev_forget_stream(hipStream_t s); // call before destroying a stream blocks were freed on
 // pinned host blocks for large result arrays (alloc.hip); host_alloc returns
 // nullptr when pinned memory is not available, host_free false for a pointer
@@ -180,21 +181,19 @@ struct PinnedBuf {
 // oriented edge is the static edge's lo endpoint.  rec[p] describes oriented
 // edge p: both of its directed lists with their first and last timestamps.
 // Triangle enumeration: every triangle u < v < x (orientation order) is found
-// from its lowest edge (u, v) by probing the members x of one endpoint's out-row
-// for membership in the other's.  The edge is owned by the endpoint with the
-// longer out-row, which is staged in LDS; the shorter row is scanned ("probe
-// segment"):
-//   mode A, |N+(v)| <= |N+(u)|: owner u, segment = row of v (x in N+(v)),
-//   mode B, |N+(u)| <  |N+(v)|: owner v, segment = row of u (x in N+(u)).
-// seg[j] = (row start, row length, oriented edge (u, v) | mode B << 31, owner),
-// grouped by owner and mode.  Items are runs of at most ITEM_SEGS segments and
-// about CHUNK probes of one owner; the triangles found by item it occupy slots
-// [tri_base[it], tri_base[it+1]).
+// from its lowest edge (u, v) by probing candidates x > v of one endpoint's
+// out-row for membership in the other's ("probe segment"):
+//   mode A: owner u, segment = the row of v;
+//   mode B: owner v, segment = the row of u past v,
+// whichever is shorter.  Edges whose shorter side is empty have no segment.
+// seg[j] = (segment start, length, oriented edge (u, v) | mode B << 31, 0), grouped
+// by owner; srng[j] = the edge's ranges.  Items are runs of at most ITEM_SEGS segments and about CHUNK
+// probes of one owner, or of several owners with few probes each ("loose", d < 0).
 // ---------------------------------------------------------------------------
 struct alignas(32) EnumItem {
-    int32_t g0, ng; // segments [g0, g0 + ng) of the owner
-    int32_t nq;     // probes: the total length of those segments' rows
-    int32_t b, d;   // the owner's out-row: start and length
+    int32_t g0, ng; // segments [g0, g0 + ng)
+    int32_t nq;     // probes: the segments' total length
+    int32_t b, d;   // the owner's out-row: start and length (d = -1: loose)
     int32_t pad[3];
 };
 
@@ -216,6 +215,31 @@ struct alignas(32) EdgeRec {
 };
 static_assert(sizeof(EdgeRec) == 32, "two records per cache line");
 
+// The triangles a filter keeps (tri_device.h)
+constexpr int CAND_STRIDE = 32; // words between two regions' counters
+constexpr int MAX_REGIONS = 32;
+// A query's scalars (64-bit words of Workspace::scal), cleared together at its start
+enum : int {
+    SCAL_THRESHOLD = 0, // [4] the threshold step's
+    SCAL_TRIAD = 4,     // [3] the exists-exists-exists totals: triangles, overflow, solutions
+    SCAL_TESTS = 8,     // temporal tests
+    SCAL_KEPT = 9,      // triangles the filter's first pass kept
+    SCAL_HITS = 10,     // triangles seen
+    SCAL_HEAVY = 11,    // heavy triangles and pieces
+    SCAL_DROPPED = 12,  // chunks dropped (32 bits)
+    SCAL_REGIONS = 16,  // chunks taken, per region (32 bits each, CAND_STRIDE words of 32 bits apart)
+    SCAL_WORDS = SCAL_REGIONS + MAX_REGIONS * CAND_STRIDE / 2
+};
+constexpr size_t SCAL_BYTES = 8 * (size_t)SCAL_WORDS;
+struct CandBuf {
+    int32_t *sv;       // 3 x 64 per chunk
+    int32_t *cnt;      // slots filled, per chunk
+    int32_t *tag;      // plans: the group of each chunk's triangles (else null)
+    uint32_t *ctr;     // chunks taken, per region
+    uint32_t *dropped; // chunks there was no room for
+    int32_t regions, per_region;
+};
+
 struct Index {
     int32_t n = 0;
     int64_t m_input = 0;
@@ -229,10 +253,15 @@ struct Index {
     // T are final, so a reader that loads it (acquire) sees them
     std::atomic<bool> tri_base_ready{false};
     // single queries of delta >= this filter in one pass (INT64_MAX: none, until
-    // a query's second filter pass re-enumerated half of the items or triangles)
+    // a query kept one triangle in 64)
     std::atomic<int64_t> one_pass_from{INT64_MAX};
+    bool one_pass_at(int64_t delta) const {
+        const int64_t from = one_pass_from.load(std::memory_order_relaxed);
+        return from != INT64_MAX && delta >= from;
+    }
     int64_t W = 0;           // oriented wedges: sum of C(|N+(x)|, 2)
-    int64_t probes = 0;      // closing probes the enumeration makes: sum over (u,v) of |N+(v)|
+    int64_t probes = 0;      // closing probes the enumeration makes: the segments' total length
+    int32_t G = 0;           // probe segments
     int32_t NI = 0;          // enumeration items
     int32_t max_core = 0;
     int32_t max_out = 0;
@@ -244,6 +273,7 @@ struct Index {
     bool tcnt_ready = false;
     double build_ms = 0;
     int32_t tshift = 0; // timestamps >> tshift fit 32 bits (0 for t < 2^32)
+    int32_t rshift = 0; // timestamps >> rshift fit 14 bits (the ranges in erng)
 
     DevBuf ts;       // int64[m]
     DevBuf perm;     // int32[m]  input position of each sorted edge
@@ -260,9 +290,12 @@ struct Index {
     DevBuf oadj;     // int32[S]  heads (new ids)
     DevBuf oeid;     // uint32[S] static edge id | direction bit
     DevBuf rec;      // EdgeRec[S]
-    DevBuf erng;     // uint2[S]  first and last timestamp >> tshift over both lists of each oriented edge
+    DevBuf erng;     // uint2[S]  first and last timestamp >> rshift of each oriented edge's two lists
+                     //           (tri_device.h, ranges)
     DevBuf otail;    // int32[S]  tail of each oriented edge (new id; released after the build)
-    DevBuf seg;      // int4[S]   probe segments grouped by owner (see EnumItem)
+    DevBuf seg;      // int4[G]   probe segments grouped by owner (see EnumItem)
+    DevBuf srng;     // uint2[G]  the ranges of each probe segment's edge
+    DevBuf owner;    // int32[G]  the owner of each probe segment
     DevBuf item;     // EnumItem[NI]
     DevBuf tri_base; // int64[NI+1]
     DevBuf tcnt;     // int32[S]  triangles on each static edge = |N(lo) & N(hi)| (computed on first use)
@@ -274,21 +307,11 @@ struct Index {
 // per-query scratch; one per concurrent caller
 struct Workspace {
     DevBuf count;   // uint32[m]
-    DevBuf sv;      // int32[3 x slots] surviving triangles (oriented edges), in their item's slots
-    DevBuf su;      // int32[NI]   survivors per item
-    DevBuf wu;      // int64[NI+1] tests per item
-    DevBuf wbase;   // int64[NI+1] exclusive offsets of wu
-    DevBuf sbase;   // int64[NI+1] exclusive offsets of su: the dense index of each item's first survivor
-    DevBuf tri_it;  // int32[NI+1] triangles per item, from the last counting filter pass
-    DevBuf pieces;  // Heavy[]     the temporal step's survivors with many tests
-    DevBuf gitem;   // int32[]     per group of 64 survivors, the item of its first (sparse slots)
-    const int64_t *slots = nullptr; // first slot of each item's survivors in sv: sbase (dense) or the index's tri_base
-    bool emit_timed = false;        // the last filter's second pass is bracketed by ev[6], ev[7]
-    bool counted_items = false;     // tri_it holds every item's triangles (a counting pass ran)
-    const Index *tri_it_of = nullptr; // the index that counting pass enumerated
-    int32_t emit_items = 0;         // items the last filter's second pass enumerated again
-    int64_t emit_triangles = 0;     // triangles those items hold
-    int32_t filter_passes = 0;      // enumeration passes of the last filter
+    DevBuf sv;      // int32[3 x 64] per chunk: the triangles the filter kept, as oriented edges
+    DevBuf svn;     // int32[] slots filled of each chunk
+    DevBuf pieces;  // Heavy[]     the temporal step's triangles with many tests
+    int64_t kept_chunks = 0;        // chunks the last filter took, or an upper bound
+    int32_t filter_passes = 0;      // passes of the last filter over its triangles
     DevBuf ncert;   // uint32[2S]
     DevBuf pairs_k; // uint64[2S]
     DevBuf pairs_v; // uint32[2S]
@@ -296,7 +319,6 @@ struct Workspace {
     DevBuf pairs_v2;
     DevBuf scal;    // small device scalars
     DevBuf cub;     // library scan/sort temporaries
-    DevBuf ilist;   // int32[NI] items with survivors
     DevBuf vtmp;    // vertex queries: per-vertex counts, flags, offsets, output
     DevBuf diff;    // int32[2m+1] interval marks of the smaller-side evaluation and their prefix sum
     DevBuf tflag;   // exists-exists-exists: uint32[(survivor slots + 3) / 4] solution bits
@@ -378,17 +400,8 @@ Result *run_query(Graph *g, const folty_query &q, Workspace &ws);
 Result *run_query_on(Graph *g, const folty_query &q, Workspace &ws, hipStream_t stream);
 Result *run_vertex_query(Graph *g, const folty_vertex_query &q, Workspace &ws);
 Result *run_triad_query(Graph *g, const folty_triad_query &q, Workspace &ws);
-// The time-range filter of one query (query.hip): surviving triangles in their
-// slots (ws.slots), tests per item and their offsets (ws.wbase).  Returns the
-// number of survivor slots; *tests is the test count, or -1 when the one-pass
-// filter left it on the device.  e0, e1 bracket the counting pass.  ss: a run
-// has min(|L1|, |L2|) tests (the smaller-side evaluation), else |L1|.
-// one_pass: write survivors into the per-item triangle slots in one pass (when
-// the index has them), else count first and emit the items with survivors.
-int64_t find_survivors(const Index &ix, int variant, int64_t dmax, Workspace &ws, hipStream_t s, hipEvent_t e0,
-                       hipEvent_t e1, int64_t *tri, int64_t *tests, bool ss, bool one_pass);
 // whether query q on g filters in one pass; with FOLTY_QUERY_ONE_PASS the
-// per-item triangle offsets are made first if missing
+// triangles are counted first if they have not been
 bool use_one_pass(Graph *g, const folty_query &q);
 double ev_ms(hipEvent_t a, hipEvent_t b);
 // The single query with its outputs in the caller's device memory: the sorted
@@ -428,11 +441,6 @@ void server_destroy(Server *s);
 void index_triangles(Index &ix, bool cache, DevBuf &cub, hipStream_t s);
 void ensure_tri_base(Index &ix, hipStream_t s); // caller holds Graph::lazy_mu once the graph is shared
 void ensure_triangles(Graph *g);                 // ensure_tri_base on the graph's stream, under lazy_mu
-// after a two-pass filter whose second pass enumerated half of the items or of
-// the triangles again (a wide window), make the per-item triangle offsets (from
-// the counting pass's per-item triangles) so later wide queries filter in one pass
-void maybe_one_pass(Graph *g, const Workspace &ws, int64_t delta);
-
 // library-primitive wrappers (rocPRIM), all on `stream`
 size_t sort_pairs_u64_i32(void *tmp, size_t tmp_bytes, const uint64_t *kin, uint64_t *kout,
                           const int32_t *vin, int32_t *vout, int64_t n, int end_bit,

@@ -706,6 +706,8 @@ void build_index(Graph *g, const folty_build_opts *opts) {
     }
     // ---- oriented-edge records and triangles per lowest vertex ------------------------
     ix.tshift = std::max(0, bit_length((uint64_t)g->tmax) - 32);
+    ix.rshift = std::max(0, bit_length((uint64_t)g->tmax) - 14); // RNG_BITS
+    ix.one_pass_from.store(INT64_MAX, std::memory_order_relaxed);
     index_triangles(ix, o.cache_triangles != 0, cub, s);
     FOLTY_HIP(hipEventRecord(e1, s));
     FOLTY_HIP(hipStreamSynchronize(s));
@@ -715,7 +717,7 @@ void build_index(Graph *g, const folty_build_opts *opts) {
 
 size_t Index::device_bytes() const {
     const DevBuf *b[] = {&ts, &perm, &sid, &soff, &smid, &slo, &shi, &deg, &core, &rank,
-                         &outdeg, &ooff, &oadj, &oeid, &rec, &erng, &item, &seg, &tri_base, &tcnt, &tri};
+                         &outdeg, &ooff, &oadj, &oeid, &rec, &erng, &item, &seg, &srng, &owner, &tri_base, &tcnt, &tri};
     size_t t = 0;
     for (auto *x : b) t += x->bytes;
     return t;

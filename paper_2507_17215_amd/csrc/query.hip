@@ -2,10 +2,10 @@
 //
 //  a.5  wedge enumeration + closing probe (paper, Algorithm OutNeighbours:
 //       (u, v) in G->_pi and w in N+(u), test whether v and w are adjacent).
-//       One wavefront per vertex u stages N+(u) in LDS, walks the wedges
-//       u -> v -> x for every v in N+(u) and x in N+(v) with coalesced reads of
-//       N+(v), and probes x in the staged N+(u).  Each static triangle is found
-//       once, from its lowest-ranked vertex, as three oriented edges.
+//       Each oriented edge (u, v) probes the shorter of N+(v) and the part of
+//       N+(u) past v for membership in the other's row, which its wavefront holds
+//       as a hash table in LDS.  Each static triangle is found once, from its
+//       lowest-ranked vertex, as three oriented edges.
 //  a.6  temporal tests (paper, Theorems 3.1 and 3.2): a temporal edge e on list
 //       L1 forms a delta-temporal triangle with the third vertex w iff, with
 //       t2 = the first entry of L2 at or after t(e) and t3 = the first entry of
@@ -56,7 +56,8 @@ __global__ void k_static_recs(const int32_t *__restrict__ soff, const int32_t *_
 // Oriented edge p (static edge e, tail lo when bit 31 of its id is set): one
 // 32-byte read of e's record, lists swapped when the tail is hi.
 __global__ void k_edge_recs(const uint32_t *__restrict__ oeid, const EdgeRec *__restrict__ srec, int32_t S,
-                            EdgeRec *__restrict__ rec, uint2 *__restrict__ erng) {
+                            int32_t tshift, int32_t rshift, EdgeRec *__restrict__ rec,
+                            uint2 *__restrict__ erng) {
     int64_t p = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (p >= S) return;
     const uint32_t id = oeid[p];
@@ -67,91 +68,123 @@ __global__ void k_edge_recs(const uint32_t *__restrict__ oeid, const EdgeRec *__
         r.bs = q.fs, r.bn = q.fn, r.blo = q.flo, r.bhi = q.fhi;
     }
     rec[p] = r;
-    // a static edge has at least one temporal edge, so one of the lists is non-empty
-    uint32_t lo = r.fn ? r.flo : r.blo, hi = r.fn ? r.fhi : r.bhi;
-    if (r.fn && r.bn) {
-        lo = r.blo < lo ? r.blo : lo;
-        hi = r.bhi > hi ? r.bhi : hi;
-    }
-    erng[p] = make_uint2(lo, hi);
+    // the record's timestamps are shifted by tshift (<= rshift) already
+    const int32_t d = rshift - tshift;
+    erng[p] = make_uint2(r.fn ? rng_pack(r.flo >> d, r.fhi >> d) : RNG_EMPTY,
+                         r.bn ? rng_pack(r.blo >> d, r.bhi >> d) : RNG_EMPTY);
 }
 
-// Probe segments: the oriented edge (u, v) at position p goes to the endpoint
-// with the longer out-row (mode A: u, scanning v's row; mode B: v, scanning
-// u's row).  Sort key: owner * 2 + mode.
+// Probe segments: for the oriented edge (u, v) at position p, the candidates
+// x > v are the entries of N+(v), or those of N+(u) past p; the shorter list is
+// the segment (mode A or B), and the other row's vertex owns it.  Sort key: the
+// owner; an edge with an empty side closes no triangle and gets key n, past all
+// owners.
 __global__ void k_seg_keys(const int32_t *__restrict__ ooff, const int32_t *__restrict__ oadj,
-                           const int32_t *__restrict__ otail, int32_t S, uint32_t *__restrict__ key,
-                           int32_t *__restrict__ val) {
+                           const int32_t *__restrict__ otail, int32_t S, int32_t n, uint32_t *__restrict__ key,
+                           uint32_t *__restrict__ val) {
     int64_t p = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (p >= S) return;
     const int32_t u = otail[p], v = oadj[p];
-    const int32_t du = ooff[u + 1] - ooff[u], dv = ooff[v + 1] - ooff[v];
-    const bool mode_b = du < dv;
-    key[p] = ((uint32_t)(mode_b ? v : u) << 1) | (mode_b ? 1u : 0u);
-    val[p] = (int32_t)p;
+    const int32_t past = ooff[u + 1] - 1 - (int32_t)p, dv = ooff[v + 1] - ooff[v];
+    const bool mode_b = past < dv;
+    key[p] = past == 0 || dv == 0 ? (uint32_t)n : (uint32_t)(mode_b ? v : u);
+    val[p] = (uint32_t)p | (mode_b ? MODE_B : 0u);
 }
 
-// first sorted position of each key 0 .. 2n
-__global__ void k_part_off(const uint32_t *__restrict__ key, int32_t S, int64_t nk, int32_t *__restrict__ off) {
-    int64_t x = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (x > nk) return;
-    int32_t a = 0, b = S;
-    while (a < b) {
-        int32_t mid = (int32_t)(((int64_t)a + b) >> 1);
-        if ((int64_t)key[mid] < x) a = mid + 1;
-        else b = mid;
-    }
-    off[x] = a;
-}
-
-// seg[j] = (row start, row length, oriented edge | mode B << 31, owner)
-__global__ void k_seg_recs(const uint32_t *__restrict__ key, const int32_t *__restrict__ val,
+// seg[j] = (segment start, length, oriented edge | mode B << 31, 0), with its ranges;
+// run[w] = the owner's first segment and the one past its last (owners without
+// segments are not written and never read); *ng = segments
+__global__ void k_seg_recs(const uint32_t *__restrict__ key, const uint32_t *__restrict__ val,
                            const int32_t *__restrict__ ooff, const int32_t *__restrict__ oadj,
-                           const int32_t *__restrict__ otail, int32_t S, int4 *__restrict__ seg,
-                           int32_t *__restrict__ len) {
+                           const int32_t *__restrict__ otail, const uint2 *__restrict__ erng, int32_t S, int32_t n,
+                           int4 *__restrict__ seg, uint2 *__restrict__ srng, int32_t *__restrict__ owner, int32_t *__restrict__ len, int2 *__restrict__ run, int32_t *__restrict__ ng) {
     int64_t j = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (j >= S) return;
-    const int32_t p = val[j];
-    const bool mode_b = key[j] & 1u;
-    const int32_t r = mode_b ? otail[p] : oadj[p]; // the vertex whose row is scanned
-    const int32_t rs = ooff[r], rl = ooff[r + 1] - rs;
-    seg[j] = make_int4(rs, rl, (int32_t)((uint32_t)p | (mode_b ? MODE_B : 0u)), (int32_t)(key[j] >> 1));
-    len[j] = rl;
+    const uint32_t k = key[j];
+    const bool first = j == 0 || key[j - 1] != k;
+    if (k == (uint32_t)n) {
+        if (first) *ng = (int32_t)j;
+        len[j] = 0;
+        return;
+    }
+    const uint32_t id = val[j];
+    const int32_t p = (int32_t)(id & ~MODE_B);
+    int32_t rs, re;
+    if (id & MODE_B) {
+        rs = p + 1;
+        re = ooff[otail[p] + 1];
+    } else {
+        const int32_t v = oadj[p];
+        rs = ooff[v];
+        re = ooff[v + 1];
+    }
+    seg[j] = make_int4(rs, re - rs, (int32_t)id, 0);
+    srng[j] = erng[p];
+    owner[j] = (int32_t)k;
+    len[j] = re - rs;
+    if (first) run[k].x = (int32_t)j;
+    if (j == S - 1 || key[j + 1] != k) {
+        run[k].y = (int32_t)j + 1;
+        if (j == S - 1) *ng = S;
+    }
 }
 
-// An item starts at the first segment of each (owner, mode) run and wherever
-// the run's probe count crosses a multiple of CHUNK or its segment count a
-// multiple of ITEM_SEGS (both indices only grow, so runs of equal value are
-// contiguous).
+// Owners with fewer than LOOSE_PROBES probes share items (their rows are searched
+// in global memory, so a wavefront's 64 lanes are filled across owners); the
+// others have items of their own.
+constexpr int64_t LOOSE_PROBES = 128;
+constexpr int64_t LOOSE_CHUNK = 1024;
+static_assert(LOOSE_CHUNK + LOOSE_PROBES <= CHUNK + CAP, "a loose item's probes fit the marks");
+
+// An item starts at the first segment of each owner with items of its own and
+// of each run of loose owners, and wherever the run's probe count crosses a
+// multiple of CHUNK or its segment count a multiple of ITEM_SEGS (loose runs: the
+// global counts, and LOOSE_CHUNK); both indices only grow, so segments of equal
+// value are contiguous.
 __global__ void k_item_flags(const uint32_t *__restrict__ key, const int64_t *__restrict__ P,
-                             const int32_t *__restrict__ part_off, int32_t S, int32_t *__restrict__ flag) {
+                             const int2 *__restrict__ run, int32_t G, int32_t *__restrict__ flag) {
     int64_t j = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (j >= S) return;
-    const int32_t p0 = part_off[key[j]];
-    const int64_t cj = (P[j] - P[p0]) / CHUNK + (j - p0) / ITEM_SEGS;
-    int f = j == p0;
-    if (!f) f = cj != (P[j - 1] - P[p0]) / CHUNK + (j - 1 - p0) / ITEM_SEGS;
+    if (j >= G) return;
+    const int2 r = run[key[j]];
+    const int64_t Pj = P[j], P0 = P[r.x];
+    const bool loose = P[r.y] - P0 < LOOSE_PROBES;
+    int f = j == 0;
+    if (j > 0) {
+        const int64_t Pp = P[j - 1];
+        if (loose) {
+            f = Pj / LOOSE_CHUNK != Pp / LOOSE_CHUNK || j % ITEM_SEGS == 0;
+            if (!f && j == r.x) {
+                const int2 rp = run[key[j - 1]];
+                f = P[rp.y] - P[rp.x] >= LOOSE_PROBES;
+            }
+        } else {
+            f = j == r.x ||
+                (Pj - P0) / CHUNK + (j - r.x) / ITEM_SEGS != (Pp - P0) / CHUNK + (j - 1 - r.x) / ITEM_SEGS;
+        }
+    }
     flag[j] = f;
 }
 
-__global__ void k_item_starts(const int32_t *__restrict__ flag, const int32_t *__restrict__ fid, int32_t S,
+__global__ void k_item_starts(const int32_t *__restrict__ flag, const int32_t *__restrict__ fid, int32_t G,
                               int32_t *__restrict__ start) {
     int64_t j = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (j < S && flag[j]) start[fid[j] - 1] = (int32_t)j;
+    if (j < G && flag[j]) start[fid[j] - 1] = (int32_t)j;
 }
 
-__global__ void k_items(const int32_t *__restrict__ start, const int4 *__restrict__ seg, const int64_t *__restrict__ P,
-                        const int32_t *__restrict__ ooff, int32_t NI, EnumItem *__restrict__ items) {
+__global__ void k_items(const int32_t *__restrict__ start, const int32_t *__restrict__ owner, const int64_t *__restrict__ P,
+                        const int2 *__restrict__ run, const int32_t *__restrict__ ooff, int32_t NI,
+                        EnumItem *__restrict__ items) {
     int64_t it = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (it >= NI) return;
     const int32_t g0 = start[it], g1 = start[it + 1];
-    const int32_t w = seg[g0].w;
+    const int32_t w = owner[g0];
+    const int2 r = run[w];
     EnumItem e{};
     e.g0 = g0;
     e.ng = g1 - g0;
     e.nq = (int32_t)(P[g1] - P[g0]);
     e.b = ooff[w];
-    e.d = ooff[w + 1] - e.b;
+    e.d = P[r.y] - P[r.x] < LOOSE_PROBES ? -1 : ooff[w + 1] - e.b;
     items[it] = e;
 }
 
@@ -316,166 +349,152 @@ unsigned enum_grid(int32_t n) {
     return (unsigned)std::max<int64_t>(1, std::min<int64_t>(g, ENUM_BLOCKS));
 }
 
-// a.5 for one predicate code and window bound, in two passes over the
-// enumeration items.  The counting pass keeps, per item, how many triangles
-// survive the time-range filter and how many tests they carry, and counts all
-// triangles; exclusive scans give each item its first survivor slot (ws.sbase)
-// and its first test (ws.wbase, total at [NI]); the emitting pass then
-// enumerates only the items that have survivors and writes them.  When the
-// index already holds per-item triangle offsets (after a plan, a server
-// submission or a stats call) one pass writes survivors into those slots
-// instead.  e0 and e1 bracket the (first) enumeration launch alone, so its
-// duration is measured on the stream it runs on.  Returns the number of
-// survivors (an upper bound in the one-pass case); *tri gets the triangle count.
-// the items with at least one survivor (any order: each item writes its own
-// slots), and the triangles those items hold
-__global__ void k_item_list(const int32_t *__restrict__ su, const int32_t *__restrict__ tri_it, int32_t NI,
-                            int32_t *__restrict__ list, int32_t *__restrict__ nlist,
-                            unsigned long long *__restrict__ tri_listed) {
-    const int64_t it = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    const bool take = it < NI && su[it] > 0;
-    const int32_t slot = wave_append(nlist, take);
-    if (take) list[slot] = (int32_t)it;
-    const int64_t t = wave_inclusive_sum((int64_t)(take ? tri_it[it] : 0));
-    if (lane_id() == 63 && t > 0) atomicAdd(tri_listed, (unsigned long long)t);
+// clears per-edge counts, per-pair counts and the query's scalars in one launch
+__global__ __launch_bounds__(BLK) void k_query_clear(uint32_t *__restrict__ count, int64_t m,
+                                                     uint32_t *__restrict__ ncert, int64_t np,
+                                                     unsigned long long *__restrict__ scal) {
+    const int64_t i0 = (int64_t)blockIdx.x * BLK + threadIdx.x, stride = (int64_t)gridDim.x * BLK;
+    uint4 *c4 = reinterpret_cast<uint4 *>(count), *n4 = reinterpret_cast<uint4 *>(ncert);
+    const uint4 zero = make_uint4(0, 0, 0, 0);
+    for (int64_t i = i0; i < (m + 3) / 4; i += stride) c4[i] = zero;
+    for (int64_t i = i0; i < (np + 3) / 4; i += stride) n4[i] = zero;
+    for (int64_t i = i0; i < SCAL_WORDS; i += stride) scal[i] = 0;
 }
 
 } // namespace
+
+// makes the workspace's scalars, and per-edge and per-pair counts if asked for,
+// and clears them
+void clear_query(const Index &ix, Workspace &ws, bool counts, hipStream_t s) {
+    ws.scal.ensure(SCAL_BYTES);
+    ws.host.ensure(SCAL_BYTES);
+    int64_t m = 0, np = 0;
+    if (counts) {
+        m = ix.m;
+        np = 2 * (int64_t)ix.S;
+        ws.count.ensure(4 * (size_t)m + 16);
+        ws.ncert.ensure(4 * (size_t)np + 16);
+    }
+    const int64_t n4 = std::max<int64_t>((std::max(m, np) + 3) / 4, SCAL_WORDS);
+    k_query_clear<<<grid_for(n4, BLK, 8192), BLK, 0, s>>>(ws.count.as<uint32_t>(), m, ws.ncert.as<uint32_t>(), np,
+                                                          ws.scal.as<unsigned long long>());
+    FOLTY_LAUNCHED();
+}
+
+// the query's scalars into ws.host; read them after the stream is synchronised
+void read_scalars(Workspace &ws, hipStream_t s) {
+    FOLTY_HIP(hipMemcpyAsync(ws.host.p, ws.scal.p, SCAL_BYTES, hipMemcpyDeviceToHost, s));
+}
+
+int64_t chunks_taken(const Workspace &ws, const CandBuf &B) {
+    const uint32_t *c = reinterpret_cast<const uint32_t *>(ws.host.as<unsigned long long>() + SCAL_REGIONS);
+    int64_t k = 0;
+    for (int r = 0; r < B.regions; r++) k += std::min<int64_t>(c[r * CAND_STRIDE], B.per_region);
+    return k;
+}
 
 namespace {
-template <bool SS>
-int64_t find_survivors_t(const Index &ix, int variant, int64_t dmax, Workspace &ws, hipStream_t s, hipEvent_t e0,
-                         hipEvent_t e1, int64_t *tri, int64_t *tests, bool one_pass) {
-    *tests = -1; // known on the host only after the two-pass filter
-    ws.emit_timed = false;
-    ws.emit_items = 0;
-    ws.emit_triangles = 0;
-    ws.counted_items = false;
-    ws.filter_passes = 1;
-    const int32_t NI = ix.NI;
-    ws.su.ensure(4 * ((size_t)NI + 1));
-    ws.tri_it.ensure(4 * ((size_t)NI + 1));
-    ws.wu.ensure(8 * ((size_t)NI + 1));
-    ws.wbase.ensure(8 * ((size_t)NI + 1));
-    ws.sbase.ensure(8 * ((size_t)NI + 1));
-    ws.scal.ensure(128);
-    ws.host.ensure(64);
-    unsigned long long *hits = ws.scal.as<unsigned long long>() + 8; // [0, 8) belong to the threshold step
-    k_fill<unsigned long long><<<1, 1, 0, s>>>(hits, 0ull, 1);
-    FOLTY_LAUNCHED();
-    auto sink_for = [&](auto V, auto M) {
-        FilterSink<decltype(V)::value, decltype(M)::value, SS> sink{};
-        sink.base = ws.sbase.as<int64_t>();
-        sink.rec = ix.rec.as<EdgeRec>();
-        sink.rng = ix.erng.as<uint2>();
-        sink.dq = range_slack(dmax, ix.tshift);
-        sink.variant = variant;
-        sink.sv = ws.sv.as<int32_t>();
-        sink.sw = nullptr; // the temporal step finds each survivor's tests itself
-        sink.su = ws.su.as<int32_t>();
-        sink.wu = ws.wu.as<int64_t>();
-        sink.hits = hits;
-        sink.tri_it = ws.tri_it.as<int32_t>();
-        return sink;
-    };
-    // all items, or the nlist items of list
-    auto run = [&](auto V, auto M, const int32_t *list, int32_t nlist) {
-        auto sink = sink_for(V, M);
-        const unsigned g = enum_grid(list ? nlist : NI);
-        if (ix.tri_cached)
-            k_filter_cached<<<g, BLK, 0, s>>>(ix.tri_base.as<int64_t>(), ix.tri.as<int32_t>(), NI, sink, list, nlist);
-        else
-            k_tri_enum<<<g, BLK, 0, s>>>(ix.item.as<EnumItem>(), ix.oadj.as<int32_t>(), ix.seg.as<int4>(), NI, sink,
-                                         list, nlist);
-        FOLTY_LAUNCHED();
-    };
-    using CountM = std::integral_constant<int, FILTER_COUNT>;
-    using EmitM = std::integral_constant<int, FILTER_EMIT>;
-    using BothM = std::integral_constant<int, FILTER_BOTH>;
-    if (one_pass && ix.tri_base_ready.load(std::memory_order_acquire)) {
-        // per-item triangle offsets exist: one pass writes survivors into them
-        ws.sv.ensure(12 * ((size_t)ix.T + 1));
-        FOLTY_HIP(hipEventRecord(e0, s));
-        dispatch_variant(variant, [&](auto V) {
-            auto sink = sink_for(V, BothM{});
-            sink.base = ix.tri_base.as<int64_t>();
-            if (ix.tri_cached)
-                k_filter_cached<<<enum_grid(NI), BLK, 0, s>>>(ix.tri_base.as<int64_t>(), ix.tri.as<int32_t>(), NI,
-                                                              sink);
-            else
-                k_tri_enum<<<enum_grid(NI), BLK, 0, s>>>(ix.item.as<EnumItem>(), ix.oadj.as<int32_t>(),
-                                                         ix.seg.as<int4>(), NI, sink);
-            FOLTY_LAUNCHED();
-        });
-        FOLTY_HIP(hipEventRecord(e1, s));
-        // su[NI] = wu[NI] = 0 so that the exclusive scans leave the totals at [NI]
-        k_fill<int32_t><<<1, 1, 0, s>>>(ws.su.as<int32_t>() + NI, 0, 1);
-        k_fill<int64_t><<<1, 1, 0, s>>>(ws.wu.as<int64_t>() + NI, (int64_t)0, 1);
-        FOLTY_LAUNCHED();
-        size_t need = std::max(
-            exclusive_scan_i64(nullptr, 0, ws.wu.as<int64_t>(), ws.wbase.as<int64_t>(), (int64_t)NI + 1, s),
-            exclusive_scan_i32_to_i64(nullptr, 0, ws.su.as<int32_t>(), ws.sbase.as<int64_t>(), (int64_t)NI + 1, s));
-        ws.cub.ensure(need);
-        exclusive_scan_i64(ws.cub.p, need, ws.wu.as<int64_t>(), ws.wbase.as<int64_t>(), (int64_t)NI + 1, s);
-        exclusive_scan_i32_to_i64(ws.cub.p, need, ws.su.as<int32_t>(), ws.sbase.as<int64_t>(), (int64_t)NI + 1, s);
-        *tri = ix.T;
-        ws.slots = ix.tri_base.as<int64_t>();
-        return ix.T; // an upper bound: the temporal step reads the exact count
-    }
-    ws.slots = ws.sbase.as<int64_t>();
-    FOLTY_HIP(hipEventRecord(e0, s));
-    dispatch_variant(variant, [&](auto V) { run(V, CountM{}, nullptr, 0); });
-    FOLTY_HIP(hipEventRecord(e1, s));
-    // su[NI] = wu[NI] = 0 so that the exclusive scans leave the totals at [NI]
-    k_fill<int32_t><<<1, 1, 0, s>>>(ws.su.as<int32_t>() + NI, 0, 1);
-    k_fill<int64_t><<<1, 1, 0, s>>>(ws.wu.as<int64_t>() + NI, (int64_t)0, 1);
-    FOLTY_LAUNCHED();
-    size_t need = std::max(
-        exclusive_scan_i64(nullptr, 0, ws.wu.as<int64_t>(), ws.wbase.as<int64_t>(), (int64_t)NI + 1, s),
-        exclusive_scan_i32_to_i64(nullptr, 0, ws.su.as<int32_t>(), ws.sbase.as<int64_t>(), (int64_t)NI + 1, s));
-    ws.cub.ensure(need);
-    exclusive_scan_i64(ws.cub.p, need, ws.wu.as<int64_t>(), ws.wbase.as<int64_t>(), (int64_t)NI + 1, s);
-    exclusive_scan_i32_to_i64(ws.cub.p, need, ws.su.as<int32_t>(), ws.sbase.as<int64_t>(), (int64_t)NI + 1, s);
-    // the items with survivors, for the emitting pass
-    ws.ilist.ensure(4 * ((size_t)NI + 1));
-    unsigned long long *sc = ws.scal.as<unsigned long long>();
-    int32_t *nlist = reinterpret_cast<int32_t *>(sc + 9);
-    k_fill<unsigned long long><<<1, 2, 0, s>>>(sc + 9, 0ull, 2); // nlist, triangles of the listed items
-    k_item_list<<<grid_for(NI, BLK), BLK, 0, s>>>(ws.su.as<int32_t>(), ws.tri_it.as<int32_t>(), NI,
-                                                 ws.ilist.as<int32_t>(), nlist, sc + 10);
-    FOLTY_LAUNCHED();
-    int64_t *h = ws.host.as<int64_t>();
-    h[3] = 0;
-    FOLTY_HIP(hipMemcpyAsync(h, ws.sbase.as<int64_t>() + NI, 8, hipMemcpyDeviceToHost, s));
-    FOLTY_HIP(hipMemcpyAsync(h + 3, nlist, 4, hipMemcpyDeviceToHost, s));
-    FOLTY_HIP(hipMemcpyAsync(h + 1, hits, 8, hipMemcpyDeviceToHost, s));
-    FOLTY_HIP(hipMemcpyAsync(h + 2, ws.wbase.as<int64_t>() + NI, 8, hipMemcpyDeviceToHost, s));
-    FOLTY_HIP(hipMemcpyAsync(h + 4, sc + 10, 8, hipMemcpyDeviceToHost, s));
-    FOLTY_HIP(hipStreamSynchronize(s));
-    const int64_t survivors = h[0];
-    *tri = h[1];
-    *tests = h[2];
-    ws.counted_items = true; // tri_it holds every item's triangles
-    ws.tri_it_of = &ix;
-    if (survivors > 0) {
-        ws.sv.ensure(12 * (size_t)survivors);
-        const int32_t nl = (int32_t)h[3];
-        FOLTY_HIP(hipEventRecord(ws.ev[6], s));
-        dispatch_variant(variant, [&](auto V) { run(V, EmitM{}, ws.ilist.as<int32_t>(), nl); });
-        FOLTY_HIP(hipEventRecord(ws.ev[7], s));
-        ws.emit_timed = true;
-        ws.emit_items = nl;
-        ws.emit_triangles = h[4];
-        ws.filter_passes = 2;
-    }
-    return survivors;
+
+// Up to this many chunks (50 MB) are allocated whatever the window keeps, so that
+// no pass has to be repeated and the host reads nothing back in between.
+constexpr int64_t SAFE_CHUNKS = 1 << 16;
+constexpr unsigned ARENA_ENUM_BLOCKS = 1024; // with a fixed scratch: fewer partly filled chunks
+// and room for at least this many bytes per vertex, so that which graphs fit the
+// scratch does not hang on how many triangles a window keeps
+constexpr int64_t ARENA_VERTEX_BYTES = 20;
+
+// chunks allocated at first for a graph of at most `triangles` triangles
+int64_t first_chunks(int64_t triangles, int64_t waves) {
+    const int64_t most = most_chunks(triangles, waves);
+    return most <= SAFE_CHUNKS ? most : std::max<int64_t>(SAFE_CHUNKS, most / 8);
 }
+
 } // namespace
 
-int64_t find_survivors(const Index &ix, int variant, int64_t dmax, Workspace &ws, hipStream_t s, hipEvent_t e0,
-                       hipEvent_t e1, int64_t *tri, int64_t *tests, bool ss, bool one_pass) {
-    return ss ? find_survivors_t<true>(ix, variant, dmax, ws, s, e0, e1, tri, tests, one_pass)
-              : find_survivors_t<false>(ix, variant, dmax, ws, s, e0, e1, tri, tests, one_pass);
+// a.5 for one predicate code and window bound: one pass over the enumeration
+// items (or the cached triangles) appends the triangles it keeps to the
+// workspace's chunks.  The first pass over an index also counts its triangles.
+// When the chunks do not suffice, they grow to what the pass would have needed
+// and it is repeated.  The scalars have been cleared.
+CandBuf filter_triangles(Index &ix, int variant, int64_t dmax, Workspace &ws, hipStream_t s, bool one_pass) {
+    const int64_t arena = arena_left();
+    int64_t T = ix.T.load();
+    const bool cached = ix.tri_cached;
+    const int64_t units = cached ? (T + 63) / 64 : ix.NI;
+    unsigned grid = enum_grid((int32_t)std::min<int64_t>(units, INT32_MAX));
+    if (arena >= 0) grid = std::min(grid, ARENA_ENUM_BLOCKS);
+    const int64_t waves = std::min<int64_t>((int64_t)grid * WPB, units);
+    const int64_t most = most_chunks(T >= 0 ? T : ix.probes, waves);
+    int64_t chunks = first_chunks(T >= 0 ? T : ix.probes, waves);
+    if (arena < 0) chunks = std::min<int64_t>(most, std::max<int64_t>(chunks, (int64_t)ws.sv.bytes / (CHUNK_BYTES - 4)));
+    else if (chunks * CHUNK_BYTES > arena / 4) chunks = 0; // counted first, then made to fit
+    CandBuf B{};
+    for (;;) {
+        const bool sure = chunks >= most;
+        B.regions = (int32_t)std::min<unsigned>(MAX_REGIONS, grid);
+        B.per_region = (int32_t)((chunks + B.regions - 1) / B.regions);
+        const size_t total = (size_t)B.regions * (size_t)B.per_region;
+        ws.sv.ensure((CHUNK_BYTES - 4) * total);
+        ws.svn.ensure(4 * total);
+        unsigned long long *scal = ws.scal.as<unsigned long long>();
+        B.sv = ws.sv.as<int32_t>();
+        B.cnt = ws.svn.as<int32_t>();
+        B.ctr = reinterpret_cast<uint32_t *>(scal + SCAL_REGIONS);
+        B.dropped = reinterpret_cast<uint32_t *>(scal + SCAL_DROPPED);
+        auto run = [&](auto V, auto M) {
+            FilterSink<decltype(V)::value, decltype(M)::value> sink{};
+            sink.rng = ix.erng.as<uint2>();
+            sink.dq = rng_slack(dmax, ix.rshift);
+            sink.out = B;
+            sink.hits = scal + SCAL_HITS;
+            if (cached) k_filter_cached<<<grid, BLK, 0, s>>>(ix.tri.as<int32_t>(), T, sink);
+            else
+                k_tri_enum<<<grid, BLK, 0, s>>>(enum_graph(ix), ix.NI, sink);
+            FOLTY_LAUNCHED();
+        };
+        dispatch_variant(variant, [&](auto V) {
+            if (T < 0) run(V, std::integral_constant<FilterMode, FILTER_COUNT>{});
+            else if (one_pass) run(V, std::integral_constant<FilterMode, FILTER_WIDE>{});
+            else run(V, std::integral_constant<FilterMode, FILTER_NARROW>{});
+        });
+        ws.kept_chunks = (int64_t)total;
+        if (sure) return B;
+        read_scalars(ws, s);
+        FOLTY_HIP(hipStreamSynchronize(s));
+        const unsigned long long *h = ws.host.as<unsigned long long>();
+        const int64_t taken = chunks_taken(ws, B);
+        const uint32_t dropped = (uint32_t)h[SCAL_DROPPED];
+        ws.kept_chunks = taken;
+        if (dropped == 0) return B;
+        if (T < 0) {
+            T = (int64_t)h[SCAL_HITS];
+            ix.T = T;
+        }
+        chunks = taken + (int64_t)dropped;
+        if (arena >= 0) chunks = std::max<int64_t>(chunks, ARENA_VERTEX_BYTES * (int64_t)ix.n / CHUNK_BYTES);
+        k_fill<unsigned long long><<<1, BLK, 0, s>>>(scal + SCAL_DROPPED, 0ull, SCAL_WORDS - SCAL_DROPPED);
+        FOLTY_LAUNCHED();
+    }
+}
+
+// After the query's scalars are on the host: the number of triangles on the first
+// query, the filter's passes, and the switch to one pass for later queries.
+// By default the filter tests a probe's two known edges first and the whole
+// triangle after (two passes).  When a window keeps at least one triangle in 64,
+// the first test drops little, and later queries of about that window or wider
+// (from an eighth of it) look every probe up and test triangles once.  70M edges,
+// filter time with two passes and one: 1 hour 1.3 and 3.8 ms (none kept), 4 weeks
+// 3.3 and 3.8 ms (1 in 5,000), 1 year 4.6 and 4.4 ms (1 in 36); 10M edges of the
+// medium graph, 4 weeks 0.25 and 0.24 ms (1 in 190), 1 year 0.34 and 0.32 ms.
+// The rule depends only on the graph and the queries, never on timing.
+void after_filter(Index &ix, Workspace &ws, int64_t delta, bool one_pass) {
+    const unsigned long long *h = ws.host.as<unsigned long long>();
+    if (ix.T.load() < 0) ix.T = (int64_t)h[SCAL_HITS];
+    const int64_t kept = (int64_t)h[SCAL_KEPT];
+    ws.filter_passes = one_pass ? 1 : 2;
+    if (!one_pass && kept > 0 && 64 * kept >= ix.T.load() &&
+        delta / 8 < ix.one_pass_from.load(std::memory_order_relaxed))
+        ix.one_pass_from.store(delta / 8, std::memory_order_relaxed);
 }
 
 bool use_one_pass(Graph *g, const folty_query &q) {
@@ -483,21 +502,21 @@ bool use_one_pass(Graph *g, const folty_query &q) {
         ensure_triangles(g);
         return true;
     }
-    return q.delta >= g->ix.one_pass_from.load(std::memory_order_relaxed);
+    return g->ix.one_pass_at(q.delta);
 }
 
 namespace {
 
 // per-edge counts of the survivors' runs (a.6)
 template <class Op, bool SS = false>
-void launch_temporal(const Index &ix, int variant, int64_t dmax, Workspace &ws, const Op &op, int64_t tests,
-                     int64_t survivors, hipStream_t s) {
+void launch_temporal(const Index &ix, int variant, int64_t dmax, Workspace &ws, const CandBuf &B, const Op &op,
+                     hipStream_t s) {
     const uint32_t dq = run_slack(range_slack(dmax, ix.tshift));
     dispatch_variant(variant, [&](auto V) {
-        launch_tests(ix, ws,
+        launch_tests(ws, B,
                      CountRunner<decltype(V)::value, Op, SS>{dq, ix.ts.as<int64_t>(), op, ws.sv.as<int32_t>(),
                                                              ix.rec.as<EdgeRec>()},
-                     survivors, tests, s);
+                     ws.kept_chunks, s);
     });
 }
 
@@ -573,7 +592,8 @@ void finish_vertex(const Graph *g, const folty_vertex_query &vq, Workspace &ws, 
 
 // any: qualify edges with count >= 1 (the inner exists of a vertex query)
 // Threshold step: certificates, per-pair certificate counts and the compacted
-// pair keys (unsorted, in ws).  Returns |Sol| and the number of pairs.
+// pair keys (unsorted, in ws), then the query's scalars to the host.  Returns
+// |Sol| and the number of pairs.
 struct PairCounts {
     int64_t ncerts;
     int32_t npairs;
@@ -583,14 +603,6 @@ PairCounts threshold_pairs(const Graph *g, const folty_query &q, const uint32_t 
                            hipStream_t s, bool any) {
     const Index &ix = g->ix;
     const int32_t S = ix.S, m = ix.m;
-    ws.ncert.ensure(8 * (size_t)S + 8);
-    ws.scal.ensure(64);
-    k_fill<unsigned long long><<<1, 8, 0, s>>>(ws.scal.as<unsigned long long>(), 0ull, 8);
-    if (S > 0) {
-        k_fill<uint32_t><<<grid_for(2 * (int64_t)S, BLK), BLK, 0, s>>>(ws.ncert.as<uint32_t>(), 0u,
-                                                                               2 * (int64_t)S);
-    }
-    FOLTY_LAUNCHED();
     unsigned long long *total = ws.scal.as<unsigned long long>();
     int32_t *np = ws.scal.as<int32_t>() + 4;
     if (m > 0) {
@@ -622,8 +634,7 @@ PairCounts threshold_pairs(const Graph *g, const folty_query &q, const uint32_t 
             ws.pairs_k.as<uint64_t>(), ws.pairs_v.as<uint32_t>(), np);
         FOLTY_LAUNCHED();
     }
-    ws.host.ensure(64);
-    FOLTY_HIP(hipMemcpyAsync(ws.host.p, ws.scal.p, 32, hipMemcpyDeviceToHost, s));
+    read_scalars(ws, s);
     FOLTY_HIP(hipStreamSynchronize(s));
     unsigned long long ncerts;
     int32_t npairs;
@@ -694,6 +705,12 @@ void keep_counts(const Graph *g, const uint32_t *count, Result *res, hipStream_t
 
 } // namespace
 
+// one pass of a sink over every item
+template <class Sink> static void enumerate_all(const Index &ix, const Sink &sink, hipStream_t s) {
+    k_tri_enum<<<enum_grid(ix.NI), BLK, 0, s>>>(enum_graph(ix), ix.NI, sink);
+    FOLTY_LAUNCHED();
+}
+
 void index_triangles(Index &ix, bool cache, DevBuf &cub, hipStream_t s) {
     const int32_t n = ix.n, S = ix.S;
     ix.rec.ensure(sizeof(EdgeRec) * ((size_t)S + 1));
@@ -705,15 +722,18 @@ void index_triangles(Index &ix, bool cache, DevBuf &cub, hipStream_t s) {
         k_static_recs<<<grid_for(S, BLK), BLK, 0, s>>>(ix.soff.as<int32_t>(), ix.smid.as<int32_t>(),
                                                        ix.ts.as<int64_t>(), S, ix.tshift, srec.as<EdgeRec>());
         k_edge_recs<<<grid_for(S, BLK), BLK, 0, s>>>(ix.oeid.as<uint32_t>(), srec.as<EdgeRec>(), S,
-                                                     ix.rec.as<EdgeRec>(), ix.erng.as<uint2>());
+                                                     ix.tshift, ix.rshift, ix.rec.as<EdgeRec>(),
+                                                     ix.erng.as<uint2>());
         FOLTY_LAUNCHED();
     }
     // probe segments grouped by (owner, mode), their probe prefix, and items
     ix.seg.ensure(sizeof(int4) * ((size_t)S + 1));
-    int32_t ni = 0;
+    ix.srng.ensure(sizeof(uint2) * ((size_t)S + 1));
+    ix.owner.ensure(4 * ((size_t)S + 1));
+    int32_t ni = 0, ng = 0;
     int64_t probes = 0;
     {
-        DevBuf key, key2, val, val2, part_off, len, P, flag, fid, start;
+        DevBuf key, key2, val, val2, run, len, P, flag, fid, start, cnt;
         key.ensure(4 * (size_t)S + 4);
         key2.ensure(4 * (size_t)S + 4);
         val.ensure(4 * (size_t)S + 4);
@@ -723,52 +743,60 @@ void index_triangles(Index &ix, bool cache, DevBuf &cub, hipStream_t s) {
         flag.ensure(4 * (size_t)S + 4);
         fid.ensure(4 * (size_t)S + 4);
         start.ensure(4 * ((size_t)S + 1));
-        const int64_t nk = 2 * (int64_t)n;
-        part_off.ensure(4 * ((size_t)nk + 1));
+        run.ensure(8 * ((size_t)n + 1));
+        cnt.ensure(4);
         if (S > 0) {
             k_seg_keys<<<grid_for(S, BLK), BLK, 0, s>>>(ix.ooff.as<int32_t>(), ix.oadj.as<int32_t>(),
-                                                        ix.otail.as<int32_t>(), S, key.as<uint32_t>(), val.as<int32_t>());
+                                                        ix.otail.as<int32_t>(), S, n, key.as<uint32_t>(),
+                                                        val.as<uint32_t>());
             FOLTY_LAUNCHED();
-            const int kb = bit_length((uint64_t)nk);
+            const int kb = bit_length((uint64_t)n);
             size_t need = sort_pairs_u32_i32(nullptr, 0, key.as<uint32_t>(), key2.as<uint32_t>(), val.as<int32_t>(),
                                              val2.as<int32_t>(), S, kb, s);
             cub.ensure(need);
             sort_pairs_u32_i32(cub.p, need, key.as<uint32_t>(), key2.as<uint32_t>(), val.as<int32_t>(),
                                val2.as<int32_t>(), S, kb, s);
-            k_part_off<<<grid_for(nk + 1, BLK), BLK, 0, s>>>(key2.as<uint32_t>(), S, nk, part_off.as<int32_t>());
-            k_seg_recs<<<grid_for(S, BLK), BLK, 0, s>>>(key2.as<uint32_t>(), val2.as<int32_t>(), ix.ooff.as<int32_t>(),
-                                                        ix.oadj.as<int32_t>(), ix.otail.as<int32_t>(), S,
-                                                        ix.seg.as<int4>(), len.as<int32_t>());
+            k_seg_recs<<<grid_for(S, BLK), BLK, 0, s>>>(key2.as<uint32_t>(), val2.as<uint32_t>(), ix.ooff.as<int32_t>(),
+                                                        ix.oadj.as<int32_t>(), ix.otail.as<int32_t>(),
+                                                        ix.erng.as<uint2>(), S, n, ix.seg.as<int4>(),
+                                                        ix.srng.as<uint2>(), ix.owner.as<int32_t>(), len.as<int32_t>(), run.as<int2>(),
+                                                        cnt.as<int32_t>());
             k_fill<int32_t><<<1, 1, 0, s>>>(len.as<int32_t>() + S, 0, 1);
             FOLTY_LAUNCHED();
             need = exclusive_scan_i32_to_i64(nullptr, 0, len.as<int32_t>(), P.as<int64_t>(), (int64_t)S + 1, s);
             cub.ensure(need);
             exclusive_scan_i32_to_i64(cub.p, need, len.as<int32_t>(), P.as<int64_t>(), (int64_t)S + 1, s);
-            k_item_flags<<<grid_for(S, BLK), BLK, 0, s>>>(key2.as<uint32_t>(), P.as<int64_t>(), part_off.as<int32_t>(),
-                                                          S, flag.as<int32_t>());
-            FOLTY_LAUNCHED();
-            need = inclusive_scan_i32(nullptr, 0, flag.as<int32_t>(), fid.as<int32_t>(), S, s);
-            cub.ensure(need);
-            inclusive_scan_i32(cub.p, need, flag.as<int32_t>(), fid.as<int32_t>(), S, s);
-            k_item_starts<<<grid_for(S, BLK), BLK, 0, s>>>(flag.as<int32_t>(), fid.as<int32_t>(), S,
-                                                           start.as<int32_t>());
-            FOLTY_LAUNCHED();
-            FOLTY_HIP(hipMemcpyAsync(&ni, fid.as<int32_t>() + (S - 1), 4, hipMemcpyDeviceToHost, s));
+            FOLTY_HIP(hipMemcpyAsync(&ng, cnt.p, 4, hipMemcpyDeviceToHost, s));
             FOLTY_HIP(hipMemcpyAsync(&probes, P.as<int64_t>() + S, 8, hipMemcpyDeviceToHost, s));
             FOLTY_HIP(hipStreamSynchronize(s));
-            k_fill<int32_t><<<1, 1, 0, s>>>(start.as<int32_t>() + ni, S, 1);
+        }
+        if (ng > 0) {
+            k_item_flags<<<grid_for(ng, BLK), BLK, 0, s>>>(key2.as<uint32_t>(), P.as<int64_t>(), run.as<int2>(), ng,
+                                                           flag.as<int32_t>());
+            FOLTY_LAUNCHED();
+            size_t need = inclusive_scan_i32(nullptr, 0, flag.as<int32_t>(), fid.as<int32_t>(), ng, s);
+            cub.ensure(need);
+            inclusive_scan_i32(cub.p, need, flag.as<int32_t>(), fid.as<int32_t>(), ng, s);
+            k_item_starts<<<grid_for(ng, BLK), BLK, 0, s>>>(flag.as<int32_t>(), fid.as<int32_t>(), ng,
+                                                            start.as<int32_t>());
+            FOLTY_LAUNCHED();
+            FOLTY_HIP(hipMemcpyAsync(&ni, fid.as<int32_t>() + (ng - 1), 4, hipMemcpyDeviceToHost, s));
+            FOLTY_HIP(hipStreamSynchronize(s));
+            k_fill<int32_t><<<1, 1, 0, s>>>(start.as<int32_t>() + ni, ng, 1);
             FOLTY_LAUNCHED();
         }
         ix.item.ensure(sizeof(EnumItem) * ((size_t)ni + 1));
         if (ni > 0) {
-            k_items<<<grid_for(ni, BLK), BLK, 0, s>>>(start.as<int32_t>(), ix.seg.as<int4>(), P.as<int64_t>(),
-                                                      ix.ooff.as<int32_t>(), ni, ix.item.as<EnumItem>());
+            k_items<<<grid_for(ni, BLK), BLK, 0, s>>>(start.as<int32_t>(), ix.owner.as<int32_t>(), P.as<int64_t>(),
+                                                      run.as<int2>(), ix.ooff.as<int32_t>(), ni,
+                                                      ix.item.as<EnumItem>());
             FOLTY_LAUNCHED();
         }
         FOLTY_HIP(hipStreamSynchronize(s)); // the temporaries go back to the pool
     }
     ix.otail.release();
     ix.NI = ni;
+    ix.G = ng;
     ix.probes = probes;
     // triangle slots per item are made on first use (plans, the server's memory
     // estimate, the cached list): a single query counts its survivors itself
@@ -781,8 +809,7 @@ void index_triangles(Index &ix, bool cache, DevBuf &cub, hipStream_t s) {
         if (ix.T > 0) {
             ix.tri.ensure(12 * (size_t)ix.T);
             CacheSink sink{ix.tri_base.as<int64_t>(), ix.tri.as<int32_t>(), 0};
-            k_tri_enum<<<enum_grid(ni), BLK, 0, s>>>(ix.item.as<EnumItem>(), ix.oadj.as<int32_t>(),
-                                                     ix.seg.as<int4>(), ni, sink);
+            enumerate_all(ix, sink, s);
             FOLTY_LAUNCHED();
             ix.tri_cached = true;
         }
@@ -817,48 +844,10 @@ void ensure_tri_base(Index &ix, hipStream_t s) {
     tri_it.ensure(4 * ((size_t)ni + 1));
     if (ni > 0) {
         CountSink cs{tri_it.as<int32_t>(), 0};
-        k_tri_enum<<<enum_grid(ni), BLK, 0, s>>>(ix.item.as<EnumItem>(), ix.oadj.as<int32_t>(),
-                                                 ix.seg.as<int4>(), ni, cs);
+        enumerate_all(ix, cs, s);
         FOLTY_LAUNCHED();
     }
     tri_base_from_counts(ix, tri_it.as<int32_t>(), s);
-}
-
-// The two-pass filter enumerates the items with survivors a second time.  At a
-// wide window those are the items that hold most triangles, and the second
-// pass costs about as much as the first (70M edges, one year: 7.1 ms on top of
-// the 6.9 ms counting pass).  When the second pass enumerated at least half of
-// the items or half of the triangles again, later queries of about this window
-// or wider (from an eighth of it) filter in one pass instead, writing survivors
-// into per-item triangle slots: 12 bytes of workspace per static triangle, so
-// only when that fits in a quarter of the free device memory.  The offsets come
-// from the counting pass's per-item triangle counts (no extra enumeration).
-// The rule depends only on the graph and the queries, never on timing.  Narrow
-// windows keep the two passes: their second pass is short, and the one pass
-// writes into slots sized for every triangle (70M edges: 5.4-5.6 ms for one
-// pass against 5.0-5.2 ms for the counting pass at 1 hour and 1 day).
-void maybe_one_pass(Graph *g, const Workspace &ws, int64_t delta) {
-    Index &ix = g->ix;
-    if (!ws.emit_timed || !ws.counted_items || ws.tri_it_of != &ix || ix.T <= 0) return;
-    if (2 * (int64_t)ws.emit_items < (int64_t)ix.NI && 2 * ws.emit_triangles < ix.T) return;
-    if (delta / 8 >= ix.one_pass_from.load(std::memory_order_relaxed)) return;
-    size_t fr = 0, tot = 0;
-    if (hipMemGetInfo(&fr, &tot) != hipSuccess) {
-        (void)hipGetLastError();
-        return;
-    }
-    if (!ix.tri_base_ready.load(std::memory_order_acquire) && (size_t)ix.T * 12 > fr / 4) return;
-    std::lock_guard<std::mutex> lk(g->lazy_mu);
-    if (!ix.tri_base_ready.load(std::memory_order_acquire)) {
-        FOLTY_HIP(hipSetDevice(g->device));
-        StreamScope sc(g->stream);
-        HookScope hs(&g->hook);
-        // the counting pass left its per-item triangles in the workspace, on a
-        // stream the caller has synchronised
-        tri_base_from_counts(ix, ws.tri_it.as<int32_t>(), g->stream);
-    }
-    if (delta / 8 < ix.one_pass_from.load(std::memory_order_relaxed))
-        ix.one_pass_from.store(delta / 8, std::memory_order_relaxed);
 }
 
 void ensure_triangles(Graph *g) {
@@ -877,8 +866,7 @@ void ensure_tcnt(Index &ix, hipStream_t s) {
         k_fill<int32_t><<<grid_for(ix.S, BLK), BLK, 0, s>>>(ix.tcnt.as<int32_t>(), 0, ix.S);
         FOLTY_LAUNCHED();
         TcntSink sink{ix.oeid.as<uint32_t>(), ix.tcnt.as<int32_t>()};
-        k_tri_enum<<<enum_grid(ix.NI), BLK, 0, s>>>(ix.item.as<EnumItem>(), ix.oadj.as<int32_t>(),
-                                                    ix.seg.as<int4>(), ix.NI, sink);
+        enumerate_all(ix, sink, s);
         FOLTY_LAUNCHED();
     }
     ix.tcnt_ready = true;
@@ -925,30 +913,21 @@ Result *run_vertex_query(Graph *g, const folty_vertex_query &vq, Workspace &ws) 
 
 // The counts of a query (paper, Algorithm ExistExistForAll, the out- and
 // in-count arrays summed): filter, temporal tests, per-edge counts in sorted
-// edge order in ws.count.  Events: ev[0] start, ev[4]/ev[5] around the counting
-// filter pass, ev[2] after the tests.  *tests receives the number of temporal
-// tests by a copy on the stream: read it after the stream is synchronised.
-static const uint32_t *query_counts(Graph *g, const folty_query &q, Workspace &ws, hipStream_t s,
-                                    int64_t *tests) {
+// edge order in ws.count.  Events: ev[0] start, ev[4]/ev[5] around the filter,
+// ev[2] after the tests.  The scalars are on the device.
+static const uint32_t *query_counts(Graph *g, const folty_query &q, Workspace &ws, hipStream_t s, bool *one_pass) {
     Index &ix = g->ix;
     ws.ensure_events();
+    *one_pass = use_one_pass(g, q);
     FOLTY_HIP(hipEventRecord(ws.ev[0], s));
-    ws.count.ensure(4 * (size_t)ix.m + 4);
+    clear_query(ix, ws, true, s);
     uint32_t *count = ws.count.as<uint32_t>();
-    if (ix.m > 0) {
-        k_fill<uint32_t><<<grid_for(ix.m, BLK), BLK, 0, s>>>(count, 0u, ix.m);
-        FOLTY_LAUNCHED();
-    }
-    int64_t tri = 0;
-    *tests = 0;
-    ws.filter_passes = 0;
+    FOLTY_HIP(hipEventRecord(ws.ev[4], s));
     if (ix.NI > 0) {
-        int64_t known = -1;
         const bool ss = (q.flags & FOLTY_QUERY_SMALLER_SIDE) != 0;
-        const bool one = use_one_pass(g, q);
-        const int64_t survivors =
-            find_survivors(ix, q.variant, q.delta, ws, s, ws.ev[4], ws.ev[5], &tri, &known, ss, one);
-        if (survivors > 0) {
+        const CandBuf B = filter_triangles(ix, q.variant, q.delta, ws, s, *one_pass);
+        FOLTY_HIP(hipEventRecord(ws.ev[5], s));
+        if (ws.kept_chunks > 0) {
             if (ss) {
                 // runs with a shorter L2 mark edge ranges in diff; its prefix sum is added at the end
                 ws.diff.ensure(4 * (2 * (size_t)ix.m + 1));
@@ -956,7 +935,7 @@ static const uint32_t *query_counts(Graph *g, const folty_query &q, Workspace &w
                 k_fill<int32_t><<<grid_for(ix.m + 1, BLK, PERSIST_BLOCKS), BLK, 0, s>>>(diff, 0, ix.m + 1);
                 FOLTY_LAUNCHED();
                 DirectOp op{q.delta, count, diff};
-                launch_temporal<DirectOp, true>(ix, q.variant, q.delta, ws, op, known, survivors, s);
+                launch_temporal<DirectOp, true>(ix, q.variant, q.delta, ws, B, op, s);
                 size_t need = inclusive_scan_i32(nullptr, 0, diff, ps, ix.m, s);
                 ws.cub.ensure(need);
                 inclusive_scan_i32(ws.cub.p, need, diff, ps, ix.m, s);
@@ -965,15 +944,12 @@ static const uint32_t *query_counts(Graph *g, const folty_query &q, Workspace &w
             } else {
                 DirectShortOp op{q.delta, count};
                 op.inl = ix.tshift == 0; // the records' end timestamps are exact
-                launch_temporal(ix, q.variant, q.delta, ws, op, known, survivors, s);
+                launch_temporal(ix, q.variant, q.delta, ws, B, op, s);
             }
-            FOLTY_HIP(hipMemcpyAsync(tests, ws.wbase.as<int64_t>() + ix.NI, 8, hipMemcpyDeviceToHost, s));
         }
     } else {
-        FOLTY_HIP(hipEventRecord(ws.ev[4], s));
         FOLTY_HIP(hipEventRecord(ws.ev[5], s));
     }
-    if (ix.T < 0) ix.T = tri; // every query enumerates every triangle once
     FOLTY_HIP(hipEventRecord(ws.ev[2], s));
     return count;
 }
@@ -985,7 +961,7 @@ void run_query_into(Graph *g, const folty_query &q, Workspace &ws, int32_t *pair
     if (pair_cap < 0) fail(FOLTY_EINVAL, "pair_cap must be >= 0");
     if (pair_cap > 0 && (!pair_u || !pair_v || !n_cert)) fail(FOLTY_EINVAL, "null pair output array");
     if (hipSetDevice(g->device) != hipSuccess) fail(FOLTY_EDEVICE, "hipSetDevice failed");
-    const Index &ix = g->ix;
+    Index &ix = g->ix;
     if (q.universe == FOLTY_UNIVERSE_COMMON && !ix.tcnt_ready)
         fail(FOLTY_EINVAL, "the universe N(a) & N(b) needs the graph's per-edge triangle counts, which this call "
                            "does not build: run one query with that universe through folty_run_fol_query first");
@@ -993,9 +969,10 @@ void run_query_into(Graph *g, const folty_query &q, Workspace &ws, int32_t *pair
         fail(FOLTY_EINVAL, "FOLTY_QUERY_ONE_PASS needs the graph's per-item triangle offsets, which this call does "
                            "not build: run one query with that flag through folty_run_fol_query first");
     hipStream_t s = g->stream;
-    int64_t tests = 0;
-    const uint32_t *count = query_counts(g, q, ws, s, &tests);
+    bool one_pass = false;
+    const uint32_t *count = query_counts(g, q, ws, s, &one_pass);
     const PairCounts pc = threshold_pairs(g, q, count, ws, s, false);
+    if (ix.T.load() < 0) ix.T = (int64_t)ws.host.as<unsigned long long>()[SCAL_HITS];
     *n_pairs = pc.npairs;
     *n_certificates = pc.ncerts;
     if (edge_count) scatter_counts(g, count, edge_count, s);
@@ -1026,46 +1003,44 @@ static Result *run_query_impl(Graph *g, const folty_query &q, Workspace &ws, hip
         FOLTY_HIP(hipStreamSynchronize(s));
     }
     std::unique_ptr<Result> res(new Result());
-    int64_t tests = 0;
-    const uint32_t *count = query_counts(g, q, ws, s, &tests);
+    bool one_pass = false;
+    const uint32_t *count = query_counts(g, q, ws, s, &one_pass);
     finish_query(g, q, count, ws, res.get(), s, vq && vq->inner == FOLTY_INNER_EXISTS);
     if (vq) finish_vertex(g, *vq, ws, res.get(), s);
     FOLTY_HIP(hipEventRecord(ws.ev[3], s));
     if (!(q.flags & FOLTY_QUERY_NO_COUNTS)) keep_counts(g, count, res.get(), s);
     FOLTY_HIP(hipStreamSynchronize(s));
+    if (ix.NI > 0) after_filter(ix, ws, q.delta, one_pass);
+    else ix.T = 0;
     fill_stats_from_index(ix, &res->stats);
-    res->stats.tests = tests;
+    res->stats.tests = (int64_t)ws.host.as<unsigned long long>()[SCAL_TESTS];
     res->stats.n_pairs = (int64_t)res->u.size();
     res->stats.n_certificates = res->n_certificates;
     res->stats.wedge_ms = ev_ms(ws.ev[4], ws.ev[5]);
     res->stats.temporal_ms = ev_ms(ws.ev[5], ws.ev[2]);
     res->stats.threshold_ms = ev_ms(ws.ev[2], ws.ev[3]);
     res->stats.query_ms = ev_ms(ws.ev[0], ws.ev[3]);
-    res->stats.filter_passes = ws.filter_passes;
-    maybe_one_pass(g, ws, q.delta);
+    res->stats.filter_passes = ix.NI > 0 ? ws.filter_passes : 0;
     return res.release();
 }
 
 // Device bytes one single query takes beyond the resident index: per-edge
-// counts, per-item survivor counts and offsets, survivor slots (at most one per
-// triangle), the smaller-side difference array, per-pair certificate counts,
+// counts, the chunks of the triangles its filter keeps, the smaller-side difference array, per-pair certificate counts,
 // pair keys and their sorted copies, sort and scan scratch, and the per-edge
 // counts handed back.
 int64_t query_footprint(const Graph *g, const folty_query &q) {
     const Index &ix = g->ix;
     const int64_t T = std::max<int64_t>(0, ix.T.load());
-    // counts; per item su, tri_it, wu, wbase, sbase, ilist; survivors and their
-    // groups; pieces; pair step
-    int64_t b = 4 * (int64_t)ix.m + 36 * ((int64_t)ix.NI + 1) + 12 * (T + 1) + 4 * (T / 64 + 3) +
-                (int64_t)sizeof(Heavy) * heavy_slots(T, -1) + 56 * (int64_t)ix.S;
+    // counts; the filter's chunks (every triangle kept); heavy triangles; pair step
+    const int64_t chunks = most_chunks(T, std::min<int64_t>((int64_t)ENUM_BLOCKS * WPB, ix.NI)) + MAX_REGIONS;
+    int64_t b = 4 * (int64_t)ix.m + CHUNK_BYTES * chunks + (int64_t)sizeof(Heavy) * heavy_slots(64 * chunks) +
+                56 * (int64_t)ix.S + (int64_t)SCAL_BYTES;
     if (q.flags & FOLTY_QUERY_SMALLER_SIDE) b += 8 * (int64_t)ix.m + 4;
     if (!(q.flags & FOLTY_QUERY_NO_COUNTS)) b += 4 * ix.m_input;
     // the library scratch the query's sorts and scans ask for (sizes only)
-    const int64_t S2 = 2 * (int64_t)ix.S, NI1 = (int64_t)ix.NI + 1;
+    const int64_t S2 = 2 * (int64_t)ix.S;
     const size_t scratch = std::max({sort_pairs_u64_u32(nullptr, 0, nullptr, nullptr, nullptr, nullptr, S2,
                                                         2 * pair_bits(ix.n), nullptr),
-                                     exclusive_scan_i64(nullptr, 0, nullptr, nullptr, NI1, nullptr),
-                                     exclusive_scan_i32_to_i64(nullptr, 0, nullptr, nullptr, NI1, nullptr),
                                      inclusive_scan_i32(nullptr, 0, nullptr, nullptr, ix.m, nullptr),
                                      exclusive_scan_i32(nullptr, 0, nullptr, nullptr, ix.n, nullptr)});
     return b + (int64_t)scratch + (1 << 20);
@@ -1096,16 +1071,16 @@ Workspace::~Workspace() {
 }
 
 size_t Workspace::device_bytes() const {
-    const DevBuf *b[] = {&count, &sv, &su, &wu, &wbase, &sbase, &tri_it, &pieces, &gitem, &ncert, &pairs_k, &pairs_v,
-                         &pairs_k2, &pairs_v2, &scal, &cub, &ilist, &vtmp, &diff, &tflag, &tinst};
+    const DevBuf *b[] = {&count, &sv, &svn, &pieces, &ncert, &pairs_k, &pairs_v,
+                         &pairs_k2, &pairs_v2, &scal, &cub, &vtmp, &diff, &tflag, &tinst};
     size_t t = 0;
     for (auto *x : b) t += x->bytes;
     return t;
 }
 
 void Workspace::forget_buffers() {
-    DevBuf *b[] = {&count, &sv, &su, &wu, &wbase, &sbase, &tri_it, &pieces, &gitem, &ncert, &pairs_k, &pairs_v,
-                   &pairs_k2, &pairs_v2, &scal, &cub, &ilist, &vtmp, &diff, &tflag, &tinst};
+    DevBuf *b[] = {&count, &sv, &svn, &pieces, &ncert, &pairs_k, &pairs_v,
+                   &pairs_k2, &pairs_v2, &scal, &cub, &vtmp, &diff, &tflag, &tinst};
     for (auto *x : b) x->forget();
 }
 

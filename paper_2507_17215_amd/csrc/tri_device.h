@@ -14,8 +14,8 @@ constexpr int BLK = 256;
 constexpr int WPB = BLK / 64;         // wavefronts per block
 constexpr int CAP = 512;              // N+(u) staged in LDS up to this length
 constexpr int PERSIST_BLOCKS = 4096;
-constexpr int ENUM_BLOCKS = 32768; // 8 x the resident blocks: about a dozen items per wavefront, balanced by the dispatcher
-constexpr int32_t CHUNK = 4096;       // closing probes per enumeration item (about; whole segments)
+constexpr int ENUM_BLOCKS = 32768; // many more than are resident: a few items per wavefront, balanced by the dispatcher
+constexpr int32_t CHUNK = 3072;       // closing probes per enumeration item (about; whole segments)
 
 __device__ inline int lane_id() { return __lane_id(); }
 
@@ -188,6 +188,26 @@ template <int VAR, bool SS = false> __device__ inline int64_t tri_work(const Tri
            run_work<VAR, 2, 0, SS>(T, dq) + run_work<VAR, 1, 2, SS>(T, dq) + run_work<VAR, 2, 1, SS>(T, dq);
 }
 
+// the runs that can count, as bits in the order of tri_work's sum
+template <int VAR> __device__ inline uint32_t tri_live(const TriLists &T, uint32_t dq) {
+    Span a, b, c;
+    return (uint32_t)run_lists<VAR, 0, 1>(T, dq, a, b, c) | (uint32_t)run_lists<VAR, 1, 0>(T, dq, a, b, c) << 1 |
+           (uint32_t)run_lists<VAR, 0, 2>(T, dq, a, b, c) << 2 | (uint32_t)run_lists<VAR, 2, 0>(T, dq, a, b, c) << 3 |
+           (uint32_t)run_lists<VAR, 1, 2>(T, dq, a, b, c) << 4 | (uint32_t)run_lists<VAR, 2, 1>(T, dq, a, b, c) << 5;
+}
+__device__ inline uint32_t tri_live_rt(int variant, const TriLists &T, uint32_t dq) {
+    switch (variant) {
+    case 0: return tri_live<0>(T, dq);
+    case 1: return tri_live<1>(T, dq);
+    case 2: return tri_live<2>(T, dq);
+    case 3: return tri_live<3>(T, dq);
+    case 4: return tri_live<4>(T, dq);
+    case 5: return tri_live<5>(T, dq);
+    case 6: return tri_live<6>(T, dq);
+    default: return tri_live<7>(T, dq);
+    }
+}
+
 // runtime predicate code (one code per job in a batch)
 __device__ inline int64_t tri_work_rt(int variant, const TriLists &T, uint32_t dq) {
     switch (variant) {
@@ -348,12 +368,41 @@ __device__ inline bool chunk_run(const TriLists &T, uint32_t dq, const int64_t *
 }
 
 // ---------------------------------------------------------------------------
-// a.5: triangle enumeration, one wavefront per lowest vertex u
+// a.5: triangle enumeration, one wavefront per item
 // ---------------------------------------------------------------------------
-// Sinks receive every probe: hit(h, p_uv, p_uw, p_vw) is called by all lanes of
-// the wave together (h = this lane found a triangle), so sinks may use ballots.
-struct CountSink {
-    static constexpr bool kCompact = false;
+// inclusive sum over the wavefront (every lane active): row shifts, then the
+// rows' totals broadcast onward
+__device__ inline int32_t wave_scan(int32_t x) {
+    x += __builtin_amdgcn_update_dpp(0, x, 0x111, 0xf, 0xf, false); // row_shr:1
+    x += __builtin_amdgcn_update_dpp(0, x, 0x112, 0xf, 0xf, false); // row_shr:2
+    x += __builtin_amdgcn_update_dpp(0, x, 0x114, 0xf, 0xf, false); // row_shr:4
+    x += __builtin_amdgcn_update_dpp(0, x, 0x118, 0xf, 0xf, false); // row_shr:8
+    x += __builtin_amdgcn_update_dpp(0, x, 0x142, 0xa, 0xf, false); // row_bcast:15
+    x += __builtin_amdgcn_update_dpp(0, x, 0x143, 0xc, 0xf, false); // row_bcast:31
+    return x;
+}
+
+constexpr uint32_t MODE_B = 0x80000000u;
+
+// Hands the triangle of segment edge (u, v) = pm, probe position p and owner-row
+// position pw to a sink as (edge (x0,x1), edge (x0,x2), edge (x1,x2)):
+// mode A: p is in v's row, pw in u's;  mode B: p is in u's row, pw in v's.
+__device__ inline void tri_edges(int32_t pm, int32_t p, int32_t pw, int32_t &e01, int32_t &e02, int32_t &e12) {
+    e01 = (int32_t)((uint32_t)pm & ~MODE_B);
+    if ((uint32_t)pm & MODE_B) {
+        e02 = p;
+        e12 = pw;
+    } else {
+        e02 = pw;
+        e12 = p;
+    }
+}
+
+// Sinks.  kRanges: the sink tests the edges' time ranges (see FilterSink); the
+// others see every triangle.
+// hit(h, e01, e02, e12) is called by all lanes of the wave together.
+struct CountSink { // triangles per item
+    static constexpr bool kRanges = false, kAll = true, kFirst = false, kHits = false;
     int32_t *tri_u;
     int32_t c;
     __device__ void begin(int64_t) { c = 0; }
@@ -361,12 +410,11 @@ struct CountSink {
     __device__ void end(int64_t u) {
         if (lane_id() == 0) tri_u[u] = c;
     }
-    __device__ void prefetch(int32_t, int32_t, bool) {}
     __device__ void finish() {}
 };
 
-struct CacheSink {
-    static constexpr bool kCompact = false;
+struct CacheSink { // the triangles themselves, from their item's offset
+    static constexpr bool kRanges = false, kAll = true, kFirst = false, kHits = false;
     const int64_t *base;
     int32_t *tri;
     int64_t slot;
@@ -382,12 +430,11 @@ struct CacheSink {
         slot += __popcll(mask);
     }
     __device__ void end(int64_t) {}
-    __device__ void prefetch(int32_t, int32_t, bool) {}
     __device__ void finish() {}
 };
 
-struct TcntSink {
-    static constexpr bool kCompact = false;
+struct TcntSink { // triangles per static edge
+    static constexpr bool kRanges = false, kAll = true, kFirst = false, kHits = false;
     const uint32_t *oeid;
     int32_t *tcnt;
     __device__ void begin(int64_t) {}
@@ -399,492 +446,547 @@ struct TcntSink {
         }
     }
     __device__ void end(int64_t) {}
-    __device__ void prefetch(int32_t, int32_t, bool) {}
     __device__ void finish() {}
 };
 
-// Slack of the range test on timestamps shifted right by `shift`: floors of two
+// Slack of a range test on timestamps shifted right by `shift`: floors of two
 // values differ by at most one unit more than their difference does.
 __host__ __device__ inline int64_t range_slack(int64_t dmax, int32_t shift) {
     return shift ? (dmax >> shift) + 1 : dmax;
 }
 
-// two oriented edges can share a run only if their time ranges come within dmax
-__device__ inline bool ranges_meet(uint2 x, uint2 y, int64_t dq) {
-    return (int64_t)x.x - (int64_t)y.y <= dq && (int64_t)y.x - (int64_t)x.y <= dq;
+// The ranges of an oriented edge's two lists (Index::erng), tail to head in x and
+// head to tail in y: per list one pair of 16-bit numbers (-first, last) in the
+// low and high half, timestamps >> rshift (RNG_BITS bits); an empty list is
+// (-32768, -32768).  In this form the tests below are packed additions whose
+// signs decide, and an empty list fails every one of them.
+constexpr int RNG_BITS = 14;
+constexpr uint32_t RNG_EMPTY = 0x80008000u;
+typedef short rng_t __attribute__((ext_vector_type(2)));
+__host__ __device__ inline uint32_t rng_pack(uint32_t first, uint32_t last) {
+    return (uint32_t)(uint16_t)(-(int32_t)first) | last << 16;
+}
+// the window bound in units of the ranges (no difference of two exceeds it)
+__host__ __device__ inline int32_t rng_slack(int64_t dmax, int32_t rshift) {
+    const int64_t d = range_slack(dmax, rshift), most = (1 << RNG_BITS) - 1;
+    return (int32_t)(d > most ? most : d);
+}
+__device__ inline rng_t rng_of(uint32_t w) { return __builtin_bit_cast(rng_t, w); }
+__device__ inline uint32_t rng_word(rng_t r) { return __builtin_bit_cast(uint32_t, r); }
+__device__ inline rng_t rng_sum(rng_t a, rng_t b) { return __builtin_elementwise_add_sat(a, b); }
+__device__ inline uint32_t rng_swap(uint32_t w) { return __builtin_amdgcn_alignbit(w, w, 16); }
+// top bit set unless both halves are >= 0
+__device__ inline uint32_t rng_bad(rng_t d) {
+    const uint32_t w = rng_word(d);
+    return w | w << 16;
+}
+// (last + dq, dq - first) of a list: summed with another list's (-first, last)
+// both halves are >= 0 iff the lists come within dq of each other
+__device__ inline uint32_t rng_near(uint32_t w, int32_t dq) {
+    return rng_word(rng_sum(rng_of(rng_swap(w)), rng_of((uint32_t)dq | (uint32_t)dq << 16)));
 }
 
-// What a filter pass does with the triangles it keeps.
-enum FilterMode {
-    FILTER_COUNT = 0, // survivors and tests per item, triangles seen; writes no survivor
-    FILTER_EMIT = 1,  // survivors into their item's slots (offsets from a counting pass)
-    FILTER_BOTH = 2,  // both, into slots sized by the item's triangle count
+// An edge's lists for the run test: p = (-first, last), q = (last + dq, -first).
+// q of one list plus p of another: both halves >= 0 iff an entry of the other can
+// follow one of the first by at most dq.
+struct RngEdge {
+    rng_t p[2], q[2];
+    __device__ RngEdge(uint32_t x, uint32_t y, int32_t dq) {
+        p[0] = rng_of(x);
+        p[1] = rng_of(y);
+        const rng_t d = rng_of((uint32_t)dq); // the low half
+        q[0] = rng_sum(rng_of(rng_swap(x)), d);
+        q[1] = rng_sum(rng_of(rng_swap(y)), d);
+    }
+};
+// list E_{xI,xJ} of a triangle with edges (x0,x1), (x0,x2), (x1,x2)
+template <int I, int J> struct RngList {
+    static constexpr int edge = I + J - 1, dir = I < J ? 0 : 1;
+};
+// top bit clear iff run (I, J) can have t <= t2 <= t3 <= t + dmax by its lists' ranges
+template <int VAR, int I, int J> __device__ inline uint32_t rng_run_bad(const RngEdge (&E)[3]) {
+    using P = Pick<VAR, I, J>;
+    using A = RngList<I, J>;
+    using B = RngList<P::L2a, P::L2b>;
+    using C = RngList<P::L3a, P::L3b>;
+    const rng_t q1 = E[A::edge].q[A::dir];
+    return rng_bad(rng_of(rng_word(rng_sum(q1, E[B::edge].p[B::dir])) | rng_word(rng_sum(q1, E[C::edge].p[C::dir])) |
+                          rng_word(rng_sum(E[B::edge].q[B::dir], E[C::edge].p[C::dir]))));
+}
+template <int VAR> __device__ inline uint32_t rng_tri_bad(const RngEdge (&E)[3]) {
+    return rng_run_bad<VAR, 0, 1>(E) & rng_run_bad<VAR, 1, 0>(E) & rng_run_bad<VAR, 0, 2>(E) &
+           rng_run_bad<VAR, 2, 0>(E) & rng_run_bad<VAR, 1, 2>(E) & rng_run_bad<VAR, 2, 1>(E);
+}
+// a run of any of the predicates (bits, the same in every lane)
+__device__ inline bool rng_can_run(uint32_t predicates, const RngEdge (&E)[3]) {
+    uint32_t bad = ~0u;
+    while (predicates) {
+        const int v = __builtin_ctz(predicates);
+        predicates &= predicates - 1;
+        switch (v) {
+        case 0: bad &= rng_tri_bad<0>(E); break;
+        case 1: bad &= rng_tri_bad<1>(E); break;
+        case 2: bad &= rng_tri_bad<2>(E); break;
+        case 3: bad &= rng_tri_bad<3>(E); break;
+        case 4: bad &= rng_tri_bad<4>(E); break;
+        case 5: bad &= rng_tri_bad<5>(E); break;
+        case 6: bad &= rng_tri_bad<6>(E); break;
+        default: bad &= rng_tri_bad<7>(E); break;
+        }
+    }
+    return (int32_t)bad >= 0;
+}
+
+// The triangles a filter keeps, in chunks of 64 slots (three oriented edges
+// each): a wavefront fills one chunk after another, taking chunk numbers from
+// its block's region (regions have counters on cache lines of their own, so
+// the atomics of thousands of wavefronts do not queue at one address) or, once
+// that is full, from the next one, and leaves the number of slots it filled in
+// cnt.  A wavefront that finds every region full drops what it keeps and counts
+// the chunks it would have needed, so the host learns what a repeat needs.
+
+struct CandAppend {
+    int32_t cur = -1;     // this wavefront's chunk (-1: none)
+    int32_t n = 64;       // slots filled in it
+    int32_t region = -1;  // where its next chunk comes from
+    uint32_t lost = 0;    // chunks dropped
+    int32_t group = 0;    // tag of the chunks taken
+    __device__ int32_t take(const CandBuf &B) {
+        if (lost) {
+            lost++;
+            return -1;
+        }
+        if (region < 0) region = (int32_t)(blockIdx.x % (unsigned)B.regions);
+        for (int32_t tries = 0; tries < B.regions; tries++) {
+            uint32_t k = 0;
+            if (lane_id() == 0) k = atomicAdd(&B.ctr[region * CAND_STRIDE], 1u);
+            k = __builtin_amdgcn_readfirstlane(k);
+            if (k < (uint32_t)B.per_region) {
+                const int32_t chunk = region * B.per_region + (int32_t)k;
+                if (B.tag && lane_id() == 0) B.tag[chunk] = group;
+                return chunk;
+            }
+            region = region + 1 == B.regions ? 0 : region + 1;
+        }
+        lost = 1;
+        return -1;
+    }
+    __device__ void close(const CandBuf &B) { // the chunk takes no more
+        if (cur >= 0 && lane_id() == 0) B.cnt[cur] = n;
+        cur = -1;
+        n = 64;
+    }
+    __device__ void push(const CandBuf &B, bool keep, int32_t a, int32_t b, int32_t c) {
+        const unsigned long long mask = __ballot(keep);
+        if (!mask) return;
+        const int32_t add = (int32_t)__popcll(mask);
+        const int32_t pos = n + (int32_t)__popcll(mask & lanes_below());
+        int32_t next = cur;
+        if (n + add > 64) {
+            if (cur >= 0 && lane_id() == 0) B.cnt[cur] = 64;
+            next = take(B);
+        }
+        const int32_t chunk = pos < 64 ? cur : next;
+        if (keep && chunk >= 0) {
+            int32_t *s = B.sv + 3 * ((int64_t)chunk * 64 + (pos & 63));
+            s[0] = a;
+            s[1] = b;
+            s[2] = c;
+        }
+        n = n + add > 64 ? n + add - 64 : n + add;
+        cur = next;
+    }
+    __device__ void finish(const CandBuf &B) {
+        close(B);
+        if (lost && lane_id() == 0) atomicAdd(B.dropped, lost);
+    }
 };
 
-// Keeps triangles with at least one run that can count, with each survivor's
-// test offset inside its item.  Every run uses one list of each of the three
-// edges, and its three timestamps lie within dmax of each other, so the edges'
-// time ranges must pairwise come within dmax: the two ranges loaded before the
-// exact search are tested first, the third edge's range is loaded only if they
-// meet (8 bytes each), and only then are the three edge records read.  The enumeration order inside an item is fixed, so a
-// counting pass and a later emitting pass agree on every survivor's position.
-// VAR < 0: the predicate code is read from `variant` at run time
-template <int VAR, int MODE, bool SS = false> struct FilterSink {
-    // a run-time predicate code inlines all eight tests: keep the enumeration's
-    // code small (one copy of the sink) for those
-    static constexpr bool kCompact = VAR < 0;
-    const int64_t *base; // EMIT, BOTH: first survivor slot of each item
-    const EdgeRec *rec;
-    const uint2 *rng; // per oriented edge: (first, last) timestamp >> shift
-    int64_t dq;       // range_slack(dmax, shift)
-    int variant;
-    int32_t *sv;      // EMIT, BOTH: survivors (three oriented edges each)
-    int64_t *sw;      // EMIT, BOTH: test offset of each survivor inside its item (null: not kept)
-    int32_t *su;      // COUNT, BOTH: survivors per item
-    int64_t *wu;      // COUNT, BOTH: tests per item
-    unsigned long long *hits; // COUNT: triangles seen (added once per wavefront)
-    int32_t *tri_it;  // COUNT: triangles of each item (null: not kept)
-    int64_t slot;
-    int32_t ns;
-    int32_t nt;
-    int64_t work;
+// Keeps the triangles with a run of one of the predicates that can count by its
+// lists' ranges (a run needs t <= t2 <= t3 <= t + dmax; the temporal step decides
+// from the records, whose ranges are exact).
+// A probe's two known edges can be tested first (do any of their lists come
+// within dmax of each other?) and the whole triangle after, or the triangle once:
+//   FILTER_NARROW  known edges, then the membership of those that pass, then the triangle;
+//   FILTER_WIDE    membership of every probe, then the triangle;
+//   FILTER_COUNT   membership of every probe, counting the triangles, then both tests.
+// VAR >= 0: one predicate, fixed at compile time; VAR < 0: the bits of `predicates`
+// (a plan's jobs), all eight tests inlined.
+enum FilterMode { FILTER_NARROW, FILTER_WIDE, FILTER_COUNT };
+template <int VAR, FilterMode MODE> struct FilterSink {
+    static constexpr bool kRanges = true;
+    static constexpr bool kAll = MODE != FILTER_NARROW; // every probe's membership is decided
+    static constexpr bool kFirst = MODE != FILTER_WIDE; // the known edges are tested first
+    static constexpr bool kHits = MODE == FILTER_COUNT;
+    const uint2 *rng;
+    int32_t dq;               // rng_slack(dmax, rshift)
+    uint32_t predicates;      // VAR < 0: bits
+    CandBuf out;
+    unsigned long long *hits; // FILTER_COUNT: triangles seen (added once per wavefront)
+    CandAppend app;
     unsigned long long nhit;
-    uint2 pra, prk; // ranges of edge (x0, x1) and of the known one of (x0, x2) / (x1, x2)
-    bool pkb;       // the known one is (x0, x2)
-    // called for every probe that may hit, before hit(): edge (x0, x1) and one of
-    // the other two are known before the search that finds the third
-    __device__ void prefetch(int32_t a, int32_t k, bool k_is_b) {
-        pra = rng[a];
-        prk = rng[k];
-        pkb = k_is_b;
+    __device__ void begin(int64_t) {}
+    __device__ void end(int64_t) {}
+    // do some list of the probed edge and some list of edge (u, v), given as
+    // rng_near words, come within dq of each other?
+    __device__ bool first(uint32_t n0, uint32_t n1, uint2 rp) const {
+        const rng_t px = rng_of(rp.x), py = rng_of(rp.y);
+        return (int32_t)(rng_bad(rng_sum(rng_of(n0), px)) & rng_bad(rng_sum(rng_of(n0), py)) &
+                         rng_bad(rng_sum(rng_of(n1), px)) & rng_bad(rng_sum(rng_of(n1), py))) >= 0;
     }
-    __device__ void begin(int64_t it) {
-        if constexpr (MODE != FILTER_COUNT) slot = base[it];
-        ns = 0;
-        nt = 0;
-        work = 0;
-    }
-    __device__ void hit(bool h, int32_t a, int32_t b, int32_t c) {
-        if constexpr (MODE == FILTER_COUNT) nt += (int32_t)__popcll(__ballot(h));
-        int64_t wk = 0;
-        // the two ranges loaded ahead first; the third edge's only if they meet
-        if (h && ranges_meet(pra, prk, dq)) {
-            const uint2 r3 = rng[pkb ? c : b];
-            if (ranges_meet(pra, r3, dq) && ranges_meet(prk, r3, dq)) {
-                if constexpr (VAR >= 0) wk = tri_work<VAR, SS>(load_lists<false>(rec, a, b, c), run_slack(dq));
-                else wk = tri_work_rt(variant, load_lists<false>(rec, a, b, c), run_slack(dq));
-            }
+    // a triangle (h) whose known edges meet; pw: the owner-row edge
+    __device__ void found(bool h, uint32_t n0, uint32_t n1, uint2 rp, int32_t pm, int32_t p, int32_t pw) {
+        bool keep = false;
+        int32_t a = 0, b = 0, c = 0;
+        if (h) {
+            const uint2 rw = rng[(uint32_t)pw];
+            const bool mode_b = ((uint32_t)pm & MODE_B) != 0;
+            const uint2 r1 = mode_b ? rp : rw, r2 = mode_b ? rw : rp;
+            // (last + dq, dq - first) back to (-first, last); an empty list stays empty
+            const rng_t d = rng_of((uint32_t)dq | (uint32_t)dq << 16);
+            const uint32_t x = rng_swap(rng_word(__builtin_elementwise_sub_sat(rng_of(n0), d)));
+            const uint32_t y = rng_swap(rng_word(__builtin_elementwise_sub_sat(rng_of(n1), d)));
+            const RngEdge E[3] = {RngEdge(x, y, dq), RngEdge(r1.x, r1.y, dq), RngEdge(r2.x, r2.y, dq)};
+            if constexpr (VAR >= 0) keep = (int32_t)rng_tri_bad<VAR>(E) >= 0;
+            else keep = rng_can_run(predicates, E);
+            tri_edges(pm, p, pw, a, b, c);
         }
-        bool keep = wk > 0;
-        unsigned long long mask = __ballot(keep);
-        if (!mask) return;
-        int64_t incl = wave_inclusive_sum(wk);
-        if constexpr (MODE != FILTER_COUNT) {
-            if (keep) {
-                int64_t pos = slot + ns + __popcll(mask & lanes_below());
-                sv[3 * pos] = a;
-                sv[3 * pos + 1] = b;
-                sv[3 * pos + 2] = c;
-                if (sw) sw[pos] = work + incl - wk;
-            }
-        }
-        ns += (int32_t)__popcll(mask);
-        work += __shfl(incl, 63);
-    }
-    __device__ void end(int64_t it) {
-        if constexpr (MODE != FILTER_EMIT) {
-            if (lane_id() == 0) {
-                su[it] = ns;
-                wu[it] = work;
-            }
-        }
-        if constexpr (MODE == FILTER_COUNT) {
-            nhit += (unsigned long long)nt;
-            if (tri_it && lane_id() == 0) tri_it[it] = nt;
-        }
+        app.push(out, keep, a, b, c);
     }
     __device__ void finish() {
-        if constexpr (MODE == FILTER_COUNT) {
+        app.finish(out);
+        if constexpr (kHits) {
             if (lane_id() == 0 && nhit) atomicAdd(hits, nhit);
         }
     }
 };
 
-// What the filter needs of one predicate code and window bound.
-struct JobFilter {
-    int64_t dq;
-    int variant;
-    int32_t *sv;
-    int64_t *sw;
-    int32_t *su;
-    int64_t *wu;
-};
-
-// FILTER_BOTH for two predicate codes over the same triangles (a plan's two
-// jobs on one graph): one enumeration and one read of the edges' ranges per
-// triangle; each code then reads the three edge records for itself (the second
-// read hits the cache), so only one code's lists are live at a time, and keeps
-// its survivors in its own slots.
-struct PairFilterSink {
-    static constexpr bool kCompact = true;
-    const int64_t *base; // first slot of each item (the graph's triangle offsets)
-    const EdgeRec *rec;
-    const uint2 *rng;
-    JobFilter f[2];
-    int64_t slot;
-    int32_t ns[2];
-    int64_t work[2];
-    uint2 pra, prk;
-    bool pkb;
-    __device__ void prefetch(int32_t a, int32_t k, bool k_is_b) {
-        pra = rng[a];
-        prk = rng[k];
-        pkb = k_is_b;
-    }
-    __device__ void begin(int64_t it) {
-        slot = base[it];
-        ns[0] = ns[1] = 0;
-        work[0] = work[1] = 0;
-    }
-    template <int J> __device__ void keep(bool pass, int32_t a, int32_t b, int32_t c) {
-        const int64_t wk = pass ? tri_work_rt(f[J].variant, load_lists<false>(rec, a, b, c), run_slack(f[J].dq)) : 0;
-        const bool kp = wk > 0;
-        const unsigned long long mask = __ballot(kp);
-        if (!mask) return;
-        const int64_t incl = wave_inclusive_sum(wk);
-        if (kp) {
-            const int64_t pos = slot + ns[J] + __popcll(mask & lanes_below());
-            f[J].sv[3 * pos] = a;
-            f[J].sv[3 * pos + 1] = b;
-            f[J].sv[3 * pos + 2] = c;
-            f[J].sw[pos] = work[J] + incl - wk;
-        }
-        ns[J] += (int32_t)__popcll(mask);
-        work[J] += __shfl(incl, 63);
-    }
-    __device__ void hit(bool h, int32_t a, int32_t b, int32_t c) {
-        bool p0 = false, p1 = false;
-        const int64_t dq = f[0].dq > f[1].dq ? f[0].dq : f[1].dq;
-        if (h && ranges_meet(pra, prk, dq)) {
-            const uint2 r3 = rng[pkb ? c : b];
-            p0 = ranges_meet(pra, prk, f[0].dq) && ranges_meet(pra, r3, f[0].dq) && ranges_meet(prk, r3, f[0].dq);
-            p1 = ranges_meet(pra, prk, f[1].dq) && ranges_meet(pra, r3, f[1].dq) && ranges_meet(prk, r3, f[1].dq);
-        }
-        keep<0>(p0, a, b, c);
-        keep<1>(p1, a, b, c);
-    }
-    __device__ void end(int64_t it) {
-        if (lane_id() == 0)
-            for (int j = 0; j < 2; j++) {
-                f[j].su[it] = ns[j];
-                f[j].wu[it] = work[j];
-            }
-    }
-    __device__ void finish() {}
-};
-
-// LDS of one wavefront's enumeration item: the owner's out-row N+(w), the
-// item's probe segments, and a bitmap with one hash bit per vertex of N+(w), so
-// a probe whose bit is clear misses without a search.  The other probes (the
-// hits and a few collisions) wait in a queue until 64 of them fill a wavefront,
-// which then searches N+(w) exactly and hands its triangles to the sink.  7 KB
-// per wavefront.
-constexpr int ITEM_SEGS = 128;              // probe segments per item
-constexpr int BM_LOG = 12;                  // 4096 bits
-constexpr int BM_WORDS = 1 << (BM_LOG - 5);
-constexpr int QCAP = 128;                   // < 64 waiting + one step's 64
-constexpr int ENUM_UNROLL = 4;              // probe steps whose loads overlap
-constexpr int Q_SHIFT = 13;                 // probes of an item < CHUNK + CAP <= 2^13
+// LDS of one wavefront's item.  Probe q in [0, nq) belongs to segment
+// popcount(marks below q): marks has a bit at q - 1 for the first probe q of
+// every segment but the first, so a step of 64 probes finds its segments with
+// one uniform 64-bit read and a bit count per lane.
+// The owner's out-row is a hash table of buckets of four entries (id << 10 |
+// position, ids by their low 22 bits): one 16-byte read and the smallest of
+// four differences decide a probe and give its position, unless the bucket is
+// full (3 % of them at the highest load, two entries per bucket).
+constexpr int ITEM_SEGS = 64;     // probe segments per item
+constexpr int TAB_BUCKETS = 256;
+constexpr int POS_BITS = 10;
+constexpr int ENUM_UNROLL = 4;    // probe steps whose loads overlap
 struct EnumLds {
-    int32_t nu[CAP];        // N+(w), ascending
-    int32_t off[ITEM_SEGS]; // row start of segment i minus PRE[i]: probe q reads oadj[off[i] + q]
-    int32_t pre[ITEM_SEGS]; // PRE[i+1] = total row length of segments j <= i
-    int32_t pm[ITEM_SEGS];  // oriented edge (u, v) of segment i | mode B << 31
-    uint32_t bm[BM_WORDS];
-    int32_t qx[QCAP];       // waiting probes: x
-    int32_t qr[QCAP];       // and q | i << Q_SHIFT
+    uint4 tab[TAB_BUCKETS];        // loose items: int2 (start, length) of each segment's owner row
+    // per segment: x: row start minus the segment's first probe (probe q reads
+    // oadj[x + q]); y: oriented edge (u, v) | mode B << 31; z, w: its ranges (rng_near)
+    uint4 sg[ITEM_SEGS];
+    unsigned long long marks[64];
 };
-static_assert(CHUNK + CAP <= (1 << Q_SHIFT) && ITEM_SEGS <= (1 << (31 - Q_SHIFT)), "queue packing");
+static_assert(CHUNK + CAP + 64 * ENUM_UNROLL <= 64 * 64, "marks cover an item's probes and the steps past them");
+static_assert(CAP <= 2 * TAB_BUCKETS && CAP < (1 << POS_BITS), "table load and positions");
 
-__device__ inline uint32_t bm_hash(int32_t x) { return ((uint32_t)x * 0x9E3779B1u) >> (32 - BM_LOG); }
+__device__ inline uint32_t tab_key(int32_t x) { return (uint32_t)x << POS_BITS; }
+__device__ inline uint32_t tab_hash(int32_t x, int tlog) { return ((uint32_t)x * 0x9E3779B1u) >> (32 - tlog); }
 
-constexpr uint32_t MODE_B = 0x80000000u;
-
-// Hands the triangle of segment edge (u, v) = pm, probe position p and owner-row
-// position pw to the sink as (edge (x0,x1), edge (x0,x2), edge (x1,x2)):
-// mode A: p is in v's row, pw in u's;  mode B: p is in u's row, pw in v's.
-__device__ inline void tri_edges(int32_t pm, int32_t p, int32_t pw, int32_t &e01, int32_t &e02, int32_t &e12) {
-    e01 = (int32_t)((uint32_t)pm & ~MODE_B);
-    if ((uint32_t)pm & MODE_B) {
-        e02 = p;
-        e12 = pw;
-    } else {
-        e02 = pw;
-        e12 = p;
-    }
+// buckets for a row of d entries, as a power of two: at most two entries each on average
+__device__ inline int tab_log(int32_t d) {
+    const int l = 32 - __builtin_clz((uint32_t)(d > 4 ? d - 1 : 4)) - 1;
+    return l < 4 ? 4 : l;
 }
 
-// the first cnt waiting probes, one per lane: exact search of x in N+(w)
-template <class Sink>
-__device__ inline void enum_batch(int32_t b, int32_t d, const EnumLds &L, int32_t cnt, Sink &sink) {
+// the owner row [b, b + d) into the table; v0: this lane's entry of the first 64
+__device__ inline void tab_build(EnumLds &L, const int32_t *__restrict__ oadj, int32_t b, int32_t d, int32_t v0,
+                                 int tlog) {
     const int lane = lane_id();
-    bool hit = false;
-    int32_t e01 = 0, e02 = 0, e12 = 0;
-    if (lane < cnt) {
-        const int32_t x = L.qx[lane], r = L.qr[lane];
-        const int32_t i = r >> Q_SHIFT;
-        const int32_t pm = L.pm[i];
-        const int32_t p = L.off[i] + (r & ((1 << Q_SHIFT) - 1));
-        sink.prefetch((int32_t)((uint32_t)pm & ~MODE_B), p, ((uint32_t)pm & MODE_B) != 0);
-        int32_t a = 0, c = d;
-        while (a < c) {
-            int32_t mid = (a + c) >> 1;
-            if (L.nu[mid] < x) a = mid + 1;
-            else c = mid;
-        }
-        hit = a < d && L.nu[a] == x;
-        tri_edges(pm, p, b + a, e01, e02, e12);
+    const uint4 none = make_uint4(~0u, ~0u, ~0u, ~0u);
+    for (int i = lane; i < (1 << tlog); i += 64) L.tab[i] = none;
+    wave_sync();
+    uint32_t *slot = reinterpret_cast<uint32_t *>(L.tab);
+    const uint32_t nslots = 4u << tlog;
+    for (int32_t i = lane; i < d; i += 64) {
+        const int32_t x = i < 64 ? v0 : oadj[b + i];
+        const uint32_t val = tab_key(x) | (uint32_t)i;
+        uint32_t at = tab_hash(x, tlog) * 4;
+        // buckets fill from their first slot on; a full one passes to the next
+        while (atomicCAS(&slot[at], ~0u, val) != ~0u) at = at + 1 == nslots ? 0 : at + 1;
     }
-    sink.hit(hit, e01, e02, e12);
+    wave_sync();
 }
 
-// The first 64 entries of an item's owner row and of its segments (this
-// lane's), loaded one item ahead.
+// position of x in the owner row, or -1.  exact: ids are below 2^22, so equal
+// low bits are equal ids; otherwise the row's entry decides.
+__device__ inline int32_t tab_find(const EnumLds &L, const int32_t *__restrict__ oadj, int32_t b, int32_t x, int tlog,
+                                   bool exact) {
+    const uint32_t key = tab_key(x);
+    uint32_t h = tab_hash(x, tlog);
+    for (;;) {
+        const uint4 s = L.tab[h];
+        const uint32_t d0 = s.x ^ key, d1 = s.y ^ key, d2 = s.z ^ key, d3 = s.w ^ key;
+        if (exact) {
+            const uint32_t m0 = d0 < d1 ? d0 : d1, m1 = d2 < d3 ? d2 : d3;
+            const uint32_t m = m0 < m1 ? m0 : m1;
+            if (m < (uint32_t)CAP) return (int32_t)m;
+        } else {
+            const uint32_t dd[4] = {d0, d1, d2, d3};
+#pragma unroll
+            for (int j = 0; j < 4; j++)
+                if (dd[j] < (uint32_t)CAP && oadj[b + (int32_t)dd[j]] == x) return (int32_t)dd[j];
+        }
+        if (s.w == ~0u) return -1;
+        h = (h + 1) & ((1u << tlog) - 1u);
+    }
+}
+
+// position of x in the ascending row [b, b + d) of global memory, or -1
+__device__ inline int32_t row_find(const int32_t *__restrict__ oadj, int32_t b, int32_t d, int32_t x) {
+    int32_t a = 0, c = d;
+    while (a < c) {
+        const int32_t mid = (a + c) >> 1;
+        if (oadj[b + mid] < x) a = mid + 1;
+        else c = mid;
+    }
+    return a < d && oadj[b + a] == x ? a : -1;
+}
+
+struct EnumGraph {
+    const EnumItem *item;
+    const int32_t *oadj;
+    const int4 *seg;
+    const uint2 *srng;    // the ranges of each segment's edge
+    const int32_t *owner; // of each segment (read for loose items)
+    const int32_t *ooff;
+    int32_t exact; // ids below 2^22 (tab_find)
+};
+
+// An item's first owner-row entries and its segments (this lane's), loaded one
+// item ahead.
 struct StageAhead {
     int32_t v;
     int4 sg;
+    uint2 r;
 };
 
-__device__ inline StageAhead stage_ahead(const EnumItem &item, const int32_t *__restrict__ oadj,
-                                         const int4 *__restrict__ seg) {
-    StageAhead a{0, make_int4(0, 0, 0, 0)};
+template <bool RANGES>
+__device__ inline StageAhead stage_ahead(const EnumItem &item, const EnumGraph &G) {
+    StageAhead a{0, make_int4(0, 0, 0, 0), make_uint2(0, 0)};
     const int lane = lane_id();
-    if (item.d >= 1 && item.d <= CAP && item.nq > 0) {
-        if (lane < item.d) a.v = oadj[item.b + lane];
-        if (lane < item.ng) a.sg = seg[item.g0 + lane];
+    if (lane < item.ng) {
+        a.sg = G.seg[item.g0 + lane];
+        if constexpr (RANGES) a.r = G.srng[item.g0 + lane];
     }
+    if (lane < item.d && item.d <= CAP) a.v = G.oadj[item.b + lane];
     return a;
 }
 
-// One wavefront per item: the owner's out-row and the item's segments, whose
-// rows are probed as one flat range q in [0, nq).  Sinks see the triangles of
-// an item in a fixed order.
-template <class Sink>
-__device__ inline void enum_item(const EnumItem &item, const StageAhead &ahead, const int32_t *__restrict__ oadj,
-                                 const int4 *__restrict__ seg, int64_t it, Sink &sink, EnumLds &L) {
+// One wavefront per item, whose segments' rows are probed as one flat range q in
+// [0, nq).  LOOSE: the segments belong to owners with few probes each, whose
+// rows are searched in global memory instead of a table.
+template <bool LOOSE, class Sink>
+__device__ inline void enum_flat(const EnumItem &item, const StageAhead &ahead, const EnumGraph &G, Sink &sink,
+                                 EnumLds &L) {
     const int lane = lane_id();
-    const int32_t b = item.b, d = item.d, ng = item.ng, nq = item.nq;
-    sink.begin(it);
-    if (d >= 1 && d <= CAP && nq > 0) {
-        // stage N+(w) and its hash bits, then the segments with a prefix of
-        // their row lengths
-        for (int w = lane; w < BM_WORDS; w += 64) L.bm[w] = 0;
-        for (int32_t i = lane; i < d; i += 64) L.nu[i] = i < 64 ? ahead.v : oadj[b + i];
-        wave_sync();
-        for (int32_t i = lane; i < d; i += 64) {
-            const uint32_t h = bm_hash(L.nu[i]);
-            atomicOr(&L.bm[h >> 5], 1u << (h & 31));
+    const int32_t *__restrict__ oadj = G.oadj;
+    const int32_t nq = item.nq, b = item.b, d = item.d;
+    const int4 sg = ahead.sg; // zero length past the item's segments
+    const int32_t start = wave_scan(sg.y) - sg.y;
+    const bool have = lane < item.ng;
+    L.marks[lane] = 0;
+    if (have) {
+        uint4 e = make_uint4((uint32_t)(sg.x - start), (uint32_t)sg.z, 0, 0);
+        if constexpr (Sink::kRanges) {
+            e.z = rng_near(ahead.r.x, sink.dq);
+            e.w = rng_near(ahead.r.y, sink.dq);
         }
-        int32_t carry = 0;
-        for (int32_t i0 = 0; i0 < ng; i0 += 64) {
-            const int32_t i = i0 + lane;
-            int4 sg = make_int4(0, 0, 0, 0);
-            if (i < ng) sg = i0 == 0 ? ahead.sg : seg[item.g0 + i];
-            const int32_t x = wave_inclusive_sum(sg.y);
-            if (i < ng) {
-                L.pre[i] = carry + x;
-                L.off[i] = sg.x - (carry + x - sg.y);
-                L.pm[i] = sg.z;
-            }
-            carry += __shfl(x, 63);
+        L.sg[lane] = e;
+        if constexpr (LOOSE) {
+            const int32_t w = G.owner[item.g0 + lane], ob = G.ooff[w];
+            reinterpret_cast<int2 *>(L.tab)[lane] = make_int2(ob, G.ooff[w + 1] - ob);
         }
+    }
+    const int tlog = LOOSE ? 0 : tab_log(d);
+    bool built = LOOSE;
+    if constexpr (!LOOSE && Sink::kAll) {
+        tab_build(L, oadj, b, d, ahead.v, tlog);
+        built = true;
+    } else {
         wave_sync();
-        int32_t i = 0;  // this lane's segment; q only grows, so i only grows
-        int32_t qn = 0; // waiting probes (wave-uniform)
-        // one probe step's candidates into the queue; a full wavefront of them
-        // (or, at the end, whatever waits) goes to the sink
-        auto enqueue = [&](bool v, int32_t x, int32_t r, bool last) {
-            bool cand = false;
-            if (v) {
-                const uint32_t h = bm_hash(x);
-                cand = (L.bm[h >> 5] >> (h & 31)) & 1u;
-            }
-            const unsigned long long mask = __ballot(cand);
-            if (cand) {
-                const int32_t slot = qn + (int32_t)__popcll(mask & lanes_below());
-                L.qx[slot] = x;
-                L.qr[slot] = r;
-            }
-            qn += (int32_t)__popcll(mask);
-            if (qn >= 64 || (last && qn > 0)) {
-                const int32_t cnt = qn < 64 ? qn : 64;
-                wave_sync();
-                enum_batch(b, d, L, cnt, sink);
-                const int32_t rest = qn - cnt;
-                int32_t tx = 0, tr = 0;
-                if (lane < rest) {
-                    tx = L.qx[64 + lane];
-                    tr = L.qr[64 + lane];
-                }
-                wave_sync();
-                if (lane < rest) {
-                    L.qx[lane] = tx;
-                    L.qr[lane] = tr;
-                }
-                qn = rest;
-                wave_sync();
-            }
-        };
-        // ENUM_UNROLL steps of 64 probes at a time: their loads of x are all in
-        // flight before the first is used.  A last pass without probes hands over
-        // the probes still waiting.
-        for (int32_t q0 = 0;; q0 += 64 * ENUM_UNROLL) {
-            const bool more = q0 < nq;
-            int32_t rk[ENUM_UNROLL], xk[ENUM_UNROLL];
-            bool vk[ENUM_UNROLL];
+    }
+    if (have && lane > 0) atomicOr(&L.marks[(start - 1) >> 6], 1ull << ((start - 1) & 63));
+    wave_sync();
+    auto find = [&](uint32_t i, int32_t x, int32_t &pw) {
+        int32_t at;
+        if constexpr (LOOSE) {
+            const int2 o = reinterpret_cast<const int2 *>(L.tab)[i];
+            at = row_find(oadj, o.x, o.y, x);
+            pw = o.x + at;
+        } else {
+            at = tab_find(L, oadj, b, x, tlog, G.exact != 0);
+            pw = b + at;
+        }
+        return at >= 0;
+    };
+    int32_t seg0 = 0; // segment of the next step's first probe
+    for (int32_t q0 = 0; q0 < nq; q0 += 64 * ENUM_UNROLL) {
+        uint4 ek[ENUM_UNROLL];
+        uint32_t ik[ENUM_UNROLL], pk[ENUM_UNROLL];
+        int32_t xk[ENUM_UNROLL];
+        uint2 rk[ENUM_UNROLL];
+        bool vk[ENUM_UNROLL];
+#pragma unroll
+        for (int k = 0; k < ENUM_UNROLL; k++) {
+            const int32_t q = q0 + 64 * k + lane;
+            const unsigned long long w = L.marks[(q0 >> 6) + k];
+            const uint32_t w0 = __builtin_amdgcn_readfirstlane((uint32_t)w);
+            const uint32_t w1 = __builtin_amdgcn_readfirstlane((uint32_t)(w >> 32));
+            const uint32_t i = __builtin_amdgcn_mbcnt_hi(w1, __builtin_amdgcn_mbcnt_lo(w0, (uint32_t)seg0));
+            ek[k] = L.sg[i];
+            if constexpr (LOOSE) ik[k] = i;
+            seg0 += __builtin_popcount(w0) + __builtin_popcount(w1);
+            vk[k] = q < nq;
+            pk[k] = ek[k].x + (uint32_t)q;
+        }
+        if constexpr (Sink::kAll) {
+#pragma unroll
+            for (int k = 0; k < ENUM_UNROLL; k++) xk[k] = vk[k] ? oadj[pk[k]] : -1;
+        }
+        if constexpr (Sink::kRanges) {
+#pragma unroll
+            for (int k = 0; k < ENUM_UNROLL; k++) rk[k] = vk[k] ? sink.rng[pk[k]] : make_uint2(RNG_EMPTY, RNG_EMPTY);
+        }
+        if constexpr (Sink::kRanges && !Sink::kAll) {
+            bool any = false;
 #pragma unroll
             for (int k = 0; k < ENUM_UNROLL; k++) {
-                const int32_t q = q0 + 64 * k + lane;
-                vk[k] = q < nq;
-                xk[k] = 0;
-                rk[k] = 0;
-                if (vk[k]) {
-                    // the segment of q (the i with PRE[i] <= q < PRE[i+1]); walk a few
-                    // segments forward before bisecting.  PRE[ng] = nq > q stops both.
-                    for (int w = 0; w < 4 && L.pre[i] <= q; w++) i++;
-                    if (L.pre[i] <= q) {
-                        int32_t lo = i + 1, hi = ng;
-                        while (lo < hi) {
-                            int32_t mid = (lo + hi) >> 1;
-                            if (L.pre[mid] <= q) lo = mid + 1;
-                            else hi = mid;
-                        }
-                        i = lo;
-                    }
-                    xk[k] = L.off[i] + q; // position of x, replaced by x below
-                    rk[k] = q | (i << Q_SHIFT);
-                }
+                vk[k] = sink.first(ek[k].z, ek[k].w, rk[k]); // false past the item's probes
+                any = any || vk[k];
+            }
+            if (!__ballot(any)) continue;
+            if (!built) {
+                tab_build(L, oadj, b, d, ahead.v, tlog);
+                built = true;
             }
 #pragma unroll
-            for (int k = 0; k < ENUM_UNROLL; k++) xk[k] = vk[k] ? oadj[xk[k]] : 0;
-            if constexpr (Sink::kCompact) {
-                // the steps enter the queue in a loop that is not unrolled (each
-                // step's values move down one register), so the sink's code is
-                // generated once
-                const int steps = more ? ENUM_UNROLL : 1;
-#pragma unroll 1
-                for (int k = 0; k < steps; k++) {
-                    enqueue(vk[0], xk[0], rk[0], !more);
-#pragma unroll
-                    for (int j = 0; j + 1 < ENUM_UNROLL; j++) {
-                        xk[j] = xk[j + 1];
-                        rk[j] = rk[j + 1];
-                        vk[j] = vk[j + 1];
-                    }
-                }
-            } else if (more) {
-#pragma unroll
-                for (int k = 0; k < ENUM_UNROLL; k++) enqueue(vk[k], xk[k], rk[k], false);
-            } else {
-                enqueue(false, 0, 0, true);
-            }
-            if (!more) break;
+            for (int k = 0; k < ENUM_UNROLL; k++) xk[k] = vk[k] ? oadj[pk[k]] : -1;
         }
-        wave_sync(); // the next item overwrites this wave's LDS
-    } else if (d > CAP && nq > 0) {
-        // long owner rows (only for orientations without the degeneracy bound):
-        // the same probes, searched in N+(w) in global memory
-        for (int32_t g = item.g0; g < item.g0 + ng; g++) {
-            const int4 sg = seg[g];
-            for (int32_t p0 = sg.x; p0 < sg.x + sg.y; p0 += 64) {
-                const int32_t p = p0 + lane;
-                bool hit = false;
+#pragma unroll
+        for (int k = 0; k < ENUM_UNROLL; k++) {
+            if (!__ballot(vk[k])) continue;
+            bool h = false;
+            int32_t pw = 0;
+            if (vk[k]) h = find(LOOSE ? ik[k] : 0u, xk[k], pw);
+            if constexpr (!Sink::kRanges) {
                 int32_t e01 = 0, e02 = 0, e12 = 0;
-                if (p < sg.x + sg.y) {
-                    sink.prefetch((int32_t)((uint32_t)sg.z & ~MODE_B), p, ((uint32_t)sg.z & MODE_B) != 0);
-                    const int32_t x = oadj[p];
-                    int32_t a = 0, c = d;
-                    while (a < c) {
-                        int32_t mid = (a + c) >> 1;
-                        if (oadj[b + mid] < x) a = mid + 1;
-                        else c = mid;
-                    }
-                    hit = a < d && oadj[b + a] == x;
-                    tri_edges(sg.z, p, b + a, e01, e02, e12);
-                }
-                sink.hit(hit, e01, e02, e12);
+                if (h) tri_edges((int32_t)ek[k].y, (int32_t)pk[k], pw, e01, e02, e12);
+                sink.hit(h, e01, e02, e12);
+            } else {
+                if constexpr (Sink::kHits) sink.nhit += (unsigned long long)__popcll(__ballot(h));
+                if constexpr (Sink::kAll && Sink::kFirst) h = h && sink.first(ek[k].z, ek[k].w, rk[k]);
+                if (__ballot(h)) sink.found(h, ek[k].z, ek[k].w, rk[k], (int32_t)ek[k].y, (int32_t)pk[k], pw);
             }
         }
     }
-    sink.end(it);
+    wave_sync(); // the next item overwrites this wave's LDS
 }
 
-// the triangles a cached list holds for one item
+// long owner rows (only in orientations without the degeneracy bound): each
+// segment in turn, searched in the owner's row in global memory
 template <class Sink>
-__device__ inline void cached_item(const int64_t *__restrict__ base, const int32_t *__restrict__ tri, int64_t it,
-                                   Sink &sink) {
+__device__ inline void enum_long(const EnumItem &item, const EnumGraph &G, Sink &sink) {
     const int lane = lane_id();
-    const int64_t b = base[it], e = base[it + 1];
-    sink.begin(it);
-    for (int64_t p0 = b; p0 < e; p0 += 64) {
-        int64_t p = p0 + lane;
-        bool valid = p < e;
-        if (valid) sink.prefetch(tri[3 * p], tri[3 * p + 2], false);
-        sink.hit(valid, valid ? tri[3 * p] : 0, valid ? tri[3 * p + 1] : 0, valid ? tri[3 * p + 2] : 0);
+    for (int32_t g = item.g0; g < item.g0 + item.ng; g++) {
+        const int4 sg = G.seg[g];
+        uint32_t n0 = 0, n1 = 0;
+        if constexpr (Sink::kRanges) {
+            const uint2 r = G.srng[g];
+            n0 = rng_near(r.x, sink.dq);
+            n1 = rng_near(r.y, sink.dq);
+        }
+        for (int32_t p0 = sg.x; p0 < sg.x + sg.y; p0 += 64) {
+            const int32_t p = p0 + lane;
+            bool h = p < sg.x + sg.y;
+            uint2 rp = make_uint2(RNG_EMPTY, RNG_EMPTY);
+            if constexpr (Sink::kRanges) {
+                if (h) rp = sink.rng[p];
+                if constexpr (!Sink::kAll) h = h && sink.first(n0, n1, rp);
+            }
+            int32_t at = -1;
+            if (h) at = row_find(G.oadj, item.b, item.d, G.oadj[p]);
+            h = at >= 0;
+            if constexpr (!Sink::kRanges) {
+                int32_t e01 = 0, e02 = 0, e12 = 0;
+                if (h) tri_edges(sg.z, p, item.b + at, e01, e02, e12);
+                sink.hit(h, e01, e02, e12);
+            } else {
+                if constexpr (Sink::kHits) sink.nhit += (unsigned long long)__popcll(__ballot(h));
+                if constexpr (Sink::kAll && Sink::kFirst) h = h && sink.first(n0, n1, rp);
+                if (__ballot(h)) sink.found(h, n0, n1, rp, sg.z, p, item.b + at);
+            }
+        }
     }
+}
+
+template <class Sink>
+__device__ inline void enum_item(const EnumItem &item, const StageAhead &ahead, const EnumGraph &G, int64_t it,
+                                 Sink &sink, EnumLds &L) {
+    sink.begin(it);
+    if (item.d < 0) enum_flat<true>(item, ahead, G, sink, L);
+    else if (item.d <= CAP) enum_flat<false>(item, ahead, G, sink, L);
+    else enum_long(item, G, sink);
     sink.end(it);
 }
 
-// Waves per SIMD the compiler must fit a sink's enumeration into (a floor): at
-// least 7 (72 VGPRs) for the query's counting filter; the others keep their size.
-template <class S> struct enum_waves { static constexpr int value = 4; };
-template <int V> struct enum_waves<FilterSink<V, FILTER_COUNT> > { static constexpr int value = 7; };
-
-// One wavefront per item; list != nullptr: only the nlist items list[0..nlist)
+// (A queue of items or batches of items, handed to a chip's worth of wavefronts
+// by one counter, was slower: atomics on one address take 11 ns each here, 0.54
+// against 0.10 ms for 45,000 items.  Many blocks let the dispatcher balance.)
 template <class Sink>
-__global__ __launch_bounds__(BLK) __attribute__((amdgpu_waves_per_eu(enum_waves<Sink>::value))) void k_tri_enum(const EnumItem *__restrict__ items, const int32_t *__restrict__ oadj,
-                                                  const int4 *__restrict__ seg, int32_t NI, Sink sink,
-                                                  const int32_t *__restrict__ list = nullptr, int32_t nlist = 0) {
+__global__ __launch_bounds__(BLK) __attribute__((amdgpu_waves_per_eu(4))) void k_tri_enum(EnumGraph G, int32_t NI,
+                                                                                          Sink sink) {
     __shared__ EnumLds lds[WPB];
     const int w = wave_id();
     const int64_t stride = (int64_t)gridDim.x * WPB;
     int64_t it = (int64_t)blockIdx.x * WPB + w;
-    if (list) {
-        // a pass over a few listed items
-        for (; it < nlist; it += stride) {
-            const int64_t li = list[it];
-            const EnumItem item = items[li];
-            enum_item(item, stage_ahead(item, oadj, seg), oadj, seg, li, sink, lds[w]);
-        }
-        sink.finish();
-        return;
-    }
-    // item headers run two items ahead and the first row and segment chunks
+    // item headers run two items ahead and the first row and segment entries
     // one item ahead, so a wavefront starts each item with its data loaded
     const EnumItem none{};
-    EnumItem h0 = it < NI ? items[it] : none;
-    EnumItem h1 = it + stride < NI ? items[it + stride] : none;
-    StageAhead a0 = stage_ahead(h0, oadj, seg);
+    EnumItem h0 = it < NI ? G.item[it] : none;
+    EnumItem h1 = it + stride < NI ? G.item[it + stride] : none;
+    StageAhead a0 = stage_ahead<Sink::kRanges>(h0, G);
     for (; it < NI; it += stride) {
         const EnumItem cur = h0;
         const StageAhead ca = a0;
         h0 = h1;
-        a0 = stage_ahead(h0, oadj, seg);
-        h1 = it + 2 * stride < NI ? items[it + 2 * stride] : none;
-        enum_item(cur, ca, oadj, seg, it, sink, lds[w]);
+        a0 = stage_ahead<Sink::kRanges>(h0, G);
+        h1 = it + 2 * stride < NI ? G.item[it + 2 * stride] : none;
+        enum_item(cur, ca, G, it, sink, lds[w]);
     }
     sink.finish();
 }
 
-// cached triangle list: the same filter, one wavefront per item
-template <int VAR, int MODE, bool SS>
-__global__ __launch_bounds__(BLK) void k_filter_cached(const int64_t *__restrict__ base, const int32_t *__restrict__ tri,
-                                                       int32_t NI, FilterSink<VAR, MODE, SS> sink,
-                                                       const int32_t *__restrict__ list = nullptr, int32_t nlist = 0) {
-    const int w = wave_id();
-    const int64_t n = list ? nlist : NI;
-    for (int64_t i = (int64_t)blockIdx.x * WPB + w; i < n; i += (int64_t)gridDim.x * WPB)
-        cached_item(base, tri, list ? (int64_t)list[i] : i, sink);
+// the filter over a cached triangle list, 64 triangles to a wavefront
+template <class Sink>
+__device__ inline void cached_triangles(const int32_t *__restrict__ tri, int64_t T, int64_t first, int64_t step,
+                                        Sink &sink) {
+    for (int64_t t0 = first * 64; t0 < T; t0 += step * 64) {
+        const int64_t t = t0 + lane_id();
+        bool h = t < T;
+        int32_t a = 0, b = 0, c = 0;
+        uint32_t n0 = 0, n1 = 0;
+        uint2 rp = make_uint2(RNG_EMPTY, RNG_EMPTY);
+        if (h) {
+            a = tri[3 * t];
+            b = tri[3 * t + 1];
+            c = tri[3 * t + 2];
+            const uint2 r = sink.rng[a];
+            n0 = rng_near(r.x, sink.dq);
+            n1 = rng_near(r.y, sink.dq);
+            rp = sink.rng[c];
+            h = sink.first(n0, n1, rp);
+        }
+        if (__ballot(h)) sink.found(h, n0, n1, rp, a, c, b); // as mode A: c probed, b in the owner's row
+    }
+}
+
+template <class Sink>
+__global__ __launch_bounds__(BLK) void k_filter_cached(const int32_t *__restrict__ tri, int64_t T, Sink sink) {
+    cached_triangles(tri, T, (int64_t)blockIdx.x * WPB + wave_id(), (int64_t)gridDim.x * WPB, sink);
     sink.finish();
 }
 
@@ -913,30 +1015,27 @@ __device__ inline void chunk_runs_rt(int variant, const TriLists &L, uint32_t dq
 }
 
 // ---------------------------------------------------------------------------
-// a.6: scheduling the tests of the surviving triangles
+// a.6: scheduling the tests of the triangles the filter kept
 // ---------------------------------------------------------------------------
-// Survivors are reached through a dense index q in [0, sbase[NI]): item u holds
-// q in [sbase[u], sbase[u + 1]), at slots slot_base[u] + (q - sbase[u]) of the
-// filter's output (slot_base null: the slots are dense, slot = q).  A wavefront
-// takes a group of 64 consecutive survivors, one per lane.  A survivor with at
-// most LIGHT_TESTS tests is run by the group.  One with more (a heavy survivor)
-// gets an entry in a list and a range of piece numbers, both from one packed
-// counter, so entries are in the order of their pieces; a second kernel runs
-// piece p (tests [4 i, 4 i + 4) of its survivor) per thread, finding its
-// entry by binary search over the entries' first pieces and starting its L2 and
-// L3 cursors with one binary search each (the merge-path split of a long run
-// over neighbouring threads).  No test pays a search over items or survivors.
-// Heavy survivors past the list's capacity run where they were found, so any
-// capacity gives the same result.
+// A wavefront takes one chunk of the filter's output, a triangle per lane, reads
+// their records and finds the runs that can count and their tests.  A triangle
+// with at most LIGHT_TESTS tests is run by the wavefront.  One with more (a
+// heavy triangle) gets an entry in a list and a range of piece numbers, both
+// from one packed counter, so entries are in the order of their pieces; a second
+// kernel runs piece p (tests [4 i, 4 i + 4) of its triangle) per thread, finding
+// its entry by binary search over the entries' first pieces and starting its L2
+// and L3 cursors with one binary search each (the merge-path split of a long run
+// over neighbouring threads).  Heavy triangles past the list's capacity run where
+// they were found, so any capacity gives the same result.
 //
-// How a group runs its light tests depends on the runner.  Flat runners (the
-// per-edge counts): the lanes stage their survivors' six list spans in LDS, and
-// the group's tests, concatenated, go one per lane, so neighbouring lanes take
+// How a wavefront runs its light tests depends on the runner.  Flat runners (the
+// per-edge counts): the lanes stage their triangles' six list spans in LDS, and
+// the tests, concatenated, go one per lane, so neighbouring lanes take
 // neighbouring tests of one run and their loads coalesce; each test finds its
-// survivor by a search over 64 prefix sums in LDS and its cursors by binary
+// triangle by a search over 64 prefix sums in LDS and its cursors by binary
 // search.  Other runners (the exists-exists-exists counting, whose window
 // bookkeeping is shared by the tests of a run): each lane runs its own
-// survivor's tests in order.
+// triangle's tests in order.
 // 70M-edge graph, one year (36.8M tests) and a graph of 5,000-edge lists closed
 // by short ones (104M tests): light limit 16 / pieces of 32: 2.45 and 3.2 ms;
 // 64 / 8: 1.97 and 1.74 ms; 64 / 4: 1.85 and 1.15 ms; 64 / 2: 1.83 and 1.30 ms
@@ -944,45 +1043,54 @@ constexpr int64_t LIGHT_TESTS = 64;
 constexpr int64_t PIECE_TESTS = 4;
 
 struct Heavy {
-    int64_t slot;  // survivor slot
+    int64_t slot;  // slot in the filter's output
     int64_t first; // its first piece number
 };
-// the counter of heavy survivors: entries in bits 40-63, piece numbers in 0-39
+// the counter of heavy triangles: entries in bits 40-63, piece numbers in 0-39
 constexpr int HEAVY_SHIFT = 40;
 constexpr unsigned long long PIECE_MASK = (1ull << HEAVY_SHIFT) - 1;
 
-// the largest u in [a, b) with sbase[u] <= q (sbase ascending, sbase[a] <= q)
-__device__ inline int32_t item_of(const int64_t *__restrict__ sbase, int32_t a, int32_t b, int64_t q) {
-    int32_t lo = a, hi = b - 1;
-    while (lo < hi) {
-        const int32_t mid = (lo + hi + 1) >> 1;
-        if (sbase[mid] <= q) lo = mid;
-        else hi = mid - 1;
-    }
-    return lo;
-}
-
-// For sparse slots: gitem[g] = the item of survivor 64 g, for every group g
-// with 64 g < sbase[NI], and gitem[g] = NI - 1 for the group past the last.
-__global__ __launch_bounds__(BLK) void k_group_items(const int64_t *__restrict__ sbase, int32_t NI, int64_t ngroups,
-                                                     int32_t *__restrict__ gitem) {
-    const int64_t nsurv = sbase[NI];
-    for (int64_t g = (int64_t)blockIdx.x * BLK + threadIdx.x; g < ngroups; g += (int64_t)gridDim.x * BLK) {
-        const int64_t q0 = g * 64;
-        if (q0 >= nsurv) {
-            if (q0 - 64 < nsurv) gitem[g] = NI - 1;
-            break;
+// The filter's chunks as one sequence (a block's copy in LDS).
+struct Chunks {
+    int32_t start[MAX_REGIONS + 1]; // chunks of the regions before each, and of all
+    int32_t total;
+    // every thread of the block calls this
+    __device__ void load(const CandBuf &B) {
+        if (threadIdx.x < 64) {
+            const int lane = lane_id();
+            int32_t k = 0;
+            if (lane < B.regions) {
+                const uint32_t c = B.ctr[lane * CAND_STRIDE];
+                k = c < (uint32_t)B.per_region ? (int32_t)c : B.per_region;
+            }
+            const int32_t incl = wave_scan(k);
+            if (lane < MAX_REGIONS) start[lane + 1] = incl;
+            if (lane == 0) start[0] = 0;
+            if (lane == 63) total = incl;
         }
-        gitem[g] = item_of(sbase, 0, NI, q0);
+        __syncthreads();
     }
-}
+    // chunk g of the sequence, g < total
+    __device__ int32_t at(const CandBuf &B, int32_t g) const {
+        int r = 0; // the last region that starts at or before g (later empty ones start past it)
+#pragma unroll
+        for (int o = MAX_REGIONS / 2; o > 0; o >>= 1)
+            if (start[r + o] <= g) r += o;
+        return r * B.per_region + g - start[r];
+    }
+};
 
-// The survivor slot of dense index q in group g (q < sbase[NI]).
-__device__ inline int64_t survivor_slot(const int64_t *__restrict__ sbase, const int64_t *__restrict__ slot_base,
-                                        const int32_t *__restrict__ gitem, int64_t g, int64_t q) {
-    if (!slot_base) return q;
-    const int32_t u = item_of(sbase, gitem[g], gitem[g + 1] + 1, q);
-    return slot_base[u] + (q - sbase[u]);
+// The exact form of the filter's test on two edges: all lists' timestamps of each
+// pair of edges come within dmax (in the records' units).
+__device__ inline bool edges_meet(const TriLists &T, uint32_t dq) {
+    auto lo = [](const Span &f, const Span &b) { return !f.n ? b.lo : !b.n || f.lo < b.lo ? f.lo : b.lo; };
+    auto hi = [](const Span &f, const Span &b) { return !f.n ? b.hi : !b.n || f.hi > b.hi ? f.hi : b.hi; };
+    const uint32_t l0 = lo(T.d01, T.d10), h0 = hi(T.d01, T.d10), l1 = lo(T.d02, T.d20), h1 = hi(T.d02, T.d20),
+                   l2 = lo(T.d12, T.d21), h2 = hi(T.d12, T.d21);
+    auto meet = [dq](uint32_t xl, uint32_t xh, uint32_t yl, uint32_t yh) {
+        return (xl <= yh || xl - yh <= dq) && (yl <= xh || yl - xh <= dq);
+    };
+    return meet(l0, h0, l1, h1) && meet(l0, h0, l2, h2) && meet(l1, h1, l2, h2);
 }
 
 // list index of E_{x_a, x_b} in TriLists order (d01, d10, d02, d20, d12, d21)
@@ -1036,6 +1144,55 @@ __device__ inline bool flat_run(const FlatLds<SHORT> &F, int si, int k, int64_t 
     return true;
 }
 
+// The three lists of run k (order of tri_live's bits) under a predicate code, as
+// indices in list_id's order: run k's own list is number k; the others sit three
+// bits each in two words, the same for every lane.
+struct RunLists {
+    uint32_t l2, l3;
+};
+__device__ inline RunLists run_list_ids(int variant) {
+    // for run (I, J) with third vertex C: the lists I -> C, C -> I, J -> C, C -> J
+    constexpr int RI[6] = {0, 1, 0, 2, 1, 2}, RJ[6] = {1, 0, 2, 0, 2, 1};
+    uint32_t ic = 0, ci = 0, jc = 0, cj = 0;
+#pragma unroll
+    for (int k = 0; k < 6; k++) {
+        const int C = 3 - RI[k] - RJ[k];
+        ic |= (uint32_t)list_id(RI[k], C) << (3 * k);
+        ci |= (uint32_t)list_id(C, RI[k]) << (3 * k);
+        jc |= (uint32_t)list_id(RJ[k], C) << (3 * k);
+        cj |= (uint32_t)list_id(C, RJ[k]) << (3 * k);
+    }
+    const bool swap = (variant & 4) != 0; // L2 hangs off J, L3 off I
+    const uint32_t x = (variant & 1) ? (swap ? cj : ci) : (swap ? jc : ic);
+    const uint32_t y = (variant & 2) ? (swap ? ci : cj) : (swap ? ic : jc);
+    return RunLists{x, y};
+}
+
+// test r of triangle si's live runs, from the staged spans, for a predicate code
+// read at run time
+template <class Op>
+__device__ inline void flat_run_rt(const FlatLds<false> &F, const RunLists &R, int si, int32_t r,
+                                   const int64_t *__restrict__ ts, const Op &op) {
+    uint32_t live = F.live[si];
+    while (live) {
+        const int k = __ffs((int)live) - 1;
+        live &= live - 1;
+        const int32_t n1 = F.ln[k][si];
+        if (r >= n1) {
+            r -= n1;
+            continue;
+        }
+        const int i2 = (int)(R.l2 >> (3 * k)) & 7, i3 = (int)(R.l3 >> (3 * k)) & 7;
+        Span l2{}, l3{};
+        l2.s = F.ls[i2][si];
+        l2.n = F.ln[i2][si];
+        l3.s = F.ls[i3][si];
+        l3.n = F.ln[i3][si];
+        op(ts, F.ls[k][si] + r, 1, l2, l3);
+        return;
+    }
+}
+
 // Runs the tests of the per-edge counts: work() is a survivor's number of
 // tests, run() takes tests [r, k1) of it in order, flat() its test r alone,
 // from the spans stage() put in LDS.
@@ -1058,13 +1215,6 @@ template <int VAR, class Op, bool SS> struct CountRunner {
         int64_t k = r;
         chunk_runs<VAR, Op, SS>(L, dq, ts, r, k, k1, op);
     }
-    // the runs that can count, as bits in the order of chunk_runs
-    __device__ inline uint32_t live(const TriLists &L) const {
-        Span a, b, c;
-        return (uint32_t)run_lists<VAR, 0, 1>(L, dq, a, b, c) | (uint32_t)run_lists<VAR, 1, 0>(L, dq, a, b, c) << 1 |
-               (uint32_t)run_lists<VAR, 0, 2>(L, dq, a, b, c) << 2 | (uint32_t)run_lists<VAR, 2, 0>(L, dq, a, b, c) << 3 |
-               (uint32_t)run_lists<VAR, 1, 2>(L, dq, a, b, c) << 4 | (uint32_t)run_lists<VAR, 2, 1>(L, dq, a, b, c) << 5;
-    }
     __device__ inline void stage(Flat &F, int lane, const TriLists &T, bool light) const {
         const Span *sp[6] = {&T.d01, &T.d10, &T.d02, &T.d20, &T.d12, &T.d21};
 #pragma unroll
@@ -1076,7 +1226,7 @@ template <int VAR, class Op, bool SS> struct CountRunner {
                 F.hi[k][lane] = sp[k]->hi;
             }
         }
-        F.live[lane] = light ? live(T) : 0u;
+        F.live[lane] = light ? tri_live<VAR>(T, dq) : 0u;
     }
     __device__ inline void flat(const Flat &F, int si, int64_t r) const {
         flat_run<VAR, 0, 1, SS>(F, si, 0, r, ts, op) || flat_run<VAR, 1, 0, SS>(F, si, 1, r, ts, op) ||
@@ -1115,55 +1265,118 @@ __device__ inline void defer_heavy(R &runner, const typename R::Surv &S, int64_t
     else runner.run(S, slot, 0, w);
 }
 
+// A wavefront's group of chunks as a dense sequence of slots: narrow windows
+// leave most chunks with an entry or two, and their triangles are taken 64 at a
+// time across chunks.  Groups of up to 64 chunks, fewer when that would leave
+// less than GROUPS_WANTED groups.
+constexpr int32_t GROUPS_WANTED = 16384;
+__device__ inline int32_t group_chunks(int32_t total) {
+    const int32_t k = total / GROUPS_WANTED;
+    return k < 1 ? 1 : k > 64 ? 64 : k;
+}
+struct GroupLds {
+    int32_t incl[64];  // slots of the group's chunks up to this one
+    int32_t chunk[64];
+};
+// chunks [g0, g1) of the sequence into the LDS; returns their slots
+__device__ inline int32_t stage_group(const CandBuf &B, const Chunks &C, int32_t g0, int32_t g1, GroupLds &L) {
+    const int lane = lane_id();
+    int32_t n = 0;
+    if (lane < g1 - g0) {
+        const int32_t chunk = C.at(B, g0 + lane);
+        L.chunk[lane] = chunk;
+        n = B.cnt[chunk];
+    }
+    const int32_t incl = wave_scan(n);
+    L.incl[lane] = incl;
+    wave_sync();
+    return __builtin_amdgcn_readlane(incl, 63);
+}
+// slot number q of a staged group
+__device__ inline int64_t group_slot(const GroupLds &L, int32_t q) {
+    int a = 0, b = 63;
+    while (a < b) {
+        const int mid = (a + b) >> 1;
+        if (L.incl[mid] > q) b = mid;
+        else a = mid + 1;
+    }
+    return (int64_t)L.chunk[a] * 64 + (q - (a ? L.incl[a - 1] : 0));
+}
+
+// totals[0] += the tests of every triangle, totals[1] += the triangles (one atomic each per block)
 template <class R>
-__global__ __launch_bounds__(BLK) void k_tests_light(const int64_t *__restrict__ sbase,
-                                                     const int64_t *__restrict__ slot_base,
-                                                     const int32_t *__restrict__ gitem, int32_t NI, R runner,
-                                                     Heavy *__restrict__ heavy,
-                                                     unsigned long long *__restrict__ counter, int64_t cap) {
+__global__ __launch_bounds__(BLK) void k_tests_light(CandBuf B, R runner, Heavy *__restrict__ heavy,
+                                                     unsigned long long *__restrict__ counter, int64_t cap,
+                                                     unsigned long long *__restrict__ totals) {
     __shared__ typename R::Flat flds[R::kFlat ? WPB : 1];
+    __shared__ GroupLds glds[WPB];
+    __shared__ Chunks C;
+    __shared__ unsigned long long s_tests[WPB];
+    __shared__ int32_t s_kept[WPB];
     const int w = wave_id();
     const int lane = lane_id();
-    const int64_t nsurv = sbase[NI];
-    const int64_t ng = (nsurv + 63) / 64;
+    C.load(B);
+    const int32_t per = group_chunks(C.total);
     bool full = false;
-    for (int64_t g = (int64_t)blockIdx.x * WPB + w; g < ng; g += (int64_t)gridDim.x * WPB) {
-        const int64_t q = g * 64 + lane;
-        const bool on = q < nsurv;
-        int64_t slot = 0, wk = 0, np = 0;
-        typename R::Surv S{};
-        if (on) {
-            slot = survivor_slot(sbase, slot_base, gitem, g, q);
-            S = runner.load(slot);
-            wk = runner.work(S);
-            if (wk > LIGHT_TESTS) np = (wk + PIECE_TESTS - 1) / PIECE_TESTS;
-        }
-        defer_heavy(runner, S, slot, wk, np, heavy, counter, cap, full);
-        const int64_t light = np ? 0 : wk;
-        if constexpr (R::kFlat) {
-            typename R::Flat &F = flds[w];
-            const int32_t incl = (int32_t)wave_inclusive_sum(light);
-            const int32_t total = __shfl(incl, 63);
-            if (total == 0) continue;
-            F.incl[lane] = incl;
-            runner.stage(F, lane, S, light != 0);
-            wave_sync();
-            for (int32_t t = lane; t < total; t += 64) {
-                // the survivor whose tests hold t: the first si with incl[si] > t
-                int a = 0, b = 63;
-                while (a < b) {
-                    const int mid = (a + b) >> 1;
-                    if (F.incl[mid] > t) b = mid;
-                    else a = mid + 1;
-                }
-                runner.flat(F, a, (int64_t)(t - (a ? F.incl[a - 1] : 0)));
+    int64_t mine = 0;
+    int32_t kept = 0;
+    for (int64_t g0 = ((int64_t)blockIdx.x * WPB + w) * per; g0 < C.total; g0 += (int64_t)gridDim.x * WPB * per) {
+        const int32_t slots = stage_group(B, C, (int32_t)g0, (int32_t)(g0 + per < C.total ? g0 + per : C.total), glds[w]);
+        kept += slots;
+        for (int32_t q0 = 0; q0 < slots; q0 += 64) {
+            const bool on = q0 + lane < slots;
+            int64_t slot = 0, wk = 0, np = 0;
+            typename R::Surv S{};
+            if (on) {
+                slot = group_slot(glds[w], q0 + lane);
+                S = runner.load(slot);
+                if (edges_meet(S, runner.dq)) wk = runner.work(S);
+                if (wk > LIGHT_TESTS) np = (wk + PIECE_TESTS - 1) / PIECE_TESTS;
             }
-            wave_sync(); // the LDS is rewritten by the next group
-        } else {
-            if (light) runner.run(S, slot, 0, light);
+            mine += wk;
+            defer_heavy(runner, S, slot, wk, np, heavy, counter, cap, full);
+            const int64_t light = np ? 0 : wk;
+            if constexpr (R::kFlat) {
+                typename R::Flat &F = flds[w];
+                const int32_t incl = wave_scan((int32_t)light);
+                const int32_t total = __builtin_amdgcn_readlane(incl, 63);
+                if (total == 0) continue;
+                F.incl[lane] = incl;
+                runner.stage(F, lane, S, light != 0);
+                wave_sync();
+                for (int32_t t = lane; t < total; t += 64) {
+                    // the triangle whose tests hold t: the first si with incl[si] > t
+                    int a = 0, b = 63;
+                    while (a < b) {
+                        const int mid = (a + b) >> 1;
+                        if (F.incl[mid] > t) b = mid;
+                        else a = mid + 1;
+                    }
+                    runner.flat(F, a, (int64_t)(t - (a ? F.incl[a - 1] : 0)));
+                }
+                wave_sync(); // the LDS is rewritten by the next triangles
+            } else {
+                if (light) runner.run(S, slot, 0, light);
+            }
         }
+        wave_sync(); // the group's LDS is rewritten by the next group
     }
     runner.finish();
+    for (int o = 32; o > 0; o >>= 1) mine += __shfl_xor(mine, o);
+    if (lane == 0) {
+        s_tests[w] = (unsigned long long)mine;
+        s_kept[w] = kept;
+    }
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        unsigned long long t = 0, k = 0;
+        for (int i = 0; i < WPB; i++) {
+            t += s_tests[i];
+            k += (unsigned long long)s_kept[i];
+        }
+        if (t) atomicAdd(&totals[0], t);
+        if (k) atomicAdd(&totals[1], k);
+    }
 }
 
 template <class R>
@@ -1207,47 +1420,47 @@ inline int64_t max_heavy() {
     return v;
 }
 
-// Entries a query's heavy list holds: no more than its tests can fill (when
-// known), and at most one per survivor (at least MIN_HEAVY, at most the limit),
-// so that 16 * heavy_slots(T, -1) bounds the list's memory on a graph of T
-// triangles.
-inline int64_t heavy_slots(int64_t survivors, int64_t tests) {
-    int64_t b = std::max<int64_t>(survivors + 1, MIN_HEAVY);
-    if (tests >= 0) b = std::min<int64_t>(b, tests / (LIGHT_TESTS + 1) + 1);
-    return std::max<int64_t>(1, std::min<int64_t>(b, max_heavy()));
+// Entries a query's heavy list holds: at most one per slot of the filter's
+// output (at least MIN_HEAVY, at most the limit).
+inline int64_t heavy_slots(int64_t slots) {
+    return std::max<int64_t>(1, std::min<int64_t>(std::max<int64_t>(slots + 1, MIN_HEAVY), max_heavy()));
 }
 
-// The tests of the survivors of the last filter (see k_tests_light): survivors is
-// their number, or an upper bound when the filter ran in one pass; tests is
-// their number of tests, or < 0 when unknown on the host.
+// The tests of the triangles the last filter kept (see k_tests_light): chunks is
+// the number of its chunks, or an upper bound.
 template <class R>
-void launch_tests(const Index &ix, Workspace &ws, const R &runner, int64_t survivors, int64_t tests, hipStream_t s) {
-    const int64_t cap = heavy_slots(survivors, tests);
+void launch_tests(Workspace &ws, const CandBuf &B, const R &runner, int64_t chunks, hipStream_t s) {
+    // any capacity gives the same result: a fixed scratch keeps it small
+    const int64_t cap = heavy_slots(arena_left() >= 0 ? 0 : 64 * chunks);
     ws.pieces.ensure(sizeof(Heavy) * (size_t)cap);
-    ws.scal.ensure(128);
-    unsigned long long *np = ws.scal.as<unsigned long long>() + 14;
-    k_fill<unsigned long long><<<1, 1, 0, s>>>(np, 0ull, 1);
+    unsigned long long *np = ws.scal.as<unsigned long long>() + SCAL_HEAVY;
+    const unsigned lb = (unsigned)std::max<int64_t>(1, std::min<int64_t>((chunks + WPB - 1) / WPB, LIGHT_BLOCKS));
+    k_tests_light<<<lb, BLK, 0, s>>>(B, runner, ws.pieces.as<Heavy>(), np, cap,
+                                     ws.scal.as<unsigned long long>() + SCAL_TESTS);
     FOLTY_LAUNCHED();
-    const int64_t groups = (survivors + 63) / 64; // an upper bound when survivors is one
-    const int64_t *sparse = ws.slots == ws.sbase.as<int64_t>() ? nullptr : ws.slots;
-    if (sparse) {
-        ws.gitem.ensure(4 * ((size_t)groups + 2));
-        const unsigned gb = (unsigned)std::max<int64_t>(1, std::min<int64_t>((groups + 1 + BLK - 1) / BLK, LIGHT_BLOCKS));
-        k_group_items<<<gb, BLK, 0, s>>>(ws.sbase.as<int64_t>(), ix.NI, groups + 1, ws.gitem.as<int32_t>());
-        FOLTY_LAUNCHED();
-    }
-    const unsigned lb = (unsigned)std::max<int64_t>(1, std::min<int64_t>((groups + WPB - 1) / WPB, LIGHT_BLOCKS));
-    k_tests_light<<<lb, BLK, 0, s>>>(ws.sbase.as<int64_t>(), sparse, ws.gitem.as<int32_t>(), ix.NI, runner,
-                                     ws.pieces.as<Heavy>(), np, cap);
-    FOLTY_LAUNCHED();
-    // the pieces are numbered on the device; with the tests known, no more
-    // threads than pieces
-    const int64_t most = tests >= 0 ? tests / PIECE_TESTS + std::min<int64_t>(cap, tests / (LIGHT_TESTS + 1)) + 1
-                                    : (int64_t)PIECE_BLOCKS * BLK;
-    const unsigned pb = (unsigned)std::max<int64_t>(1, std::min<int64_t>((most + BLK - 1) / BLK, PIECE_BLOCKS));
+    // the pieces are numbered on the device
+    const unsigned pb = (unsigned)std::max<int64_t>(1, std::min<int64_t>(chunks * 16, PIECE_BLOCKS));
     k_tests_pieces<<<pb, BLK, 0, s>>>(ws.pieces.as<Heavy>(), np, cap, runner);
     FOLTY_LAUNCHED();
 }
 
+inline EnumGraph enum_graph(const Index &ix) {
+    return EnumGraph{ix.item.as<EnumItem>(), ix.oadj.as<int32_t>(),  ix.seg.as<int4>(),
+                     ix.srng.as<uint2>(),    ix.owner.as<int32_t>(), ix.ooff.as<int32_t>(),
+                     ix.n <= (1 << 22)};
+}
+
+// Chunks that hold every triangle of a graph, `waves` wavefronts filling them: a
+// wavefront leaves at most one chunk partly filled, and none empty.
+inline int64_t most_chunks(int64_t triangles, int64_t waves) { return std::min(triangles, triangles / 64 + waves); }
+constexpr int64_t CHUNK_BYTES = 3 * 4 * 64 + 4;
 } // namespace
+
+// query.hip: the single-query filter and its scalars
+void clear_query(const Index &ix, Workspace &ws, bool counts, hipStream_t s);
+void read_scalars(Workspace &ws, hipStream_t s);
+int64_t chunks_taken(const Workspace &ws, const CandBuf &B);
+CandBuf filter_triangles(Index &ix, int variant, int64_t dmax, Workspace &ws, hipStream_t s, bool one_pass);
+void after_filter(Index &ix, Workspace &ws, int64_t delta, bool one_pass);
+
 } // namespace folty

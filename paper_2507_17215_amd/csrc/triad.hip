@@ -177,32 +177,36 @@ template <int VAR, bool INST> struct TriadRunner {
     }
 };
 
-// The survivors of item u sit in slots [base[u], base[u] + su[u]): per-item
-// slots of the one-pass filter (sparse over all triangles) or the compact slots
-// of the two-pass one.  The passes below touch only those slots; slot p's bits
-// are byte p of the flag array.
-__global__ __launch_bounds__(BLK) void k_triad_clear(const int64_t *__restrict__ base, const int32_t *__restrict__ su,
-                                                     int32_t NI, uint8_t *__restrict__ flag8) {
-    for (int64_t u = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; u < NI; u += (int64_t)gridDim.x * blockDim.x) {
-        const int64_t p0 = base[u], p1 = p0 + su[u];
-        for (int64_t p = p0; p < p1; p++) flag8[p] = 0;
+// The passes below go over the chunks of triangles the filter kept, a wavefront
+// per chunk; slot p's bits are byte p of the flag array.
+__global__ __launch_bounds__(BLK) void k_triad_clear(CandBuf B, uint32_t *__restrict__ flag) {
+    __shared__ Chunks C;
+    C.load(B);
+    for (int32_t g = (int32_t)blockIdx.x * WPB + wave_id(); g < C.total; g += (int32_t)gridDim.x * WPB) {
+        const int32_t chunk = __builtin_amdgcn_readfirstlane(C.at(B, g));
+        if (lane_id() < 16) flag[(int64_t)chunk * 16 + lane_id()] = 0;
     }
 }
 
-// solutions per item (optional) and their total
-__global__ __launch_bounds__(BLK) void k_triad_count(const int64_t *__restrict__ base, const int32_t *__restrict__ su,
-                                                     int32_t NI, const uint8_t *__restrict__ flag8,
-                                                     int32_t *__restrict__ icnt, unsigned long long *total) {
+// solutions of a chunk's triangles
+__device__ inline uint32_t slot_bits(const CandBuf &B, const uint8_t *__restrict__ flag8, int32_t chunk) {
+    return lane_id() < B.cnt[chunk] ? flag8[(int64_t)chunk * 64 + lane_id()] & 0x3fu : 0u;
+}
+
+// solutions per chunk, in the chunks' sequence (optional), and their total
+__global__ __launch_bounds__(BLK) void k_triad_count(CandBuf B, const uint8_t *__restrict__ flag8,
+                                                     int32_t *__restrict__ ccnt, unsigned long long *total) {
+    __shared__ Chunks C;
+    C.load(B);
     unsigned long long c = 0;
-    for (int64_t u = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; u < NI; u += (int64_t)gridDim.x * blockDim.x) {
-        const int64_t p0 = base[u], p1 = p0 + su[u];
-        int32_t x = 0;
-        for (int64_t p = p0; p < p1; p++) x += __popc(flag8[p] & 0x3fu);
-        if (icnt) icnt[u] = x;
-        c += (unsigned)x;
+    for (int32_t g = (int32_t)blockIdx.x * WPB + wave_id(); g < C.total; g += (int32_t)gridDim.x * WPB) {
+        const int32_t x = wave_scan(__popc(slot_bits(B, flag8, __builtin_amdgcn_readfirstlane(C.at(B, g)))));
+        if (lane_id() == 63) {
+            if (ccnt) ccnt[g] = x;
+            c += (unsigned)x;
+        }
     }
-    for (int off = 32; off > 0; off >>= 1) c += __shfl_xor(c, off);
-    if (lane_id() == 0 && c) atomicAdd(total, c);
+    if (total && lane_id() == 63 && c) atomicAdd(total, c);
 }
 
 // the endpoints (original ids) of oriented edge q: tail, head
@@ -215,34 +219,35 @@ __device__ inline void oriented_ends(const uint32_t *__restrict__ oeid, const in
     head = (x >> 31) ? hi : lo;
 }
 
-// each set bit as (w, its index, pair key a n + b), from the item's offset
-__global__ __launch_bounds__(BLK) void k_triad_emit(const int64_t *__restrict__ base, const int32_t *__restrict__ su,
-                                                    int32_t NI, const int64_t *__restrict__ ioff,
-                                                    const uint8_t *__restrict__ flag8, const int32_t *__restrict__ sv,
+// each set bit as (w, its index, pair key a n + b), from the chunk's offset
+__global__ __launch_bounds__(BLK) void k_triad_emit(CandBuf B, const int64_t *__restrict__ coff,
+                                                    const uint8_t *__restrict__ flag8,
                                                     const uint32_t *__restrict__ oeid, const int32_t *__restrict__ slo,
                                                     const int32_t *__restrict__ shi, int64_t n,
                                                     uint32_t *__restrict__ wkey, int32_t *__restrict__ idx,
                                                     unsigned long long *__restrict__ pkey) {
-    const int64_t u = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (u >= NI) return;
-    const int64_t p0 = base[u], p1 = p0 + su[u];
-    int64_t o = ioff[u];
-    for (int64_t p = p0; p < p1; p++) {
-        const uint32_t bits = flag8[p] & 0x3fu;
+    __shared__ Chunks C;
+    C.load(B);
+    for (int32_t g = (int32_t)blockIdx.x * WPB + wave_id(); g < C.total; g += (int32_t)gridDim.x * WPB) {
+        const int32_t chunk = __builtin_amdgcn_readfirstlane(C.at(B, g));
+        const uint32_t bits = slot_bits(B, flag8, chunk);
+        const int32_t mine = __popc(bits);
+        int64_t o = coff[g] + wave_scan(mine) - mine;
         if (!bits) continue;
+        const int32_t *e = B.sv + 3 * ((int64_t)chunk * 64 + lane_id());
         int32_t x0, x1, x2, t;
-        oriented_ends(oeid, slo, shi, sv[3 * p], x0, x1);
-        oriented_ends(oeid, slo, shi, sv[3 * p + 1], t, x2);
+        oriented_ends(oeid, slo, shi, e[0], x0, x1);
+        oriented_ends(oeid, slo, shi, e[1], t, x2);
         // run -> (a, b, w): (x0,x1,x2) (x1,x0,x2) (x0,x2,x1) (x2,x0,x1) (x1,x2,x0) (x2,x1,x0)
         const int32_t A[6] = {x0, x1, x0, x2, x1, x2};
-        const int32_t B[6] = {x1, x0, x2, x0, x2, x1};
+        const int32_t Bv[6] = {x1, x0, x2, x0, x2, x1};
         const int32_t W[6] = {x2, x2, x1, x1, x0, x0};
 #pragma unroll
         for (int run = 0; run < 6; run++) {
             if (!((bits >> run) & 1u)) continue;
             wkey[o] = (uint32_t)W[run];
             idx[o] = (int32_t)o;
-            pkey[o] = (unsigned long long)A[run] * (unsigned long long)n + (unsigned long long)B[run];
+            pkey[o] = (unsigned long long)A[run] * (unsigned long long)n + (unsigned long long)Bv[run];
             o++;
         }
     }
@@ -275,28 +280,30 @@ void check_triad(const Graph *g, const folty_triad_query &q) {
         if (q.reserved[i]) fail(FOLTY_EINVAL, "reserved fields of the triad query must be 0");
 }
 
-// the listed triples, sorted by (a, b, w), copied to res->trip
-void list_triples(const Index &ix, const Workspace &ws, int64_t nsol, Result *res, hipStream_t s) {
+unsigned chunk_grid(int64_t chunks) {
+    return (unsigned)std::max<int64_t>(1, std::min<int64_t>((chunks + WPB - 1) / WPB, PERSIST_BLOCKS));
+}
+
+// the listed triples, sorted by (a, b, w), copied to res->trip; the filter took
+// `chunks` chunks
+void list_triples(const Index &ix, const Workspace &ws, const CandBuf &B, int64_t chunks, int64_t nsol, Result *res,
+                  hipStream_t s) {
     if (nsol > INT32_MAX) fail(FOLTY_EOVERFLOW, "%lld solution triples exceed the listing limit of 2^31 - 1",
                                (long long)nsol);
-    const int32_t NI = ix.NI;
-    DevBuf icnt, ioff, wk, ix0, pk, wk2, ix2, pk2, trip;
-    icnt.ensure(4 * (size_t)NI + 4);
-    ioff.ensure(8 * (size_t)NI + 8);
-    unsigned long long *dummy = ws.scal.as<unsigned long long>() + 12;
-    k_fill<unsigned long long><<<1, 1, 0, s>>>(dummy, 0ull, 1);
-    k_triad_count<<<grid_for(NI, BLK, PERSIST_BLOCKS), BLK, 0, s>>>(ws.slots, ws.su.as<int32_t>(), NI,
-                                                                     ws.tflag.as<uint8_t>(), icnt.as<int32_t>(), dummy);
+    DevBuf ccnt, coff, wk, ix0, pk, wk2, ix2, pk2, trip;
+    ccnt.ensure(4 * (size_t)chunks + 4);
+    coff.ensure(8 * (size_t)chunks + 8);
+    k_triad_count<<<chunk_grid(chunks), BLK, 0, s>>>(B, ws.tflag.as<uint8_t>(), ccnt.as<int32_t>(), nullptr);
     FOLTY_LAUNCHED();
     DevBuf cub;
-    size_t need = exclusive_scan_i32_to_i64(nullptr, 0, icnt.as<int32_t>(), ioff.as<int64_t>(), NI, s);
+    size_t need = exclusive_scan_i32_to_i64(nullptr, 0, ccnt.as<int32_t>(), coff.as<int64_t>(), chunks, s);
     const size_t k = (size_t)nsol;
     const int endw = std::max(1, bit_length((uint64_t)ix.n - 1));
     const int endp = std::max(1, bit_length((uint64_t)ix.n * (uint64_t)ix.n - 1));
     need = std::max(need, sort_pairs_u32_i32(nullptr, 0, nullptr, nullptr, nullptr, nullptr, (int64_t)k, endw, s));
     need = std::max(need, sort_pairs_u64_i32(nullptr, 0, nullptr, nullptr, nullptr, nullptr, (int64_t)k, endp, s));
     cub.ensure(need);
-    exclusive_scan_i32_to_i64(cub.p, need, icnt.as<int32_t>(), ioff.as<int64_t>(), NI, s);
+    exclusive_scan_i32_to_i64(cub.p, need, ccnt.as<int32_t>(), coff.as<int64_t>(), chunks, s);
     wk.ensure(4 * k);
     ix0.ensure(4 * k);
     pk.ensure(8 * k);
@@ -304,10 +311,10 @@ void list_triples(const Index &ix, const Workspace &ws, int64_t nsol, Result *re
     ix2.ensure(4 * k);
     pk2.ensure(8 * k);
     trip.ensure(12 * k);
-    k_triad_emit<<<grid_for(NI, BLK), BLK, 0, s>>>(ws.slots, ws.su.as<int32_t>(), NI, ioff.as<int64_t>(),
-                                                   ws.tflag.as<uint8_t>(), ws.sv.as<int32_t>(), ix.oeid.as<uint32_t>(),
-                                                   ix.slo.as<int32_t>(), ix.shi.as<int32_t>(), ix.n, wk.as<uint32_t>(),
-                                                   ix0.as<int32_t>(), pk.as<unsigned long long>());
+    k_triad_emit<<<chunk_grid(chunks), BLK, 0, s>>>(B, coff.as<int64_t>(), ws.tflag.as<uint8_t>(),
+                                                    ix.oeid.as<uint32_t>(), ix.slo.as<int32_t>(), ix.shi.as<int32_t>(),
+                                                    ix.n, wk.as<uint32_t>(), ix0.as<int32_t>(),
+                                                    pk.as<unsigned long long>());
     FOLTY_LAUNCHED();
     // by w, then stably by the pair key: (a, b, w) order
     sort_pairs_u32_i32(cub.p, need, wk.as<uint32_t>(), wk2.as<uint32_t>(), ix0.as<int32_t>(), ix2.as<int32_t>(),
@@ -338,13 +345,9 @@ Result *run_triad_query(Graph *g, const folty_triad_query &q, Workspace &ws) {
     res->triad = true;
     res->device = g->device;
     ws.ensure_events();
-    ws.scal.ensure(128);
-    ws.host.ensure(64);
     FOLTY_HIP(hipEventRecord(ws.ev[0], s));
-    // [0] temporal triangles, [1] overflow, [2] solutions ([8, 12) belong to the filter)
-    unsigned long long *tot = ws.scal.as<unsigned long long>();
-    k_fill<unsigned long long><<<1, 4, 0, s>>>(tot, 0ull, 4);
-    FOLTY_LAUNCHED();
+    clear_query(ix, ws, false, s);
+    unsigned long long *tot = ws.scal.as<unsigned long long>() + SCAL_TRIAD; // triangles, overflow, solutions
     if (edge) {
         // counted straight into input order (self-loops keep their 0)
         ws.tinst.ensure(8 * (size_t)ix.m_input + 8);
@@ -354,17 +357,16 @@ Result *run_triad_query(Graph *g, const folty_triad_query &q, Workspace &ws) {
             FOLTY_LAUNCHED();
         }
     }
-    int64_t tests = 0, tri = 0, slots = 0;
-    ws.filter_passes = 0;
+    const bool one = ix.one_pass_at(q.delta);
+    CandBuf B{};
+    FOLTY_HIP(hipEventRecord(ws.ev[4], s));
     if (ix.NI > 0) {
-        int64_t known = -1;
-        const bool one = q.delta >= ix.one_pass_from.load(std::memory_order_relaxed);
-        slots = find_survivors(ix, q.variant, q.delta, ws, s, ws.ev[4], ws.ev[5], &tri, &known, false, one);
-        if (slots > 0) {
-            const int64_t nw = (slots + 3) / 4;
-            ws.tflag.ensure(4 * (size_t)nw);
-            k_triad_clear<<<grid_for(ix.NI, BLK, PERSIST_BLOCKS), BLK, 0, s>>>(ws.slots, ws.su.as<int32_t>(), ix.NI,
-                                                                                ws.tflag.as<uint8_t>());
+        B = filter_triangles(ix, q.variant, q.delta, ws, s, one);
+        FOLTY_HIP(hipEventRecord(ws.ev[5], s));
+        const int64_t chunks = ws.kept_chunks;
+        if (chunks > 0) {
+            ws.tflag.ensure(64 * (size_t)B.regions * (size_t)B.per_region);
+            k_triad_clear<<<chunk_grid(chunks), BLK, 0, s>>>(B, ws.tflag.as<uint32_t>());
             FOLTY_LAUNCHED();
             TriadOut o{q.delta, ws.tflag.as<uint32_t>(), edge ? ws.tinst.as<unsigned long long>() : nullptr,
                        ix.perm.as<int32_t>()};
@@ -373,34 +375,28 @@ Result *run_triad_query(Graph *g, const folty_triad_query &q, Workspace &ws) {
                 constexpr int VAR = decltype(V)::value;
                 const int32_t *sv = ws.sv.as<int32_t>();
                 const EdgeRec *rec = ix.rec.as<EdgeRec>();
-                if (inst)
-                    launch_tests(ix, ws, TriadRunner<VAR, true>{dq, ix.ts.as<int64_t>(), o, tot, sv, rec}, slots, known,
-                                 s);
-                else
-                    launch_tests(ix, ws, TriadRunner<VAR, false>{dq, ix.ts.as<int64_t>(), o, tot, sv, rec}, slots,
-                                 known, s);
+                if (inst) launch_tests(ws, B, TriadRunner<VAR, true>{dq, ix.ts.as<int64_t>(), o, tot, sv, rec}, chunks, s);
+                else launch_tests(ws, B, TriadRunner<VAR, false>{dq, ix.ts.as<int64_t>(), o, tot, sv, rec}, chunks, s);
             });
             FOLTY_LAUNCHED();
-            k_triad_count<<<grid_for(ix.NI, BLK, PERSIST_BLOCKS), BLK, 0, s>>>(ws.slots, ws.su.as<int32_t>(), ix.NI,
-                                                                                ws.tflag.as<uint8_t>(), nullptr, tot + 2);
+            k_triad_count<<<chunk_grid(chunks), BLK, 0, s>>>(B, ws.tflag.as<uint8_t>(), nullptr, tot + 2);
             FOLTY_LAUNCHED();
-            FOLTY_HIP(hipMemcpyAsync(&tests, ws.wbase.as<int64_t>() + ix.NI, 8, hipMemcpyDeviceToHost, s));
         }
     } else {
-        FOLTY_HIP(hipEventRecord(ws.ev[4], s));
         FOLTY_HIP(hipEventRecord(ws.ev[5], s));
     }
-    if (ix.T < 0) ix.T = tri;
     FOLTY_HIP(hipEventRecord(ws.ev[2], s));
-    unsigned long long *h = ws.host.as<unsigned long long>();
-    FOLTY_HIP(hipMemcpyAsync(h, tot, 24, hipMemcpyDeviceToHost, s));
+    read_scalars(ws, s);
     FOLTY_HIP(hipStreamSynchronize(s));
+    if (ix.NI > 0) after_filter(ix, ws, q.delta, one);
+    else ix.T = 0;
+    const unsigned long long *h = ws.host.as<unsigned long long>() + SCAL_TRIAD;
     if (h[1] || h[0] > (unsigned long long)INT64_MAX)
         fail(FOLTY_EOVERFLOW, "the temporal triangles number 2^63 or more");
     res->n_triads = (int64_t)h[2];
     res->n_tinst = inst ? (int64_t)h[0] : -1;
     if ((q.flags & FOLTY_TRIAD_TRIPLES) && res->n_triads > 0)
-        list_triples(ix, ws, res->n_triads, res.get(), s);
+        list_triples(ix, ws, B, chunks_taken(ws, B), res->n_triads, res.get(), s);
     FOLTY_HIP(hipEventRecord(ws.ev[3], s));
     if (edge) {
         res->tinst.resize((size_t)ix.m_input);
@@ -410,13 +406,12 @@ Result *run_triad_query(Graph *g, const folty_triad_query &q, Workspace &ws) {
     }
     FOLTY_HIP(hipStreamSynchronize(s));
     fill_stats_from_index(ix, &res->stats);
-    res->stats.tests = tests;
+    res->stats.tests = (int64_t)ws.host.as<unsigned long long>()[SCAL_TESTS];
     res->stats.wedge_ms = ev_ms(ws.ev[4], ws.ev[5]);
     res->stats.temporal_ms = ev_ms(ws.ev[5], ws.ev[2]);
     res->stats.threshold_ms = ev_ms(ws.ev[2], ws.ev[3]);
     res->stats.query_ms = ev_ms(ws.ev[0], ws.ev[3]);
-    res->stats.filter_passes = ws.filter_passes;
-    maybe_one_pass(g, ws, q.delta);
+    res->stats.filter_passes = ix.NI > 0 ? ws.filter_passes : 0;
     return res.release();
 }
 

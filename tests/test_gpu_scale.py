@@ -115,3 +115,59 @@ def test_wide_timestamps_tiny_workload_all_query_kinds():
         r = G.query(d, (1, 4), 0, one_pass=True)
         assert r.stats["filter_passes"] == 1
         assert_same(r, o.query(d, 1, 4, 0))
+
+
+def test_filter_output_larger_than_its_first_chunks():
+    """A complete graph of 400 vertices has 10.6M triangles; with every edge at the
+    same time all of them pass the filter, more than the 4.2M its chunks hold at
+    first, so the pass is repeated with chunks that suffice.  A second query finds
+    them large enough, and the same graph as a plan holds every triangle at once.
+    All equal the closed form: 398 third vertices for a transitive edge order."""
+    n = 400
+    src, dst = (x.astype(np.int32) for x in np.triu_indices(n, 1))
+    t = np.full(src.size, 1000, np.int64)
+    G = folty.Graph(n, src, dst, t).build()
+    # edges run from lower to higher id: (a, b, w) needs a -> w and b -> w, so w > b
+    want = (n - 1 - dst).astype(np.uint32)
+    for one in (False, True, False):
+        say("complete graph", one)
+        r = G.query(0, (1, 4), 0, one_pass=one)
+        assert np.array_equal(r.counts(), want)
+        assert r.stats["triangles"] == n * (n - 1) * (n - 2) // 6
+    say("complete graph: fresh index, triples")
+    G2 = folty.Graph(n, src, dst, t).build()
+    assert G2.triad_query(0, 0, triples=False).triads()["n_instances"] == n * (n - 1) * (n - 2) // 6
+    say("complete graph: plan")
+    plan = folty.Plan([G, G2], [(0, dict(delta=0, theta=(1, 4))), (1, dict(delta=5, theta=(1, 2), variant=3))])
+    r0, r1 = plan.run()
+    assert np.array_equal(r0.counts(), want)
+    assert np.array_equal(r1.counts(), src.astype(np.uint32))  # w -> a and w -> b: w < a
+
+
+@pytest.mark.parametrize("d", [1, 4, 5, 63, 64, 65, 127, 128, 129, 255, 256, 257, 510, 511, 512, 513, 600])
+def test_enumeration_at_row_length_edges(d):
+    """Owner rows of up to d entries, probed from segments of every length below d:
+    table sizes, the last staged row length and the first long one, items of one
+    owner and of several (few probes each).  Random directions and times, all eight
+    predicates (two for the larger cliques), against the oracle."""
+    rng = np.random.default_rng(d)
+    # a clique of d + 1 vertices (out-rows of d, d - 1, ..., 0) beside sparse ones
+    k = d + 1
+    i, j = np.triu_indices(k, 1)
+    extra = rng.integers(0, k + 200, size=(400, 2))
+    a = np.concatenate([i, extra[:, 0]])
+    b = np.concatenate([j, extra[:, 1]])
+    flip = rng.random(a.size) < 0.5
+    src = np.where(flip, b, a).astype(np.int32)
+    dst = np.where(flip, a, b).astype(np.int32)
+    t = np.sort(rng.integers(0, 10_000, size=src.size)).astype(np.int64)
+    n = k + 200
+    o = Oracle(n, src, dst, t)
+    for mode in (folty.RANK_DEGENERACY, folty.RANK_DEGREE)[:2 if d < 130 else 1]:
+        G = folty.Graph(n, src, dst, t).build(rank_mode=mode)
+        for v in range(8) if d < 130 else (0, 6):
+            say("row edges", d, mode, v)
+            for delta, one in ((300, False), (5_000, True)):
+                r = G.query(delta, (1, 4), v, one_pass=one)
+                assert np.array_equal(r.counts(), o.query(delta, 1, 4, v)["counts"])
+    o.close()
