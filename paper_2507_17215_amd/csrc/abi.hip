@@ -43,9 +43,7 @@ Graph::~Graph() {
     if (own_stream && stream) {
         // the index's buffers are freed after this body, with no stream of
         // their own; blocks freed on this stream before lose their events here
-        (void)hipStreamSynchronize(stream);
-        dev_forget_stream(stream);
-        (void)hipStreamDestroy(stream);
+        stream_give(stream, device);
     }
 }
 

@@ -7,8 +7,10 @@
 // stream waits for that event first, a reuse on the same stream is ordered by
 // the stream itself.  Every public call synchronises its stream before it
 // returns, so blocks freed outside any call are idle.
+#include <exception>
 #include <map>
 #include <mutex>
+#include <vector>
 
 #include "folty_internal.h"
 
@@ -274,13 +276,113 @@ bool host_free(void *p) {
     return true;
 }
 
+static size_t small_trim();
+
 size_t host_trim() {
+    const size_t small = small_trim();
     HostPool &P = host_pool();
     std::lock_guard<std::mutex> lk(P.mu);
-    size_t n = P.cached;
+    size_t n = P.cached + small;
     for (auto &kv : P.free_blocks) (void)hipHostFree(kv.second);
     P.free_blocks.clear();
     P.cached = 0;
+    return n;
+}
+
+// ---------------------------------------------------------------------------
+// Small pinned blocks (read-back scratch of builds and workspaces) and streams.
+// Making and freeing either costs 60-230 us, several times what a small build's
+// kernels take, so a few idle ones are kept: blocks of PIN_BYTES, at most
+// PIN_KEEP, and STREAM_KEEP streams per device, all given back by
+// folty_release_cached_memory.
+// ---------------------------------------------------------------------------
+namespace {
+constexpr size_t PIN_KEEP = 64;
+constexpr size_t STREAM_KEEP = 16;
+struct SmallPool {
+    std::mutex mu;
+    std::vector<void *> pins;
+    std::map<int, std::vector<hipStream_t>> streams;
+};
+SmallPool &small_pool() {
+    static SmallPool *p = new SmallPool(); // kept until the process ends
+    return *p;
+}
+} // namespace
+
+void *pinned_take() {
+    SmallPool &P = small_pool();
+    {
+        std::lock_guard<std::mutex> lk(P.mu);
+        if (!P.pins.empty()) {
+            void *p = P.pins.back();
+            P.pins.pop_back();
+            return p;
+        }
+    }
+    void *p = nullptr;
+    FOLTY_HIP(hipHostMalloc(&p, PIN_BYTES, hipHostMallocPortable));
+    return p;
+}
+
+void pinned_give(void *p) {
+    // a block given back while an error unwinds may still be the target of a copy
+    if (std::uncaught_exceptions() == 0) {
+        SmallPool &P = small_pool();
+        std::lock_guard<std::mutex> lk(P.mu);
+        if (P.pins.size() < PIN_KEEP) {
+            P.pins.push_back(p);
+            return;
+        }
+    }
+    (void)hipHostFree(p);
+}
+
+hipStream_t stream_take() {
+    int dev = 0;
+    FOLTY_HIP(hipGetDevice(&dev));
+    SmallPool &P = small_pool();
+    {
+        std::lock_guard<std::mutex> lk(P.mu);
+        auto &v = P.streams[dev];
+        if (!v.empty()) {
+            hipStream_t s = v.back();
+            v.pop_back();
+            return s;
+        }
+    }
+    hipStream_t s = nullptr;
+    FOLTY_HIP(hipStreamCreateWithFlags(&s, hipStreamNonBlocking));
+    return s;
+}
+
+void stream_give(hipStream_t s, int dev) {
+    if (!s) return;
+    const bool idle = hipStreamSynchronize(s) == hipSuccess;
+    dev_forget_stream(s);
+    if (idle) {
+        SmallPool &P = small_pool();
+        std::lock_guard<std::mutex> lk(P.mu);
+        auto &v = P.streams[dev];
+        if (v.size() < STREAM_KEEP) {
+            v.push_back(s);
+            return;
+        }
+    }
+    (void)hipGetLastError();
+    (void)hipStreamDestroy(s);
+}
+
+static size_t small_trim() {
+    SmallPool &P = small_pool();
+    std::lock_guard<std::mutex> lk(P.mu);
+    const size_t n = P.pins.size() * PIN_BYTES;
+    for (void *p : P.pins) (void)hipHostFree(p);
+    P.pins.clear();
+    for (auto &kv : P.streams) {
+        for (hipStream_t s : kv.second) (void)hipStreamDestroy(s);
+        kv.second.clear();
+    }
     return n;
 }
 

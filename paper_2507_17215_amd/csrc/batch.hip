@@ -520,9 +520,7 @@ Plan::~Plan() {
         vals.release();
         keys2.release();
         vals2.release();
-        (void)hipStreamSynchronize(stream);
-        dev_forget_stream(stream);
-        (void)hipStreamDestroy(stream);
+        stream_give(stream, device);
     }
 }
 
@@ -683,7 +681,7 @@ Plan *plan_create(Graph *const *gs, int ng, const folty_query *qs, const int32_t
     std::unique_ptr<Plan> P(new Plan());
     P->device = dev;
     P->oneshot = oneshot;
-    FOLTY_HIP(hipStreamCreateWithFlags(&P->stream, hipStreamNonBlocking));
+    P->stream = stream_take();
     for (auto &e : P->ev) FOLTY_HIP(hipEventCreate(&e));
     hipStream_t s = P->stream;
     StreamScope sc(s);

@@ -236,6 +236,13 @@ __device__ inline Pusher make_pusher(PushLds *P, const ListSet &L) {
     return p;
 }
 
+__global__ __launch_bounds__(BLK) void k_clear(int32_t *__restrict__ a, int32_t na, int32_t *__restrict__ b, int32_t nb) {
+    for (int32_t i = (int32_t)(blockIdx.x * BLK + threadIdx.x); i < nb; i += (int32_t)gridDim.x * BLK) {
+        b[i] = 0;
+        if (i < na) a[i] = 0;
+    }
+}
+
 // ---- global h-index of the degrees: an upper bound of every core number -----------
 // degrees above `cap` are counted in bin cap
 __global__ __launch_bounds__(BLK) void k_deg_hist(const int32_t *__restrict__ deg, int32_t n, int32_t cap,
@@ -1145,17 +1152,15 @@ __global__ void k_level_keys(const uint16_t *__restrict__ c, const int32_t *__re
 } // namespace
 
 // Core numbers (into `core`, original ids) and the rank keys (into `key`); returns
-// the number of key bits.  uoff/uadj: the undirected CSR (neighbour ids only).
-int core_rank_keys(int32_t n, const int64_t *uoff, const int32_t *uadj, const int32_t *deg, int32_t *core,
+// the number of key bits.  uoff/uadj: the undirected CSR (neighbour ids only) of
+// adj_n entries.
+int core_rank_keys(int32_t n, int64_t adj_n, const int64_t *uoff, const int32_t *uadj, const int32_t *deg, int32_t *core,
                    uint32_t *key, hipStream_t s, CoreStats *out) {
     *out = CoreStats{};
     if (n <= 0) return 1;
     PinnedBuf hb;
     hb.ensure(4 * CT_WORDS);
     int32_t *h = hb.as<int32_t>();
-    int64_t adj_n = 0;
-    FOLTY_HIP(hipMemcpyAsync(&adj_n, uoff + n, 8, hipMemcpyDeviceToHost, s));
-    FOLTY_HIP(hipStreamSynchronize(s));
     // chunk lists: every class-2 row has more than C1_MAX entries
     const int64_t chunk_cap = adj_n / CH + adj_n / (C1_MAX + 1) + 1;
     DevBuf ctr, hist, val, old, stamp, cnt, lr, bigid, all, allc, pool, poolc;
@@ -1171,8 +1176,8 @@ int core_rank_keys(int32_t n, const int64_t *uoff, const int32_t *uadj, const in
     allc.ensure(sizeof(int2) * (size_t)chunk_cap);
     pool.ensure(4 * 8 * (size_t)n);
     poolc.ensure(sizeof(int2) * 3 * (size_t)chunk_cap);
-    FOLTY_HIP(hipMemsetAsync(ctr.p, 0, 4 * CT_WORDS, s));
-    FOLTY_HIP(hipMemsetAsync(hist.p, 0, 4 * (size_t)HG_BINS, s));
+    k_clear<<<grid_for(HG_BINS, BLK, 64), BLK, 0, s>>>(ctr.as<int32_t>(), CT_WORDS, hist.as<int32_t>(), HG_BINS);
+    FOLTY_LAUNCHED();
     CoreBufs B{};
     B.uoff = uoff;
     B.uadj = uadj;

@@ -64,7 +64,14 @@ void dev_forget_stream(hipStream_t s); // call before destroying a stream blocks
 // it did not hand out
 void *host_alloc(size_t bytes);
 bool host_free(void *p);
-size_t host_trim();  // give the cached pinned blocks back; returns bytes
+size_t host_trim();  // give the cached pinned blocks and idle streams back; returns bytes
+// pinned blocks of PIN_BYTES and non-blocking streams of the current device, kept
+// when given back (alloc.hip)
+constexpr size_t PIN_BYTES = 32 << 10;
+void *pinned_take();
+void pinned_give(void *p);
+hipStream_t stream_take();
+void stream_give(hipStream_t s, int dev); // waits for the stream first
 
 // A caller's allocator (folty_build_opts) and the scope in which the device
 // buffers a thread asks for come from it; a buffer remembers where its memory
@@ -149,9 +156,16 @@ struct PinnedBuf {
     PinnedBuf() = default;
     PinnedBuf(const PinnedBuf &) = delete;
     PinnedBuf &operator=(const PinnedBuf &) = delete;
-    ~PinnedBuf() { if (p && own) (void)hipHostFree(p); }
+    ~PinnedBuf() { drop(); }
+    void drop() {
+        if (p && own) {
+            if (bytes == PIN_BYTES) pinned_give(p);
+            else (void)hipHostFree(p);
+        }
+        p = nullptr;
+    }
     void lend(void *q, size_t b) {
-        if (p && own) (void)hipHostFree(p);
+        drop();
         p = q;
         bytes = b;
         own = false;
@@ -159,10 +173,14 @@ struct PinnedBuf {
     void ensure(size_t b) {
         if (b <= bytes && p) return;
         if (!own) fail(FOLTY_EINVAL, "a lent host buffer of %zu bytes cannot grow to %zu", bytes, b);
-        if (p) (void)hipHostFree(p);
-        p = nullptr;
-        FOLTY_HIP(hipHostMalloc(&p, b ? b : 64, hipHostMallocDefault));
-        bytes = b ? b : 64;
+        drop();
+        if (b <= PIN_BYTES) {
+            p = pinned_take();
+            bytes = PIN_BYTES;
+        } else {
+            FOLTY_HIP(hipHostMalloc(&p, b, hipHostMallocDefault));
+            bytes = b;
+        }
     }
     template <class T> T *as() const { return static_cast<T *>(p); }
 };
@@ -231,6 +249,11 @@ enum : int {
     SCAL_WORDS = SCAL_REGIONS + MAX_REGIONS * CAND_STRIDE / 2
 };
 constexpr size_t SCAL_BYTES = 8 * (size_t)SCAL_WORDS;
+// past the scalars: the sorted pairs of a small result (u, v, certificates), so
+// that one copy brings back everything
+constexpr int SMALL_PAIRS = 1024;
+constexpr size_t SCAL_ALL_BYTES = SCAL_BYTES + 12 * (size_t)SMALL_PAIRS;
+static_assert(SCAL_ALL_BYTES <= PIN_BYTES, "one pinned block holds the scalars");
 struct CandBuf {
     int32_t *sv;       // 3 x 64 per chunk
     int32_t *cnt;      // slots filled, per chunk
@@ -468,7 +491,7 @@ struct CoreStats {
     int32_t rounds = 0;   // rounds of the all-levels peel
     int32_t global_h = 0; // h-index of the degree sequence (the starting bound)
 };
-int core_rank_keys(int32_t n, const int64_t *uoff, const int32_t *uadj, const int32_t *deg, int32_t *core,
+int core_rank_keys(int32_t n, int64_t adj_n, const int64_t *uoff, const int32_t *uadj, const int32_t *deg, int32_t *core,
                    uint32_t *key, hipStream_t s, CoreStats *out);
 
 inline int bit_length(uint64_t x) {

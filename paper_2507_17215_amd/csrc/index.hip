@@ -427,7 +427,7 @@ void load_graph(Graph *g, int32_t n, int64_t m, const int32_t *src, const int32_
     if (stream) {
         g->stream = (hipStream_t)stream;
     } else {
-        FOLTY_HIP(hipStreamCreateWithFlags(&g->stream, hipStreamNonBlocking));
+        g->stream = stream_take();
         g->own_stream = true;
     }
     hipStream_t s = g->stream;
@@ -463,9 +463,11 @@ void load_graph(Graph *g, int32_t n, int64_t m, const int32_t *src, const int32_
         k_validate<<<grid_for(m, BLK, 1024), BLK, 0, s>>>(g->in_src, g->in_dst, g->in_t, m, n, vo.as<ValOut>());
         FOLTY_LAUNCHED();
     }
-    ValOut h{};
-    FOLTY_HIP(hipMemcpyAsync(&h, vo.p, sizeof(ValOut), hipMemcpyDeviceToHost, s));
+    PinnedBuf hb;
+    hb.ensure(sizeof(ValOut));
+    FOLTY_HIP(hipMemcpyAsync(hb.p, vo.p, sizeof(ValOut), hipMemcpyDeviceToHost, s));
     FOLTY_HIP(hipStreamSynchronize(s));
+    const ValOut h = *hb.as<ValOut>();
     if (h.first_bad != ~0ull)
         fail(FOLTY_EINVAL, "temporal edge %llu has a vertex id outside [0, %d) or a timestamp outside [0, 2^62)",
              h.first_bad, n);
@@ -568,18 +570,23 @@ void build_index(Graph *g, const folty_build_opts *opts) {
     ix.smid.ensure(4 * (size_t)S + 4);
     ix.slo.ensure(4 * (size_t)S + 4);
     ix.shi.ensure(4 * (size_t)S + 4);
-    DevBuf pstat;
-    pstat.ensure(sizeof(PairStats));
-    FOLTY_HIP(hipMemsetAsync(pstat.p, 0, sizeof(PairStats), s));
+    // PairStats, then at STAT_ORIENT the OrientStats
+    constexpr size_t STAT_ORIENT = 32;
+    DevBuf stat;
+    stat.ensure(64);
+    static_assert(sizeof(PairStats) <= STAT_ORIENT && sizeof(OrientStats) <= STAT_ORIENT, "");
+    k_fill<unsigned long long><<<1, 8, 0, s>>>(stat.as<unsigned long long>(), 0ull, 8);
+    FOLTY_LAUNCHED();
     if (S == 0) {
-        FOLTY_HIP(hipMemsetAsync(ix.soff.p, 0, 4, s));
+        k_fill<int32_t><<<1, 1, 0, s>>>(ix.soff.as<int32_t>(), 0, 1);
+        FOLTY_LAUNCHED();
     } else {
         k_fill<int32_t><<<grid_for(S, BLK), BLK, 0, s>>>(ix.smid.as<int32_t>(), -1, S);
         k_static_table<<<grid_for(m, BLK), BLK, 0, s>>>(pkey2.as<uint64_t>(), ix.sid.as<int32_t>(), m, n,
                                                         1.0 / (double)n, ix.soff.as<int32_t>(), ix.smid.as<int32_t>(),
                                                         ix.slo.as<int32_t>(), ix.shi.as<int32_t>());
         k_fix_smid_stats<<<grid_for(S, BLK, 2048), BLK, 0, s>>>(ix.soff.as<int32_t>(), ix.smid.as<int32_t>(), S,
-                                                                pstat.as<PairStats>());
+                                                                stat.as<PairStats>());
         FOLTY_LAUNCHED();
     }
     pkey2.release();
@@ -621,7 +628,7 @@ void build_index(Graph *g, const folty_build_opts *opts) {
     DevBuf rnd;
     rnd.ensure(4 * (size_t)n);
     CoreStats cst{};
-    const int key_bits = core_rank_keys(n, uoff.as<int64_t>(), uadj.as<int32_t>(), ix.deg.as<int32_t>(),
+    const int key_bits = core_rank_keys(n, 2 * (int64_t)S, uoff.as<int64_t>(), uadj.as<int32_t>(), ix.deg.as<int32_t>(),
                                         ix.core.as<int32_t>(), rnd.as<uint32_t>(), s, &cst);
     ix.peel_rounds = cst.rounds;
     ix.core_sweeps = cst.sweeps;
@@ -678,26 +685,22 @@ void build_index(Graph *g, const folty_build_opts *opts) {
         k_orient_rows<<<grid_for((int64_t)n + 1, BLK), BLK, 0, s>>>(key2.as<uint64_t>(), S, n, ix.ooff.as<int32_t>());
         FOLTY_LAUNCHED();
     }
-    DevBuf ostat;
-    ostat.ensure(sizeof(OrientStats));
-    FOLTY_HIP(hipMemsetAsync(ostat.p, 0, sizeof(OrientStats), s));
     // 512 blocks: few per-vertex reads, and each block's closing atomics share
     // one cache line (4M vertices: 52 us; 2,048 blocks 86 us)
     k_orient_stats<<<grid_for(n, BLK, 512), BLK, 0, s>>>(ix.ooff.as<int32_t>(), ix.rank.as<int32_t>(),
                                                           ix.core.as<int32_t>(), n, ix.outdeg.as<int32_t>(),
-                                                          ostat.as<OrientStats>());
+                                                          reinterpret_cast<OrientStats *>(stat.as<char>() + STAT_ORIENT));
     FOLTY_LAUNCHED();
 
     // ---- read back sizes ------------------------------------------------------------
     {
         char *h = hb.as<char>();
-        FOLTY_HIP(hipMemcpyAsync(h, pstat.p, sizeof(PairStats), hipMemcpyDeviceToHost, s));
-        FOLTY_HIP(hipMemcpyAsync(h + 32, ostat.p, sizeof(OrientStats), hipMemcpyDeviceToHost, s));
+        FOLTY_HIP(hipMemcpyAsync(h, stat.p, 64, hipMemcpyDeviceToHost, s));
         FOLTY_HIP(hipStreamSynchronize(s));
         PairStats ps;
         OrientStats os;
         memcpy(&ps, h, sizeof ps);
-        memcpy(&os, h + 32, sizeof os);
+        memcpy(&os, h + STAT_ORIENT, sizeof os);
         ix.P = (int64_t)ps.pairs;
         ix.sigma_max = (int64_t)ps.sigma_max;
         ix.W = (int64_t)os.wedges;

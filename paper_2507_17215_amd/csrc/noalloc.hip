@@ -27,7 +27,7 @@ struct NoAllocDevice {
     void *ptr = nullptr;
     std::mutex mu;
     Workspace ws;
-    alignas(64) char host[8192];
+    alignas(64) char host[SCAL_ALL_BYTES];
 };
 
 std::mutex g_mu;

@@ -318,6 +318,30 @@ __global__ void k_pairs_unpack(const uint64_t *__restrict__ keys, int32_t np, in
     v[i] = (int32_t)(k & ((1ull << nbits) - 1));
 }
 
+// Sorts a small result (at most SMALL_PAIRS pairs, otherwise nothing is done): one
+// block, each pair's rank counted against all keys in LDS, u, v and the
+// certificates written behind the scalars.  Launched before the host knows the
+// number of pairs, so a small query is one stream of launches and one copy.
+constexpr int SMALL_BLK = 1024;
+__global__ __launch_bounds__(SMALL_BLK) void k_pairs_small(const uint64_t *__restrict__ keys,
+                                                           const uint32_t *__restrict__ vals,
+                                                           const int32_t *__restrict__ npairs, int nbits,
+                                                           int32_t *__restrict__ out) {
+    __shared__ uint64_t s_k[SMALL_PAIRS];
+    static_assert(SMALL_PAIRS == SMALL_BLK, "a pair per thread");
+    const int np = *npairs, i = threadIdx.x;
+    if (np > SMALL_PAIRS) return;
+    const uint64_t k = i < np ? keys[i] : ~0ull;
+    s_k[i] = k;
+    __syncthreads();
+    if (i >= np) return;
+    int r = 0;
+    for (int j = 0; j < np; j++) r += s_k[j] < k; // keys differ
+    out[r] = (int32_t)(k >> nbits);
+    out[SMALL_PAIRS + r] = (int32_t)(k & ((1ull << nbits) - 1));
+    out[2 * SMALL_PAIRS + r] = (int32_t)vals[i];
+}
+
 // count[e] += the prefix sum of the interval marks at e
 __global__ void k_add_counts(const int32_t *__restrict__ ps, int32_t m, uint32_t *__restrict__ count) {
     for (int64_t e = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; e < m; e += (int64_t)gridDim.x * blockDim.x)
@@ -366,8 +390,8 @@ __global__ __launch_bounds__(BLK) void k_query_clear(uint32_t *__restrict__ coun
 // makes the workspace's scalars, and per-edge and per-pair counts if asked for,
 // and clears them
 void clear_query(const Index &ix, Workspace &ws, bool counts, hipStream_t s) {
-    ws.scal.ensure(SCAL_BYTES);
-    ws.host.ensure(SCAL_BYTES);
+    ws.scal.ensure(SCAL_ALL_BYTES);
+    ws.host.ensure(SCAL_ALL_BYTES);
     int64_t m = 0, np = 0;
     if (counts) {
         m = ix.m;
@@ -381,9 +405,10 @@ void clear_query(const Index &ix, Workspace &ws, bool counts, hipStream_t s) {
     FOLTY_LAUNCHED();
 }
 
-// the query's scalars into ws.host; read them after the stream is synchronised
-void read_scalars(Workspace &ws, hipStream_t s) {
-    FOLTY_HIP(hipMemcpyAsync(ws.host.p, ws.scal.p, SCAL_BYTES, hipMemcpyDeviceToHost, s));
+// the query's scalars (and a small result's pairs) into ws.host; read them after
+// the stream is synchronised
+void read_scalars(Workspace &ws, hipStream_t s, bool pairs) {
+    FOLTY_HIP(hipMemcpyAsync(ws.host.p, ws.scal.p, pairs ? SCAL_ALL_BYTES : SCAL_BYTES, hipMemcpyDeviceToHost, s));
 }
 
 int64_t chunks_taken(const Workspace &ws, const CandBuf &B) {
@@ -459,7 +484,7 @@ CandBuf filter_triangles(Index &ix, int variant, int64_t dmax, Workspace &ws, hi
         });
         ws.kept_chunks = (int64_t)total;
         if (sure) return B;
-        read_scalars(ws, s);
+        read_scalars(ws, s, false);
         FOLTY_HIP(hipStreamSynchronize(s));
         const unsigned long long *h = ws.host.as<unsigned long long>();
         const int64_t taken = chunks_taken(ws, B);
@@ -576,7 +601,7 @@ void finish_vertex(const Graph *g, const folty_vertex_query &vq, Workspace &ws, 
     exclusive_scan_i32(ws.cub.p, need, flag, pos, n, s);
     k_vertex_compact<<<grid_for(n, BLK), BLK, 0, s>>>(flag, pos, good, n, vert, vgood);
     FOLTY_LAUNCHED();
-    int32_t last[2] = {0, 0};
+    int32_t *last = reinterpret_cast<int32_t *>(ws.host.as<char>() + SCAL_BYTES); // the pairs have been taken
     FOLTY_HIP(hipMemcpyAsync(&last[0], pos + n - 1, 4, hipMemcpyDeviceToHost, s));
     FOLTY_HIP(hipMemcpyAsync(&last[1], flag + n - 1, 4, hipMemcpyDeviceToHost, s));
     FOLTY_HIP(hipStreamSynchronize(s));
@@ -590,16 +615,15 @@ void finish_vertex(const Graph *g, const folty_vertex_query &vq, Workspace &ws, 
     }
 }
 
-// any: qualify edges with count >= 1 (the inner exists of a vertex query)
-// Threshold step: certificates, per-pair certificate counts and the compacted
-// pair keys (unsorted, in ws), then the query's scalars to the host.  Returns
-// |Sol| and the number of pairs.
 struct PairCounts {
     int64_t ncerts;
     int32_t npairs;
 };
 
-PairCounts threshold_pairs(const Graph *g, const folty_query &q, const uint32_t *count, Workspace &ws,
+// Threshold step: certificates, per-pair certificate counts and the compacted
+// pair keys (unsorted, in ws); a small result is sorted behind the scalars.
+// any: qualify edges with count >= 1 (the inner exists of a vertex query)
+void threshold_pairs(const Graph *g, const folty_query &q, const uint32_t *count, Workspace &ws,
                            hipStream_t s, bool any) {
     const Index &ix = g->ix;
     const int32_t S = ix.S, m = ix.m;
@@ -632,10 +656,14 @@ PairCounts threshold_pairs(const Graph *g, const folty_query &q, const uint32_t 
         k_pairs_compact<<<grid_for(2 * (int64_t)S, BLK * PAIR_ITEMS), BLK, 0, s>>>(
             ws.ncert.as<uint32_t>(), S, ix.slo.as<int32_t>(), ix.shi.as<int32_t>(), pair_bits(ix.n),
             ws.pairs_k.as<uint64_t>(), ws.pairs_v.as<uint32_t>(), np);
+        k_pairs_small<<<1, SMALL_BLK, 0, s>>>(ws.pairs_k.as<uint64_t>(), ws.pairs_v.as<uint32_t>(), np,
+                                              pair_bits(ix.n), reinterpret_cast<int32_t *>(ws.scal.as<char>() + SCAL_BYTES));
         FOLTY_LAUNCHED();
     }
-    read_scalars(ws, s);
-    FOLTY_HIP(hipStreamSynchronize(s));
+}
+
+// |Sol| and the number of pairs, from the scalars on the host
+PairCounts pair_counts(const Workspace &ws) {
     unsigned long long ncerts;
     int32_t npairs;
     memcpy(&ncerts, ws.host.p, 8);
@@ -664,25 +692,6 @@ void sort_pairs(const Graph *g, Workspace &ws, int32_t npairs, hipStream_t s, in
     FOLTY_LAUNCHED();
 }
 
-void finish_query(const Graph *g, const folty_query &q, const uint32_t *count, Workspace &ws, Result *res,
-                  hipStream_t s, bool any = false) {
-    const PairCounts pc = threshold_pairs(g, q, count, ws, s, any);
-    const int32_t npairs = pc.npairs;
-    res->n_certificates = pc.ncerts;
-    res->u.resize(npairs);
-    res->v.resize(npairs);
-    res->n_cert.resize(npairs);
-    if (npairs > 0) {
-        int32_t *du, *dv;
-        uint32_t *dn;
-        sort_pairs(g, ws, npairs, s, &du, &dv, &dn);
-        FOLTY_HIP(hipMemcpyAsync(res->u.data(), du, 4 * (size_t)npairs, hipMemcpyDeviceToHost, s));
-        FOLTY_HIP(hipMemcpyAsync(res->v.data(), dv, 4 * (size_t)npairs, hipMemcpyDeviceToHost, s));
-        FOLTY_HIP(hipMemcpyAsync(res->n_cert.data(), dn, 4 * (size_t)npairs, hipMemcpyDeviceToHost, s));
-        FOLTY_HIP(hipStreamSynchronize(s));
-    }
-}
-
 // per-edge counts in input order (0xFFFFFFFF for self-loops) into out
 void scatter_counts(const Graph *g, const uint32_t *count, uint32_t *out, hipStream_t s) {
     const Index &ix = g->ix;
@@ -693,6 +702,40 @@ void scatter_counts(const Graph *g, const uint32_t *count, uint32_t *out, hipStr
     if (ix.m > 0) {
         k_counts_scatter<<<grid_for(ix.m, BLK), BLK, 0, s>>>(count, ix.perm.as<int32_t>(), ix.m, out);
         FOLTY_LAUNCHED();
+    }
+}
+
+void keep_counts(const Graph *g, const uint32_t *count, Result *res, hipStream_t s);
+
+// threshold, pairs and (kept) per-edge counts into res.  The stream is idle after
+// it; ev[3] follows the pair step.
+void finish_query(const Graph *g, const folty_query &q, const uint32_t *count, Workspace &ws, Result *res,
+                  hipStream_t s, bool any) {
+    threshold_pairs(g, q, count, ws, s, any);
+    read_scalars(ws, s, true);
+    FOLTY_HIP(hipEventRecord(ws.ev[3], s));
+    if (!(q.flags & FOLTY_QUERY_NO_COUNTS)) keep_counts(g, count, res, s);
+    FOLTY_HIP(hipStreamSynchronize(s));
+    const PairCounts pc = pair_counts(ws);
+    const int32_t npairs = pc.npairs;
+    res->n_certificates = pc.ncerts;
+    res->u.resize(npairs);
+    res->v.resize(npairs);
+    res->n_cert.resize(npairs);
+    if (npairs > SMALL_PAIRS) {
+        int32_t *du, *dv;
+        uint32_t *dn;
+        sort_pairs(g, ws, npairs, s, &du, &dv, &dn);
+        FOLTY_HIP(hipMemcpyAsync(res->u.data(), du, 4 * (size_t)npairs, hipMemcpyDeviceToHost, s));
+        FOLTY_HIP(hipMemcpyAsync(res->v.data(), dv, 4 * (size_t)npairs, hipMemcpyDeviceToHost, s));
+        FOLTY_HIP(hipMemcpyAsync(res->n_cert.data(), dn, 4 * (size_t)npairs, hipMemcpyDeviceToHost, s));
+        FOLTY_HIP(hipEventRecord(ws.ev[3], s));
+        FOLTY_HIP(hipStreamSynchronize(s));
+    } else if (npairs > 0) {
+        const int32_t *p = reinterpret_cast<const int32_t *>(ws.host.as<char>() + SCAL_BYTES);
+        memcpy(res->u.data(), p, 4 * (size_t)npairs);
+        memcpy(res->v.data(), p + SMALL_PAIRS, 4 * (size_t)npairs);
+        memcpy(res->n_cert.data(), p + 2 * SMALL_PAIRS, 4 * (size_t)npairs);
     }
 }
 
@@ -733,6 +776,8 @@ void index_triangles(Index &ix, bool cache, DevBuf &cub, hipStream_t s) {
     int32_t ni = 0, ng = 0;
     int64_t probes = 0;
     {
+        PinnedBuf hb;
+        hb.ensure(64);
         DevBuf key, key2, val, val2, run, len, P, flag, fid, start, cnt;
         key.ensure(4 * (size_t)S + 4);
         key2.ensure(4 * (size_t)S + 4);
@@ -766,9 +811,11 @@ void index_triangles(Index &ix, bool cache, DevBuf &cub, hipStream_t s) {
             need = exclusive_scan_i32_to_i64(nullptr, 0, len.as<int32_t>(), P.as<int64_t>(), (int64_t)S + 1, s);
             cub.ensure(need);
             exclusive_scan_i32_to_i64(cub.p, need, len.as<int32_t>(), P.as<int64_t>(), (int64_t)S + 1, s);
-            FOLTY_HIP(hipMemcpyAsync(&ng, cnt.p, 4, hipMemcpyDeviceToHost, s));
-            FOLTY_HIP(hipMemcpyAsync(&probes, P.as<int64_t>() + S, 8, hipMemcpyDeviceToHost, s));
+            FOLTY_HIP(hipMemcpyAsync(hb.p, cnt.p, 4, hipMemcpyDeviceToHost, s));
+            FOLTY_HIP(hipMemcpyAsync(hb.as<int64_t>() + 1, P.as<int64_t>() + S, 8, hipMemcpyDeviceToHost, s));
             FOLTY_HIP(hipStreamSynchronize(s));
+            ng = *hb.as<int32_t>();
+            probes = hb.as<int64_t>()[1];
         }
         if (ng > 0) {
             k_item_flags<<<grid_for(ng, BLK), BLK, 0, s>>>(key2.as<uint32_t>(), P.as<int64_t>(), run.as<int2>(), ng,
@@ -780,8 +827,9 @@ void index_triangles(Index &ix, bool cache, DevBuf &cub, hipStream_t s) {
             k_item_starts<<<grid_for(ng, BLK), BLK, 0, s>>>(flag.as<int32_t>(), fid.as<int32_t>(), ng,
                                                             start.as<int32_t>());
             FOLTY_LAUNCHED();
-            FOLTY_HIP(hipMemcpyAsync(&ni, fid.as<int32_t>() + (ng - 1), 4, hipMemcpyDeviceToHost, s));
+            FOLTY_HIP(hipMemcpyAsync(hb.p, fid.as<int32_t>() + (ng - 1), 4, hipMemcpyDeviceToHost, s));
             FOLTY_HIP(hipStreamSynchronize(s));
+            ni = *hb.as<int32_t>();
             k_fill<int32_t><<<1, 1, 0, s>>>(start.as<int32_t>() + ni, ng, 1);
             FOLTY_LAUNCHED();
         }
@@ -971,7 +1019,10 @@ void run_query_into(Graph *g, const folty_query &q, Workspace &ws, int32_t *pair
     hipStream_t s = g->stream;
     bool one_pass = false;
     const uint32_t *count = query_counts(g, q, ws, s, &one_pass);
-    const PairCounts pc = threshold_pairs(g, q, count, ws, s, false);
+    threshold_pairs(g, q, count, ws, s, false);
+    read_scalars(ws, s, false);
+    FOLTY_HIP(hipStreamSynchronize(s));
+    const PairCounts pc = pair_counts(ws);
     if (ix.T.load() < 0) ix.T = (int64_t)ws.host.as<unsigned long long>()[SCAL_HITS];
     *n_pairs = pc.npairs;
     *n_certificates = pc.ncerts;
@@ -1006,10 +1057,11 @@ static Result *run_query_impl(Graph *g, const folty_query &q, Workspace &ws, hip
     bool one_pass = false;
     const uint32_t *count = query_counts(g, q, ws, s, &one_pass);
     finish_query(g, q, count, ws, res.get(), s, vq && vq->inner == FOLTY_INNER_EXISTS);
-    if (vq) finish_vertex(g, *vq, ws, res.get(), s);
-    FOLTY_HIP(hipEventRecord(ws.ev[3], s));
-    if (!(q.flags & FOLTY_QUERY_NO_COUNTS)) keep_counts(g, count, res.get(), s);
-    FOLTY_HIP(hipStreamSynchronize(s));
+    if (vq) {
+        finish_vertex(g, *vq, ws, res.get(), s);
+        FOLTY_HIP(hipEventRecord(ws.ev[3], s));
+        FOLTY_HIP(hipStreamSynchronize(s));
+    }
     if (ix.NI > 0) after_filter(ix, ws, q.delta, one_pass);
     else ix.T = 0;
     fill_stats_from_index(ix, &res->stats);

@@ -1458,7 +1458,7 @@ constexpr int64_t CHUNK_BYTES = 3 * 4 * 64 + 4;
 
 // query.hip: the single-query filter and its scalars
 void clear_query(const Index &ix, Workspace &ws, bool counts, hipStream_t s);
-void read_scalars(Workspace &ws, hipStream_t s);
+void read_scalars(Workspace &ws, hipStream_t s, bool pairs);
 int64_t chunks_taken(const Workspace &ws, const CandBuf &B);
 CandBuf filter_triangles(Index &ix, int variant, int64_t dmax, Workspace &ws, hipStream_t s, bool one_pass);
 void after_filter(Index &ix, Workspace &ws, int64_t delta, bool one_pass);

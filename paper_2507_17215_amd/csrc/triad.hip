@@ -386,7 +386,7 @@ Result *run_triad_query(Graph *g, const folty_triad_query &q, Workspace &ws) {
         FOLTY_HIP(hipEventRecord(ws.ev[5], s));
     }
     FOLTY_HIP(hipEventRecord(ws.ev[2], s));
-    read_scalars(ws, s);
+    read_scalars(ws, s, false);
     FOLTY_HIP(hipStreamSynchronize(s));
     if (ix.NI > 0) after_filter(ix, ws, q.delta, one);
     else ix.T = 0;
