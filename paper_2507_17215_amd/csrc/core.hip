@@ -1137,6 +1137,320 @@ __global__ __launch_bounds__(BLK) void k_level_round(CoreBufs B, int32_t r) {
     push_finish(p);
 }
 
+// ---- small graphs: everything in one block ------------------------------------------------
+// Up to SMALL_N vertices and SMALL_ADJ adjacency entries the sweeps and rounds
+// above are a chain of some sixty launches of about 10 us each (six dependent
+// loads), whatever their grid.  Here one block of 16 wavefronts runs them with the
+// values, counts and one bit per vertex to re-evaluate in LDS, a wavefront per 64
+// vertices: rows of up to C0_MAX entries in their lane, longer ones over 16 lanes
+// or the whole wavefront.  It is bound by one CU's instruction rate (a sweep over
+// all of 33,000 static edges 23 us).  Whole build, launches -> one block: 2,000
+// edges 0.64 -> 0.40 ms, 20,000 1.24 -> 0.65 ms, 40,000 1.04 -> 0.69 ms, 100,000
+// (66,000 adjacency entries) 1.31 -> 1.15 ms; 92,000 entries 1.33 -> 1.36 ms.
+constexpr int SMALL_BLOCK = 1024;
+constexpr int32_t SMALL_N = 12288;
+constexpr int64_t SMALL_ADJ = 80000;
+constexpr int32_t SMALL_W = SMALL_N / 64;
+
+struct SmallLds {
+    int32_t off[SMALL_N + 1];              // row starts
+    uint16_t c[SMALL_N];                   // value: upper bound of the core number, at the end the core number
+    uint16_t cnt[SMALL_N];                 // remaining neighbours of its level
+    unsigned long long mark[2][SMALL_W];   // sweeps: to re-evaluate, by parity; rounds: frontier, removed
+    int32_t flag[3];                       // some mark was set, by step mod 3
+    int32_t max_core;
+};
+
+// row entries at or above h, by the whole wavefront (a row of more than 1024 entries)
+__device__ inline int32_t long_count(const uint16_t *c, const int32_t *__restrict__ adj, int64_t b, int32_t d, int32_t h) {
+    int32_t k = 0;
+    for (int32_t i = lane_id(); i < d; i += 64) k += c[adj[b + i]] >= h ? 1 : 0;
+    return wave_sum(k);
+}
+__device__ inline int32_t h_long(const uint16_t *c, const int32_t *__restrict__ adj, int64_t b, int32_t d, int32_t x) {
+    const int32_t ge = long_count(c, adj, b, d, x);
+    if (ge >= x) return x;
+    // neighbours' values may fall between two counts; each count is of an upper
+    // bound's moment, so the answer stays one and a later mark re-evaluates the row
+    int32_t lo = 0, hi = x - 1;
+    while (lo < hi) {
+        const int32_t mid = (lo + hi + 1) >> 1;
+        if (long_count(c, adj, b, d, mid) >= mid) lo = mid;
+        else hi = mid - 1;
+    }
+    return lo;
+}
+
+// sum over a group of 16 lanes, in every lane of it (row rotations)
+__device__ inline int32_t sum16(int32_t v) {
+    v += __builtin_amdgcn_update_dpp(0, v, 0x128, 0xf, 0xf, false); // row_ror:8
+    v += __builtin_amdgcn_update_dpp(0, v, 0x124, 0xf, 0xf, false); // row_ror:4
+    v += __builtin_amdgcn_update_dpp(0, v, 0x122, 0xf, 0xf, false); // row_ror:2
+    v += __builtin_amdgcn_update_dpp(0, v, 0x121, 0xf, 0xf, false); // row_ror:1
+    return v;
+}
+
+// the (lane / 16)-th lowest set bit of m, or -1
+__device__ inline int group_bit(unsigned long long m) {
+    for (int g = lane_id() >> 4; g > 0; g--) m &= m - 1;
+    return m ? __ffsll((long long)m) - 1 : -1;
+}
+
+// a row of up to C0_MAX entries, all loads in flight together (-1 past its end)
+struct Row16 {
+    int32_t u[C0_MAX];
+    __device__ Row16(const int32_t *__restrict__ adj, int32_t b, int32_t d) {
+#pragma unroll
+        for (int j = 0; j < C0_MAX; j++) u[j] = j < d ? adj[b + j] : -1;
+    }
+};
+
+__global__ __launch_bounds__(SMALL_BLOCK) void k_core_small(const int64_t *__restrict__ uoff,
+                                                            const int32_t *__restrict__ uadj, int32_t n,
+                                                            int32_t *__restrict__ lr, int32_t *__restrict__ core,
+                                                            uint32_t *__restrict__ key, CoreStats *out) {
+    __shared__ SmallLds L;
+    const int lane = lane_id(), wave = threadIdx.x >> 6;
+    constexpr int NW = SMALL_BLOCK / 64;
+    const int32_t words = (n + 63) / 64;
+    for (int32_t v = threadIdx.x; v <= n; v += SMALL_BLOCK) L.off[v] = (int32_t)uoff[v];
+    __syncthreads();
+    for (int32_t v = threadIdx.x; v < n; v += SMALL_BLOCK) L.c[v] = (uint16_t)(L.off[v + 1] - L.off[v]); // below n
+    for (int32_t w = threadIdx.x; w < words; w += SMALL_BLOCK) {
+        L.mark[0][w] = w == words - 1 && (n & 63) ? (1ull << (n & 63)) - 1 : ~0ull;
+        L.mark[1][w] = 0;
+    }
+    if (threadIdx.x < 3) L.flag[threadIdx.x] = 0;
+    if (threadIdx.x == 0) L.max_core = 0;
+    __syncthreads();
+    // Sweeps.  A vertex whose value drops to h marks every neighbour whose value is
+    // above h: those are the ones whose count it may have left.  Each sweep with a
+    // mark lowers some value or is the last, so at most sum of degrees + 2 sweeps.
+    int32_t s = 0;
+    for (;; s++) {
+        unsigned long long *now = L.mark[s & 1], *next = L.mark[(s & 1) ^ 1];
+        int32_t *flag = &L.flag[s % 3];
+        if (threadIdx.x == 0) L.flag[(s + 1) % 3] = 0;
+        for (int32_t w = wave; w < words; w += NW) {
+            const unsigned long long m = now[w];
+            if (!m) continue;
+            if (lane == 0) now[w] = 0;
+            const int32_t v = 64 * w + lane;
+            const bool on = (m >> lane) & 1ull;
+            int32_t b = 0, d = 0;
+            if (on) {
+                b = L.off[v];
+                d = L.off[v + 1] - b;
+            }
+            bool marked = false;
+            if (on && d <= C0_MAX) {
+                const Row16 row(uadj, b, d);
+                int32_t val[C0_MAX];
+#pragma unroll
+                for (int j = 0; j < C0_MAX; j++) val[j] = row.u[j] >= 0 ? L.c[row.u[j]] : -1;
+                auto count = [&](int32_t h) {
+                    int32_t k = 0;
+#pragma unroll
+                    for (int j = 0; j < C0_MAX; j++) k += val[j] >= h ? 1 : 0;
+                    return k;
+                };
+                const int32_t x = L.c[v], ge = count(x);
+                if (ge < x) {
+                    int32_t lo = ge, hi = x - 1;
+                    while (lo < hi) {
+                        const int32_t mid = (lo + hi + 1) >> 1;
+                        if (count(mid) >= mid) lo = mid;
+                        else hi = mid - 1;
+                    }
+                    L.c[v] = (uint16_t)lo;
+#pragma unroll
+                    for (int j = 0; j < C0_MAX; j++) {
+                        const int32_t u = row.u[j];
+                        if (u >= 0 && (int32_t)L.c[u] > lo) {
+                            atomicOr(&next[u >> 6], 1ull << (u & 63));
+                            marked = true;
+                        }
+                    }
+                }
+            }
+            // rows of up to 64 entries, four at a time over 16 lanes each
+            unsigned long long mid = __ballot(on && d > C0_MAX && d <= 64);
+            while (mid) {
+                const int src = group_bit(mid);
+                const int32_t bb = __shfl(b, src & 63);
+                const int32_t ds = __shfl(d, src & 63), dd = src < 0 ? 0 : ds, vv = 64 * w + (src & 63);
+                int32_t u[4], val[4];
+#pragma unroll
+                for (int j = 0; j < 4; j++) u[j] = (lane & 15) + 16 * j < dd ? uadj[bb + (lane & 15) + 16 * j] : -1;
+#pragma unroll
+                for (int j = 0; j < 4; j++) val[j] = u[j] >= 0 ? L.c[u[j]] : -1;
+                auto count = [&](int32_t h) {
+                    int32_t k = 0;
+#pragma unroll
+                    for (int j = 0; j < 4; j++) k += val[j] >= h ? 1 : 0;
+                    return sum16(k);
+                };
+                const int32_t x = src < 0 ? 0 : L.c[vv], ge = count(x);
+                int32_t lo = ge < x ? ge : x, hi = ge < x ? x - 1 : x;
+                while (__ballot(lo < hi)) { // the groups search together
+                    const int32_t m2 = (lo + hi + 1) >> 1;
+                    const bool up = count(m2) >= m2;
+                    if (lo < hi) {
+                        if (up) lo = m2;
+                        else hi = m2 - 1;
+                    }
+                }
+                if (lo < x) {
+                    if ((lane & 15) == 0) L.c[vv] = (uint16_t)lo;
+#pragma unroll
+                    for (int j = 0; j < 4; j++)
+                        if (u[j] >= 0 && (int32_t)L.c[u[j]] > lo) {
+                            atomicOr(&next[u[j] >> 6], 1ull << (u[j] & 63));
+                            marked = true;
+                        }
+                }
+                for (int g = 0; g < 4 && mid; g++) mid &= mid - 1;
+            }
+            unsigned long long big = __ballot(on && d > 64);
+            while (big) {
+                const int src = __ffsll((long long)big) - 1;
+                big &= big - 1;
+                const int32_t vv = 64 * w + src, dd = __shfl(d, src), bb = __shfl(b, src);
+                const int32_t x = L.c[vv];
+                int32_t ge;
+                const int32_t h = dd <= C1_MAX ? h_wave(L.c, uadj, bb, dd, x, ge) : h_long(L.c, uadj, bb, dd, x);
+                if (h >= x) continue;
+                if (lane == 0) L.c[vv] = (uint16_t)h;
+                for (int32_t i = lane; i < dd; i += 64) {
+                    const int32_t u = uadj[bb + i];
+                    if ((int32_t)L.c[u] > h) {
+                        atomicOr(&next[u >> 6], 1ull << (u & 63));
+                        marked = true;
+                    }
+                }
+            }
+            if (__ballot(marked) && lane == 0) *flag = 1;
+        }
+        __syncthreads();
+        if (!*flag) break;
+    }
+    // counts of neighbours at or above each vertex's core number
+    for (int32_t w = wave; w < words; w += NW) {
+        const int32_t v = 64 * w + lane;
+        int32_t b = 0, d = 0, k = 0;
+        if (v < n) {
+            b = L.off[v];
+            d = L.off[v + 1] - b;
+            k = L.c[v];
+        }
+        if (v < n && d <= C0_MAX) {
+            const Row16 row(uadj, b, d);
+            int32_t x = 0;
+#pragma unroll
+            for (int j = 0; j < C0_MAX; j++) x += row.u[j] >= 0 && L.c[row.u[j]] >= k ? 1 : 0;
+            L.cnt[v] = (uint16_t)x;
+        }
+        unsigned long long big = __ballot(d > C0_MAX);
+        while (big) {
+            const int src = group_bit(big);
+            const int32_t bb = __shfl(b, src & 63), kk = __shfl(k, src & 63);
+            const int32_t ds = __shfl(d, src & 63), dd = src < 0 ? 0 : ds;
+            int32_t x = 0;
+            for (int32_t i = lane & 15; i < dd; i += 64) {
+                int32_t u[4];
+#pragma unroll
+                for (int j = 0; j < 4; j++) u[j] = i + 16 * j < dd ? uadj[bb + i + 16 * j] : -1;
+#pragma unroll
+                for (int j = 0; j < 4; j++) x += u[j] >= 0 && L.c[u[j]] >= kk ? 1 : 0;
+            }
+            x = sum16(x);
+            if (src >= 0 && (lane & 15) == 0) L.cnt[64 * w + src] = (uint16_t)x;
+            for (int g = 0; g < 4 && big; g++) big &= big - 1;
+        }
+        for (int o = 32; o > 0; o >>= 1) {
+            const int32_t y = __shfl_xor(k, o);
+            k = y > k ? y : k;
+        }
+        if (lane == 0) {
+            atomicMax(&L.max_core, k);
+            L.mark[1][w] = 0; // none removed
+        }
+    }
+    if (threadIdx.x < 3) L.flag[threadIdx.x] = 0;
+    __syncthreads();
+    // Rounds of all levels at once: a round removes every vertex left with at most
+    // its core number of neighbours; each takes one from its neighbours of the same
+    // core that are still there.
+    unsigned long long *front = L.mark[0], *gone = L.mark[1];
+    uint32_t *cnt32 = reinterpret_cast<uint32_t *>(L.cnt);
+    int32_t r = 0;
+    for (;; r++) {
+        int32_t *flag = &L.flag[r % 3];
+        if (threadIdx.x == 0) L.flag[(r + 1) % 3] = 0;
+        for (int32_t w = wave; w < words; w += NW) {
+            const int32_t v = 64 * w + lane;
+            const unsigned long long g = gone[w];
+            const bool go = v < n && !((g >> lane) & 1ull) && L.cnt[v] <= L.c[v];
+            const unsigned long long m = __ballot(go);
+            if (go) lr[v] = r;
+            if (lane == 0) {
+                front[w] = m;
+                gone[w] = g | m;
+                if (m) *flag = 1;
+            }
+        }
+        __syncthreads();
+        if (!*flag) break;
+        for (int32_t w = wave; w < words; w += NW) {
+            const unsigned long long m = front[w];
+            if (!m) continue;
+            const int32_t v = 64 * w + lane;
+            const bool on = (m >> lane) & 1ull;
+            int32_t b = 0, d = 0, k = 0;
+            if (on) {
+                b = L.off[v];
+                d = L.off[v + 1] - b;
+                k = L.c[v];
+            }
+            auto take = [&](int32_t u, int32_t kk) {
+                if (L.c[u] == kk && !((gone[u >> 6] >> (u & 63)) & 1ull))
+                    atomicSub(&cnt32[u >> 1], 1u << (16 * (u & 1))); // its count is at least what is taken
+            };
+            if (on && d <= C0_MAX) {
+                const Row16 row(uadj, b, d);
+#pragma unroll
+                for (int j = 0; j < C0_MAX; j++)
+                    if (row.u[j] >= 0) take(row.u[j], k);
+            }
+            // longer rows, four at a time over 16 lanes each
+            unsigned long long big = __ballot(on && d > C0_MAX);
+            while (big) {
+                const int src = group_bit(big);
+                const int32_t bb = __shfl(b, src & 63), kk = __shfl(k, src & 63);
+                const int32_t ds = __shfl(d, src & 63), dd = src < 0 ? 0 : ds;
+                for (int32_t i = lane & 15; i < dd; i += 64) {
+                    int32_t u[4];
+#pragma unroll
+                    for (int j = 0; j < 4; j++) u[j] = i + 16 * j < dd ? uadj[bb + i + 16 * j] : -1;
+#pragma unroll
+                    for (int j = 0; j < 4; j++)
+                        if (u[j] >= 0) take(u[j], kk);
+                }
+                for (int g = 0; g < 4 && big; g++) big &= big - 1;
+            }
+        }
+        __syncthreads();
+    }
+    const int32_t rounds = r > 0 ? r : 1;
+    for (int32_t w = wave; w < words; w += NW) {
+        const int32_t v = 64 * w + lane;
+        if (v >= n) continue;
+        core[v] = L.c[v];
+        key[v] = (uint32_t)L.c[v] * (uint32_t)rounds + (uint32_t)lr[v];
+    }
+    if (threadIdx.x == 0) *out = CoreStats{s + 1, rounds, L.max_core};
+}
+
 // rank key core * R + round within the level (R = the rounds taken); the sort
 // that follows breaks ties by id
 __global__ void k_level_keys(const uint16_t *__restrict__ c, const int32_t *__restrict__ lr, int32_t n, uint32_t R,
@@ -1151,13 +1465,23 @@ __global__ void k_level_keys(const uint16_t *__restrict__ c, const int32_t *__re
 
 } // namespace
 
-// Core numbers (into `core`, original ids) and the rank keys (into `key`); returns
-// the number of key bits.  uoff/uadj: the undirected CSR (neighbour ids only) of
-// adj_n entries.
-int core_rank_keys(int32_t n, int64_t adj_n, const int64_t *uoff, const int32_t *uadj, const int32_t *deg, int32_t *core,
-                   uint32_t *key, hipStream_t s, CoreStats *out) {
+// Core numbers (into `core`, original ids) and the rank keys (into `key`, *key_bits
+// bits).  uoff/uadj: the undirected CSR (neighbour ids only) of adj_n entries.
+bool core_rank_keys(int32_t n, int64_t adj_n, const int64_t *uoff, const int32_t *uadj, const int32_t *deg,
+                    int32_t *core, uint32_t *key, hipStream_t s, CoreStats *out, CoreStats *dev, int *key_bits) {
     *out = CoreStats{};
-    if (n <= 0) return 1;
+    *key_bits = 1;
+    if (n <= 0) return false;
+    if (n <= SMALL_N && adj_n <= SMALL_ADJ) {
+        DevBuf round;
+        round.ensure(4 * (size_t)n);
+        k_core_small<<<1, SMALL_BLOCK, 0, s>>>(uoff, uadj, n, round.as<int32_t>(), core, key, dev);
+        FOLTY_LAUNCHED();
+        // core numbers and rounds are below n: their product fits 32 bits
+        *key_bits = 2 * bit_length((uint64_t)n);
+        static_assert((int64_t)SMALL_N * SMALL_N < (int64_t)1 << 32, "rank keys of small graphs");
+        return true;
+    }
     PinnedBuf hb;
     hb.ensure(4 * CT_WORDS);
     int32_t *h = hb.as<int32_t>();
@@ -1293,7 +1617,8 @@ int core_rank_keys(int32_t n, int64_t adj_n, const int64_t *uoff, const int32_t 
     out->sweeps = sweeps;
     out->rounds = rounds;
     out->global_h = hg;
-    return bit_length(max_key > 0 ? max_key : 1);
+    *key_bits = bit_length(max_key > 0 ? max_key : 1);
+    return false;
 }
 
 } // namespace folty

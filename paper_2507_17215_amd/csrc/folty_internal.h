@@ -480,8 +480,10 @@ size_t exclusive_scan_i32_to_i64(void *tmp, size_t tmp_bytes, const int32_t *in,
                                  int64_t n, hipStream_t stream);
 size_t inclusive_scan_i32(void *tmp, size_t tmp_bytes, const int32_t *in, int32_t *out, int64_t n,
                           hipStream_t stream);
-size_t inclusive_scan_pair_starts(void *tmp, size_t tb, const uint64_t *key, int32_t *out, int64_t n,
-                                  hipStream_t s);
+// out[k] = 1 + the index of the static pair of sorted key k: the `bits` bits from
+// bit `shift` on
+size_t inclusive_scan_pair_starts(void *tmp, size_t tb, const uint64_t *key, int shift, int bits, int32_t *out,
+                                  int64_t n, hipStream_t s);
 size_t exclusive_scan_i32(void *tmp, size_t tmp_bytes, const int32_t *in, int32_t *out, int64_t n,
                           hipStream_t stream);
 
@@ -491,8 +493,10 @@ struct CoreStats {
     int32_t rounds = 0;   // rounds of the all-levels peel
     int32_t global_h = 0; // h-index of the degree sequence (the starting bound)
 };
-int core_rank_keys(int32_t n, int64_t adj_n, const int64_t *uoff, const int32_t *uadj, const int32_t *deg, int32_t *core,
-                   uint32_t *key, hipStream_t s, CoreStats *out);
+// dev: zeroed device memory; a small graph's stats are left there instead of in
+// *out, without a synchronisation, and true is returned
+bool core_rank_keys(int32_t n, int64_t adj_n, const int64_t *uoff, const int32_t *uadj, const int32_t *deg,
+                    int32_t *core, uint32_t *key, hipStream_t s, CoreStats *out, CoreStats *dev, int *key_bits);
 
 inline int bit_length(uint64_t x) {
     int b = 0;

@@ -10,6 +10,7 @@
 //     CSR sorted by head;
 //   * count static triangles per oriented edge and per static edge (the latter
 //     is |N(u) & N(v)|, the counter c_uv of Section 3's preamble).
+#include <algorithm>
 #include <cstring>
 
 #include "folty_internal.h"
@@ -82,7 +83,8 @@ __global__ void k_validate(const int32_t *__restrict__ src, const int32_t *__res
             if (i > 0 && prev > ti[u]) desc++;
         }
     }
-    // one atomic per wavefront and quantity
+    // one atomic per block and quantity: they share a cache line and take about
+    // 11 ns each, so a wavefront's own would outlast the loads of a small input
     for (int o = 32; o > 0; o >>= 1) {
         loops += __shfl_xor(loops, o);
         desc += __shfl_xor(desc, o);
@@ -90,7 +92,22 @@ __global__ void k_validate(const int32_t *__restrict__ src, const int32_t *__res
         tmax = tm > tmax ? tm : tmax;
         bad = bd < bad ? bd : bad;
     }
-    if (lane_id() != 0) return;
+    __shared__ unsigned long long s_v[4][BLK / 64];
+    if (lane == 0) {
+        const int w = threadIdx.x >> 6;
+        s_v[0][w] = loops;
+        s_v[1][w] = desc;
+        s_v[2][w] = tmax;
+        s_v[3][w] = bad;
+    }
+    __syncthreads();
+    if (threadIdx.x != 0) return;
+    for (int w = 1; w < BLK / 64; w++) {
+        loops += s_v[0][w];
+        desc += s_v[1][w];
+        tmax = s_v[2][w] > tmax ? s_v[2][w] : tmax;
+        bad = s_v[3][w] < bad ? s_v[3][w] : bad;
+    }
     if (loops) atomicAdd(&out->loops, loops);
     if (desc) atomicAdd(&out->descents, desc);
     if (tmax) atomicMax(&out->tmax, tmax);
@@ -118,32 +135,65 @@ __global__ void k_iota_tkeys(const int64_t *__restrict__ t, uint64_t *__restrict
     }
 }
 
-// pair key of the edge at time-order position j: ((lo * n + hi) * 2 + dir);
-// self-loops get 2 n^2, which sorts after every real key
+// pair key of an edge: ((lo * n + hi) * 2 + dir); self-loops get 2 n^2, which
+// sorts after every real key
+__device__ inline uint64_t pair_key(int64_t a, int64_t b, int64_t n) {
+    if (a == b) return 2ull * (uint64_t)n * (uint64_t)n;
+    const uint64_t lo = a < b ? a : b, hi = a < b ? b : a;
+    return (lo * (uint64_t)n + hi) * 2ull + (a > b ? 1ull : 0ull);
+}
+
+// Where a grouping key holds the pair key (kb bits from bit ps) and the low bits
+// of the timestamp (low bits from bit ts; none if low is 0).  An input in time order
+// is sorted by the pair alone, which then sits in the lowest bits; otherwise the
+// timestamp sits below the pair and is sorted too.
+struct KeyForm {
+    int kb, ps, low, ts;
+    __host__ __device__ uint64_t pair(uint64_t key) const { return key >> ps & ((1ull << kb) - 1); }
+    __host__ __device__ uint64_t time(uint64_t key) const { return key >> ts & ((1ull << low) - 1); }
+};
+
+// Keys that carry the timestamp's low bits beside the pair key, values the
+// input positions: the sort moves the timestamps along in bits it has to spare.
+__global__ void k_pair_time_keys(const int32_t *__restrict__ src, const int32_t *__restrict__ dst,
+                                 const int64_t *__restrict__ t, int64_t n, KeyForm F, uint64_t *__restrict__ key,
+                                 int32_t *__restrict__ pos, int64_t m) {
+    const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    if (i >= m) return;
+    key[i] = pair_key(src[i], dst[i], n) << F.ps | ((uint64_t)t[i] & ((1ull << F.low) - 1)) << F.ts;
+    pos[i] = (int32_t)i;
+}
+
+// first[h] = the first input position with t >> low >= h, h in [0, nh] (t ascending)
+__global__ void k_time_steps(const int64_t *__restrict__ t, int64_t m, int low, int32_t nh, int32_t *__restrict__ first) {
+    const int32_t h = (int32_t)(blockIdx.x * blockDim.x + threadIdx.x);
+    if (h > nh) return;
+    int64_t a = 0, b = m;
+    while (a < b) {
+        const int64_t mid = (a + b) >> 1;
+        if ((t[mid] >> low) < h) a = mid + 1;
+        else b = mid;
+    }
+    first[h] = (int32_t)a;
+}
+
+// pair keys alone, in time order (idx_t: input positions in time order, null when
+// the input is), values the time-order positions
 __global__ void k_pair_keys(const int32_t *__restrict__ idx_t, const int32_t *__restrict__ src,
                             const int32_t *__restrict__ dst, int64_t n, uint64_t *__restrict__ key,
                             int32_t *__restrict__ pos, int64_t m) {
     int64_t j = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (j >= m) return;
     int64_t i = idx_t ? idx_t[j] : j;
-    int64_t a = src[i], b = dst[i];
-    uint64_t k;
-    if (a == b) {
-        k = 2ull * (uint64_t)n * (uint64_t)n;
-    } else {
-        uint64_t lo = a < b ? a : b, hi = a < b ? b : a;
-        k = (lo * (uint64_t)n + hi) * 2ull + (a > b ? 1ull : 0ull);
-    }
-    key[j] = k;
+    key[j] = pair_key(src[i], dst[i], n);
     pos[j] = (int32_t)j;
 }
 
-__global__ void k_gather_sorted(const int32_t *__restrict__ pos, const int32_t *__restrict__ idx_t,
-                                const int64_t *__restrict__ t, int32_t *__restrict__ perm,
-                                int64_t *__restrict__ ts, int64_t m) {
+__global__ void k_gather_sorted(const int32_t *__restrict__ idx_t, const int64_t *__restrict__ t,
+                                int32_t *__restrict__ perm, int64_t *__restrict__ ts, int64_t m) {
     int64_t k = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (k >= m) return;
-    int32_t j = pos[k];
+    int32_t j = perm[k];
     int32_t i = idx_t ? idx_t[j] : j;
     perm[k] = i;
     ts[k] = t[i];
@@ -167,25 +217,50 @@ __device__ inline void divmod_n(uint64_t x, uint64_t n, double inv_n, int32_t &q
     r = (int32_t)rr;
 }
 
-__global__ void k_static_table(const uint64_t *__restrict__ key, int32_t *__restrict__ sid, int32_t m,
-                               int64_t n, double inv_n, int32_t *__restrict__ soff, int32_t *__restrict__ smid,
-                               int32_t *__restrict__ slo, int32_t *__restrict__ shi) {
-    int64_t k = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (k >= m) return;
-    int32_t s = sid[k] - 1;
-    sid[k] = s;
-    uint64_t kk = key[k];
-    uint64_t pk = kk >> 1;
-    bool first = (k == 0) || ((key[k - 1] >> 1) != pk);
-    if (first) {
-        soff[s] = (int32_t)k;
-        int32_t lo, hi;
-        divmod_n(pk, (uint64_t)n, inv_n, lo, hi);
-        slo[s] = lo;
-        shi[s] = hi;
+// Static edge table from the sorted keys.  If those carry timestamps it also writes the
+// timestamps: their bits above F.low are 0 when nh = 0, or, for an input in time order, the step that holds the edge's input position
+// (steps: k_time_steps' array in LDS).
+constexpr int MAX_STEPS = 4096;
+__global__ __launch_bounds__(BLK) void k_static_table(const uint64_t *__restrict__ key, const int32_t *__restrict__ perm,
+                                                      int32_t *__restrict__ sid, int32_t m, int64_t n, double inv_n,
+                                                      KeyForm F, const int32_t *__restrict__ steps, int32_t nh,
+                                                      int64_t *__restrict__ ts, int32_t *__restrict__ soff,
+                                                      int32_t *__restrict__ smid, int32_t *__restrict__ slo,
+                                                      int32_t *__restrict__ shi) {
+    extern __shared__ int32_t s_step[];
+    for (int32_t i = threadIdx.x; i < nh; i += BLK) s_step[i] = steps[i + 1]; // first position past step i
+    __syncthreads();
+    const int64_t stride = (int64_t)gridDim.x * BLK;
+    for (int64_t k = (int64_t)blockIdx.x * BLK + threadIdx.x; k < m; k += stride) {
+        const int32_t s = sid[k] - 1;
+        sid[k] = s;
+        const uint64_t full = key[k], kk = F.pair(full);
+        const uint64_t prev = k > 0 ? F.pair(key[k - 1]) : ~0ull;
+        if (F.low > 0) {
+            int32_t h = 0;
+            if (nh > 0) { // the number of steps that end at or before the position
+                const int32_t i = perm[k];
+                int32_t b = nh;
+                while (h < b) {
+                    const int32_t mid = (h + b) >> 1;
+                    if (s_step[mid] <= i) h = mid + 1;
+                    else b = mid;
+                }
+            }
+            ts[k] = (int64_t)h << F.low | (int64_t)F.time(full);
+        }
+        const uint64_t pk = kk >> 1;
+        const bool first = k == 0 || (prev >> 1) != pk;
+        if (first) {
+            soff[s] = (int32_t)k;
+            int32_t lo, hi;
+            divmod_n(pk, (uint64_t)n, inv_n, lo, hi);
+            slo[s] = lo;
+            shi[s] = hi;
+        }
+        if ((kk & 1ull) && (first || (prev & 1ull) == 0)) smid[s] = (int32_t)k;
+        if (k == m - 1) soff[s + 1] = m;
     }
-    if ((kk & 1ull) && (first || (key[k - 1] & 1ull) == 0)) smid[s] = (int32_t)k;
-    if (k == m - 1) soff[s + 1] = m;
 }
 
 struct PairStats {
@@ -457,10 +532,8 @@ void load_graph(Graph *g, int32_t n, int64_t m, const int32_t *src, const int32_
     k_init_val<<<1, 1, 0, s>>>(vo.as<ValOut>());
     FOLTY_LAUNCHED();
     if (m > 0) {
-        // 1,024 blocks: the wavefronts' closing atomics on one cache line are
-        // serialised (a few ns each), so a larger grid loses more there than it
-        // gains in loads in flight (70M edges: 0.21 ms; 4,096 blocks 0.28 ms)
-        k_validate<<<grid_for(m, BLK, 1024), BLK, 0, s>>>(g->in_src, g->in_dst, g->in_t, m, n, vo.as<ValOut>());
+        // 16 edges per thread or more, and at most 2,048 blocks
+        k_validate<<<grid_for((m + 15) / 16, BLK, 2048), BLK, 0, s>>>(g->in_src, g->in_dst, g->in_t, m, n, vo.as<ValOut>());
         FOLTY_LAUNCHED();
     }
     PinnedBuf hb;
@@ -508,59 +581,85 @@ void build_index(Graph *g, const folty_build_opts *opts) {
     // ---- a.2: group by (lo, hi, dir, t, input position) ----------------------
     const int32_t m = (int32_t)(min - ix.self_loops);
     ix.m = m;
-    DevBuf idx_t, tkeys, tkeys2, idx_t2, pkey, pkey2, pos, pos2;
+    // A sort key has 64 bits, the pair key takes kb of them.  The timestamps ride
+    // along in the rest when they fit (then an unsorted input needs no sort by time
+    // of its own: the one sort takes all the bits), or all but their highest few
+    // bits when the input is in time order (those follow from the input position).
+    // That replaces a random gather of every timestamp, 1.4 ms at 70M edges.
+    DevBuf idx_t, tkeys, tkeys2, idx_t2, pkey, pkey2, pos, steps;
     const int32_t *idx_time = nullptr; // nullptr = identity (input already in time order)
-    if (min > 0 && !g->sorted_by_time) {
-        tkeys.ensure(8 * min);
-        tkeys2.ensure(8 * min);
-        idx_t.ensure(4 * min);
-        idx_t2.ensure(4 * min);
-        k_iota_tkeys<<<grid_for(min, BLK), BLK, 0, s>>>(g->in_t, tkeys.as<uint64_t>(),
-                                                        idx_t.as<int32_t>(), min);
-        FOLTY_LAUNCHED();
-        int tb = bit_length((uint64_t)g->tmax);
-        size_t need = sort_pairs_u64_i32(nullptr, 0, tkeys.as<uint64_t>(), tkeys2.as<uint64_t>(),
-                                         idx_t.as<int32_t>(), idx_t2.as<int32_t>(), min, tb, s);
-        sort_pairs_u64_i32(cub_ensure(need), need, tkeys.as<uint64_t>(), tkeys2.as<uint64_t>(),
-                           idx_t.as<int32_t>(), idx_t2.as<int32_t>(), min, tb, s);
-        tkeys.release();
-        tkeys2.release();
-        idx_time = idx_t2.as<int32_t>();
+    const int kb = bit_length(2ull * (uint64_t)n * (uint64_t)n), tb = bit_length((uint64_t)g->tmax);
+    int low = std::max(1, tb);
+    int32_t nh = 0;
+    if (kb + low > 64) {
+        low = 64 - kb;
+        const int high = tb - low;
+        if (!g->sorted_by_time || low < 1 || high > 12 || (1 << high) > MAX_STEPS) low = 0;
+        else nh = (int32_t)(g->tmax >> low) + 1;
     }
+    // an input in time order is sorted by the pair bits alone: stable, so equal pairs
+    // keep the time order
+    const KeyForm form = g->sorted_by_time || low == 0 ? KeyForm{kb, 0, low, kb} : KeyForm{kb, low, low, 0};
+    const int bits = form.ps + kb;
+    ix.ts.ensure(8 * (size_t)m);
+    ix.perm.ensure(4 * (size_t)min);
+    ix.sid.ensure(4 * (size_t)m);
     if (min > 0) {
         pkey.ensure(8 * min);
         pkey2.ensure(8 * min);
         pos.ensure(4 * min);
-        pos2.ensure(4 * min);
-        k_pair_keys<<<grid_for(min, BLK), BLK, 0, s>>>(idx_time, g->in_src, g->in_dst,
-                                                       n, pkey.as<uint64_t>(), pos.as<int32_t>(), min);
-        FOLTY_LAUNCHED();
-        int kb = bit_length(2ull * (uint64_t)n * (uint64_t)n);
-        size_t need = sort_pairs_u64_i32(nullptr, 0, pkey.as<uint64_t>(), pkey2.as<uint64_t>(),
-                                         pos.as<int32_t>(), pos2.as<int32_t>(), min, kb, s);
-        sort_pairs_u64_i32(cub_ensure(need), need, pkey.as<uint64_t>(), pkey2.as<uint64_t>(),
-                           pos.as<int32_t>(), pos2.as<int32_t>(), min, kb, s);
+        if (low > 0) {
+            k_pair_time_keys<<<grid_for(min, BLK), BLK, 0, s>>>(g->in_src, g->in_dst, g->in_t, n, form,
+                                                                pkey.as<uint64_t>(), pos.as<int32_t>(), min);
+            if (nh > 0) {
+                steps.ensure(4 * ((size_t)nh + 1));
+                k_time_steps<<<grid_for(nh + 1, BLK), BLK, 0, s>>>(g->in_t, min, low, nh, steps.as<int32_t>());
+            }
+            FOLTY_LAUNCHED();
+        } else {
+            if (!g->sorted_by_time) {
+                tkeys.ensure(8 * min);
+                tkeys2.ensure(8 * min);
+                idx_t.ensure(4 * min);
+                idx_t2.ensure(4 * min);
+                k_iota_tkeys<<<grid_for(min, BLK), BLK, 0, s>>>(g->in_t, tkeys.as<uint64_t>(), idx_t.as<int32_t>(),
+                                                                min);
+                FOLTY_LAUNCHED();
+                size_t need = sort_pairs_u64_i32(nullptr, 0, tkeys.as<uint64_t>(), tkeys2.as<uint64_t>(),
+                                                 idx_t.as<int32_t>(), idx_t2.as<int32_t>(), min, tb, s);
+                sort_pairs_u64_i32(cub_ensure(need), need, tkeys.as<uint64_t>(), tkeys2.as<uint64_t>(),
+                                   idx_t.as<int32_t>(), idx_t2.as<int32_t>(), min, tb, s);
+                tkeys.release();
+                tkeys2.release();
+                idx_time = idx_t2.as<int32_t>();
+            }
+            k_pair_keys<<<grid_for(min, BLK), BLK, 0, s>>>(idx_time, g->in_src, g->in_dst, n, pkey.as<uint64_t>(),
+                                                           pos.as<int32_t>(), min);
+            FOLTY_LAUNCHED();
+        }
+        size_t need = sort_pairs_u64_i32(nullptr, 0, pkey.as<uint64_t>(), pkey2.as<uint64_t>(), pos.as<int32_t>(),
+                                         ix.perm.as<int32_t>(), min, bits, s);
+        sort_pairs_u64_i32(cub_ensure(need), need, pkey.as<uint64_t>(), pkey2.as<uint64_t>(), pos.as<int32_t>(),
+                           ix.perm.as<int32_t>(), min, bits, s);
         pkey.release();
         pos.release();
     }
-    ix.ts.ensure(8 * (size_t)m);
-    ix.perm.ensure(4 * (size_t)m);
-    ix.sid.ensure(4 * (size_t)m);
-    if (m > 0) {
-        k_gather_sorted<<<grid_for(m, BLK), BLK, 0, s>>>(pos2.as<int32_t>(), idx_time, g->in_t,
-                                                         ix.perm.as<int32_t>(), ix.ts.as<int64_t>(), m);
+    if (m > 0 && low == 0) {
+        k_gather_sorted<<<grid_for(m, BLK), BLK, 0, s>>>(idx_time, g->in_t, ix.perm.as<int32_t>(),
+                                                         ix.ts.as<int64_t>(), m);
         FOLTY_LAUNCHED();
     }
     idx_t.release();
     idx_t2.release();
-    pos2.release();
 
     // ---- static edge table -----------------------------------------------------
     int32_t S = 0;
     if (m > 0) {
         // sid[k] = 1 + the static pair of sorted edge k (k_static_table makes it 0-based)
-        size_t need = inclusive_scan_pair_starts(nullptr, 0, pkey2.as<uint64_t>(), ix.sid.as<int32_t>(), m, s);
-        inclusive_scan_pair_starts(cub_ensure(need), need, pkey2.as<uint64_t>(), ix.sid.as<int32_t>(), m, s);
+        size_t need = inclusive_scan_pair_starts(nullptr, 0, pkey2.as<uint64_t>(), form.ps + 1, kb - 1,
+                                                 ix.sid.as<int32_t>(), m, s);
+        inclusive_scan_pair_starts(cub_ensure(need), need, pkey2.as<uint64_t>(), form.ps + 1, kb - 1,
+                                                 ix.sid.as<int32_t>(), m, s);
         FOLTY_HIP(hipMemcpyAsync(hb.p, ix.sid.as<int32_t>() + (m - 1), 4, hipMemcpyDeviceToHost, s));
         FOLTY_HIP(hipStreamSynchronize(s));
         S = *hb.as<int32_t>();
@@ -570,21 +669,23 @@ void build_index(Graph *g, const folty_build_opts *opts) {
     ix.smid.ensure(4 * (size_t)S + 4);
     ix.slo.ensure(4 * (size_t)S + 4);
     ix.shi.ensure(4 * (size_t)S + 4);
-    // PairStats, then at STAT_ORIENT the OrientStats
-    constexpr size_t STAT_ORIENT = 32;
+    // PairStats, then the OrientStats and a small graph's CoreStats
+    constexpr size_t STAT_ORIENT = 32, STAT_CORE = 64, STAT_BYTES = 96;
     DevBuf stat;
-    stat.ensure(64);
+    stat.ensure(STAT_BYTES);
     static_assert(sizeof(PairStats) <= STAT_ORIENT && sizeof(OrientStats) <= STAT_ORIENT, "");
-    k_fill<unsigned long long><<<1, 8, 0, s>>>(stat.as<unsigned long long>(), 0ull, 8);
+    k_fill<unsigned long long><<<1, 64, 0, s>>>(stat.as<unsigned long long>(), 0ull, STAT_BYTES / 8);
     FOLTY_LAUNCHED();
     if (S == 0) {
         k_fill<int32_t><<<1, 1, 0, s>>>(ix.soff.as<int32_t>(), 0, 1);
         FOLTY_LAUNCHED();
     } else {
         k_fill<int32_t><<<grid_for(S, BLK), BLK, 0, s>>>(ix.smid.as<int32_t>(), -1, S);
-        k_static_table<<<grid_for(m, BLK), BLK, 0, s>>>(pkey2.as<uint64_t>(), ix.sid.as<int32_t>(), m, n,
-                                                        1.0 / (double)n, ix.soff.as<int32_t>(), ix.smid.as<int32_t>(),
-                                                        ix.slo.as<int32_t>(), ix.shi.as<int32_t>());
+        // with steps to stage, a grid of a few blocks per CU
+        k_static_table<<<grid_for(m, BLK, nh > 0 ? 4096 : 0), BLK, 4 * (size_t)nh, s>>>(
+            pkey2.as<uint64_t>(), ix.perm.as<int32_t>(), ix.sid.as<int32_t>(), m, n, 1.0 / (double)n, form,
+            steps.as<int32_t>(), nh, ix.ts.as<int64_t>(), ix.soff.as<int32_t>(), ix.smid.as<int32_t>(),
+            ix.slo.as<int32_t>(), ix.shi.as<int32_t>());
         k_fix_smid_stats<<<grid_for(S, BLK, 2048), BLK, 0, s>>>(ix.soff.as<int32_t>(), ix.smid.as<int32_t>(), S,
                                                                 stat.as<PairStats>());
         FOLTY_LAUNCHED();
@@ -628,10 +729,11 @@ void build_index(Graph *g, const folty_build_opts *opts) {
     DevBuf rnd;
     rnd.ensure(4 * (size_t)n);
     CoreStats cst{};
-    const int key_bits = core_rank_keys(n, 2 * (int64_t)S, uoff.as<int64_t>(), uadj.as<int32_t>(), ix.deg.as<int32_t>(),
-                                        ix.core.as<int32_t>(), rnd.as<uint32_t>(), s, &cst);
-    ix.peel_rounds = cst.rounds;
-    ix.core_sweeps = cst.sweeps;
+    int key_bits = 32;
+    const bool core_on_device =
+        core_rank_keys(n, 2 * (int64_t)S, uoff.as<int64_t>(), uadj.as<int32_t>(), ix.deg.as<int32_t>(),
+                       ix.core.as<int32_t>(), rnd.as<uint32_t>(), s, &cst,
+                       reinterpret_cast<CoreStats *>(stat.as<char>() + STAT_CORE), &key_bits);
     uoff.release();
     uadj.release();
 
@@ -695,12 +797,15 @@ void build_index(Graph *g, const folty_build_opts *opts) {
     // ---- read back sizes ------------------------------------------------------------
     {
         char *h = hb.as<char>();
-        FOLTY_HIP(hipMemcpyAsync(h, stat.p, 64, hipMemcpyDeviceToHost, s));
+        FOLTY_HIP(hipMemcpyAsync(h, stat.p, STAT_BYTES, hipMemcpyDeviceToHost, s));
         FOLTY_HIP(hipStreamSynchronize(s));
         PairStats ps;
         OrientStats os;
         memcpy(&ps, h, sizeof ps);
         memcpy(&os, h + STAT_ORIENT, sizeof os);
+        if (core_on_device) memcpy(&cst, h + STAT_CORE, sizeof cst);
+        ix.peel_rounds = cst.rounds;
+        ix.core_sweeps = cst.sweeps;
         ix.P = (int64_t)ps.pairs;
         ix.sigma_max = (int64_t)ps.sigma_max;
         ix.W = (int64_t)os.wedges;

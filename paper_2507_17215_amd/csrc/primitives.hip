@@ -109,20 +109,23 @@ size_t exclusive_scan_i32(void *tmp, size_t tb, const int32_t *in, int32_t *out,
 }
 
 namespace {
-// 1 where a new (lo, hi) pair starts in the sorted grouping keys (key >> 1)
+// 1 where a new (lo, hi) pair starts in the sorted grouping keys
 struct PairStart {
     const uint64_t *key;
-    __device__ int32_t operator()(int64_t k) const { return k == 0 || (key[k] >> 1) != (key[k - 1] >> 1); }
+    int shift;
+    uint64_t mask; // of the shifted pair
+    __device__ int32_t operator()(int64_t k) const { return k == 0 || ((key[k] ^ key[k - 1]) >> shift & mask) != 0; }
 };
 } // namespace
 
 // out[k] = 1 + the index of the static pair of sorted key k: an inclusive scan
 // of pair starts computed from the keys as the scan reads them
-size_t inclusive_scan_pair_starts(void *tmp, size_t tb, const uint64_t *key, int32_t *out, int64_t n,
+size_t inclusive_scan_pair_starts(void *tmp, size_t tb, const uint64_t *key, int shift, int bits, int32_t *out,
+                                  int64_t n,
                                   hipStream_t s) {
     // rocPRIM's default configuration: with 64 items per thread the key reads of
     // the transform slow it down (70M keys: 0.32 ms default, 0.40 ms with 64)
-    auto in = rocprim::make_transform_iterator(rocprim::counting_iterator<int64_t>(0), PairStart{key});
+    auto in = rocprim::make_transform_iterator(rocprim::counting_iterator<int64_t>(0), PairStart{key, shift, (1ull << bits) - 1});
     size_t need = 0;
     FOLTY_PRIM(rocprim::inclusive_scan(nullptr, need, in, out, (size_t)n, rocprim::plus<int32_t>(), s));
     if (!tmp) return need;

@@ -171,3 +171,40 @@ def test_enumeration_at_row_length_edges(d):
                 r = G.query(delta, (1, 4), v, one_pass=one)
                 assert np.array_equal(r.counts(), o.query(delta, 1, 4, v)["counts"])
     o.close()
+
+
+@pytest.mark.parametrize("n,m,tmax,loops,shuffle", [
+    (2, 5, 3, False, False), (7, 64, 1, True, True), (300, 4097, 0, True, False),
+    (3000, 20_000, (1 << 62) - 1, True, True),       # pair and time bits do not fit one key, not in order
+    (3000, 20_000, (1 << 62) - 1, True, False),      # nor their low bits with a table of steps
+    (1 << 22, 30_000, (1 << 24) - 5, True, False),   # 46 + 24 bits: the low 18 in the key, 64 steps
+    (1 << 22, 30_000, (1 << 30) - 9, False, False),  # 12 high bits: the most the steps take
+    (1 << 22, 30_000, (1 << 31) - 9, False, False),  # 13: gathered
+    (1 << 22, 30_000, (1 << 24) - 5, True, True),    # too long for one key, unsorted: sorted by time first
+    (12_288, 39_000, 5_000, False, True), (12_289, 39_000, 5_000, False, True),  # the one-block core phase and past it
+])
+def test_grouping_keys_and_core_phase_sizes(n, m, tmax, loops, shuffle):
+    """Every form of the grouping keys (timestamps beside the pair in one 64-bit
+    key, their high bits from the input position, sorts by time and pair) and the
+    core phase of small graphs at its size limit: counts and pairs against the
+    oracle, core numbers and ranks against its peel."""
+    rng = np.random.default_rng(n + m)
+    hubs = rng.integers(0, n, size=40)
+    src = np.where(rng.random(m) < 0.4, hubs[rng.integers(0, 40, m)], rng.integers(0, min(n, 2000), m)).astype(np.int32)
+    dst = np.where(rng.random(m) < 0.4, hubs[rng.integers(0, 40, m)], rng.integers(0, min(n, 2000), m)).astype(np.int32)
+    if not loops:
+        keep = src != dst
+        src, dst = src[keep], dst[keep]
+    t = np.sort(rng.integers(0, tmax, size=src.size, endpoint=True)).astype(np.int64)
+    if shuffle:
+        p = rng.permutation(src.size)
+        src, dst, t = src[p], dst[p], t[p]
+    say("grouping", n, m, tmax, loops, shuffle)
+    o = Oracle(n, src, dst, t)
+    G = folty.Graph(n, src, dst, t).build()
+    for d in (tmax // 50, tmax):
+        for v in (0, 6):
+            assert_same(G.query(d, (1, 4), v), o.query(d, 1, 4, v))
+    assert np.array_equal(G.core_numbers(), o.core_numbers())
+    assert np.array_equal(G.ranks(), o.degeneracy_rank())
+    o.close()
