@@ -147,7 +147,7 @@ constexpr int HEAVY_JOB = 40; // slots are below 2^40
 __global__ __launch_bounds__(BLK) void k_plan_light(CandBuf B, const GroupDev *__restrict__ groups,
                                                     const int32_t *__restrict__ gjobs, const JobDev *__restrict__ jobs,
                                                     Heavy *__restrict__ heavy, unsigned long long *__restrict__ counter,
-                                                    int64_t cap, int piece, unsigned long long *__restrict__ tests) {
+                                                    int64_t cap, int piece, unsigned long long *__restrict__ scal) {
     __shared__ FlatLds<false> flds[WPB];
     const int w = wave_id();
     const int lane = lane_id();
@@ -199,7 +199,7 @@ __global__ __launch_bounds__(BLK) void k_plan_light(CandBuf B, const GroupDev *_
         }
     }
     for (int o = 32; o > 0; o >>= 1) mine += __shfl_xor(mine, o);
-    if (lane == 0 && mine) atomicAdd(tests, (unsigned long long)mine);
+    if (lane == 0 && mine) region_add(scal, REGION_TESTS, (unsigned long long)mine);
 }
 
 __global__ __launch_bounds__(BLK) void k_plan_pieces(CandBuf B, const JobDev *__restrict__ jobs,
@@ -541,7 +541,7 @@ static void enqueue_tests(Plan &P, int ipt, int blocks, hipStream_t s) {
     unsigned long long *scal = P.scal.as<unsigned long long>();
     const unsigned lb = (unsigned)std::max<int64_t>(1, std::min<int64_t>((P.chunks + WPB - 1) / WPB, blocks));
     k_plan_light<<<lb, BLK, 0, s>>>(P.cand, P.d_groups.as<GroupDev>(), P.d_gjobs.as<int32_t>(), P.d_jobs.as<JobDev>(),
-                                    P.heavy.as<Heavy>(), scal + SCAL_HEAVY, P.heavy_cap, ipt, scal + SCAL_TESTS);
+                                    P.heavy.as<Heavy>(), scal + SCAL_HEAVY, P.heavy_cap, ipt, scal);
     const unsigned pb = (unsigned)std::max<int64_t>(1, std::min<int64_t>(P.chunks * 16, PIECE_BLOCKS));
     k_plan_pieces<<<pb, BLK, 0, s>>>(P.cand, P.d_jobs.as<JobDev>(), P.heavy.as<Heavy>(), scal + SCAL_HEAVY,
                                      P.heavy_cap, ipt);
@@ -579,8 +579,11 @@ static void tune(Plan &P) {
     const int nj = (int)P.jobs.size();
     hipStream_t s = P.stream;
     int64_t tests = 0;
-    FOLTY_HIP(hipMemcpyAsync(&tests, P.scal.as<int64_t>() + SCAL_TESTS, 8, hipMemcpyDeviceToHost, s));
+    PinnedBuf hb;
+    hb.ensure(SCAL_BYTES);
+    FOLTY_HIP(hipMemcpyAsync(hb.p, P.scal.p, SCAL_BYTES, hipMemcpyDeviceToHost, s));
     FOLTY_HIP(hipStreamSynchronize(s));
+    for (int r = 0; r < MAX_REGIONS; r++) tests += hb.as<int64_t>()[SCAL_REGIONS + r * REGION_WORDS + REGION_TESTS];
     P.last_tests = tests;
     const std::pair<int, int> bucket{log2_ceil(tests), log2_ceil(P.total_w)};
     {
@@ -607,8 +610,8 @@ static void tune(Plan &P) {
     for (int ip : ipts)
         for (int bl : blocks) {
             for (int j = 0; j < nj; j++) clear_hist(P, j, s);
-            k_fill<unsigned long long><<<1, BLK, 0, s>>>(P.scal.as<unsigned long long>() + SCAL_TESTS, 0ull,
-                                                         SCAL_HEAVY + 1 - SCAL_TESTS); // the filter's chunks stay
+            // the filter's chunks stay (the tests' count has been read)
+            k_fill<unsigned long long><<<1, 1, 0, s>>>(P.scal.as<unsigned long long>() + SCAL_HEAVY, 0ull, 1);
             FOLTY_HIP(hipEventRecord(P.ev[1], s));
             enqueue_tests(P, ip, bl, s);
             FOLTY_HIP(hipEventRecord(P.ev[2], s));

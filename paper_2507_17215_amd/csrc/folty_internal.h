@@ -236,18 +236,25 @@ static_assert(sizeof(EdgeRec) == 32, "two records per cache line");
 // The triangles a filter keeps (tri_device.h)
 constexpr int CAND_STRIDE = 32; // words between two regions' counters
 constexpr int MAX_REGIONS = 32;
-// A query's scalars (64-bit words of Workspace::scal), cleared together at its start
+// A query's scalars (64-bit words of Workspace::scal), cleared together at its start.
+// Atomics on one address take about 11 ns each here, one after another, so what
+// thousands of wavefronts or blocks add up is kept per region, on the region's
+// cache line, and summed on the host.
 enum : int {
     SCAL_THRESHOLD = 0, // [4] the threshold step's
     SCAL_TRIAD = 4,     // [3] the exists-exists-exists totals: triangles, overflow, solutions
-    SCAL_TESTS = 8,     // temporal tests
-    SCAL_KEPT = 9,      // triangles the filter's first pass kept
-    SCAL_HITS = 10,     // triangles seen
     SCAL_HEAVY = 11,    // heavy triangles and pieces
     SCAL_DROPPED = 12,  // chunks dropped (32 bits)
-    SCAL_REGIONS = 16,  // chunks taken, per region (32 bits each, CAND_STRIDE words of 32 bits apart)
-    SCAL_WORDS = SCAL_REGIONS + MAX_REGIONS * CAND_STRIDE / 2
+    SCAL_REGIONS = 16,  // the regions' lines, REGION_WORDS words each
+    REGION_WORDS = 16,
+    REGION_CHUNKS = 0,  // chunks taken (32 bits)
+    REGION_HITS = 1,    // triangles seen
+    REGION_TESTS = 2,   // temporal tests
+    REGION_KEPT = 3,    // triangles kept
+    REGION_CERTS = 4,   // certificates
+    SCAL_WORDS = SCAL_REGIONS + MAX_REGIONS * REGION_WORDS
 };
+static_assert(2 * REGION_WORDS == CAND_STRIDE, "a cache line per region");
 constexpr size_t SCAL_BYTES = 8 * (size_t)SCAL_WORDS;
 // past the scalars: the sorted pairs of a small result (u, v, certificates), so
 // that one copy brings back everything

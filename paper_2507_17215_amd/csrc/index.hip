@@ -532,8 +532,9 @@ void load_graph(Graph *g, int32_t n, int64_t m, const int32_t *src, const int32_
     k_init_val<<<1, 1, 0, s>>>(vo.as<ValOut>());
     FOLTY_LAUNCHED();
     if (m > 0) {
-        // 16 edges per thread or more, and at most 2,048 blocks
-        k_validate<<<grid_for((m + 15) / 16, BLK, 2048), BLK, 0, s>>>(g->in_src, g->in_dst, g->in_t, m, n, vo.as<ValOut>());
+        // 16 edges per thread or more, and at most 768 blocks: more of them gain less
+        // in loads in flight than their atomics cost
+        k_validate<<<grid_for((m + 15) / 16, BLK, 768), BLK, 0, s>>>(g->in_src, g->in_dst, g->in_t, m, n, vo.as<ValOut>());
         FOLTY_LAUNCHED();
     }
     PinnedBuf hb;
@@ -686,7 +687,7 @@ void build_index(Graph *g, const folty_build_opts *opts) {
             pkey2.as<uint64_t>(), ix.perm.as<int32_t>(), ix.sid.as<int32_t>(), m, n, 1.0 / (double)n, form,
             steps.as<int32_t>(), nh, ix.ts.as<int64_t>(), ix.soff.as<int32_t>(), ix.smid.as<int32_t>(),
             ix.slo.as<int32_t>(), ix.shi.as<int32_t>());
-        k_fix_smid_stats<<<grid_for(S, BLK, 2048), BLK, 0, s>>>(ix.soff.as<int32_t>(), ix.smid.as<int32_t>(), S,
+        k_fix_smid_stats<<<grid_for(S, BLK, 768), BLK, 0, s>>>(ix.soff.as<int32_t>(), ix.smid.as<int32_t>(), S,
                                                                 stat.as<PairStats>());
         FOLTY_LAUNCHED();
     }

@@ -200,57 +200,64 @@ struct ThreshArgs {
     int zero_never;                  // theta > 0 and |U| >= 1 for every edge: count 0 never certifies
     int any;                         // the inner exists of a vertex query: count >= 1 qualifies
     uint32_t *ncert;                 // [2S]: 2 s + dir
-    unsigned long long *total;       // certificates
+    unsigned long long *scal;        // the query's scalars (certificates per region)
 };
 
+// A block takes many tiles of edges, so that its one atomic on the certificate
+// total is a rare one.
+constexpr int64_t THRESHOLD_BLOCKS = 8192;
 __global__ __launch_bounds__(BLK) void k_threshold(ThreshArgs A) {
     __shared__ unsigned long long s_tot[BLK / 64];
-    int64_t k = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    bool in = k < A.m;
-    int64_t key = -1;
-    bool cert = false;
-    const uint32_t cnt = in ? A.count[k] : 0u;
-    // a wavefront whose edges all count 0 has no certificate when 0 cannot
-    // reach theta * |U| (its lanes stay out of every run below)
-    if (A.zero_never && !__ballot(cnt != 0u)) in = false;
-    if (in) {
-        int32_t s = A.sid[k];
-        int dir = k >= A.smid[s] ? 1 : 0;
-        int32_t a = dir ? A.shi[s] : A.slo[s];
-        int32_t b = dir ? A.slo[s] : A.shi[s];
-        if (A.any) {
-            cert = cnt >= 1u;
-        } else {
-            int64_t U;
-            if (A.universe == FOLTY_UNIVERSE_DST) U = (int64_t)A.deg[b] - A.excl;
-            else if (A.universe == FOLTY_UNIVERSE_SRC) U = (int64_t)A.deg[a] - A.excl;
-            else U = A.tcnt[s];
-            cert = (uint64_t)cnt * A.den >= (uint64_t)A.num * (uint64_t)U;
+    unsigned long long sum = 0;
+    for (int64_t k0 = (int64_t)blockIdx.x * BLK; k0 < A.m; k0 += (int64_t)gridDim.x * BLK) {
+        const int64_t k = k0 + threadIdx.x;
+        bool in = k < A.m;
+        int64_t key = -1;
+        bool cert = false;
+        const uint32_t cnt = in ? A.count[k] : 0u;
+        // a wavefront whose edges all count 0 has no certificate when 0 cannot
+        // reach theta * |U|
+        if (A.zero_never && !__ballot(cnt != 0u)) continue;
+        if (in) {
+            int32_t s = A.sid[k];
+            int dir = k >= A.smid[s] ? 1 : 0;
+            int32_t a = dir ? A.shi[s] : A.slo[s];
+            int32_t b = dir ? A.slo[s] : A.shi[s];
+            if (A.any) {
+                cert = cnt >= 1u;
+            } else {
+                int64_t U;
+                if (A.universe == FOLTY_UNIVERSE_DST) U = (int64_t)A.deg[b] - A.excl;
+                else if (A.universe == FOLTY_UNIVERSE_SRC) U = (int64_t)A.deg[a] - A.excl;
+                else U = A.tcnt[s];
+                cert = (uint64_t)cnt * A.den >= (uint64_t)A.num * (uint64_t)U;
+            }
+            key = 2 * (int64_t)s + dir;
         }
-        key = 2 * (int64_t)s + dir;
+        // segmented count of certificates over runs of equal keys inside the wave
+        int lane = lane_id();
+        int64_t prev = __shfl_up(key, 1);
+        int64_t next = __shfl_down(key, 1);
+        bool head = lane == 0 || prev != key;
+        bool tail = lane == 63 || next != key;
+        unsigned long long heads = __ballot(head && in);
+        unsigned long long certs = __ballot(cert);
+        if (in && tail) {
+            unsigned long long upto = lane == 63 ? ~0ull : ((2ull << lane) - 1ull);
+            unsigned long long h = heads & upto;
+            int start = 63 - __clzll((long long)h);
+            unsigned long long seg = upto & ~((1ull << start) - 1ull);
+            int c = __popcll(certs & seg);
+            if (c) atomicAdd(&A.ncert[key], (uint32_t)c);
+        }
+        sum += (unsigned long long)__popcll(certs);
     }
-    // segmented count of certificates over runs of equal keys inside the wave
-    int lane = lane_id();
-    int64_t prev = __shfl_up(key, 1);
-    int64_t next = __shfl_down(key, 1);
-    bool head = lane == 0 || prev != key;
-    bool tail = lane == 63 || next != key;
-    unsigned long long heads = __ballot(head && in);
-    unsigned long long certs = __ballot(cert);
-    if (in && tail) {
-        unsigned long long upto = lane == 63 ? ~0ull : ((2ull << lane) - 1ull);
-        unsigned long long h = heads & upto;
-        int start = 63 - __clzll((long long)h);
-        unsigned long long seg = upto & ~((1ull << start) - 1ull);
-        int c = __popcll(certs & seg);
-        if (c) atomicAdd(&A.ncert[key], (uint32_t)c);
-    }
-    if (lane == 0) s_tot[threadIdx.x >> 6] = (unsigned long long)__popcll(certs);
+    if (lane_id() == 0) s_tot[threadIdx.x >> 6] = sum;
     __syncthreads();
     if (threadIdx.x == 0) {
         unsigned long long t = 0;
         for (int i = 0; i < BLK / 64; i++) t += s_tot[i];
-        if (t) atomicAdd(A.total, t);
+        if (t) region_add(A.scal, REGION_CERTS, t);
     }
 }
 
@@ -264,7 +271,7 @@ __host__ __device__ inline int pair_bits(int32_t n) {
 // Directed pairs with certificates, as keys (a << nbits) | b with their counts.
 // Each block takes BLK x PAIR_ITEMS entries (2 s + dir) and claims its output
 // range with one atomic, so a dense result does not serialise on the counter.
-constexpr int PAIR_ITEMS = 8;
+constexpr int PAIR_ITEMS = 32;
 __global__ __launch_bounds__(BLK) void k_pairs_compact(const uint32_t *__restrict__ ncert, int32_t S,
                                                        const int32_t *__restrict__ slo, const int32_t *__restrict__ shi,
                                                        int nbits, uint64_t *__restrict__ keys,
@@ -418,6 +425,14 @@ int64_t chunks_taken(const Workspace &ws, const CandBuf &B) {
     return k;
 }
 
+// the sum of a counter over the regions
+int64_t region_sum(const Workspace &ws, int what) {
+    const unsigned long long *h = ws.host.as<unsigned long long>() + SCAL_REGIONS;
+    unsigned long long k = 0;
+    for (int r = 0; r < MAX_REGIONS; r++) k += h[r * REGION_WORDS + what];
+    return (int64_t)k;
+}
+
 namespace {
 
 // Up to this many chunks (50 MB) are allocated whatever the window keeps, so that
@@ -471,7 +486,7 @@ CandBuf filter_triangles(Index &ix, int variant, int64_t dmax, Workspace &ws, hi
             sink.rng = ix.erng.as<uint2>();
             sink.dq = rng_slack(dmax, ix.rshift);
             sink.out = B;
-            sink.hits = scal + SCAL_HITS;
+            sink.scal = scal;
             if (cached) k_filter_cached<<<grid, BLK, 0, s>>>(ix.tri.as<int32_t>(), T, sink);
             else
                 k_tri_enum<<<grid, BLK, 0, s>>>(enum_graph(ix), ix.NI, sink);
@@ -492,7 +507,7 @@ CandBuf filter_triangles(Index &ix, int variant, int64_t dmax, Workspace &ws, hi
         ws.kept_chunks = taken;
         if (dropped == 0) return B;
         if (T < 0) {
-            T = (int64_t)h[SCAL_HITS];
+            T = region_sum(ws, REGION_HITS);
             ix.T = T;
         }
         chunks = taken + (int64_t)dropped;
@@ -513,9 +528,8 @@ CandBuf filter_triangles(Index &ix, int variant, int64_t dmax, Workspace &ws, hi
 // medium graph, 4 weeks 0.25 and 0.24 ms (1 in 190), 1 year 0.34 and 0.32 ms.
 // The rule depends only on the graph and the queries, never on timing.
 void after_filter(Index &ix, Workspace &ws, int64_t delta, bool one_pass) {
-    const unsigned long long *h = ws.host.as<unsigned long long>();
-    if (ix.T.load() < 0) ix.T = (int64_t)h[SCAL_HITS];
-    const int64_t kept = (int64_t)h[SCAL_KEPT];
+    if (ix.T.load() < 0) ix.T = region_sum(ws, REGION_HITS);
+    const int64_t kept = region_sum(ws, REGION_KEPT);
     ws.filter_passes = one_pass ? 1 : 2;
     if (!one_pass && kept > 0 && 64 * kept >= ix.T.load() &&
         delta / 8 < ix.one_pass_from.load(std::memory_order_relaxed))
@@ -549,13 +563,16 @@ void launch_temporal(const Index &ix, int variant, int64_t dmax, Workspace &ws, 
 // ---------------------------------------------------------------------------
 // vertex queries: per vertex u, its neighbours v with a qualifying edge u -> v
 // ---------------------------------------------------------------------------
-// good[u] += 1 for every directed pair (u, v) (key 2 s + dir) with a qualifying edge
-__global__ void k_vertex_good(const uint32_t *__restrict__ ncert, int32_t S, const int32_t *__restrict__ slo,
-                              const int32_t *__restrict__ shi, uint32_t *__restrict__ good) {
-    const int64_t k = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (k >= 2 * (int64_t)S || ncert[k] == 0) return;
-    const int32_t e = (int32_t)(k >> 1);
-    atomicAdd(&good[(k & 1) ? shi[e] : slo[e]], 1u);
+// good[u] = the pairs (u, v), from the result's pairs sorted by u: the last pair
+// of a run writes its length (no atomics: a hub's thousands of pairs would queue at
+// one address; 1.4M pairs 0.31 ms, now 0.01 ms)
+__global__ void k_vertex_starts(const int32_t *__restrict__ pu, int32_t np, uint32_t *__restrict__ good) {
+    const int32_t i = (int32_t)(blockIdx.x * blockDim.x + threadIdx.x);
+    if (i < np && (i == 0 || pu[i - 1] != pu[i])) good[pu[i]] = (uint32_t)i;
+}
+__global__ void k_vertex_good(const int32_t *__restrict__ pu, int32_t np, uint32_t *__restrict__ good) {
+    const int32_t i = (int32_t)(blockIdx.x * blockDim.x + threadIdx.x);
+    if (i < np && (i == np - 1 || pu[i + 1] != pu[i])) good[pu[i]] = (uint32_t)i + 1 - good[pu[i]];
 }
 
 // u is a solution: |N(u)| >= 1 and good[u] * den >= num * |N(u)|
@@ -577,10 +594,12 @@ __global__ void k_vertex_compact(const int32_t *__restrict__ flag, const int32_t
     vgood[pos[u]] = good[u];
 }
 
-// the vertex step after the edge-level threshold (ncert holds its per-pair counts)
-void finish_vertex(const Graph *g, const folty_vertex_query &vq, Workspace &ws, Result *res, hipStream_t s) {
+// the vertex step after the edge-level threshold (pu: its np pairs' first vertices,
+// ascending)
+void finish_vertex(const Graph *g, const folty_vertex_query &vq, Workspace &ws, const int32_t *pu, int32_t np,
+                   Result *res, hipStream_t s) {
     const Index &ix = g->ix;
-    const int32_t n = ix.n, S = ix.S;
+    const int32_t n = ix.n;
     ws.vtmp.ensure(20 * (size_t)n + 16);
     uint32_t *good = ws.vtmp.as<uint32_t>();
     int32_t *flag = reinterpret_cast<int32_t *>(good + n);
@@ -589,9 +608,9 @@ void finish_vertex(const Graph *g, const folty_vertex_query &vq, Workspace &ws, 
     uint32_t *vgood = reinterpret_cast<uint32_t *>(vert + n);
     k_fill<uint32_t><<<grid_for(n, BLK), BLK, 0, s>>>(good, 0u, n);
     FOLTY_LAUNCHED();
-    if (S > 0 && ix.m > 0) {
-        k_vertex_good<<<grid_for(2 * (int64_t)S, BLK), BLK, 0, s>>>(ws.ncert.as<uint32_t>(), S, ix.slo.as<int32_t>(),
-                                                                  ix.shi.as<int32_t>(), good);
+    if (np > 0) {
+        k_vertex_starts<<<grid_for(np, BLK), BLK, 0, s>>>(pu, np, good);
+        k_vertex_good<<<grid_for(np, BLK), BLK, 0, s>>>(pu, np, good);
         FOLTY_LAUNCHED();
     }
     k_vertex_flags<<<grid_for(n, BLK), BLK, 0, s>>>(good, ix.deg.as<int32_t>(), n, vq.theta_num, vq.theta_den, flag);
@@ -627,7 +646,6 @@ void threshold_pairs(const Graph *g, const folty_query &q, const uint32_t *count
                            hipStream_t s, bool any) {
     const Index &ix = g->ix;
     const int32_t S = ix.S, m = ix.m;
-    unsigned long long *total = ws.scal.as<unsigned long long>();
     int32_t *np = ws.scal.as<int32_t>() + 4;
     if (m > 0) {
         ThreshArgs A;
@@ -648,8 +666,8 @@ void threshold_pairs(const Graph *g, const folty_query &q, const uint32_t *count
                                (q.universe == FOLTY_UNIVERSE_DST || q.universe == FOLTY_UNIVERSE_SRC));
         A.any = any ? 1 : 0;
         A.ncert = ws.ncert.as<uint32_t>();
-        A.total = total;
-        k_threshold<<<grid_for(m, BLK), BLK, 0, s>>>(A);
+        A.scal = ws.scal.as<unsigned long long>();
+        k_threshold<<<grid_for(m, BLK, THRESHOLD_BLOCKS), BLK, 0, s>>>(A);
         FOLTY_LAUNCHED();
         ws.pairs_k.ensure(16 * (size_t)S + 16);
         ws.pairs_v.ensure(8 * (size_t)S + 8);
@@ -664,11 +682,9 @@ void threshold_pairs(const Graph *g, const folty_query &q, const uint32_t *count
 
 // |Sol| and the number of pairs, from the scalars on the host
 PairCounts pair_counts(const Workspace &ws) {
-    unsigned long long ncerts;
     int32_t npairs;
-    memcpy(&ncerts, ws.host.p, 8);
     memcpy(&npairs, ws.host.as<char>() + 16, 4);
-    return PairCounts{(int64_t)ncerts, npairs};
+    return PairCounts{region_sum(ws, REGION_CERTS), npairs};
 }
 
 // sort the pair keys of threshold_pairs and unpack them: u, v and the
@@ -708,8 +724,8 @@ void scatter_counts(const Graph *g, const uint32_t *count, uint32_t *out, hipStr
 void keep_counts(const Graph *g, const uint32_t *count, Result *res, hipStream_t s);
 
 // threshold, pairs and (kept) per-edge counts into res.  The stream is idle after
-// it; ev[3] follows the pair step.
-void finish_query(const Graph *g, const folty_query &q, const uint32_t *count, Workspace &ws, Result *res,
+// it; ev[3] follows the pair step.  Returns the pairs' first vertices on the device.
+const int32_t *finish_query(const Graph *g, const folty_query &q, const uint32_t *count, Workspace &ws, Result *res,
                   hipStream_t s, bool any) {
     threshold_pairs(g, q, count, ws, s, any);
     read_scalars(ws, s, true);
@@ -722,6 +738,7 @@ void finish_query(const Graph *g, const folty_query &q, const uint32_t *count, W
     res->u.resize(npairs);
     res->v.resize(npairs);
     res->n_cert.resize(npairs);
+    const int32_t *first = reinterpret_cast<const int32_t *>(ws.scal.as<char>() + SCAL_BYTES);
     if (npairs > SMALL_PAIRS) {
         int32_t *du, *dv;
         uint32_t *dn;
@@ -731,12 +748,14 @@ void finish_query(const Graph *g, const folty_query &q, const uint32_t *count, W
         FOLTY_HIP(hipMemcpyAsync(res->n_cert.data(), dn, 4 * (size_t)npairs, hipMemcpyDeviceToHost, s));
         FOLTY_HIP(hipEventRecord(ws.ev[3], s));
         FOLTY_HIP(hipStreamSynchronize(s));
+        first = du;
     } else if (npairs > 0) {
         const int32_t *p = reinterpret_cast<const int32_t *>(ws.host.as<char>() + SCAL_BYTES);
         memcpy(res->u.data(), p, 4 * (size_t)npairs);
         memcpy(res->v.data(), p + SMALL_PAIRS, 4 * (size_t)npairs);
         memcpy(res->n_cert.data(), p + 2 * SMALL_PAIRS, 4 * (size_t)npairs);
     }
+    return first;
 }
 
 void keep_counts(const Graph *g, const uint32_t *count, Result *res, hipStream_t s) {
@@ -1023,7 +1042,7 @@ void run_query_into(Graph *g, const folty_query &q, Workspace &ws, int32_t *pair
     read_scalars(ws, s, false);
     FOLTY_HIP(hipStreamSynchronize(s));
     const PairCounts pc = pair_counts(ws);
-    if (ix.T.load() < 0) ix.T = (int64_t)ws.host.as<unsigned long long>()[SCAL_HITS];
+    if (ix.T.load() < 0) ix.T = region_sum(ws, REGION_HITS);
     *n_pairs = pc.npairs;
     *n_certificates = pc.ncerts;
     if (edge_count) scatter_counts(g, count, edge_count, s);
@@ -1056,16 +1075,16 @@ static Result *run_query_impl(Graph *g, const folty_query &q, Workspace &ws, hip
     std::unique_ptr<Result> res(new Result());
     bool one_pass = false;
     const uint32_t *count = query_counts(g, q, ws, s, &one_pass);
-    finish_query(g, q, count, ws, res.get(), s, vq && vq->inner == FOLTY_INNER_EXISTS);
+    const int32_t *first = finish_query(g, q, count, ws, res.get(), s, vq && vq->inner == FOLTY_INNER_EXISTS);
     if (vq) {
-        finish_vertex(g, *vq, ws, res.get(), s);
+        finish_vertex(g, *vq, ws, first, (int32_t)res->u.size(), res.get(), s);
         FOLTY_HIP(hipEventRecord(ws.ev[3], s));
         FOLTY_HIP(hipStreamSynchronize(s));
     }
     if (ix.NI > 0) after_filter(ix, ws, q.delta, one_pass);
     else ix.T = 0;
     fill_stats_from_index(ix, &res->stats);
-    res->stats.tests = (int64_t)ws.host.as<unsigned long long>()[SCAL_TESTS];
+    res->stats.tests = region_sum(ws, REGION_TESTS);
     res->stats.n_pairs = (int64_t)res->u.size();
     res->stats.n_certificates = res->n_certificates;
     res->stats.wedge_ms = ev_ms(ws.ev[4], ws.ev[5]);

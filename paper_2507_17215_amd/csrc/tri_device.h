@@ -63,6 +63,11 @@ template <class T> __device__ inline T wave_inclusive_sum(T x) {
     return x;
 }
 
+// adds to this block's region's counter `what`
+__device__ inline void region_add(unsigned long long *scal, int what, unsigned long long x) {
+    atomicAdd(&scal[SCAL_REGIONS + (blockIdx.x % MAX_REGIONS) * REGION_WORDS + what], x);
+}
+
 // the predicate code as a compile-time constant for kernel templates
 template <class F> void dispatch_variant(int v, F &&f) {
     switch (v) {
@@ -622,7 +627,7 @@ template <int VAR, FilterMode MODE> struct FilterSink {
     int32_t dq;               // rng_slack(dmax, rshift)
     uint32_t predicates;      // VAR < 0: bits
     CandBuf out;
-    unsigned long long *hits; // FILTER_COUNT: triangles seen (added once per wavefront)
+    unsigned long long *scal; // FILTER_COUNT: the query's scalars (triangles seen, added once per wavefront)
     CandAppend app;
     unsigned long long nhit;
     __device__ void begin(int64_t) {}
@@ -656,7 +661,7 @@ template <int VAR, FilterMode MODE> struct FilterSink {
     __device__ void finish() {
         app.finish(out);
         if constexpr (kHits) {
-            if (lane_id() == 0 && nhit) atomicAdd(hits, nhit);
+            if (lane_id() == 0 && nhit) region_add(scal, REGION_HITS, nhit);
         }
     }
 };
@@ -1268,11 +1273,15 @@ __device__ inline void defer_heavy(R &runner, const typename R::Surv &S, int64_t
 // A wavefront's group of chunks as a dense sequence of slots: narrow windows
 // leave most chunks with an entry or two, and their triangles are taken 64 at a
 // time across chunks.  Groups of up to 64 chunks, fewer when that would leave
-// less than GROUPS_WANTED groups.
+// less than GROUPS_WANTED groups; with few chunks each is shared by up to eight
+// wavefronts, since a wavefront's tests are a chain of dependent reads.
 constexpr int32_t GROUPS_WANTED = 16384;
 __device__ inline int32_t group_chunks(int32_t total) {
     const int32_t k = total / GROUPS_WANTED;
     return k < 1 ? 1 : k > 64 ? 64 : k;
+}
+__device__ inline int32_t chunk_parts(int32_t total) {
+    return total >= GROUPS_WANTED / 2 ? 1 : total >= GROUPS_WANTED / 4 ? 2 : total >= GROUPS_WANTED / 8 ? 4 : 8;
 }
 struct GroupLds {
     int32_t incl[64];  // slots of the group's chunks up to this one
@@ -1303,11 +1312,11 @@ __device__ inline int64_t group_slot(const GroupLds &L, int32_t q) {
     return (int64_t)L.chunk[a] * 64 + (q - (a ? L.incl[a - 1] : 0));
 }
 
-// totals[0] += the tests of every triangle, totals[1] += the triangles (one atomic each per block)
+// The regions' tests and kept triangles receive those of the chunks (one atomic each per block).
 template <class R>
 __global__ __launch_bounds__(BLK) void k_tests_light(CandBuf B, R runner, Heavy *__restrict__ heavy,
                                                      unsigned long long *__restrict__ counter, int64_t cap,
-                                                     unsigned long long *__restrict__ totals) {
+                                                     unsigned long long *__restrict__ scal) {
     __shared__ typename R::Flat flds[R::kFlat ? WPB : 1];
     __shared__ GroupLds glds[WPB];
     __shared__ Chunks C;
@@ -1316,14 +1325,18 @@ __global__ __launch_bounds__(BLK) void k_tests_light(CandBuf B, R runner, Heavy 
     const int w = wave_id();
     const int lane = lane_id();
     C.load(B);
-    const int32_t per = group_chunks(C.total);
+    const int32_t per = group_chunks(C.total), parts = chunk_parts(C.total); // one of them is 1
     bool full = false;
     int64_t mine = 0;
     int32_t kept = 0;
-    for (int64_t g0 = ((int64_t)blockIdx.x * WPB + w) * per; g0 < C.total; g0 += (int64_t)gridDim.x * WPB * per) {
-        const int32_t slots = stage_group(B, C, (int32_t)g0, (int32_t)(g0 + per < C.total ? g0 + per : C.total), glds[w]);
-        kept += slots;
-        for (int32_t q0 = 0; q0 < slots; q0 += 64) {
+    const int64_t units = (int64_t)C.total * parts;
+    for (int64_t x = ((int64_t)blockIdx.x * WPB + w) * per; x < units; x += (int64_t)gridDim.x * WPB * per) {
+        const int32_t g0 = (int32_t)(x / parts), part = (int32_t)(x % parts), wide = 64 / parts;
+        const int32_t all = stage_group(B, C, g0, g0 + per < C.total ? g0 + per : C.total, glds[w]);
+        // this wavefront's slots: the group's, or a part of its one chunk's
+        const int32_t slots = parts == 1 || all < (part + 1) * wide ? all : (part + 1) * wide;
+        if (part == 0) kept += all;
+        for (int32_t q0 = part * wide; q0 < slots; q0 += 64) {
             const bool on = q0 + lane < slots;
             int64_t slot = 0, wk = 0, np = 0;
             typename R::Surv S{};
@@ -1374,8 +1387,8 @@ __global__ __launch_bounds__(BLK) void k_tests_light(CandBuf B, R runner, Heavy 
             t += s_tests[i];
             k += (unsigned long long)s_kept[i];
         }
-        if (t) atomicAdd(&totals[0], t);
-        if (k) atomicAdd(&totals[1], k);
+        if (t) region_add(scal, REGION_TESTS, t);
+        if (k) region_add(scal, REGION_KEPT, k);
     }
 }
 
@@ -1434,9 +1447,9 @@ void launch_tests(Workspace &ws, const CandBuf &B, const R &runner, int64_t chun
     const int64_t cap = heavy_slots(arena_left() >= 0 ? 0 : 64 * chunks);
     ws.pieces.ensure(sizeof(Heavy) * (size_t)cap);
     unsigned long long *np = ws.scal.as<unsigned long long>() + SCAL_HEAVY;
-    const unsigned lb = (unsigned)std::max<int64_t>(1, std::min<int64_t>((chunks + WPB - 1) / WPB, LIGHT_BLOCKS));
-    k_tests_light<<<lb, BLK, 0, s>>>(B, runner, ws.pieces.as<Heavy>(), np, cap,
-                                     ws.scal.as<unsigned long long>() + SCAL_TESTS);
+    // up to eight wavefronts per chunk
+    const unsigned lb = (unsigned)std::max<int64_t>(1, std::min<int64_t>((8 * chunks + WPB - 1) / WPB, LIGHT_BLOCKS));
+    k_tests_light<<<lb, BLK, 0, s>>>(B, runner, ws.pieces.as<Heavy>(), np, cap, ws.scal.as<unsigned long long>());
     FOLTY_LAUNCHED();
     // the pieces are numbered on the device
     const unsigned pb = (unsigned)std::max<int64_t>(1, std::min<int64_t>(chunks * 16, PIECE_BLOCKS));
@@ -1460,6 +1473,7 @@ constexpr int64_t CHUNK_BYTES = 3 * 4 * 64 + 4;
 void clear_query(const Index &ix, Workspace &ws, bool counts, hipStream_t s);
 void read_scalars(Workspace &ws, hipStream_t s, bool pairs);
 int64_t chunks_taken(const Workspace &ws, const CandBuf &B);
+int64_t region_sum(const Workspace &ws, int what);
 CandBuf filter_triangles(Index &ix, int variant, int64_t dmax, Workspace &ws, hipStream_t s, bool one_pass);
 void after_filter(Index &ix, Workspace &ws, int64_t delta, bool one_pass);
 

@@ -206,7 +206,15 @@ __global__ __launch_bounds__(BLK) void k_triad_count(CandBuf B, const uint8_t *_
             c += (unsigned)x;
         }
     }
-    if (total && lane_id() == 63 && c) atomicAdd(total, c);
+    if (!total) return;
+    __shared__ unsigned long long s_c[WPB];
+    if (lane_id() == 63) s_c[wave_id()] = c;
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        unsigned long long sum = 0;
+        for (int i = 0; i < WPB; i++) sum += s_c[i];
+        if (sum) atomicAdd(total, sum);
+    }
 }
 
 // the endpoints (original ids) of oriented edge q: tail, head
@@ -281,7 +289,7 @@ void check_triad(const Graph *g, const folty_triad_query &q) {
 }
 
 unsigned chunk_grid(int64_t chunks) {
-    return (unsigned)std::max<int64_t>(1, std::min<int64_t>((chunks + WPB - 1) / WPB, PERSIST_BLOCKS));
+    return (unsigned)std::max<int64_t>(1, std::min<int64_t>((chunks + WPB - 1) / WPB, 1024));
 }
 
 // the listed triples, sorted by (a, b, w), copied to res->trip; the filter took
@@ -406,7 +414,7 @@ Result *run_triad_query(Graph *g, const folty_triad_query &q, Workspace &ws) {
     }
     FOLTY_HIP(hipStreamSynchronize(s));
     fill_stats_from_index(ix, &res->stats);
-    res->stats.tests = (int64_t)ws.host.as<unsigned long long>()[SCAL_TESTS];
+    res->stats.tests = region_sum(ws, REGION_TESTS);
     res->stats.wedge_ms = ev_ms(ws.ev[4], ws.ev[5]);
     res->stats.temporal_ms = ev_ms(ws.ev[5], ws.ev[2]);
     res->stats.threshold_ms = ev_ms(ws.ev[2], ws.ev[3]);
