@@ -13,6 +13,12 @@
 // Histogram blocks of 256 x 12 keys: 3.36 / 1.32 / 0.69 / 0.19 ms.  8-bit
 // digits were slower at every size, 10-bit digits much slower (4.90 ms for the
 // 70M keys), and 11 or 12 bits exceed the LDS of one workgroup.
+// Up to MID_FROM keys rocPRIM's merge sort (the fewest passes), from there up to
+// MID_TO tiles of 4 keys per thread, which give the chip twice the blocks, instead
+// of the merge sort that the library's default keeps up to 1M keys.  Merge / 4 keys /
+// 8 keys per thread, keys of 44 bits, us: 200k 73 / 85 / 115, 300k 132 / 92 / 121,
+// 500k 144 / 109 / 129, 1M 194 / 127 / 146, 2M - / 179 / 165.
+#include <algorithm>
 #include <cstring>
 #include <rocprim/device/device_radix_sort.hpp>
 #include <rocprim/device/device_scan.hpp>
@@ -37,6 +43,13 @@ using Onesweep = rocprim::radix_sort_config<
     rocprim::radix_sort_onesweep_config<rocprim::kernel_config<512, 32>, rocprim::kernel_config<1024, 8>, 9,
                                         rocprim::block_radix_rank_algorithm::match>>;
 
+constexpr int64_t MID_FROM = 256 * 1024, MID_TO = 1536 * 1024;
+using OnesweepMid = rocprim::radix_sort_config<
+    rocprim::default_config, rocprim::default_config,
+    rocprim::radix_sort_onesweep_config<rocprim::kernel_config<512, 8>, rocprim::kernel_config<1024, 4>, 9,
+                                        rocprim::block_radix_rank_algorithm::match>,
+    0>; // never the merge sort
+
 template <class Cfg, class K, class V>
 size_t sort_with(void *tmp, size_t tmp_bytes, const K *kin, K *kout, const V *vin, V *vout, int64_t n, int end_bit,
                  hipStream_t s) {
@@ -56,7 +69,12 @@ size_t sort_pairs(void *tmp, size_t tmp_bytes, const K *kin, K *kout, const V *v
                   hipStream_t s) {
     if (end_bit < 1) end_bit = 1;
     if (end_bit > (int)(8 * sizeof(K))) end_bit = 8 * sizeof(K);
-    return sort_with<Onesweep>(tmp, tmp_bytes, kin, kout, vin, vout, n, end_bit, s);
+    if (n > MID_FROM && n <= MID_TO) return sort_with<OnesweepMid>(tmp, tmp_bytes, kin, kout, vin, vout, n, end_bit, s);
+    const size_t need = sort_with<Onesweep>(tmp, tmp_bytes, kin, kout, vin, vout, n, end_bit, s);
+    // storage asked for n keys also serves every smaller n: smaller tiles need a little more
+    if (!tmp && n > MID_TO)
+        return std::max(need, sort_with<OnesweepMid>(tmp, 0, kin, kout, vin, vout, MID_TO, end_bit, s));
+    return need;
 }
 
 // Scans: 256-thread blocks with more items per thread than rocPRIM's default
