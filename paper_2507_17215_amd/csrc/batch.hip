@@ -43,6 +43,7 @@ struct JobDev {
     int32_t variant;
     uint32_t dq; // run slack of the job's largest delta
     const int64_t *lv;
+    int64_t dmax; // the job's largest delta
     int32_t nl, nls, m;
     uint32_t *hist;  // hist_words(m, nls) counters, tiled (see hist_at)
     unsigned long long *tmask; // per tile of 64 edges: which edges have a non-zero counter
@@ -52,6 +53,7 @@ struct JobDev {
     int32_t q0, q1;
     int32_t keep_prefix; // some query of the job hands back its per-edge counts
     int32_t reset;       // the threshold step clears the tiles it read (reused plans)
+    int32_t zero_never;  // no query of the job is met by a count of 0 (theta > 0 and |U| >= 1 for every edge)
 };
 
 // a plan's queries in job order, each job's by level (one scalar load each)
@@ -124,79 +126,83 @@ __global__ __launch_bounds__(BLK) __attribute__((amdgpu_waves_per_eu(4))) void k
     sink.finish();
 }
 
-// a job's tests of one triangle
-struct JobRunner {
-    int32_t variant;
-    uint32_t dq;
+// a job's tests
+struct JobTests {
     const int64_t *ts;
     PoolOp op;
-    using Surv = TriLists;
-    __device__ explicit JobRunner(const JobDev &J)
-        : variant(J.variant), dq(J.dq), ts(global_ptr(J.ts)),
-          op{global_ptr(J.lv), J.nl, J.nls, global_ptr(J.hist), global_ptr(J.tmask)} {}
-    __device__ inline void run(const TriLists &L, int64_t, int64_t r, int64_t k1) {
-        int64_t k = r;
-        chunk_runs_rt(variant, L, dq, ts, r, k, k1, op);
-    }
+    RunLists ids;
+    __device__ explicit JobTests(const JobDev &J)
+        : ts(global_ptr(J.ts)), op{global_ptr(J.lv), J.nl, J.nls, J.dmax, global_ptr(J.hist), global_ptr(J.tmask)},
+          ids(run_list_ids(J.variant)) {}
 };
 
-// The tests of every job on one chunk of kept triangles per wavefront, scheduled
-// as a single query's (k_tests_light).  Heavy entries carry their job above the
-// slot.
+// The tests of every job on a group of the filter's chunks per wavefront,
+// scheduled as a single query's (k_tests_light); the chunks of one graph go
+// together.  Heavy entries carry their job above the slot.
 constexpr int HEAVY_JOB = 40; // slots are below 2^40
 __global__ __launch_bounds__(BLK) void k_plan_light(CandBuf B, const GroupDev *__restrict__ groups,
                                                     const int32_t *__restrict__ gjobs, const JobDev *__restrict__ jobs,
                                                     Heavy *__restrict__ heavy, unsigned long long *__restrict__ counter,
                                                     int64_t cap, int piece, unsigned long long *__restrict__ scal) {
-    __shared__ FlatLds<false> flds[WPB];
+    __shared__ RunLds<false> flds[WPB];
+    __shared__ GroupLds glds[WPB];
+    __shared__ Chunks C;
     const int w = wave_id();
     const int lane = lane_id();
-    FlatLds<false> &F = flds[w];
-    __shared__ Chunks C;
+    RunLds<false> &F = flds[w];
     C.load(B);
+    const int32_t per = group_chunks(C.total), parts = chunk_parts(C.total); // one of them is 1
     bool full = false;
     int64_t mine = 0;
-    for (int32_t g = (int32_t)blockIdx.x * WPB + w; g < C.total; g += (int32_t)gridDim.x * WPB) {
-        const int32_t chunk = __builtin_amdgcn_readfirstlane(C.at(B, g));
-        const GroupDev &G = groups[__builtin_amdgcn_readfirstlane(B.tag[chunk])];
-        const int64_t slot = (int64_t)chunk * 64 + lane;
-        const bool on = lane < B.cnt[chunk];
-        TriLists L{};
-        if (on) L = load_lists(global_ptr(jobs[gjobs[G.j0]].rec), B.sv[3 * slot], B.sv[3 * slot + 1], B.sv[3 * slot + 2]);
-        const Span *sp[6] = {&L.d01, &L.d10, &L.d02, &L.d20, &L.d12, &L.d21};
-#pragma unroll
-        for (int k = 0; k < 6; k++) {
-            F.ls[k][lane] = sp[k]->s;
-            F.ln[k][lane] = sp[k]->n;
-        }
-        for (int32_t jj = G.j0; jj < G.j1; jj++) {
-            const int32_t j = __builtin_amdgcn_readfirstlane(gjobs[jj]);
-            JobRunner R(jobs[j]);
-            const uint32_t live = on && edges_meet(L, R.dq) ? tri_live_rt(R.variant, L, R.dq) : 0u;
-            int64_t wk = 0;
-#pragma unroll
-            for (int k = 0; k < 6; k++) wk += (live >> k & 1u) ? sp[k]->n : 0;
-            const int64_t np = wk > LIGHT_TESTS ? (wk + piece - 1) / piece : 0;
-            mine += wk;
-            defer_heavy(R, L, slot | (int64_t)j << HEAVY_JOB, wk, np, heavy, counter, cap, full);
-            const int32_t incl = wave_scan(np ? 0 : (int32_t)wk);
-            const int32_t total = __builtin_amdgcn_readlane(incl, 63);
-            if (total == 0) continue;
-            F.incl[lane] = incl;
-            F.live[lane] = np ? 0u : live;
-            wave_sync();
-            const RunLists ids = run_list_ids(R.variant);
-            for (int32_t t = lane; t < total; t += 64) {
-                int a = 0, b = 63;
-                while (a < b) {
-                    const int mid = (a + b) >> 1;
-                    if (F.incl[mid] > t) b = mid;
-                    else a = mid + 1;
+    const int64_t units = (int64_t)C.total * parts;
+    for (int64_t x = ((int64_t)blockIdx.x * WPB + w) * per; x < units; x += (int64_t)gridDim.x * WPB * per) {
+        const int32_t g0 = (int32_t)(x / parts), part = (int32_t)(x % parts), wide = 64 / parts;
+        const int32_t nc = (g0 + per < C.total ? g0 + per : C.total) - g0;
+        stage_group(B, C, g0, g0 + nc, glds[w]);
+        const int32_t tag = lane < nc ? B.tag[glds[w].chunk[lane]] : -1;
+        for (int32_t c0 = 0; c0 < nc;) { // chunks [c0, c1) hold one graph's triangles
+            const int32_t gi = __builtin_amdgcn_readfirstlane(__shfl(tag, c0));
+            const unsigned long long other = __ballot(lane > c0 && tag != gi);
+            const int32_t c1 = other ? (int32_t)__builtin_ctzll(other) : nc;
+            const GroupDev &G = groups[gi];
+            const int32_t s0 = c0 ? glds[w].incl[c0 - 1] : 0, s1 = glds[w].incl[c1 - 1];
+            // this wavefront's slots: the chunks', or a part of its one chunk's
+            const int32_t slots = parts == 1 || s1 < (part + 1) * wide ? s1 : (part + 1) * wide;
+            c0 = c1;
+            for (int32_t q0 = s0 + part * wide; q0 < slots; q0 += 64) {
+                const bool on = q0 + lane < slots;
+                int64_t slot = 0;
+                int32_t e[3] = {0, 0, 0};
+                TriLists L{};
+                if (on) {
+                    slot = group_slot(glds[w], q0 + lane);
+                    for (int k = 0; k < 3; k++) e[k] = B.sv[3 * slot + k];
+                    L = load_lists(global_ptr(jobs[gjobs[G.j0]].rec), e[0], e[1], e[2]);
                 }
-                flat_run_rt(F, ids, a, t - (a ? F.incl[a - 1] : 0), R.ts, R.op);
+                stage_runs(F, lane, L, e, 0u, slot);
+                for (int32_t jj = G.j0; jj < G.j1; jj++) {
+                    const int32_t j = __builtin_amdgcn_readfirstlane(gjobs[jj]);
+                    const JobDev &J = jobs[j];
+                    const uint32_t live = on && edges_meet(L, J.dq) ? tri_live_rt(J.variant, L, J.dq) : 0u;
+                    int64_t wk = 0;
+                    for (int k = 0; k < 6; k++) wk += (live >> k & 1u) ? F.n[k][lane] : 0;
+                    const int64_t np = wk > LIGHT_TESTS ? (wk + piece - 1) / piece : 0;
+                    mine += wk;
+                    const bool listed = defer_heavy(slot | (int64_t)j << HEAVY_JOB, np, heavy, counter, cap, full);
+                    const int32_t incl = wave_scan(np ? 0 : (int32_t)wk);
+                    F.incl[lane] = incl;
+                    F.live[lane] = live;
+                    wave_sync();
+                    const JobTests R(J);
+                    spread_units(
+                        F, incl, np && !listed,
+                        [&](int si, int64_t r) { staged_tests<false, true>(F, R.ids, si, r, 1, R.ts, nullptr, R.op); },
+                        [&](int si) { return __shfl(wk, si); });
+                    wave_sync(); // the next job or chunk rewrites the LDS
+                }
             }
-            wave_sync(); // the next job or chunk rewrites the LDS
         }
+        wave_sync(); // the group's LDS is rewritten by the next group
     }
     for (int o = 32; o > 0; o >>= 1) mine += __shfl_xor(mine, o);
     if (lane == 0 && mine) region_add(scal, REGION_TESTS, (unsigned long long)mine);
@@ -206,24 +212,23 @@ __global__ __launch_bounds__(BLK) void k_plan_pieces(CandBuf B, const JobDev *__
                                                      const Heavy *__restrict__ heavy,
                                                      const unsigned long long *__restrict__ counter, int64_t cap,
                                                      int piece) {
+    __shared__ RunLds<false> flds[WPB];
+    RunLds<false> &F = flds[wave_id()];
+    const int lane = lane_id();
     const unsigned long long c = *counter;
     const int64_t ne = (int64_t)(c >> HEAVY_SHIFT) < cap ? (int64_t)(c >> HEAVY_SHIFT) : cap;
     const int64_t np = (int64_t)(c & PIECE_MASK);
     if (ne <= 0) return;
     for (int64_t p = (int64_t)blockIdx.x * BLK + threadIdx.x; p < np; p += (int64_t)gridDim.x * BLK) {
-        // the last entry whose first piece is <= p (entry 0 starts at piece 0)
-        int64_t a = 0, b = ne - 1;
-        while (a < b) {
-            const int64_t mid = (a + b + 1) >> 1;
-            if (heavy[mid].first <= p) a = mid;
-            else b = mid - 1;
-        }
-        const Heavy h = heavy[a];
+        const Heavy h = heavy_of(heavy, ne, p);
         const int64_t slot = h.slot & (((int64_t)1 << HEAVY_JOB) - 1);
         const JobDev &J = jobs[h.slot >> HEAVY_JOB];
-        const int64_t k0 = (p - h.first) * piece;
-        JobRunner R(J);
-        R.run(load_lists(global_ptr(J.rec), B.sv[3 * slot], B.sv[3 * slot + 1], B.sv[3 * slot + 2]), slot, k0, k0 + piece);
+        int32_t e[3];
+        for (int k = 0; k < 3; k++) e[k] = B.sv[3 * slot + k];
+        const TriLists L = load_lists(global_ptr(J.rec), e[0], e[1], e[2]);
+        stage_runs(F, lane, L, e, tri_live_rt(J.variant, L, J.dq), slot); // this lane's own column
+        const JobTests R(J);
+        staged_tests<false, false>(F, R.ids, lane, (p - h.first) * piece, piece, R.ts, nullptr, R.op);
     }
 }
 
@@ -283,6 +288,11 @@ __global__ __launch_bounds__(BLK) void k_job_threshold(const JobDev *__restrict_
         const JobDev &J = jobs[j];
         const int64_t e = x0 - job_w_base[j] + lane;
         const bool in = e < J.m;
+        const int64_t tile = (x0 - job_w_base[j]) >> 6;
+        unsigned long long *tmask = global_ptr(J.tmask);
+        const unsigned long long tm = tmask[tile];
+        // edges no test added to certify nothing, and their counters are clear
+        if (tm == 0ull && J.zero_never) continue;
         int32_t s = 0, dir = 0, du = 0, da = 0, tc = 0;
         uint64_t ab = 0;
         const int32_t *tcnt = global_ptr(J.tcnt);
@@ -300,9 +310,6 @@ __global__ __launch_bounds__(BLK) void k_job_threshold(const JobDev *__restrict_
         const int64_t run = in ? 2 * (int64_t)s + dir : -1;
         // this wavefront's tile: block c holds levels 4c..4c+3 of its 64 edges.
         // Edges no test added to hold zeros and are not read.
-        const int64_t tile = (x0 - job_w_base[j]) >> 6;
-        unsigned long long *tmask = global_ptr(J.tmask);
-        const unsigned long long tm = tmask[tile];
         const bool touched = (tm >> lane) & 1ull;
         uint4 *hrow = reinterpret_cast<uint4 *>(global_ptr(J.hist) + hist_at(tile << 6, 0, J.nls)) + lane;
         uint32_t acc = 0;
@@ -763,6 +770,7 @@ Plan *plan_create(Graph *const *gs, int ng, const folty_query *qs, const int32_t
         d.variant = P->jobs[j].variant;
         d.dq = run_slack(range_slack(lvs.back(), ix.tshift));
         d.lv = P->lv[j].as<int64_t>();
+        d.dmax = lvs.back();
         d.nl = (int32_t)lvs.size();
         d.nls = padded_levels(lvs.size());
         d.m = ix.m;
@@ -777,7 +785,13 @@ Plan *plan_create(Graph *const *gs, int ng, const folty_query *qs, const int32_t
         d.q0 = jq0[j];
         d.q1 = jq1[j];
         d.keep_prefix = 0;
+        d.zero_never = 1;
         for (int i = d.q0; i < d.q1; i++) {
+            const folty_query &q = qs[jq[i]];
+            // N(b) and N(a) hold the other endpoint, so |U| >= 1 unless it is left out
+            if (q.theta_num <= 0 || q.exclude_other ||
+                !(q.universe == FOLTY_UNIVERSE_DST || q.universe == FOLTY_UNIVERSE_SRC))
+                d.zero_never = 0;
             if (qs[jq[i]].universe == FOLTY_UNIVERSE_COMMON) d.tcnt = ix.tcnt.as<int32_t>();
             if (!(qs[jq[i]].flags & FOLTY_QUERY_NO_COUNTS)) d.keep_prefix = 1;
         }

@@ -547,14 +547,14 @@ bool use_one_pass(Graph *g, const folty_query &q) {
 namespace {
 
 // per-edge counts of the survivors' runs (a.6)
-template <class Op, bool SS = false>
-void launch_temporal(const Index &ix, int variant, int64_t dmax, Workspace &ws, const CandBuf &B, const Op &op,
+template <bool SS>
+void launch_temporal(const Index &ix, int variant, int64_t dmax, Workspace &ws, const CandBuf &B, const DirectOp &op,
                      hipStream_t s) {
     const uint32_t dq = run_slack(range_slack(dmax, ix.tshift));
     dispatch_variant(variant, [&](auto V) {
         launch_tests(ws, B,
-                     CountRunner<decltype(V)::value, Op, SS>{dq, ix.ts.as<int64_t>(), op, ws.sv.as<int32_t>(),
-                                                             ix.rec.as<EdgeRec>()},
+                     CountRunner<decltype(V)::value, DirectOp, SS>{dq, ix.ts.as<int64_t>(), op, ws.sv.as<int32_t>(),
+                                                                   ix.rec.as<EdgeRec>(), ix.tshift == 0},
                      ws.kept_chunks, s);
     });
 }
@@ -1002,16 +1002,14 @@ static const uint32_t *query_counts(Graph *g, const folty_query &q, Workspace &w
                 k_fill<int32_t><<<grid_for(ix.m + 1, BLK, PERSIST_BLOCKS), BLK, 0, s>>>(diff, 0, ix.m + 1);
                 FOLTY_LAUNCHED();
                 DirectOp op{q.delta, count, diff};
-                launch_temporal<DirectOp, true>(ix, q.variant, q.delta, ws, B, op, s);
+                launch_temporal<true>(ix, q.variant, q.delta, ws, B, op, s);
                 size_t need = inclusive_scan_i32(nullptr, 0, diff, ps, ix.m, s);
                 ws.cub.ensure(need);
                 inclusive_scan_i32(ws.cub.p, need, diff, ps, ix.m, s);
                 k_add_counts<<<grid_for(ix.m, BLK, PERSIST_BLOCKS), BLK, 0, s>>>(ps, ix.m, count);
                 FOLTY_LAUNCHED();
             } else {
-                DirectShortOp op{q.delta, count};
-                op.inl = ix.tshift == 0; // the records' end timestamps are exact
-                launch_temporal(ix, q.variant, q.delta, ws, B, op, s);
+                launch_temporal<false>(ix, q.variant, q.delta, ws, B, DirectOp{q.delta, count, nullptr}, s);
             }
         }
     } else {

@@ -227,55 +227,108 @@ __device__ inline int64_t tri_work_rt(int variant, const TriLists &T, uint32_t d
     }
 }
 
+// Searches probe four entries at a time: a search is a chain of dependent reads,
+// and four reads take as long as one (a list of up to four entries is decided by
+// one step, one of 5,000 by six instead of thirteen).
+struct Probe {
+    int64_t x[4];
+};
+__device__ inline int32_t probe_step(int32_t len) { return len > 4 ? len >> 2 : 1; }
+// entries a, a + step, a + 2 step, a + 3 step of L[a, b) (its last one past the end); b >= 1
+__device__ inline Probe probe(const int64_t *__restrict__ L, int32_t a, int32_t b) {
+    const int32_t q = probe_step(b - a);
+    Probe P;
+#pragma unroll
+    for (int k = 0; k < 4; k++) {
+        const int32_t i = a + k * q;
+        P.x[k] = L[i < b ? i : b - 1];
+    }
+    return P;
+}
+// first position in [a, n) with L[position] >= key (n if none), whose entry is
+// left in val; P = probe(L, a, n)
+__device__ inline int32_t lower_bound(const int64_t *__restrict__ L, int32_t a, int32_t n, int64_t key, Probe P,
+                                      int64_t &val) {
+    int32_t b = n;
+    while (a < b) {
+        const int32_t q = probe_step(b - a);
+        const int c = (P.x[0] < key) + (a + q < b && P.x[1] < key) + (a + 2 * q < b && P.x[2] < key) +
+                      (a + 3 * q < b && P.x[3] < key); // probes below key: the first c
+        const int32_t hi = a + c * q;
+        if (c == 0) {
+            val = P.x[0];
+            return a;
+        }
+        if (c < 4 && hi < b) {
+            val = c == 1 ? P.x[1] : c == 2 ? P.x[2] : P.x[3];
+            b = hi;
+        }
+        a += (c - 1) * q + 1;
+        if (a < b) P = probe(L, a, b);
+    }
+    return b;
+}
 // first position p in [from, n) with L[p] >= key (n if none)
 __device__ inline int32_t lower_bound_from(const int64_t *__restrict__ L, int32_t from, int32_t n, int64_t key) {
-    if (from >= n || L[from] >= key) return from;
-    int32_t a = from + 1, b = n;
-    while (a < b) {
-        int32_t mid = (a + b) >> 1;
-        if (L[mid] < key) a = mid + 1;
-        else b = mid;
-    }
-    return a;
+    if (from >= n || L[from] >= key) return from; // a cursor often stays where it is
+    int64_t val;
+    return from + 1 < n ? lower_bound(L, from + 1, n, key, probe(L, from + 1, n), val) : n;
 }
 
-// Entry k of a list of at most two entries, from its record's first and last
-// timestamps (exact when the timestamps fit 32 bits, tshift = 0).
-__device__ inline int64_t short_at(const Span &l, int32_t k) { return (int64_t)(k == 0 ? l.lo : l.hi); }
-__device__ inline int32_t short_lower_bound(const Span &l, int32_t from, int64_t key) {
-    int32_t p = from;
-    while (p < l.n && short_at(l, p) < key) p++;
-    return p;
-}
-
-// cnt consecutive temporal edges of L1 starting at l1s against (L2, L3).  With
-// SHORT and `inl` (timestamps below 2^32) a list of one or two entries is read
-// from its span's first and last timestamps instead of ts: most lists are that
-// short, and their entries are scattered reads that no neighbouring test
-// shares.  (A compile-time switch: the branches cost registers where unused.)
-template <bool SHORT> struct DirectOpT {
-    static constexpr bool kShort = SHORT;
-    int64_t delta;
-    uint32_t *count;
-    int32_t *diff = nullptr; // per sorted edge + 1: +1 / -1 at the ends of edge ranges (interval evaluation)
-    bool inl = false;
-    __device__ inline void operator()(const int64_t *__restrict__ ts, int32_t l1s, int32_t cnt, const Span &l2,
-                                      const Span &l3) const {
-        const int64_t *L2 = ts + l2.s, *L3 = ts + l3.s;
-        const bool s2 = SHORT && inl && l2.n <= 2, s3 = SHORT && inl && l3.n <= 2;
-        int32_t c2 = 0, c3 = 0;
-        for (int32_t q = 0; q < cnt; q++) {
-            int32_t e = l1s + q;
-            int64_t t = ts[e];
-            c2 = s2 ? short_lower_bound(l2, c2, t) : lower_bound_from(L2, c2, l2.n, t);
-            if (c2 == l2.n) break; // later edges are no earlier: no t2 for them either
-            int64_t t2 = s2 ? short_at(l2, c2) : L2[c2];
-            if (t2 - t > delta) continue;
-            c3 = s3 ? short_lower_bound(l3, c3, t2) : lower_bound_from(L3, c3, l3.n, t2);
-            if (c3 == l3.n) break;
-            if ((s3 ? short_at(l3, c3) : L3[c3]) - t <= delta) atomicAdd(&count[e], 1u);
+// A run's list L2 or L3.  ends: null, or the record's first and last timestamp
+// (32 bits each), from which a list of one or two entries is read: most lists are
+// that short, their entries are scattered reads that no neighbouring test shares,
+// and the record has just been read.
+struct List {
+    const int64_t *p;
+    int32_t n;
+    const int64_t *ends;
+    template <bool SHORT> __device__ inline Probe at(int32_t a) const {
+        if constexpr (SHORT) {
+            const int32_t q = probe_step(n - a);
+            Probe P;
+#pragma unroll
+            for (int k = 0; k < 4; k++) {
+                const int32_t i = a + k * q;
+                const int64_t *r = ends ? ends : p + (i < n ? i : n - 1);
+                P.x[k] = *r;
+            }
+            if (ends) {
+                const int64_t lo = (int64_t)(uint32_t)P.x[0], hi = (int64_t)((uint64_t)P.x[0] >> 32);
+                P.x[0] = a == 0 ? lo : hi;
+                P.x[1] = P.x[2] = P.x[3] = hi;
+            }
+            return P;
+        } else {
+            return probe(p, a, n);
         }
     }
+};
+
+// The test of an edge at time t (paper, Theorems 3.1 and 3.2): with t2 the first
+// entry of L2 at or after t and t3 the first of L3 at or after t2, the edge's
+// smallest window is t3 - t.  c2, c3: positions before which no entry can matter
+// (below the lists' lengths), moved forward; p2, p3: the probes there.
+enum TestEnd { TEST_MISS, TEST_HIT, TEST_END }; // TEST_END: nothing for any later edge either
+__device__ inline TestEnd window_test(const List &l2, const List &l3, int32_t &c2, int32_t &c3, const Probe &p2,
+                                      const Probe &p3, int64_t t, int64_t dmax, int64_t &win) {
+    int64_t t2 = 0, t3 = 0;
+    c2 = lower_bound(l2.p, c2, l2.n, t, p2, t2);
+    if (c2 == l2.n) return TEST_END;
+    if (t2 - t > dmax) return TEST_MISS;
+    c3 = lower_bound(l3.p, c3, l3.n, t2, p3, t3);
+    if (c3 == l3.n) return TEST_END;
+    win = t3 - t;
+    return win <= dmax ? TEST_HIT : TEST_MISS;
+}
+
+// counts the edges whose window is at most delta
+struct DirectOp {
+    int64_t delta;
+    uint32_t *count;
+    int32_t *diff; // per sorted edge + 1: +1 / -1 at the ends of edge ranges (interval evaluation)
+    __device__ inline int64_t most() const { return delta; }
+    __device__ inline void hit(int32_t e, int64_t) const { atomicAdd(&count[e], 1u); }
 
     // The same run evaluated from L2 (paper, the in-neighbour theorem: e forms
     // a triangle with w iff some entry t2 of L2, with t3 the first entry of L3
@@ -284,93 +337,48 @@ template <bool SHORT> struct DirectOpT {
     // times in [max(t3 - delta, t2' + 1), t2] (t2' the entry before it) to the
     // union of the earlier ones; each such piece is a range of L1 marked +1 / -1
     // in diff, whose prefix sum over the sorted edges adds one per third vertex.
-    // Entries [j0, j0 + cnt) of L2.
-    __device__ inline void iv(const int64_t *__restrict__ ts, const Span &l1, int32_t j0, int32_t cnt,
-                              const Span &l2, const Span &l3) const {
-        const int64_t *L1 = ts + l1.s, *L2 = ts + l2.s, *L3 = ts + l3.s;
+    // Entries [j0, j0 + cnt) of L2; l1s: L1's start among the sorted edges.
+    __device__ inline void iv(const List &l1, int32_t l1s, int32_t j0, int32_t cnt, const List &l2,
+                              const List &l3) const {
         int32_t c3 = 0, a = 0, b = 0;
-        for (int32_t q = 0; q < cnt; q++) {
-            const int32_t j = j0 + q;
-            const int64_t t2 = L2[j];
-            c3 = lower_bound_from(L3, c3, l3.n, t2);
+        for (int32_t j = j0; j < j0 + cnt; j++) {
+            const Probe p3 = probe(l3.p, c3, l3.n);
+            const Probe p1 = probe(l1.p, b, l1.n); // b < |L1| (see below)
+            const int64_t t2 = l2.p[j], before = l2.p[j > 0 ? j - 1 : 0];
+            int64_t t3 = 0, x = 0;
+            c3 = lower_bound(l3.p, c3, l3.n, t2, p3, t3);
             if (c3 == l3.n) break; // no t3 for this or any later entry
-            const int64_t t3 = L3[c3];
             if (t3 - t2 > delta) continue; // an empty interval
             int64_t lo = t3 - delta;
-            if (j > 0 && L2[j - 1] + 1 > lo) lo = L2[j - 1] + 1;
+            if (j > 0 && before + 1 > lo) lo = before + 1;
             if (lo > t2) continue;
-            a = lower_bound_from(L1, a, l1.n, lo);
-            b = lower_bound_from(L1, a > b ? a : b, l1.n, t2 + 1);
+            // ends are past the earlier ones: lo > t2' >= the times before b
+            a = lower_bound(l1.p, b, l1.n, lo, p1, x);
+            if (a == l1.n) break; // later intervals start no earlier
+            b = lower_bound(l1.p, a, l1.n, t2 + 1, probe(l1.p, a, l1.n), x);
             if (a < b) {
-                atomicAdd(&diff[l1.s + a], 1);
-                atomicAdd(&diff[l1.s + b], -1);
+                atomicAdd(&diff[l1s + a], 1);
+                atomicAdd(&diff[l1s + b], -1);
+                if (b == l1.n) break;
             }
         }
     }
 };
-using DirectOp = DirectOpT<false>;      // plain tests (also the interval evaluation)
-using DirectShortOp = DirectOpT<true>;  // short lists from their spans' end timestamps
 
 // the smallest window per (e, w) into a histogram over sorted window levels:
 // level j counts w whose smallest window lies in (lv[j-1], lv[j]]
 struct PoolOp {
     const int64_t *lv;
     int nl, nls;
+    int64_t dmax; // the last level
     uint32_t *hist;
     unsigned long long *tmask; // per tile of 64 edges: bit e & 63 set once a counter of edge e is non-zero
-    __device__ inline void operator()(const int64_t *__restrict__ ts, int32_t l1s, int32_t cnt, const Span &l2,
-                                      const Span &l3) const {
-        const int64_t *L2 = ts + l2.s, *L3 = ts + l3.s;
-        const int64_t dmax = lv[nl - 1];
-        int32_t c2 = 0, c3 = 0;
-        for (int32_t q = 0; q < cnt; q++) {
-            int32_t e = l1s + q;
-            int64_t t = ts[e];
-            c2 = lower_bound_from(L2, c2, l2.n, t);
-            if (c2 == l2.n) break;
-            int64_t t2 = L2[c2];
-            if (t2 - t > dmax) continue;
-            c3 = lower_bound_from(L3, c3, l3.n, t2);
-            if (c3 == l3.n) break;
-            int64_t win = L3[c3] - t;
-            if (win > dmax) continue;
-            int a = 0, b = nl;
-            while (a < b) {
-                int mid = (a + b) >> 1;
-                if (lv[mid] < win) a = mid + 1;
-                else b = mid;
-            }
-            if (atomicAdd(&hist[hist_at(e, a, nls)], 1u) == 0u) atomicOr(&tmask[e >> 6], 1ull << (e & 63));
-        }
+    __device__ inline int64_t most() const { return dmax; }
+    __device__ inline void hit(int32_t e, int64_t win) const {
+        const int32_t a = lower_bound_from(lv, 0, nl, win); // win <= dmax, the last level
+        if (atomicAdd(&hist[hist_at(e, a, nls)], 1u) == 0u) atomicOr(&tmask[e >> 6], 1ull << (e & 63));
     }
 };
-
-// one run of a surviving triangle within the chunk [k, k1); r = tests of this
-// triangle still to skip.  Returns false once the chunk is used up.  With SS (and
-// a filter that counted tests the same way) a run whose L2 is shorter than L1
-// has |L2| tests, the entries of L2, and is evaluated from them.
-template <int VAR, int I, int J, class Op, bool SS = false>
-__device__ inline bool chunk_run(const TriLists &T, uint32_t dq, const int64_t *ts, int64_t &r, int64_t &k,
-                                 int64_t k1, const Op &op) {
-    Span l1, l2, l3;
-    if (!run_lists<VAR, I, J>(T, dq, l1, l2, l3)) return true;
-    const int32_t w = run_tests<SS>(l1, l2);
-    if (r >= w) {
-        r -= w;
-        return true;
-    }
-    int64_t cnt = w - r;
-    if (cnt > k1 - k) cnt = k1 - k;
-    if constexpr (SS) {
-        if (w < l1.n) op.iv(ts, l1, (int32_t)r, (int32_t)cnt, l2, l3);
-        else op(ts, l1.s + (int32_t)r, (int32_t)cnt, l2, l3);
-    } else {
-        op(ts, l1.s + (int32_t)r, (int32_t)cnt, l2, l3);
-    }
-    k += cnt;
-    r = 0;
-    return k < k1;
-}
 
 // ---------------------------------------------------------------------------
 // a.5: triangle enumeration, one wavefront per item
@@ -995,55 +1003,33 @@ __global__ __launch_bounds__(BLK) void k_filter_cached(const int32_t *__restrict
     sink.finish();
 }
 
-template <int VAR, class Op, bool SS = false>
-__device__ inline void chunk_runs(const TriLists &L, uint32_t dq, const int64_t *ts, int64_t &r, int64_t &k, int64_t k1,
-                                  const Op &op) {
-    if (chunk_run<VAR, 0, 1, Op, SS>(L, dq, ts, r, k, k1, op) && chunk_run<VAR, 1, 0, Op, SS>(L, dq, ts, r, k, k1, op) &&
-        chunk_run<VAR, 0, 2, Op, SS>(L, dq, ts, r, k, k1, op) && chunk_run<VAR, 2, 0, Op, SS>(L, dq, ts, r, k, k1, op) &&
-        chunk_run<VAR, 1, 2, Op, SS>(L, dq, ts, r, k, k1, op))
-        chunk_run<VAR, 2, 1, Op, SS>(L, dq, ts, r, k, k1, op);
-}
-
-template <class Op>
-__device__ inline void chunk_runs_rt(int variant, const TriLists &L, uint32_t dq, const int64_t *ts, int64_t &r,
-                                     int64_t &k, int64_t k1, const Op &op) {
-    switch (variant) {
-    case 0: chunk_runs<0>(L, dq, ts, r, k, k1, op); break;
-    case 1: chunk_runs<1>(L, dq, ts, r, k, k1, op); break;
-    case 2: chunk_runs<2>(L, dq, ts, r, k, k1, op); break;
-    case 3: chunk_runs<3>(L, dq, ts, r, k, k1, op); break;
-    case 4: chunk_runs<4>(L, dq, ts, r, k, k1, op); break;
-    case 5: chunk_runs<5>(L, dq, ts, r, k, k1, op); break;
-    case 6: chunk_runs<6>(L, dq, ts, r, k, k1, op); break;
-    default: chunk_runs<7>(L, dq, ts, r, k, k1, op); break;
-    }
-}
-
 // ---------------------------------------------------------------------------
 // a.6: scheduling the tests of the triangles the filter kept
 // ---------------------------------------------------------------------------
-// A wavefront takes one chunk of the filter's output, a triangle per lane, reads
-// their records and finds the runs that can count and their tests.  A triangle
-// with at most LIGHT_TESTS tests is run by the wavefront.  One with more (a
-// heavy triangle) gets an entry in a list and a range of piece numbers, both
-// from one packed counter, so entries are in the order of their pieces; a second
-// kernel runs piece p (tests [4 i, 4 i + 4) of its triangle) per thread, finding
-// its entry by binary search over the entries' first pieces and starting its L2
-// and L3 cursors with one binary search each (the merge-path split of a long run
-// over neighbouring threads).  Heavy triangles past the list's capacity run where
-// they were found, so any capacity gives the same result.
-//
-// How a wavefront runs its light tests depends on the runner.  Flat runners (the
-// per-edge counts): the lanes stage their triangles' six list spans in LDS, and
-// the tests, concatenated, go one per lane, so neighbouring lanes take
-// neighbouring tests of one run and their loads coalesce; each test finds its
-// triangle by a search over 64 prefix sums in LDS and its cursors by binary
-// search.  Other runners (the exists-exists-exists counting, whose window
-// bookkeeping is shared by the tests of a run): each lane runs its own
-// triangle's tests in order.
-// 70M-edge graph, one year (36.8M tests) and a graph of 5,000-edge lists closed
-// by short ones (104M tests): light limit 16 / pieces of 32: 2.45 and 3.2 ms;
-// 64 / 8: 1.97 and 1.74 ms; 64 / 4: 1.85 and 1.15 ms; 64 / 2: 1.83 and 1.30 ms
+// A wavefront takes a group of the filter's chunks, a triangle per lane, reads
+// their records and finds the runs that can count and their tests.  The lanes
+// stage their triangles' runs in LDS, and the work of triangles with at most
+// LIGHT_TESTS tests, concatenated, is spread over the lanes: each finds its
+// triangle by a search over 64 prefix sums and its run by the triangle's bits,
+// and all lanes run one copy of the test whatever their run or predicate.
+// (A copy per run, six in turn with part of the lanes each, took 2.2 ms where
+// this takes 1.5 ms: 36.6M tests of the 70M-edge graph at one year.)  The
+// per-edge counts take a test per lane, so neighbouring lanes take neighbouring
+// tests of one run and their loads coalesce; the exists-exists-exists counting,
+// whose window bookkeeping the tests of a run share, takes a few of them per lane.
+// A triangle with more tests (a heavy one) gets an entry in a list and a range of
+// piece numbers, both from one packed counter, so entries are in the order of
+// their pieces; a second kernel runs piece p (tests [4 i, 4 i + 4) of its
+// triangle) per thread, finding its entry by binary search over the entries'
+// first pieces (the merge-path split of a long run over neighbouring threads).
+// Heavy triangles past the list's capacity run where they were found, so any
+// capacity gives the same result.
+// Both kernels wait on dependent reads, so registers and LDS are kept small
+// enough for six to eight wavefronts per SIMD.
+// 70M-edge graph, one year (14.1M triangles, 36.6M tests) and a graph of
+// 5,000-edge lists closed by short ones (2.9M triangles, 106M tests), both kernels:
+// light limit 32 / 64 / 128 with pieces of 4: 1.67, 1.62, 1.58 and 1.13, 1.14, 1.10 ms;
+// limit 64 with pieces of 2 / 8: 1.60, 1.71 and 1.22, 1.68 ms.
 constexpr int64_t LIGHT_TESTS = 64;
 constexpr int64_t PIECE_TESTS = 4;
 
@@ -1101,52 +1087,31 @@ __device__ inline bool edges_meet(const TriLists &T, uint32_t dq) {
 // list index of E_{x_a, x_b} in TriLists order (d01, d10, d02, d20, d12, d21)
 constexpr int list_id(int a, int b) { return a == 0 ? (b == 1 ? 0 : 2) : a == 1 ? (b == 0 ? 1 : 4) : (b == 0 ? 3 : 5); }
 
-// One light group's survivors in LDS: start and length of each directed list,
-// the runs that can count (bit k: run k in the order of chunk_runs), and the
-// inclusive prefix of the survivors' tests.
-// SHORT also keeps each list's first and last timestamp (3 KB more per
-// wavefront), for tests that read short lists from them.
-template <bool SHORT> struct FlatLds;
-template <> struct FlatLds<false> {
+// A wavefront's triangles in LDS: start and length of each directed list, the
+// runs that can count (bit k: run k in the order of tri_live), and the inclusive
+// prefix of the triangles' work.  SHORT: also the edges, for tests that read
+// short lists from their records (see List).  SLOT: also their slots.
+template <bool SHORT, bool SLOT = false> struct RunLds {
     int32_t incl[64];
-    int32_t ls[6][64];
-    int32_t ln[6][64];
     uint32_t live[64];
+    int32_t n[6][64];
+    int32_t s[6][64];
+    int32_t e[SHORT ? 3 : 1][64];
+    int64_t slot[SLOT ? 64 : 1];
 };
-template <> struct FlatLds<true> : FlatLds<false> {
-    uint32_t lo[6][64]; // first and last timestamp >> tshift
-    uint32_t hi[6][64];
-};
-
-// run k = (I, J) of survivor si holds test r (r < that run's tests): run it
-template <int VAR, int I, int J, bool SS, class Op, bool SHORT>
-__device__ inline bool flat_run(const FlatLds<SHORT> &F, int si, int k, int64_t &r, const int64_t *__restrict__ ts,
-                                const Op &op) {
-    if (!((F.live[si] >> k) & 1u)) return false;
-    using P = Pick<VAR, I, J>;
-    constexpr int i1 = list_id(I, J), i2 = list_id(P::L2a, P::L2b), i3 = list_id(P::L3a, P::L3b);
-    const int32_t n1 = F.ln[i1][si], n2 = F.ln[i2][si];
-    const int32_t nt = SS && n2 < n1 ? n2 : n1;
-    if (r >= nt) {
-        r -= nt;
-        return false;
+template <bool SHORT, bool SLOT>
+__device__ inline void stage_runs(RunLds<SHORT, SLOT> &F, int lane, const TriLists &T, const int32_t (&e)[3],
+                                  uint32_t live, int64_t slot) {
+    const Span *sp[6] = {&T.d01, &T.d10, &T.d02, &T.d20, &T.d12, &T.d21};
+#pragma unroll
+    for (int k = 0; k < 6; k++) {
+        F.s[k][lane] = sp[k]->s;
+        F.n[k][lane] = sp[k]->n;
     }
-    Span l1{}, l2{}, l3{};
-    l1.s = F.ls[i1][si];
-    l1.n = n1;
-    l2.s = F.ls[i2][si];
-    l2.n = n2;
-    l3.s = F.ls[i3][si];
-    l3.n = F.ln[i3][si];
-    if constexpr (SHORT) {
-        l2.lo = F.lo[i2][si];
-        l2.hi = F.hi[i2][si];
-        l3.lo = F.lo[i3][si];
-        l3.hi = F.hi[i3][si];
-    }
-    if (SS && nt < n1) op.iv(ts, l1, (int32_t)r, 1, l2, l3);
-    else op(ts, l1.s + (int32_t)r, 1, l2, l3);
-    return true;
+    if constexpr (SHORT)
+        for (int k = 0; k < 3; k++) F.e[k][lane] = e[k];
+    if constexpr (SLOT) F.slot[lane] = slot;
+    F.live[lane] = live;
 }
 
 // The three lists of run k (order of tri_live's bits) under a predicate code, as
@@ -1155,7 +1120,7 @@ __device__ inline bool flat_run(const FlatLds<SHORT> &F, int si, int k, int64_t 
 struct RunLists {
     uint32_t l2, l3;
 };
-__device__ inline RunLists run_list_ids(int variant) {
+__host__ __device__ constexpr RunLists run_list_ids(int variant) {
     // for run (I, J) with third vertex C: the lists I -> C, C -> I, J -> C, C -> J
     constexpr int RI[6] = {0, 1, 0, 2, 1, 2}, RJ[6] = {1, 0, 2, 0, 2, 1};
     uint32_t ic = 0, ci = 0, jc = 0, cj = 0;
@@ -1173,101 +1138,140 @@ __device__ inline RunLists run_list_ids(int variant) {
     return RunLists{x, y};
 }
 
-// test r of triangle si's live runs, from the staged spans, for a predicate code
-// read at run time
-template <class Op>
-__device__ inline void flat_run_rt(const FlatLds<false> &F, const RunLists &R, int si, int32_t r,
-                                   const int64_t *__restrict__ ts, const Op &op) {
+// list `id` of staged triangle si; rec: the edges' records when its end
+// timestamps are exact, else null
+template <bool SHORT>
+__device__ inline List staged_list(const RunLds<SHORT> &F, int id, int si, const int64_t *__restrict__ ts,
+                                   const EdgeRec *__restrict__ rec) {
+    List l{ts + F.s[id][si], F.n[id][si], nullptr};
+    if constexpr (SHORT)
+        if (rec && l.n <= 2) l.ends = reinterpret_cast<const int64_t *>(rec + F.e[id >> 1][si]) + 2 + (id & 1);
+    return l;
+}
+
+// Tests [r, r + cnt) of staged triangle si's runs in order (ONE: cnt = 1, and
+// r is below their number).  SS: a run whose L2 is shorter than L1 has |L2|
+// tests, the entries of L2, and is evaluated from them.
+template <bool SS, bool ONE, class Op, bool SHORT>
+__device__ inline void staged_tests(const RunLds<SHORT> &F, const RunLists &ids, int si, int64_t r, int32_t cnt,
+                                    const int64_t *__restrict__ ts, const EdgeRec *__restrict__ rec, const Op &op) {
     uint32_t live = F.live[si];
     while (live) {
         const int k = __ffs((int)live) - 1;
         live &= live - 1;
-        const int32_t n1 = F.ln[k][si];
-        if (r >= n1) {
-            r -= n1;
+        const int i2 = (int)(ids.l2 >> (3 * k)) & 7, i3 = (int)(ids.l3 >> (3 * k)) & 7;
+        const int32_t n1 = F.n[k][si];
+        const int32_t nt = SS && F.n[i2][si] < n1 ? F.n[i2][si] : n1;
+        if (r >= nt) {
+            r -= nt;
             continue;
         }
-        const int i2 = (int)(R.l2 >> (3 * k)) & 7, i3 = (int)(R.l3 >> (3 * k)) & 7;
-        Span l2{}, l3{};
-        l2.s = F.ls[i2][si];
-        l2.n = F.ln[i2][si];
-        l3.s = F.ls[i3][si];
-        l3.n = F.ln[i3][si];
-        op(ts, F.ls[k][si] + r, 1, l2, l3);
-        return;
+        const int32_t l1s = F.s[k][si];
+        const List l2 = staged_list(F, i2, si, ts, rec), l3 = staged_list(F, i3, si, ts, rec);
+        const int32_t first = (int32_t)r, m = ONE || cnt < nt - first ? (ONE ? 1 : cnt) : nt - first;
+        bool done = false;
+        if constexpr (SS) {
+            if (nt < n1) {
+                op.iv(List{ts + l1s, n1, nullptr}, l1s, first, m, l2, l3);
+                done = true;
+            }
+        }
+        if (!done) {
+            int32_t c2 = 0, c3 = 0;
+            for (int32_t q = 0; q < m; q++) {
+                const int32_t e = l1s + first + q;
+                const Probe p2 = l2.template at<SHORT>(c2), p3 = l3.template at<SHORT>(c3);
+                int64_t win = 0;
+                const TestEnd x = window_test(l2, l3, c2, c3, p2, p3, ts[e], op.most(), win);
+                if (x == TEST_HIT) op.hit(e, win);
+                if (x == TEST_END) break;
+            }
+        }
+        cnt -= m;
+        if (ONE || cnt == 0) return;
+        r = 0;
     }
 }
 
-// Runs the tests of the per-edge counts: work() is a survivor's number of
-// tests, run() takes tests [r, k1) of it in order, flat() its test r alone,
-// from the spans stage() put in LDS.
+// Runs the tests of the per-edge counts (see k_tests_light): units() is a light
+// triangle's work items, flat() runs one of them, piece() tests [r, r + cnt).
 template <int VAR, class Op, bool SS> struct CountRunner {
-    static constexpr bool kFlat = true;
-    static constexpr bool kShort = Op::kShort && !SS; // staging keeps the lists' end timestamps
-    static_assert(!(Op::kShort && SS), "short lists are read only by the plain evaluation");
-    using Flat = FlatLds<kShort>;
-    using Surv = TriLists;
+    static constexpr bool kShort = !SS;
+    using Lds = RunLds<kShort>;
     uint32_t dq;
     const int64_t *ts;
     Op op;
-    const int32_t *sv; // survivors as three oriented edges
+    const int32_t *sv; // the triangles as three oriented edges
     const EdgeRec *rec;
-    __device__ inline TriLists load(int64_t slot) const {
-        return load_lists(rec, sv[3 * slot], sv[3 * slot + 1], sv[3 * slot + 2]);
-    }
+    bool inl; // timestamps are below 2^32, so the records' are exact
+    __device__ inline uint32_t live(const TriLists &L) const { return tri_live<VAR>(L, dq); }
     __device__ inline int64_t work(const TriLists &L) const { return tri_work<VAR, SS>(L, dq); }
-    __device__ inline void run(const TriLists &L, int64_t, int64_t r, int64_t k1) {
-        int64_t k = r;
-        chunk_runs<VAR, Op, SS>(L, dq, ts, r, k, k1, op);
+    __device__ inline int64_t units(const Lds &, int, int64_t tests) const { return tests; }
+    __device__ inline const EdgeRec *ends() const { return inl ? rec : nullptr; }
+    __device__ inline void flat(const Lds &F, int si, int64_t r) {
+        staged_tests<SS, true>(F, run_list_ids(VAR), si, r, 1, ts, ends(), op);
     }
-    __device__ inline void stage(Flat &F, int lane, const TriLists &T, bool light) const {
-        const Span *sp[6] = {&T.d01, &T.d10, &T.d02, &T.d20, &T.d12, &T.d21};
-#pragma unroll
-        for (int k = 0; k < 6; k++) {
-            F.ls[k][lane] = sp[k]->s;
-            F.ln[k][lane] = sp[k]->n;
-            if constexpr (kShort) {
-                F.lo[k][lane] = sp[k]->lo;
-                F.hi[k][lane] = sp[k]->hi;
-            }
-        }
-        F.live[lane] = light ? tri_live<VAR>(T, dq) : 0u;
-    }
-    __device__ inline void flat(const Flat &F, int si, int64_t r) const {
-        flat_run<VAR, 0, 1, SS>(F, si, 0, r, ts, op) || flat_run<VAR, 1, 0, SS>(F, si, 1, r, ts, op) ||
-            flat_run<VAR, 0, 2, SS>(F, si, 2, r, ts, op) || flat_run<VAR, 2, 0, SS>(F, si, 3, r, ts, op) ||
-            flat_run<VAR, 1, 2, SS>(F, si, 4, r, ts, op) || flat_run<VAR, 2, 1, SS>(F, si, 5, r, ts, op);
+    __device__ inline void piece(const Lds &F, int si, int64_t r, int32_t cnt) {
+        staged_tests<SS, false>(F, run_list_ids(VAR), si, r, cnt, ts, ends(), op);
     }
     __device__ inline void finish() {}
 };
 
-// Lanes with np > 0 (heavy survivors, np pieces each) take list entries and
-// piece numbers for the whole wavefront with one atomic.  A survivor whose
-// entry lies past cap runs here; the piece numbers it reserved follow every
-// listed one.  `full` is set once this wavefront's atomic returned an entry
-// count of cap or more, after which it lists nothing: each wavefront adds at
-// most 64 entries past cap, so the entry count stays below cap + 64 x (the
-// grid's wavefronts), far below 2^24.
-template <class R>
-__device__ inline void defer_heavy(R &runner, const typename R::Surv &S, int64_t slot, int64_t w, int64_t np,
-                                   Heavy *__restrict__ heavy, unsigned long long *__restrict__ counter, int64_t cap,
-                                   bool &full) {
-    if (!__ballot(np > 0)) return;
-    if (full) {
-        if (np > 0) runner.run(S, slot, 0, w);
-        return;
-    }
+// Lanes with np > 0 (heavy triangles, np pieces each) take list entries and
+// piece numbers for the whole wavefront with one atomic; returns which of them
+// are listed.  The piece numbers that one past cap reserved follow every listed
+// one.  `full` is set once this wavefront's atomic returned an entry count of cap
+// or more, after which it lists nothing: each wavefront adds at most 64 entries
+// past cap, so the entry count stays below cap + 64 x (the grid's wavefronts),
+// far below 2^24.
+__device__ inline bool defer_heavy(int64_t slot, int64_t np, Heavy *__restrict__ heavy,
+                                   unsigned long long *__restrict__ counter, int64_t cap, bool &full) {
+    if (full || !__ballot(np > 0)) return false;
     const unsigned long long add = np > 0 ? (1ull << HEAVY_SHIFT) | (unsigned long long)np : 0ull;
     const unsigned long long incl = wave_inclusive_sum(add);
     unsigned long long at = 0;
     if (lane_id() == 63) at = atomicAdd(counter, incl);
     at = __shfl(at, 63);
     full = (int64_t)(at >> HEAVY_SHIFT) + 64 >= cap;
-    if (np == 0) return;
+    if (np == 0) return false;
     const unsigned long long mine = at + incl - add;
     const int64_t e = (int64_t)(mine >> HEAVY_SHIFT);
-    if (e < cap) heavy[e] = Heavy{slot, (int64_t)(mine & PIECE_MASK)};
-    else runner.run(S, slot, 0, w);
+    if (e >= cap) return false;
+    heavy[e] = Heavy{slot, (int64_t)(mine & PIECE_MASK)};
+    return true;
+}
+
+// The staged triangles' work over the lanes: flat(si, r) is item r of triangle
+// si, this lane's triangle has `units` items (at most LIGHT_TESTS); triangles
+// with `own` set (heavy, not listed) have alone(si) items each and go one after
+// another.
+template <class Lds, class Flat, class Alone>
+__device__ inline void spread_units(Lds &F, int32_t incl, bool own, const Flat &flat, const Alone &alone) {
+    const int lane = lane_id();
+    int64_t total = __builtin_amdgcn_readlane(incl, 63);
+    unsigned long long left = __ballot(own);
+    int src = -1;
+    for (;;) {
+        for (int64_t t = lane; t < total; t += 64) {
+            int si = src;
+            int64_t r = t;
+            if (src < 0) { // the triangle whose items hold t: the first with incl > t
+                int a = 0, b = 63;
+                while (a < b) {
+                    const int mid = (a + b) >> 1;
+                    if (F.incl[mid] > (int32_t)t) b = mid;
+                    else a = mid + 1;
+                }
+                si = a;
+                r = t - (a ? F.incl[a - 1] : 0);
+            }
+            flat(si, r);
+        }
+        if (!left) break;
+        src = __builtin_ctzll(left);
+        left &= left - 1;
+        total = alone(src);
+    }
 }
 
 // A wavefront's group of chunks as a dense sequence of slots: narrow windows
@@ -1317,13 +1321,12 @@ template <class R>
 __global__ __launch_bounds__(BLK) void k_tests_light(CandBuf B, R runner, Heavy *__restrict__ heavy,
                                                      unsigned long long *__restrict__ counter, int64_t cap,
                                                      unsigned long long *__restrict__ scal) {
-    __shared__ typename R::Flat flds[R::kFlat ? WPB : 1];
+    __shared__ typename R::Lds flds[WPB];
     __shared__ GroupLds glds[WPB];
     __shared__ Chunks C;
-    __shared__ unsigned long long s_tests[WPB];
-    __shared__ int32_t s_kept[WPB];
     const int w = wave_id();
     const int lane = lane_id();
+    typename R::Lds &F = flds[w];
     C.load(B);
     const int32_t per = group_chunks(C.total), parts = chunk_parts(C.total); // one of them is 1
     bool full = false;
@@ -1337,45 +1340,38 @@ __global__ __launch_bounds__(BLK) void k_tests_light(CandBuf B, R runner, Heavy 
         const int32_t slots = parts == 1 || all < (part + 1) * wide ? all : (part + 1) * wide;
         if (part == 0) kept += all;
         for (int32_t q0 = part * wide; q0 < slots; q0 += 64) {
-            const bool on = q0 + lane < slots;
             int64_t slot = 0, wk = 0, np = 0;
-            typename R::Surv S{};
-            if (on) {
+            int32_t e[3] = {0, 0, 0};
+            TriLists T{};
+            uint32_t live = 0;
+            if (q0 + lane < slots) {
                 slot = group_slot(glds[w], q0 + lane);
-                S = runner.load(slot);
-                if (edges_meet(S, runner.dq)) wk = runner.work(S);
+                for (int k = 0; k < 3; k++) e[k] = runner.sv[3 * slot + k];
+                T = load_lists(runner.rec, e[0], e[1], e[2]);
+                if (edges_meet(T, runner.dq)) {
+                    live = runner.live(T);
+                    wk = runner.work(T);
+                }
                 if (wk > LIGHT_TESTS) np = (wk + PIECE_TESTS - 1) / PIECE_TESTS;
             }
             mine += wk;
-            defer_heavy(runner, S, slot, wk, np, heavy, counter, cap, full);
-            const int64_t light = np ? 0 : wk;
-            if constexpr (R::kFlat) {
-                typename R::Flat &F = flds[w];
-                const int32_t incl = wave_scan((int32_t)light);
-                const int32_t total = __builtin_amdgcn_readlane(incl, 63);
-                if (total == 0) continue;
-                F.incl[lane] = incl;
-                runner.stage(F, lane, S, light != 0);
-                wave_sync();
-                for (int32_t t = lane; t < total; t += 64) {
-                    // the triangle whose tests hold t: the first si with incl[si] > t
-                    int a = 0, b = 63;
-                    while (a < b) {
-                        const int mid = (a + b) >> 1;
-                        if (F.incl[mid] > t) b = mid;
-                        else a = mid + 1;
-                    }
-                    runner.flat(F, a, (int64_t)(t - (a ? F.incl[a - 1] : 0)));
-                }
-                wave_sync(); // the LDS is rewritten by the next triangles
-            } else {
-                if (light) runner.run(S, slot, 0, light);
-            }
+            const bool listed = defer_heavy(slot, np, heavy, counter, cap, full);
+            stage_runs(F, lane, T, e, live, slot);
+            const int32_t incl = wave_scan(np ? 0 : (int32_t)runner.units(F, lane, wk));
+            F.incl[lane] = incl;
+            wave_sync();
+            spread_units(
+                F, incl, np && !listed,
+                [&](int si, int64_t r) { runner.flat(F, si, r); },
+                [&](int si) { return runner.units(F, si, __shfl(wk, si)); }); // si: the same in every lane
+            wave_sync(); // the LDS is rewritten by the next triangles
         }
         wave_sync(); // the group's LDS is rewritten by the next group
     }
     runner.finish();
     for (int o = 32; o > 0; o >>= 1) mine += __shfl_xor(mine, o);
+    __shared__ unsigned long long s_tests[WPB];
+    __shared__ int32_t s_kept[WPB];
     if (lane == 0) {
         s_tests[w] = (unsigned long long)mine;
         s_kept[w] = kept;
@@ -1392,27 +1388,37 @@ __global__ __launch_bounds__(BLK) void k_tests_light(CandBuf B, R runner, Heavy 
     }
 }
 
+// the entry of piece p: the last whose first piece is <= p (entry 0 starts at piece 0)
+__device__ inline Heavy heavy_of(const Heavy *__restrict__ heavy, int64_t ne, int64_t p) {
+    int64_t a = 0, b = ne - 1;
+    while (a < b) {
+        const int64_t mid = (a + b + 1) >> 1;
+        if (heavy[mid].first <= p) a = mid;
+        else b = mid - 1;
+    }
+    return heavy[a];
+}
+
 template <class R>
 __global__ __launch_bounds__(BLK) void k_tests_pieces(const Heavy *__restrict__ heavy,
                                                       const unsigned long long *__restrict__ counter, int64_t cap,
                                                       R runner) {
+    __shared__ typename R::Lds flds[WPB];
+    typename R::Lds &F = flds[wave_id()];
+    const int lane = lane_id();
     const unsigned long long c = *counter;
     const int64_t ne = (int64_t)(c >> HEAVY_SHIFT) < cap ? (int64_t)(c >> HEAVY_SHIFT) : cap;
     const int64_t np = (int64_t)(c & PIECE_MASK);
     if (ne > 0) {
         for (int64_t p = (int64_t)blockIdx.x * BLK + threadIdx.x; p < np; p += (int64_t)gridDim.x * BLK) {
-            // the last entry whose first piece is <= p (entry 0 starts at piece 0)
-            int64_t a = 0, b = ne - 1;
-            while (a < b) {
-                const int64_t mid = (a + b + 1) >> 1;
-                if (heavy[mid].first <= p) a = mid;
-                else b = mid - 1;
-            }
-            const Heavy h = heavy[a];
-            const int64_t k0 = (p - h.first) * PIECE_TESTS;
-            // pieces past the last listed survivor's belong to ones that ran
-            // where they were found: k0 lies past every run, nothing is tested
-            runner.run(runner.load(h.slot), h.slot, k0, k0 + PIECE_TESTS);
+            const Heavy h = heavy_of(heavy, ne, p);
+            int32_t e[3];
+            for (int k = 0; k < 3; k++) e[k] = runner.sv[3 * h.slot + k];
+            const TriLists T = load_lists(runner.rec, e[0], e[1], e[2]);
+            stage_runs(F, lane, T, e, runner.live(T), h.slot); // this lane's own column
+            // pieces past the last listed triangle's belong to ones that ran
+            // where they were found: they lie past every run, nothing is tested
+            runner.piece(F, lane, (p - h.first) * PIECE_TESTS, PIECE_TESTS);
         }
     }
     runner.finish();

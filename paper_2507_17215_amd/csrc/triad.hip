@@ -105,59 +105,63 @@ __device__ inline void triad_chunk(const TriadOut &o, const int64_t *__restrict_
     if (any) atomicOr(&o.flag[slot >> 2], 1u << (((int)(slot & 3) << 3) + run));
 }
 
-// one run (I, J) of a surviving triangle inside the chunk [k, k1); r = tests of
-// this triangle still to skip.  Returns false once the chunk is used up.
-template <int VAR, int I, int J, int RUN, bool INST>
-__device__ inline bool triad_run(const TriLists &T, uint32_t dq, const int64_t *ts, int64_t &r, int64_t &k,
-                                 int64_t k1, const TriadOut &o, int64_t slot, unsigned long long &acc, bool &ovf) {
-    Span l1, l2, l3;
-    if (!run_lists<VAR, I, J>(T, dq, l1, l2, l3)) return true;
-    if (r >= l1.n) {
-        r -= l1.n;
-        return true;
-    }
-    int64_t cnt = l1.n - r;
-    if (cnt > k1 - k) cnt = k1 - k;
-    triad_chunk<INST>(o, ts, l1.s + (int32_t)r, (int32_t)cnt, l2, l3, slot, RUN, acc, ovf);
-    k += cnt;
-    r = 0;
-    return k < k1;
-}
-
-// run numbers: (x0, x1), (x1, x0), (x0, x2), (x2, x0), (x1, x2), (x2, x1)
-template <int VAR, bool INST>
-__device__ inline void triad_runs(const TriLists &L, uint32_t dq, const int64_t *ts, int64_t &r, int64_t &k,
-                                  int64_t k1, const TriadOut &o, int64_t slot, unsigned long long &acc, bool &ovf) {
-    if (triad_run<VAR, 0, 1, 0, INST>(L, dq, ts, r, k, k1, o, slot, acc, ovf) &&
-        triad_run<VAR, 1, 0, 1, INST>(L, dq, ts, r, k, k1, o, slot, acc, ovf) &&
-        triad_run<VAR, 0, 2, 2, INST>(L, dq, ts, r, k, k1, o, slot, acc, ovf) &&
-        triad_run<VAR, 2, 0, 3, INST>(L, dq, ts, r, k, k1, o, slot, acc, ovf) &&
-        triad_run<VAR, 1, 2, 4, INST>(L, dq, ts, r, k, k1, o, slot, acc, ovf))
-        triad_run<VAR, 2, 1, 5, INST>(L, dq, ts, r, k, k1, o, slot, acc, ovf);
-}
-
-// The surviving runs' tests, scheduled as the count's (k_tests_light, then the
-// pieces of survivors with many tests); total[0] += temporal triangles, total[1]
-// = 1 on a 64-bit overflow.
+// The triangles' runs, scheduled as the count's (k_tests_light, a few
+// tests of a run per lane; then the pieces of triangles with many tests); total[0] += temporal triangles,
+// total[1] = 1 on a 64-bit overflow.
 template <int VAR, bool INST> struct TriadRunner {
-    static constexpr bool kFlat = false; // a run's tests share their window bookkeeping
-    using Flat = FlatLds<false>;
-    using Surv = TriLists;
+    using Lds = RunLds<false, true>;
     uint32_t dq;
     const int64_t *ts;
     TriadOut o;
     unsigned long long *total;
-    const int32_t *sv;  // survivors as three oriented edges
+    const int32_t *sv;  // the triangles as three oriented edges
     const EdgeRec *rec;
     unsigned long long acc = 0;
     bool ovf = false;
-    __device__ inline TriLists load(int64_t slot) const {
-        return load_lists(rec, sv[3 * slot], sv[3 * slot + 1], sv[3 * slot + 2]);
-    }
+    __device__ inline uint32_t live(const TriLists &L) const { return tri_live<VAR>(L, dq); }
     __device__ inline int64_t work(const TriLists &L) const { return tri_work<VAR, false>(L, dq); }
-    __device__ inline void run(const TriLists &L, int64_t slot, int64_t r, int64_t k1) {
-        int64_t k = r;
-        triad_runs<VAR, INST>(L, dq, ts, r, k, k1, o, slot, acc, ovf);
+    // A light triangle's items are pieces of its runs: a whole run of 64 tests is a
+    // chain of some hundred dependent reads, which the slowest lane's wavefront
+    // waits for.
+    __device__ inline int64_t units(const Lds &F, int si, int64_t) const {
+        int64_t c = 0;
+        for (uint32_t live = F.live[si]; live; live &= live - 1)
+            c += (F.n[__ffs((int)live) - 1][si] + (int32_t)PIECE_TESTS - 1) / (int32_t)PIECE_TESTS;
+        return c;
+    }
+    // edges [first, first + cnt) of run k
+    __device__ inline void run(const Lds &F, int si, int k, int32_t first, int32_t cnt) {
+        constexpr RunLists ids = run_list_ids(VAR);
+        const int i2 = (int)(ids.l2 >> (3 * k)) & 7, i3 = (int)(ids.l3 >> (3 * k)) & 7;
+        const Span l2{F.s[i2][si], F.n[i2][si], 0, 0}, l3{F.s[i3][si], F.n[i3][si], 0, 0};
+        triad_chunk<INST>(o, ts, F.s[k][si] + first, cnt, l2, l3, F.slot[si], k, acc, ovf);
+    }
+    __device__ inline void flat(const Lds &F, int si, int64_t r) {
+        for (uint32_t live = F.live[si]; live; live &= live - 1) {
+            const int k = __ffs((int)live) - 1;
+            const int32_t n1 = F.n[k][si], c = (n1 + (int32_t)PIECE_TESTS - 1) / (int32_t)PIECE_TESTS;
+            if (r < c) {
+                const int32_t first = (int32_t)(r * PIECE_TESTS);
+                run(F, si, k, first, n1 - first < (int32_t)PIECE_TESTS ? n1 - first : (int32_t)PIECE_TESTS);
+                return;
+            }
+            r -= c;
+        }
+    }
+    __device__ inline void piece(const Lds &F, int si, int64_t r, int32_t cnt) {
+        for (uint32_t live = F.live[si]; live; live &= live - 1) {
+            const int k = __ffs((int)live) - 1;
+            const int32_t n1 = F.n[k][si];
+            if (r >= n1) {
+                r -= n1;
+                continue;
+            }
+            const int32_t m = cnt < n1 - (int32_t)r ? cnt : n1 - (int32_t)r;
+            run(F, si, k, (int32_t)r, m);
+            cnt -= m;
+            if (cnt == 0) return;
+            r = 0;
+        }
     }
     // every lane of the wavefront calls this once, at the end
     __device__ inline void finish() {

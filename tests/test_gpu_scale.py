@@ -208,3 +208,63 @@ def test_grouping_keys_and_core_phase_sizes(n, m, tmax, loops, shuffle):
     assert np.array_equal(G.core_numbers(), o.core_numbers())
     assert np.array_equal(G.ranks(), o.degeneracy_rank())
     o.close()
+
+
+@pytest.mark.parametrize("scale", [1, 1 << 30])
+def test_list_lengths_at_search_steps(scale):
+    """Triangles whose six lists take every pair of lengths around the steps of the
+    searches (1 to 4 entries, 5, 16, 17, ...), the pieces of a run and the light limit,
+    with many equal timestamps; in 32 bits, where lists of one or two entries come from
+    the records, and beyond.  Direct and smaller-side counts, temporal triangles per
+    edge and a plan (one query that a count of 0 meets, jobs that none does) against
+    the oracle."""
+    rng = np.random.default_rng(scale & 1023)
+    lens = [0, 1, 2, 3, 4, 5, 7, 8, 9, 16, 17, 20, 21, 63, 64, 65, 130]
+    src, dst, v0 = [], [], 0
+    for x in lens:
+        for y in lens:
+            ends = [(0, 1, x), (1, 0, y), (1, 2, int(rng.choice(lens))), (2, 1, x), (0, 2, y),
+                    (2, 0, int(rng.choice(lens)))]
+            for a, b, k in ends:
+                src += [v0 + a] * k
+                dst += [v0 + b] * k
+            v0 += 3
+    p = rng.permutation(len(src))
+    src, dst = np.asarray(src, np.int32)[p], np.asarray(dst, np.int32)[p]
+    t = np.sort(rng.integers(0, 400, size=src.size)).astype(np.int64) * scale
+    o = Oracle(v0, src, dst, t)
+    G = folty.Graph(v0, src, dst, t).build()
+    for v in range(8):
+        for delta in (0, 3 * scale, 60 * scale, 400 * scale):
+            say("list lengths", scale, v, delta // scale)
+            want = o.query(delta, 1, 1, v)
+            assert_same(G.query(delta, (1, 1), v), want)
+            assert_same(G.query(delta, (1, 1), v, smaller_side=True), want)
+        got = G.triad_query(20 * scale, v, triples=False, edge_instances=True).edge_instances()
+        assert np.array_equal(got, o.triad_instances(20 * scale, v))
+    qs = [dict(delta=d * scale, theta=th, variant=v, exclude_other=x)
+          for v, th, x in ((0, (1, 1), False), (3, (1, 2), True), (5, (0, 1), False), (6, (1, 2), False))
+          for d in (2, 50)]
+    plan = folty.Plan([G], [(0, q) for q in qs])
+    for _ in range(3):
+        for q, r in zip(qs, plan.run()):
+            say("list lengths: plan", q)
+            assert_same(r, o.query(q["delta"], *q["theta"], q["variant"], exclude_other=q["exclude_other"]))
+    o.close()
+
+
+@pytest.mark.parametrize("pairs", [1024, 1025, 262_144, 262_145, 1_572_864, 1_572_865])
+def test_pair_sorts_at_their_size_limits(pairs):
+    """As many solution pairs as each kind of sort takes at most and one more: with
+    theta = 0 every directed pair is one, and they come sorted with their edges."""
+    rng = np.random.default_rng(pairs)
+    n = 40_000
+    key = np.unique(rng.integers(0, n * n, size=pairs + pairs // 4 + 64))
+    key = key[key // n != key % n]
+    key = np.sort(rng.permutation(key)[:pairs])
+    assert key.size == pairs
+    p = rng.permutation(np.concatenate([key, key[: pairs // 3]]))
+    say("pair sorts", pairs)
+    r = folty.Graph(n, (p // n).astype(np.int32), (p % n).astype(np.int32), np.arange(p.size)).build().query(5, (0, 1), 0)
+    assert np.array_equal(r.pair_u, key // n) and np.array_equal(r.pair_v, key % n)
+    assert np.array_equal(r.n_cert, 1 + (np.arange(pairs) < pairs // 3))
