@@ -141,8 +141,8 @@ typedef struct {
 
 /* Query flag: test triangles once.  Without it the filter tests the two known
  * edges of a closing probe first and the whole triangle after (two passes),
- * unless an earlier query on the graph kept at least one triangle in 64 (a wide
- * window): then queries of at least an eighth of that window look every probe up
+ * unless an earlier query on the graph kept at least one triangle in 12 (a wide
+ * window): then queries of at least half of that window look every probe up
  * and test whole triangles only, by themselves.  Results are identical either
  * way.  The graph's triangles are counted first if they have not been.  Single and
  * vertex queries (plans always use two passes; exists-exists-exists queries
@@ -234,8 +234,8 @@ int folty_build_index(folty_graph *g, const folty_build_opts *opts);
  * that can have a run to chunks in the workspace (12 bytes each).  When the chunks
  * do not suffice (they start at an eighth of what every triangle would take, at
  * least 50 MB) they grow to what the pass needed and it is repeated.  After a
- * query that kept at least one triangle in 64, later queries on the graph whose
- * delta is at least an eighth of that query's test whole triangles only
+ * query that kept at least one triangle in 12, later queries on the graph whose
+ * delta is at least half of that query's test whole triangles only
  * (FOLTY_QUERY_ONE_PASS asks for that on any query).  The choice depends only on
  * the graph and the queries run before.
  *

@@ -283,7 +283,7 @@ struct Index {
     // T are final, so a reader that loads it (acquire) sees them
     std::atomic<bool> tri_base_ready{false};
     // single queries of delta >= this filter in one pass (INT64_MAX: none, until
-    // a query kept one triangle in 64)
+    // a query kept one triangle in 12)
     std::atomic<int64_t> one_pass_from{INT64_MAX};
     bool one_pass_at(int64_t delta) const {
         const int64_t from = one_pass_from.load(std::memory_order_relaxed);

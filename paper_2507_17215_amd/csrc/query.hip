@@ -520,20 +520,21 @@ CandBuf filter_triangles(Index &ix, int variant, int64_t dmax, Workspace &ws, hi
 // After the query's scalars are on the host: the number of triangles on the first
 // query, the filter's passes, and the switch to one pass for later queries.
 // By default the filter tests a probe's two known edges first and the whole
-// triangle after (two passes).  When a window keeps at least one triangle in 64,
-// the first test drops little, and later queries of about that window or wider
-// (from an eighth of it) look every probe up and test triangles once.  70M edges,
-// filter time with two passes and one: 1 hour 1.3 and 3.8 ms (none kept), 4 weeks
-// 3.3 and 3.8 ms (1 in 5,000), 1 year 4.6 and 4.4 ms (1 in 36); 10M edges of the
-// medium graph, 4 weeks 0.25 and 0.24 ms (1 in 190), 1 year 0.34 and 0.32 ms.
+// triangle after (two passes).  When a window keeps at least one triangle in 12,
+// the first test drops too little, and later queries of about that window or wider
+// (from half of it) look every probe up and test triangles once.  Filter with two
+// passes and one: 70M edges, 1 hour 1.28 and 3.45 ms (none kept), 1 year 3.41 and
+// 3.95 ms (0.028 kept); 10M edges of the medium graph, 4 weeks 0.18 and 0.25 ms
+// (0.005), 13 weeks 0.26 and 0.28 ms (0.05), half a year 0.34 and 0.29 ms (0.15), 1
+// year 0.40 and 0.31 ms (0.30); 10M uniform edges 0.10 and 0.07 ms (0.34-0.44).
 // The rule depends only on the graph and the queries, never on timing.
 void after_filter(Index &ix, Workspace &ws, int64_t delta, bool one_pass) {
     if (ix.T.load() < 0) ix.T = region_sum(ws, REGION_HITS);
     const int64_t kept = region_sum(ws, REGION_KEPT);
     ws.filter_passes = one_pass ? 1 : 2;
-    if (!one_pass && kept > 0 && 64 * kept >= ix.T.load() &&
-        delta / 8 < ix.one_pass_from.load(std::memory_order_relaxed))
-        ix.one_pass_from.store(delta / 8, std::memory_order_relaxed);
+    if (!one_pass && kept > 0 && 12 * kept >= ix.T.load() &&
+        delta / 2 < ix.one_pass_from.load(std::memory_order_relaxed))
+        ix.one_pass_from.store(delta / 2, std::memory_order_relaxed);
 }
 
 bool use_one_pass(Graph *g, const folty_query &q) {
