@@ -196,7 +196,9 @@ __global__ __launch_bounds__(BLK) void k_plan_light(CandBuf B, const GroupDev *_
                     const JobTests R(J);
                     spread_units(
                         F, incl, np && !listed,
-                        [&](int si, int64_t r) { staged_tests<false, true>(F, R.ids, si, r, 1, R.ts, nullptr, R.op); },
+                        [&](int si, int64_t r, bool run) {
+                            if (run) staged_tests<false, true>(F, R.ids, si, r, 1, R.ts, nullptr, R.op);
+                        },
                         [&](int si) { return __shfl(wk, si); });
                     wave_sync(); // the next job or chunk rewrites the LDS
                 }
@@ -243,23 +245,23 @@ __device__ inline QueryDev next_query(const QueryDev *__restrict__ qs, int32_t q
 }
 
 // Certificates of one query over a wavefront of edges: per run of equal
-// (static edge, direction) keys, the number of certifying edges.  The tail lane
-// of each run with certificates appends one record (query, a, b) -> count.
+// (static edge, direction) keys, the number of certifying edges.  The last
+// certifying lane of each run appends one record (query, a, b) -> count.
 __device__ inline void wave_run_records(int64_t key, bool in, bool cert, uint64_t rec_key,
                                         uint64_t *__restrict__ rk, uint32_t *__restrict__ rv,
                                         int32_t *__restrict__ nrec, int64_t cap) {
     const int lane = lane_id();
     const int64_t prev = __shfl_up(key, 1);
-    const int64_t next = __shfl_down(key, 1);
     const bool head = lane == 0 || prev != key;
-    const bool tail = lane == 63 || next != key;
-    const unsigned long long heads = __ballot(head && in);
+    const unsigned long long heads = __ballot(head);
     const unsigned long long flags = __ballot(cert);
     int c = 0;
-    if (in && tail) {
+    if (in && cert) {
         const unsigned long long upto = lane == 63 ? ~0ull : ((2ull << lane) - 1ull);
         const int start = 63 - __clzll((long long)(heads & upto));
-        c = __popcll(flags & upto & ~((1ull << start) - 1ull));
+        const unsigned long long later = heads & ~upto; // the next runs' heads
+        const unsigned long long run = (later ? (later & -later) - 1ull : ~0ull) & ~((1ull << start) - 1ull);
+        if ((flags & run & ~upto) == 0ull) c = __popcll(flags & run);
     }
     const int32_t slot = wave_append(nrec, c > 0);
     if (slot >= 0 && slot < cap) {
@@ -296,10 +298,13 @@ __global__ __launch_bounds__(BLK) void k_job_threshold(const JobDev *__restrict_
         int32_t s = 0, dir = 0, du = 0, da = 0, tc = 0;
         uint64_t ab = 0;
         const int32_t *tcnt = global_ptr(J.tcnt);
+        const bool touched = (tm >> lane) & 1ull;
         if (in) {
-            const int32_t *slo = global_ptr(J.slo), *shi = global_ptr(J.shi), *deg = global_ptr(J.deg);
             s = global_ptr(J.sid)[e];
             dir = e >= global_ptr(J.smid)[s] ? 1 : 0;
+        }
+        if (in && (touched || !J.zero_never)) { // the others certify nothing
+            const int32_t *slo = global_ptr(J.slo), *shi = global_ptr(J.shi), *deg = global_ptr(J.deg);
             const int32_t a = dir ? shi[s] : slo[s];
             const int32_t b = dir ? slo[s] : shi[s];
             du = deg[b];
@@ -310,7 +315,6 @@ __global__ __launch_bounds__(BLK) void k_job_threshold(const JobDev *__restrict_
         const int64_t run = in ? 2 * (int64_t)s + dir : -1;
         // this wavefront's tile: block c holds levels 4c..4c+3 of its 64 edges.
         // Edges no test added to hold zeros and are not read.
-        const bool touched = (tm >> lane) & 1ull;
         uint4 *hrow = reinterpret_cast<uint4 *>(global_ptr(J.hist) + hist_at(tile << 6, 0, J.nls)) + lane;
         uint32_t acc = 0;
         int32_t qi = J.q0;
@@ -333,7 +337,7 @@ __global__ __launch_bounds__(BLK) void k_job_threshold(const JobDev *__restrict_
                                                   : Q.universe == FOLTY_UNIVERSE_SRC ? da
                                                                                      : tc) -
                                        (uint32_t)Q.excl;
-                    const bool cert = in && (uint64_t)acc * Q.den >= (uint64_t)Q.num * U;
+                    const bool cert = in && (touched || !J.zero_never) && (uint64_t)acc * Q.den >= (uint64_t)Q.num * U;
                     if (__ballot(cert))
                         wave_run_records(run, in, cert, ((uint64_t)Q.q << (2 * nbits)) | ab, rk, rv, nrec, cap);
                     Q = next_query(qs, ++qi, J.q1);

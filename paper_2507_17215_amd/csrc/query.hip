@@ -221,11 +221,11 @@ __global__ __launch_bounds__(BLK) void k_threshold(ThreshArgs A) {
         if (in) {
             int32_t s = A.sid[k];
             int dir = k >= A.smid[s] ? 1 : 0;
-            int32_t a = dir ? A.shi[s] : A.slo[s];
-            int32_t b = dir ? A.slo[s] : A.shi[s];
             if (A.any) {
                 cert = cnt >= 1u;
-            } else {
+            } else if (cnt != 0u || !A.zero_never) {
+                int32_t a = dir ? A.shi[s] : A.slo[s];
+                int32_t b = dir ? A.slo[s] : A.shi[s];
                 int64_t U;
                 if (A.universe == FOLTY_UNIVERSE_DST) U = (int64_t)A.deg[b] - A.excl;
                 else if (A.universe == FOLTY_UNIVERSE_SRC) U = (int64_t)A.deg[a] - A.excl;

@@ -376,7 +376,10 @@ struct PoolOp {
     __device__ inline int64_t most() const { return dmax; }
     __device__ inline void hit(int32_t e, int64_t win) const {
         const int32_t a = lower_bound_from(lv, 0, nl, win); // win <= dmax, the last level
-        if (atomicAdd(&hist[hist_at(e, a, nls)], 1u) == 0u) atomicOr(&tmask[e >> 6], 1ull << (e & 63));
+        // two atomics that nothing waits for, rather than one that returns whether
+        // the other is needed
+        atomicAdd(&hist[hist_at(e, a, nls)], 1u);
+        atomicOr(&tmask[e >> 6], 1ull << (e & 63));
     }
 };
 
@@ -1240,11 +1243,11 @@ template <int VAR, class Op, bool SS> struct CountRunner {
     __device__ inline int64_t work(const TriLists &L) const { return tri_work<VAR, SS>(L, dq); }
     __device__ inline int64_t units(const Lds &, int, int64_t tests) const { return tests; }
     __device__ inline const EdgeRec *ends() const { return inl ? rec : nullptr; }
-    __device__ inline void flat(const Lds &F, int si, int64_t r) {
-        staged_tests<SS, true>(F, run_list_ids(VAR), si, r, 1, ts, ends(), op);
+    __device__ inline void flat(Lds &F, int si, int64_t r, bool on) {
+        if (on) staged_tests<SS, true>(F, run_list_ids(VAR), si, r, 1, ts, ends(), op);
     }
-    __device__ inline void piece(const Lds &F, int si, int64_t r, int32_t cnt) {
-        staged_tests<SS, false>(F, run_list_ids(VAR), si, r, cnt, ts, ends(), op);
+    __device__ inline void piece(Lds &F, int si, int64_t r, int32_t cnt, bool on) {
+        if (on) staged_tests<SS, false>(F, run_list_ids(VAR), si, r, cnt, ts, ends(), op);
     }
     __device__ inline void finish() {}
 };
@@ -1273,8 +1276,19 @@ __device__ inline bool defer_heavy(int64_t slot, int64_t np, Heavy *__restrict__
     return true;
 }
 
-// The staged triangles' work over the lanes: flat(si, r) is item r of triangle
-// si, this lane's triangle has `units` items (at most LIGHT_TESTS); triangles
+// the first of 64 ascending prefix sums that is above x (63 if none)
+__device__ inline int staged_owner(const int32_t *incl, int32_t x) {
+    int a = 0, b = 63;
+    while (a < b) {
+        const int mid = (a + b) >> 1;
+        if (incl[mid] > x) b = mid;
+        else a = mid + 1;
+    }
+    return a;
+}
+
+// The staged triangles' work over the lanes: flat(si, r, on) is item r of triangle
+// si (called by all lanes together, with on false past the last item), this lane's triangle has `units` items (at most LIGHT_TESTS); triangles
 // with `own` set (heavy, not listed) have alone(si) items each and go one after
 // another.
 template <class Lds, class Flat, class Alone>
@@ -1284,20 +1298,16 @@ __device__ inline void spread_units(Lds &F, int32_t incl, bool own, const Flat &
     unsigned long long left = __ballot(own);
     int src = -1;
     for (;;) {
-        for (int64_t t = lane; t < total; t += 64) {
+        for (int64_t t0 = 0; t0 < total; t0 += 64) {
+            const int64_t t = t0 + lane;
             int si = src;
             int64_t r = t;
-            if (src < 0) { // the triangle whose items hold t: the first with incl > t
-                int a = 0, b = 63;
-                while (a < b) {
-                    const int mid = (a + b) >> 1;
-                    if (F.incl[mid] > (int32_t)t) b = mid;
-                    else a = mid + 1;
-                }
+            if (src < 0) { // the triangle whose items hold t
+                const int a = staged_owner(F.incl, (int32_t)t);
                 si = a;
                 r = t - (a ? F.incl[a - 1] : 0);
             }
-            flat(si, r);
+            flat(si, r, t < total);
         }
         if (!left) break;
         src = __builtin_ctzll(left);
@@ -1394,7 +1404,7 @@ __global__ __launch_bounds__(BLK) void k_tests_light(CandBuf B, R runner, Heavy 
             wave_sync();
             spread_units(
                 F, incl, np && !listed,
-                [&](int si, int64_t r) { runner.flat(F, si, r); },
+                [&](int si, int64_t r, bool on) { runner.flat(F, si, r, on); },
                 [&](int si) { return runner.units(F, si, __shfl(wk, si)); }); // si: the same in every lane
             wave_sync(); // the LDS is rewritten by the next triangles
         }
@@ -1442,15 +1452,17 @@ __global__ __launch_bounds__(BLK) void k_tests_pieces(const Heavy *__restrict__ 
     const int64_t ne = (int64_t)(c >> HEAVY_SHIFT) < cap ? (int64_t)(c >> HEAVY_SHIFT) : cap;
     const int64_t np = (int64_t)(c & PIECE_MASK);
     if (ne > 0) {
-        for (int64_t p = (int64_t)blockIdx.x * BLK + threadIdx.x; p < np; p += (int64_t)gridDim.x * BLK) {
-            const Heavy h = heavy_of(heavy, ne, p);
+        for (int64_t p0 = (int64_t)blockIdx.x * BLK + 64 * wave_id(); p0 < np; p0 += (int64_t)gridDim.x * BLK) {
+            const int64_t p = p0 + lane;
+            const bool on = p < np;
+            const Heavy h = heavy_of(heavy, ne, on ? p : p0);
             int32_t e[3];
             for (int k = 0; k < 3; k++) e[k] = runner.sv[3 * h.slot + k];
             const TriLists T = load_lists(runner.rec, e[0], e[1], e[2]);
             stage_runs(F, lane, T, e, runner.live(T), h.slot); // this lane's own column
             // pieces past the last listed triangle's belong to ones that ran
             // where they were found: they lie past every run, nothing is tested
-            runner.piece(F, lane, (p - h.first) * PIECE_TESTS, PIECE_TESTS);
+            runner.piece(F, lane, (p - h.first) * PIECE_TESTS, PIECE_TESTS, on);
         }
     }
     runner.finish();

@@ -31,12 +31,16 @@ namespace {
 __device__ inline int32_t past_window(const int64_t *__restrict__ L, int32_t from, int32_t n, int64_t t, int64_t d) {
     if (from >= n || L[from] - t > d) return from;
     int32_t a = from + 1, b = n;
-    while (a < b) {
-        int32_t mid = (a + b) >> 1;
-        if (L[mid] - t <= d) a = mid + 1;
-        else b = mid;
+    while (a < b) { // four entries per step, as in lower_bound
+        const int32_t q = probe_step(b - a);
+        const Probe P = probe(L, a, b);
+        const int c = (P.x[0] - t <= d) + (a + q < b && P.x[1] - t <= d) + (a + 2 * q < b && P.x[2] - t <= d) +
+                      (a + 3 * q < b && P.x[3] - t <= d);
+        if (c == 0) return a;
+        if (c < 4 && a + c * q < b) b = a + c * q;
+        a += (c - 1) * q + 1;
     }
-    return a;
+    return b;
 }
 
 struct TriadOut {
@@ -46,70 +50,113 @@ struct TriadOut {
     const int32_t *perm;           // input position of each sorted edge (with inst)
 };
 
-// edges [l1s, l1s + cnt) of one run against its lists (L2, L3)
-template <bool INST>
-__device__ inline void triad_chunk(const TriadOut &o, const int64_t *__restrict__ ts, int32_t l1s, int32_t cnt,
-                                   const Span &l2, const Span &l3, int64_t slot, int run, unsigned long long &acc,
-                                   bool &ovf) {
-    const int64_t *L2 = ts + l2.s, *L3 = ts + l3.s;
-    const int32_t n2 = l2.n, n3 = l3.n;
-    const int64_t d = o.delta;
-    bool any = false;
-    if (!INST) {
-        int32_t c2 = 0, c3 = 0;
-        for (int32_t q = 0; q < cnt; q++) {
-            const int64_t t = ts[l1s + q];
-            c2 = lower_bound_from(L2, c2, n2, t);
-            if (c2 == n2) break; // later edges are no earlier: no t2 for them either
-            const int64_t t2 = L2[c2];
-            if (t2 - t > d) continue;
-            c3 = lower_bound_from(L3, c3, n3, t2);
-            if (c3 == n3) break;
-            if (L3[c3] - t <= d) {
-                any = true;
-                break;
-            }
+// LDS of a wavefront: its staged triangles, and the ranges that its lanes sum together
+struct TriadLds : RunLds<false, true> {
+    int32_t cum[64];            // entries of the lanes' ranges up to this one
+    int32_t j0[64];             // first entry of the range, in ts
+    int32_t l3[64], n3[64];     // its L3
+    unsigned long long sum[64];
+};
+
+// Sum over entries j in [a, b) of L2 of f(j) = entries of L3 before L2[j], for each
+// lane's own lists and range (all lanes together; a lane without a range passes
+// a >= b).  f0: a position that no f(j) lies before.  A range's entries go one
+// after another with a moving cursor when the lanes' ranges are about as long;
+// otherwise all lanes' entries are spread over the wavefront, each with a search of
+// its own: a window holds a few entries mostly and hundreds at times, and the
+// wavefront would wait for that one lane.
+__device__ inline unsigned long long range_sum(TriadLds &F, const int64_t *__restrict__ ts, int32_t l2s, int32_t l3s,
+                                               int32_t n3, int32_t a, int32_t b, int32_t &f0) {
+    const int lane = lane_id();
+    const int32_t len = b > a ? b - a : 0;
+    const int32_t incl = wave_scan(len);
+    const int32_t total = __builtin_amdgcn_readlane(incl, 63);
+    if (!__ballot(len > 0)) return 0;
+    // (the prefix sums of ranges below 2^24 fit 32 bits)
+    if (__ballot(len >= 1 << 24) || !__ballot(len > 4 + 4 * (total >> 6))) {
+        unsigned long long s = 0;
+        for (int32_t j = a; j < b; j++) {
+            f0 = lower_bound_from(ts + l3s, f0, n3, ts[l2s + j]);
+            s += (unsigned)f0;
         }
-    } else {
-        int32_t lo = lower_bound_from(L2, 0, n2, ts[l1s]);
-        int32_t hi = lo, flo = 0, fhi = 0, h3 = 0;
-        unsigned long long Flo = 0, Fhi = 0; // sums of f over L2[lo0, lo) and L2[lo0, hi)
-        for (int32_t q = 0; q < cnt; q++) {
-            const int32_t e = l1s + q;
-            const int64_t t = ts[e];
-            while (hi < n2 && L2[hi] - t <= d) {
-                fhi = lower_bound_from(L3, fhi, n3, L2[hi]);
-                Fhi += (unsigned)fhi;
-                hi++;
-            }
-            while (lo < hi && L2[lo] < t) {
-                flo = lower_bound_from(L3, flo, n3, L2[lo]);
-                Flo += (unsigned)flo;
-                lo++;
-            }
-            if (lo == hi) {
-                if (lo == n2) break; // no t2 at or after t for this or any later edge
-                continue;
-            }
-            h3 = past_window(L3, h3, n3, t, d);
-            const unsigned long long pairs = (unsigned long long)(hi - lo) * (unsigned)h3 - (Fhi - Flo);
+        return s;
+    }
+    wave_sync();
+    F.cum[lane] = incl;
+    F.j0[lane] = l2s + a;
+    F.l3[lane] = l3s;
+    F.n3[lane] = n3;
+    F.sum[lane] = 0;
+    wave_sync();
+    for (int32_t t = lane; t < total; t += 64) {
+        const int o = staged_owner(F.cum, t);
+        const int64_t x = ts[F.j0[o] + (t - (o ? F.cum[o - 1] : 0))];
+        atomicAdd(&F.sum[o], (unsigned long long)(unsigned)lower_bound_from(ts + F.l3[o], 0, F.n3[o], x));
+    }
+    wave_sync();
+    return F.sum[lane];
+}
+
+// Temporal triangles of edges [l1s, l1s + cnt) of each lane's run (all lanes
+// together; cnt = 0: none) against its lists (L2, L3).
+__device__ inline void triad_instances(TriadLds &F, const TriadOut &o, const int64_t *__restrict__ ts, int32_t l1s,
+                                       int32_t cnt, const Span &l2, const Span &l3, int64_t slot, int run,
+                                       unsigned long long &acc, bool &ovf) {
+    const int64_t *L2 = ts + l2.s, *L3 = ts + l3.s;
+    const int64_t d = o.delta;
+    // the window's entries of L2, [lo, hi), and the sum of f over them
+    int32_t lo = 0, hi = 0, fin = 0, fout = 0, h3 = 0;
+    unsigned long long S = 0;
+    bool any = false;
+    for (int32_t q = 0; __ballot(q < cnt); q++) {
+        int32_t nlo = lo, nhi = hi;
+        int64_t t = 0;
+        if (q < cnt) {
+            t = ts[l1s + q];
+            nlo = lower_bound_from(L2, lo, l2.n, t);
+            nhi = past_window(L2, nlo > hi ? nlo : hi, l2.n, t, d);
+        }
+        S += range_sum(F, ts, l2.s, l3.s, l3.n, nlo > hi ? nlo : hi, nhi, fin);
+        if (__ballot(nlo < nhi)) S -= range_sum(F, ts, l2.s, l3.s, l3.n, lo, nlo < hi ? nlo : hi, fout);
+        lo = nlo;
+        hi = nhi;
+        if (lo == hi) {
+            S = 0;
+            if (lo == l2.n) cnt = 0; // no t2 at or after t for this or any later edge
+        } else if (q < cnt) {
+            h3 = past_window(L3, h3, l3.n, t, d);
+            const unsigned long long pairs = (unsigned long long)(hi - lo) * (unsigned)h3 - S;
             if (pairs) {
                 any = true;
-                if (o.inst) atomicAdd(&o.inst[o.perm[e]], pairs);
-                const unsigned long long s = acc + pairs;
-                ovf |= s < acc;
-                acc = s;
+                if (o.inst) atomicAdd(&o.inst[o.perm[l1s + q]], pairs);
+                const unsigned long long x = acc + pairs;
+                ovf |= x < acc;
+                acc = x;
             }
         }
     }
     if (any) atomicOr(&o.flag[slot >> 2], 1u << (((int)(slot & 3) << 3) + run));
 }
 
+// Does any of edges [l1s, l1s + cnt) close a triangle?
+__device__ inline void triad_any(const TriadOut &o, const int64_t *__restrict__ ts, int32_t l1s, int32_t cnt,
+                                 const Span &l2, const Span &l3, int64_t slot, int run) {
+    const List a{ts + l2.s, l2.n, nullptr}, b{ts + l3.s, l3.n, nullptr};
+    int32_t c2 = 0, c3 = 0;
+    for (int32_t q = 0; q < cnt; q++) {
+        const Probe p2 = probe(a.p, c2, a.n), p3 = probe(b.p, c3, b.n);
+        int64_t win;
+        const TestEnd x = window_test(a, b, c2, c3, p2, p3, ts[l1s + q], o.delta, win);
+        if (x == TEST_HIT) atomicOr(&o.flag[slot >> 2], 1u << (((int)(slot & 3) << 3) + run));
+        if (x != TEST_MISS) return;
+    }
+}
+
 // The triangles' runs, scheduled as the count's (k_tests_light, a few
 // tests of a run per lane; then the pieces of triangles with many tests); total[0] += temporal triangles,
 // total[1] = 1 on a 64-bit overflow.
 template <int VAR, bool INST> struct TriadRunner {
-    using Lds = RunLds<false, true>;
+    using Lds = TriadLds;
     uint32_t dq;
     const int64_t *ts;
     TriadOut o;
@@ -129,38 +176,48 @@ template <int VAR, bool INST> struct TriadRunner {
             c += (F.n[__ffs((int)live) - 1][si] + (int32_t)PIECE_TESTS - 1) / (int32_t)PIECE_TESTS;
         return c;
     }
-    // edges [first, first + cnt) of run k
-    __device__ inline void run(const Lds &F, int si, int k, int32_t first, int32_t cnt) {
+    // edges [first, first + cnt) of each lane's run k (cnt = 0: none)
+    __device__ inline void run(Lds &F, int si, int k, int32_t first, int32_t cnt) {
         constexpr RunLists ids = run_list_ids(VAR);
         const int i2 = (int)(ids.l2 >> (3 * k)) & 7, i3 = (int)(ids.l3 >> (3 * k)) & 7;
         const Span l2{F.s[i2][si], F.n[i2][si], 0, 0}, l3{F.s[i3][si], F.n[i3][si], 0, 0};
-        triad_chunk<INST>(o, ts, F.s[k][si] + first, cnt, l2, l3, F.slot[si], k, acc, ovf);
+        if constexpr (INST) triad_instances(F, o, ts, F.s[k][si] + first, cnt, l2, l3, F.slot[si], k, acc, ovf);
+        else triad_any(o, ts, F.s[k][si] + first, cnt, l2, l3, F.slot[si], k);
     }
-    __device__ inline void flat(const Lds &F, int si, int64_t r) {
-        for (uint32_t live = F.live[si]; live; live &= live - 1) {
-            const int k = __ffs((int)live) - 1;
+    __device__ inline void flat(Lds &F, int si, int64_t r, bool on) {
+        int k = 0;
+        int32_t first = 0, cnt = 0;
+        for (uint32_t live = on ? F.live[si] : 0u; live; live &= live - 1) {
+            k = __ffs((int)live) - 1;
             const int32_t n1 = F.n[k][si], c = (n1 + (int32_t)PIECE_TESTS - 1) / (int32_t)PIECE_TESTS;
             if (r < c) {
-                const int32_t first = (int32_t)(r * PIECE_TESTS);
-                run(F, si, k, first, n1 - first < (int32_t)PIECE_TESTS ? n1 - first : (int32_t)PIECE_TESTS);
-                return;
+                first = (int32_t)(r * PIECE_TESTS);
+                cnt = n1 - first < (int32_t)PIECE_TESTS ? n1 - first : (int32_t)PIECE_TESTS;
+                break;
             }
             r -= c;
         }
+        run(F, si, k, first, cnt);
     }
-    __device__ inline void piece(const Lds &F, int si, int64_t r, int32_t cnt) {
-        for (uint32_t live = F.live[si]; live; live &= live - 1) {
-            const int k = __ffs((int)live) - 1;
-            const int32_t n1 = F.n[k][si];
-            if (r >= n1) {
-                r -= n1;
-                continue;
+    __device__ inline void piece(Lds &F, int si, int64_t r, int32_t cnt, bool on) {
+        uint32_t live = on ? F.live[si] : 0u;
+        while (__ballot(live != 0u && cnt > 0)) { // each lane's next run with tests of the piece
+            int k = 0;
+            int32_t first = 0, m = 0;
+            while (live && cnt > 0 && m == 0) {
+                k = __ffs((int)live) - 1;
+                live &= live - 1;
+                const int32_t n1 = F.n[k][si];
+                if (r >= n1) {
+                    r -= n1;
+                } else {
+                    first = (int32_t)r;
+                    m = cnt < n1 - first ? cnt : n1 - first;
+                    cnt -= m;
+                    r = 0;
+                }
             }
-            const int32_t m = cnt < n1 - (int32_t)r ? cnt : n1 - (int32_t)r;
-            run(F, si, k, (int32_t)r, m);
-            cnt -= m;
-            if (cnt == 0) return;
-            r = 0;
+            run(F, si, k, first, m);
         }
     }
     // every lane of the wavefront calls this once, at the end
