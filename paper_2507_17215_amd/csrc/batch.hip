@@ -56,7 +56,7 @@ struct JobDev {
     int32_t zero_never;  // no query of the job is met by a count of 0 (theta > 0 and |U| >= 1 for every edge)
 };
 
-// a plan's queries in job order, each job's by level (one scalar load each)
+// a plan's queries in job order, each job's by level
 struct alignas(32) QueryDev {
     int32_t level; // index of the query's delta among its job's levels
     uint32_t num, den;
@@ -194,10 +194,13 @@ __global__ __launch_bounds__(BLK) void k_plan_light(CandBuf B, const GroupDev *_
                     F.live[lane] = live;
                     wave_sync();
                     const JobTests R(J);
-                    spread_units(
-                        F, incl, np && !listed,
-                        [&](int si, int64_t r, bool run) {
-                            if (run) staged_tests<false, true>(F, R.ids, si, r, 1, R.ts, nullptr, R.op);
+                    spread_units<true>(
+                        F, incl, np && !listed, [&](int, int64_t, bool) {},
+                        [&](int s0, int64_t r0, int s1, int64_t r1, bool two) {
+                            const OneTest<false> a(F, R.ids, s0, r0, R.ts, nullptr);
+                            const OneTest<false> b(F, R.ids, two ? s1 : s0, two ? r1 : r0, R.ts, nullptr);
+                            a.run(R.op);
+                            if (two) b.run(R.op);
                         },
                         [&](int si) { return __shfl(wk, si); });
                     wave_sync(); // the next job or chunk rewrites the LDS
@@ -234,15 +237,33 @@ __global__ __launch_bounds__(BLK) void k_plan_pieces(CandBuf B, const JobDev *__
     }
 }
 
-// the plan's query at position qi, or one with no level past the job's last
-// (qi is the same in every lane; saying so keeps the load scalar, all eight
-// words at once)
-__device__ inline QueryDev next_query(const QueryDev *__restrict__ qs, int32_t qi, int32_t q1) {
-    QueryDev Q{};
-    if (qi < q1) Q = qs[__builtin_amdgcn_readfirstlane(qi)];
-    else Q.level = INT32_MAX;
-    return Q;
-}
+// A job's queries, a lane each, 64 at a time: a wavefront steps through them without
+// a read per query.
+struct QueryLanes {
+    QueryDev q;      // this lane's
+    int32_t first;   // position of lane 0's
+    int32_t end;     // of the job's last + 1
+    const QueryDev *__restrict__ qs;
+    __device__ void load(int32_t qi) { // the same qi in every lane
+        first = qi;
+        if (qi + lane_id() < end) q = qs[qi + lane_id()];
+    }
+    // the query at qi (in every lane), or one with no level past the job's last
+    __device__ QueryDev at(int32_t qi) {
+        QueryDev r{};
+        r.level = INT32_MAX;
+        if (qi >= end) return r;
+        if (qi < first || qi - first >= 64) load(qi);
+        const int i = __builtin_amdgcn_readfirstlane(qi - first);
+        r.level = __builtin_amdgcn_readlane(q.level, i);
+        r.num = (uint32_t)__builtin_amdgcn_readlane((int32_t)q.num, i);
+        r.den = (uint32_t)__builtin_amdgcn_readlane((int32_t)q.den, i);
+        r.universe = __builtin_amdgcn_readlane(q.universe, i);
+        r.excl = __builtin_amdgcn_readlane(q.excl, i);
+        r.q = __builtin_amdgcn_readlane(q.q, i);
+        return r;
+    }
+};
 
 // Certificates of one query over a wavefront of edges: per run of equal
 // (static edge, direction) keys, the number of certifying edges.  The last
@@ -275,82 +296,96 @@ __device__ inline void wave_run_records(int64_t key, bool in, bool cert, uint64_
 // load) is summed level by level in a register (count[e] at each delta of the
 // job), and at each level the job's queries of that delta test
 // count * den >= num * |U|.  Certificates are counted per query and emitted as
-// (query, a, b) records, one per run of a wavefront.  Every wavefront lies
-// inside one job (job slices are padded to 64 edges), so the per-query loop and
-// its ballots are uniform.
+// (query, a, b) records, one per run of a tile of 64 edges.  A wavefront takes
+// `tiles` tiles of one job (job slices are padded to that), so the per-query loop
+// and its ballots are uniform.  Most tiles of a plan over a large graph have no
+// edge that a test added to; unless a count of 0 meets some query of the job they
+// are passed over, and one read tells which of a wavefront's they are (64 queries
+// on 10M edges, two jobs: 0.58 ms with every tile read, 0.20 with a wavefront per
+// tile, XTHR now).
 __global__ __launch_bounds__(BLK) void k_job_threshold(const JobDev *__restrict__ jobs, int32_t nj,
                                                        const int64_t *__restrict__ job_w_base, int64_t total_w,
-                                                       const QueryDev *__restrict__ qs, int nbits,
+                                                       int32_t tiles, const QueryDev *__restrict__ qs, int nbits,
                                                        uint64_t *__restrict__ rk, uint32_t *__restrict__ rv,
                                                        int32_t *__restrict__ nrec, int64_t cap) {
     const int lane = lane_id();
-    const int64_t stride = (int64_t)gridDim.x * blockDim.x;
-    for (int64_t x0 = (int64_t)blockIdx.x * blockDim.x + 64 * wave_id(); x0 < total_w; x0 += stride) {
+    const int64_t stride = (int64_t)gridDim.x * BLK * tiles;
+    for (int64_t x0 = ((int64_t)blockIdx.x * WPB + wave_id()) * 64 * tiles; x0 < total_w; x0 += stride) {
         const int32_t j = owner_of(job_w_base, nj, x0);
         const JobDev &J = jobs[j];
-        const int64_t e = x0 - job_w_base[j] + lane;
-        const bool in = e < J.m;
-        const int64_t tile = (x0 - job_w_base[j]) >> 6;
+        const int64_t tile0 = (x0 - job_w_base[j]) >> 6, left = (((int64_t)J.m + 63) >> 6) - tile0;
         unsigned long long *tmask = global_ptr(J.tmask);
-        const unsigned long long tm = tmask[tile];
+        const int32_t nt = left < tiles ? (int32_t)(left < 0 ? 0 : left) : tiles;
+        const unsigned long long word = lane < nt ? tmask[tile0 + lane] : 0ull;
         // edges no test added to certify nothing, and their counters are clear
-        if (tm == 0ull && J.zero_never) continue;
-        int32_t s = 0, dir = 0, du = 0, da = 0, tc = 0;
-        uint64_t ab = 0;
-        const int32_t *tcnt = global_ptr(J.tcnt);
-        const bool touched = (tm >> lane) & 1ull;
-        if (in) {
-            s = global_ptr(J.sid)[e];
-            dir = e >= global_ptr(J.smid)[s] ? 1 : 0;
-        }
-        if (in && (touched || !J.zero_never)) { // the others certify nothing
-            const int32_t *slo = global_ptr(J.slo), *shi = global_ptr(J.shi), *deg = global_ptr(J.deg);
-            const int32_t a = dir ? shi[s] : slo[s];
-            const int32_t b = dir ? slo[s] : shi[s];
-            du = deg[b];
-            da = deg[a];
-            if (tcnt) tc = tcnt[s];
-            ab = ((uint64_t)(uint32_t)a << nbits) | (uint64_t)(uint32_t)b;
-        }
-        const int64_t run = in ? 2 * (int64_t)s + dir : -1;
-        // this wavefront's tile: block c holds levels 4c..4c+3 of its 64 edges.
-        // Edges no test added to hold zeros and are not read.
-        uint4 *hrow = reinterpret_cast<uint4 *>(global_ptr(J.hist) + hist_at(tile << 6, 0, J.nls)) + lane;
-        uint32_t acc = 0;
-        int32_t qi = J.q0;
-        QueryDev Q = next_query(qs, qi, J.q1);
-        const uint4 zero4 = make_uint4(0, 0, 0, 0);
-        uint4 next = touched ? hrow[0] : zero4;
-        for (int32_t l0 = 0; l0 < J.nl; l0 += 4) {
-            const uint4 cur = next;
-            if (touched && l0 + 4 < J.nl) next = hrow[((l0 >> 2) + 1) * 64]; // one block ahead
-            uint32_t hv[4] = {cur.x, cur.y, cur.z, cur.w};
-#pragma unroll
-            for (int jj = 0; jj < 4; jj++) {
-                const int32_t l = l0 + jj;
-                if (l >= J.nl) break;
-                acc += hv[jj];
-                hv[jj] = acc;
-                while (Q.level == l) {
-                    // |U| >= 0: an edge's endpoints have degree >= 1
-                    const uint32_t U = (uint32_t)(Q.universe == FOLTY_UNIVERSE_DST   ? du
-                                                  : Q.universe == FOLTY_UNIVERSE_SRC ? da
-                                                                                     : tc) -
-                                       (uint32_t)Q.excl;
-                    const bool cert = in && (touched || !J.zero_never) && (uint64_t)acc * Q.den >= (uint64_t)Q.num * U;
-                    if (__ballot(cert))
-                        wave_run_records(run, in, cert, ((uint64_t)Q.q << (2 * nbits)) | ab, rk, rv, nrec, cap);
-                    Q = next_query(qs, ++qi, J.q1);
+        unsigned long long todo = J.zero_never ? __ballot(word != 0ull) : (1ull << nt) - 1ull;
+        if (!todo) continue;
+        QueryLanes L{};
+        L.qs = qs;
+        L.end = J.q1;
+        L.load(J.q0);
+        for (; todo; todo &= todo - 1) {
+            const int ti = __builtin_ctzll(todo);
+            const int64_t tile = tile0 + ti, e = (tile << 6) + lane;
+            const unsigned long long tm = __shfl(word, ti);
+            const bool in = e < J.m;
+            int32_t s = 0, dir = 0, du = 0, da = 0, tc = 0;
+            uint64_t ab = 0;
+            const int32_t *tcnt = global_ptr(J.tcnt);
+            const bool touched = (tm >> lane) & 1ull;
+            if (in) {
+                s = global_ptr(J.sid)[e];
+                dir = e >= global_ptr(J.smid)[s] ? 1 : 0;
+            }
+            if (in && (touched || !J.zero_never)) { // the others certify nothing
+                const int32_t *slo = global_ptr(J.slo), *shi = global_ptr(J.shi), *deg = global_ptr(J.deg);
+                const int32_t a = dir ? shi[s] : slo[s];
+                const int32_t b = dir ? slo[s] : shi[s];
+                du = deg[b];
+                da = deg[a];
+                if (tcnt) tc = tcnt[s];
+                ab = ((uint64_t)(uint32_t)a << nbits) | (uint64_t)(uint32_t)b;
+            }
+            const int64_t run = in ? 2 * (int64_t)s + dir : -1;
+            // this wavefront's tile: block c holds levels 4c..4c+3 of its 64 edges.
+            // Edges no test added to hold zeros and are not read.
+            uint4 *hrow = reinterpret_cast<uint4 *>(global_ptr(J.hist) + hist_at(tile << 6, 0, J.nls)) + lane;
+            uint32_t acc = 0;
+            int32_t qi = J.q0;
+            QueryDev Q = L.at(qi);
+            const uint4 zero4 = make_uint4(0, 0, 0, 0);
+            uint4 next = touched ? hrow[0] : zero4;
+            for (int32_t l0 = 0; l0 < J.nl; l0 += 4) {
+                const uint4 cur = next;
+                if (touched && l0 + 4 < J.nl) next = hrow[((l0 >> 2) + 1) * 64]; // one block ahead
+                uint32_t hv[4] = {cur.x, cur.y, cur.z, cur.w};
+    #pragma unroll
+                for (int jj = 0; jj < 4; jj++) {
+                    const int32_t l = l0 + jj;
+                    if (l >= J.nl) break;
+                    acc += hv[jj];
+                    hv[jj] = acc;
+                    while (Q.level == l) {
+                        // |U| >= 0: an edge's endpoints have degree >= 1
+                        const uint32_t U = (uint32_t)(Q.universe == FOLTY_UNIVERSE_DST   ? du
+                                                      : Q.universe == FOLTY_UNIVERSE_SRC ? da
+                                                                                         : tc) -
+                                           (uint32_t)Q.excl;
+                        const bool cert = in && (touched || !J.zero_never) && (uint64_t)acc * Q.den >= (uint64_t)Q.num * U;
+                        if (__ballot(cert))
+                            wave_run_records(run, in, cert, ((uint64_t)Q.q << (2 * nbits)) | ab, rk, rv, nrec, cap);
+                        Q = L.at(++qi);
+                    }
+                }
+                // per-edge counts read back: the running sums stay; otherwise the
+                // tile is left cleared for the next run
+                if (touched) {
+                    if (J.keep_prefix) hrow[(l0 >> 2) * 64] = make_uint4(hv[0], hv[1], hv[2], hv[3]);
+                    else if (J.reset) hrow[(l0 >> 2) * 64] = zero4;
                 }
             }
-            // per-edge counts read back: the running sums stay; otherwise the
-            // tile is left cleared for the next run
-            if (touched) {
-                if (J.keep_prefix) hrow[(l0 >> 2) * 64] = make_uint4(hv[0], hv[1], hv[2], hv[3]);
-                else if (J.reset) hrow[(l0 >> 2) * 64] = zero4;
-            }
+            if (tm && J.reset && lane == 0) tmask[tile] = 0ull;
         }
-        if (tm && J.reset && lane == 0) tmask[tile] = 0ull;
     }
 }
 
@@ -480,6 +515,8 @@ struct Plan {
     std::vector<int64_t> job_w_base, unit_base;
     int32_t ngroups = 0;
     int64_t items = 0, units = 0, total_w = 0, rec_cap = 0; // items: over the jobs; units: over the groups
+    int64_t thr_w = 0;     // total_w with the jobs padded to whole wavefronts of the threshold step
+    int32_t thr_tiles = 1; // its tiles per wavefront
     int nbits = 0;
     CandBuf cand{};
     int64_t chunks = 0, heavy_cap = 1;
@@ -575,9 +612,9 @@ static void enqueue_compute(Plan &P, hipStream_t s) {
         FOLTY_LAUNCHED();
     }
     enqueue_tests(P, P.ipt, P.tblocks, s);
-    if (P.total_w > 0) {
-        k_job_threshold<<<grid_for(P.total_w, BLK, 8192), BLK, 0, s>>>(
-            P.d_jobs.as<JobDev>(), nj, P.d_job_w_base.as<int64_t>(), P.total_w, P.d_queries.as<QueryDev>(),
+    if (P.thr_w > 0) {
+        k_job_threshold<<<grid_for(P.thr_w, (int64_t)BLK * P.thr_tiles, 8192), BLK, 0, s>>>(
+            P.d_jobs.as<JobDev>(), nj, P.d_job_w_base.as<int64_t>(), P.thr_w, P.thr_tiles, P.d_queries.as<QueryDev>(),
             P.nbits, P.keys.as<uint64_t>(), P.vals.as<uint32_t>(), P.nrec.as<int32_t>(),
             P.rec_cap);
         FOLTY_LAUNCHED();
@@ -746,10 +783,15 @@ Plan *plan_create(Graph *const *gs, int ng, const folty_query *qs, const int32_t
     P->job_w_base.assign(nj + 1, 0);
     for (int j = 0; j < nj; j++) {
         P->items += P->graphs[P->jobs[j].graph]->ix.NI;
-        // each job's edges start on a wavefront boundary
-        P->job_w_base[j + 1] = P->job_w_base[j] + (((int64_t)P->graphs[P->jobs[j].graph]->ix.m + 63) & ~63ll);
+        P->total_w += ((int64_t)P->graphs[P->jobs[j].graph]->ix.m + 63) & ~63ll;
     }
-    P->total_w = P->job_w_base[nj];
+    // tiles per wavefront of the threshold step: up to 16 once that leaves 16,384
+    // wavefronts; each job's edges start on a wavefront's first tile
+    P->thr_tiles = (int32_t)std::max<int64_t>(1, std::min<int64_t>(16, P->total_w / 64 / 16384));
+    const int64_t slice = 64 * (int64_t)P->thr_tiles;
+    for (int j = 0; j < nj; j++)
+        P->job_w_base[j + 1] = P->job_w_base[j] + (P->graphs[P->jobs[j].graph]->ix.m + slice - 1) / slice * slice;
+    P->thr_w = P->job_w_base[nj];
     // the plan's queries grouped by job, each job's by level
     std::vector<int32_t> jq(nq);
     for (int q = 0; q < nq; q++) jq[q] = q;

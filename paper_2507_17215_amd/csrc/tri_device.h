@@ -1049,9 +1049,11 @@ __global__ __launch_bounds__(BLK) void k_filter_cached(const int32_t *__restrict
 // and all lanes run one copy of the test whatever their run or predicate.
 // (A copy per run, six in turn with part of the lanes each, took 2.2 ms where
 // this takes 1.5 ms: 36.6M tests of the 70M-edge graph at one year.)  The
-// per-edge counts take a test per lane, so neighbouring lanes take neighbouring
-// tests of one run and their loads coalesce; the exists-exists-exists counting,
-// whose window bookkeeping the tests of a run share, takes a few of them per lane.
+// per-edge counts take two tests per lane at a time (their first reads go together:
+// 545,000 tests in 12,000 chunks 0.11 -> 0.07 ms), so neighbouring lanes take
+// neighbouring tests of one run and their loads coalesce; the exists-exists-exists
+// counting, whose window bookkeeping the tests of a run share, takes a few of them
+// per lane.
 // A triangle with more tests (a heavy one) gets an entry in a list and a range of
 // piece numbers, both from one packed counter, so entries are in the order of
 // their pieces; a second kernel runs piece p (tests [4 i, 4 i + 4) of its
@@ -1060,7 +1062,7 @@ __global__ __launch_bounds__(BLK) void k_filter_cached(const int32_t *__restrict
 // Heavy triangles past the list's capacity run where they were found, so any
 // capacity gives the same result.
 // Both kernels wait on dependent reads, so registers and LDS are kept small
-// enough for six to eight wavefronts per SIMD.
+// enough for four to eight wavefronts per SIMD.
 // 70M-edge graph, one year (14.1M triangles, 36.6M tests) and a graph of
 // 5,000-edge lists closed by short ones (2.9M triangles, 106M tests), both kernels:
 // light limit 32 / 64 / 128 with pieces of 4: 1.67, 1.62, 1.58 and 1.13, 1.14, 1.10 ms;
@@ -1228,6 +1230,36 @@ __device__ inline void staged_tests(const RunLds<SHORT> &F, const RunLists &ids,
     }
 }
 
+// One test, r of staged triangle si's runs, in two steps: its reads that depend on
+// nothing else are issued when it is set up, so two tests' go together.
+template <bool SHORT> struct OneTest {
+    List l2, l3;
+    Probe p2, p3;
+    int64_t t;
+    int32_t e;
+    __device__ inline OneTest(const RunLds<SHORT> &F, const RunLists &ids, int si, int64_t r,
+                              const int64_t *__restrict__ ts, const EdgeRec *__restrict__ rec) {
+        int k = 0;
+        for (uint32_t live = F.live[si];;) {
+            k = __ffs((int)live) - 1;
+            live &= live - 1;
+            if (r < F.n[k][si] || !live) break;
+            r -= F.n[k][si];
+        }
+        e = F.s[k][si] + (int32_t)r;
+        l2 = staged_list(F, (int)(ids.l2 >> (3 * k)) & 7, si, ts, rec);
+        l3 = staged_list(F, (int)(ids.l3 >> (3 * k)) & 7, si, ts, rec);
+        p2 = l2.template at<SHORT>(0);
+        p3 = l3.template at<SHORT>(0);
+        t = ts[e];
+    }
+    template <class Op> __device__ inline void run(const Op &op) const {
+        int32_t c2 = 0, c3 = 0;
+        int64_t win = 0;
+        if (window_test(l2, l3, c2, c3, p2, p3, t, op.most(), win) == TEST_HIT) op.hit(e, win);
+    }
+};
+
 // Runs the tests of the per-edge counts (see k_tests_light): units() is a light
 // triangle's work items, flat() runs one of them, piece() tests [r, r + cnt).
 template <int VAR, class Op, bool SS> struct CountRunner {
@@ -1245,6 +1277,14 @@ template <int VAR, class Op, bool SS> struct CountRunner {
     __device__ inline const EdgeRec *ends() const { return inl ? rec : nullptr; }
     __device__ inline void flat(Lds &F, int si, int64_t r, bool on) {
         if (on) staged_tests<SS, true>(F, run_list_ids(VAR), si, r, 1, ts, ends(), op);
+    }
+    // items of two triangles; the second may be off
+    static constexpr bool kTwo = !SS;
+    __device__ inline void flat2(Lds &F, int s0, int64_t r0, int s1, int64_t r1, bool two) {
+        const OneTest<kShort> a(F, run_list_ids(VAR), s0, r0, ts, ends());
+        const OneTest<kShort> b(F, run_list_ids(VAR), two ? s1 : s0, two ? r1 : r0, ts, ends());
+        a.run(op);
+        if (two) b.run(op);
     }
     __device__ inline void piece(Lds &F, int si, int64_t r, int32_t cnt, bool on) {
         if (on) staged_tests<SS, false>(F, run_list_ids(VAR), si, r, cnt, ts, ends(), op);
@@ -1288,26 +1328,41 @@ __device__ inline int staged_owner(const int32_t *incl, int32_t x) {
 }
 
 // The staged triangles' work over the lanes: flat(si, r, on) is item r of triangle
-// si (called by all lanes together, with on false past the last item), this lane's triangle has `units` items (at most LIGHT_TESTS); triangles
-// with `own` set (heavy, not listed) have alone(si) items each and go one after
-// another.
-template <class Lds, class Flat, class Alone>
-__device__ inline void spread_units(Lds &F, int32_t incl, bool own, const Flat &flat, const Alone &alone) {
+// si (called by all lanes together, with on false past the last item), this lane's
+// triangle has `units` items (at most LIGHT_TESTS); triangles with `own` set (heavy,
+// not listed) have alone(si) items each and go one after another.  TWO: a lane takes
+// two items at a time, flat2(si, r, si', r', whether there is a second).
+template <bool TWO, class Lds, class Flat, class Flat2, class Alone>
+__device__ inline void spread_units(Lds &F, int32_t incl, bool own, const Flat &flat, const Flat2 &flat2,
+                                    const Alone &alone) {
     const int lane = lane_id();
     int64_t total = __builtin_amdgcn_readlane(incl, 63);
     unsigned long long left = __ballot(own);
     int src = -1;
+    auto item = [&](int64_t t, int &si, int64_t &r) {
+        si = src;
+        r = t;
+        if (src < 0) { // the triangle whose items hold t
+            si = staged_owner(F.incl, (int32_t)t);
+            r = t - (si ? F.incl[si - 1] : 0);
+        }
+    };
     for (;;) {
-        for (int64_t t0 = 0; t0 < total; t0 += 64) {
-            const int64_t t = t0 + lane;
-            int si = src;
-            int64_t r = t;
-            if (src < 0) { // the triangle whose items hold t
-                const int a = staged_owner(F.incl, (int32_t)t);
-                si = a;
-                r = t - (a ? F.incl[a - 1] : 0);
+        if constexpr (TWO) {
+            for (int64_t t = lane; t < total; t += 128) {
+                int s0, s1;
+                int64_t r0, r1;
+                item(t, s0, r0);
+                item(t + 64, s1, r1);
+                flat2(s0, r0, s1, r1, t + 64 < total);
             }
-            flat(si, r, t < total);
+        } else {
+            for (int64_t t0 = 0; t0 < total; t0 += 64) {
+                int si;
+                int64_t r;
+                item(t0 + lane, si, r);
+                flat(si, r, t0 + lane < total);
+            }
         }
         if (!left) break;
         src = __builtin_ctzll(left);
@@ -1319,15 +1374,18 @@ __device__ inline void spread_units(Lds &F, int32_t incl, bool own, const Flat &
 // A wavefront's group of chunks as a dense sequence of slots: narrow windows
 // leave most chunks with an entry or two, and their triangles are taken 64 at a
 // time across chunks.  Groups of up to 64 chunks, fewer when that would leave
-// less than GROUPS_WANTED groups; with few chunks each is shared by up to eight
-// wavefronts, since a wavefront's tests are a chain of dependent reads.
+// less than GROUPS_WANTED groups (8,192 and 4,096 of them were slower: 1.70 ms
+// against 1.62 at one year, 0.15 against 0.11 for 10M uniform edges); with few
+// chunks each is shared by up to eight wavefronts, since a wavefront's tests are a
+// chain of dependent reads (temporal step, one / two / four / eight wavefronts per
+// chunk: 500 triangles 20 / - / 15 / 14 us, 19,000 in 5,200 chunks 37 / 30 / 47 / 61).
 constexpr int32_t GROUPS_WANTED = 16384;
 __device__ inline int32_t group_chunks(int32_t total) {
     const int32_t k = total / GROUPS_WANTED;
     return k < 1 ? 1 : k > 64 ? 64 : k;
 }
 __device__ inline int32_t chunk_parts(int32_t total) {
-    return total >= GROUPS_WANTED / 2 ? 1 : total >= GROUPS_WANTED / 4 ? 2 : total >= GROUPS_WANTED / 8 ? 4 : 8;
+    return total >= GROUPS_WANTED / 4 ? 1 : total >= GROUPS_WANTED / 16 ? 2 : total >= GROUPS_WANTED / 32 ? 4 : 8;
 }
 struct GroupLds {
     int32_t incl[64];  // slots of the group's chunks up to this one
@@ -1394,17 +1452,20 @@ __global__ __launch_bounds__(BLK) void k_tests_light(CandBuf B, R runner, Heavy 
                     live = runner.live(T);
                     wk = runner.work(T);
                 }
-                if (wk > LIGHT_TESTS) np = (wk + PIECE_TESTS - 1) / PIECE_TESTS;
             }
+            if (wk > LIGHT_TESTS) np = (wk + PIECE_TESTS - 1) / PIECE_TESTS;
             mine += wk;
             const bool listed = defer_heavy(slot, np, heavy, counter, cap, full);
             stage_runs(F, lane, T, e, live, slot);
             const int32_t incl = wave_scan(np ? 0 : (int32_t)runner.units(F, lane, wk));
             F.incl[lane] = incl;
             wave_sync();
-            spread_units(
+            spread_units<R::kTwo>(
                 F, incl, np && !listed,
                 [&](int si, int64_t r, bool on) { runner.flat(F, si, r, on); },
+                [&](int s0, int64_t r0, int s1, int64_t r1, bool two) {
+                    if constexpr (R::kTwo) runner.flat2(F, s0, r0, s1, r1, two);
+                },
                 [&](int si) { return runner.units(F, si, __shfl(wk, si)); }); // si: the same in every lane
             wave_sync(); // the LDS is rewritten by the next triangles
         }
@@ -1470,7 +1531,7 @@ __global__ __launch_bounds__(BLK) void k_tests_pieces(const Heavy *__restrict__ 
 
 constexpr int64_t MAX_HEAVY = 1 << 22; // 64 MB of heavy-survivor entries at most
 constexpr int64_t MIN_HEAVY = 1 << 16; // room for this many whatever the survivors
-constexpr int64_t LIGHT_BLOCKS = 16384;
+constexpr int64_t LIGHT_BLOCKS = 4096; // a group per wavefront or two; 16,384 blocks mostly started for nothing
 constexpr int64_t PIECE_BLOCKS = 8192;
 
 // the heavy list's capacity limit: MAX_HEAVY, or FOLTY_MAX_HEAVY (>= 1) when set

@@ -157,6 +157,7 @@ __device__ inline void triad_any(const TriadOut &o, const int64_t *__restrict__ 
 // total[1] = 1 on a 64-bit overflow.
 template <int VAR, bool INST> struct TriadRunner {
     using Lds = TriadLds;
+    static constexpr bool kTwo = false;
     uint32_t dq;
     const int64_t *ts;
     TriadOut o;
