@@ -237,33 +237,15 @@ __global__ __launch_bounds__(BLK) void k_plan_pieces(CandBuf B, const JobDev *__
     }
 }
 
-// A job's queries, a lane each, 64 at a time: a wavefront steps through them without
-// a read per query.
-struct QueryLanes {
-    QueryDev q;      // this lane's
-    int32_t first;   // position of lane 0's
-    int32_t end;     // of the job's last + 1
-    const QueryDev *__restrict__ qs;
-    __device__ void load(int32_t qi) { // the same qi in every lane
-        first = qi;
-        if (qi + lane_id() < end) q = qs[qi + lane_id()];
-    }
-    // the query at qi (in every lane), or one with no level past the job's last
-    __device__ QueryDev at(int32_t qi) {
-        QueryDev r{};
-        r.level = INT32_MAX;
-        if (qi >= end) return r;
-        if (qi < first || qi - first >= 64) load(qi);
-        const int i = __builtin_amdgcn_readfirstlane(qi - first);
-        r.level = __builtin_amdgcn_readlane(q.level, i);
-        r.num = (uint32_t)__builtin_amdgcn_readlane((int32_t)q.num, i);
-        r.den = (uint32_t)__builtin_amdgcn_readlane((int32_t)q.den, i);
-        r.universe = __builtin_amdgcn_readlane(q.universe, i);
-        r.excl = __builtin_amdgcn_readlane(q.excl, i);
-        r.q = __builtin_amdgcn_readlane(q.q, i);
-        return r;
-    }
-};
+// the plan's query at position qi, or one with no level past the job's last
+// (qi is the same in every lane; saying so keeps the load scalar, all eight
+// words at once)
+__device__ inline QueryDev next_query(const QueryDev *__restrict__ qs, int32_t qi, int32_t q1) {
+    QueryDev Q{};
+    if (qi < q1) Q = qs[__builtin_amdgcn_readfirstlane(qi)];
+    else Q.level = INT32_MAX;
+    return Q;
+}
 
 // Certificates of one query over a wavefront of edges: per run of equal
 // (static edge, direction) keys, the number of certifying edges.  The last
@@ -297,36 +279,30 @@ __device__ inline void wave_run_records(int64_t key, bool in, bool cert, uint64_
 // job), and at each level the job's queries of that delta test
 // count * den >= num * |U|.  Certificates are counted per query and emitted as
 // (query, a, b) records, one per run of a tile of 64 edges.  A wavefront takes
-// `tiles` tiles of one job (job slices are padded to that), so the per-query loop
-// and its ballots are uniform.  Most tiles of a plan over a large graph have no
+// up to 4 tiles of one job, spread evenly over the job's (job_base: wavefronts of the
+// jobs before each), so the per-query loop and its ballots are uniform.  Most tiles of a plan over a large graph have no
 // edge that a test added to; unless a count of 0 meets some query of the job they
-// are passed over, and one read tells which of a wavefront's they are (64 queries
-// on 10M edges, two jobs: 0.58 ms with every tile read, 0.20 with a wavefront per
-// tile, XTHR now).
+// are passed over (64 queries on 10M edges, two jobs: 0.58 ms with every tile
+// read; now 0.24, 0.22 and 0.24 ms with 1, 4 and 16 tiles to a wavefront).
 __global__ __launch_bounds__(BLK) void k_job_threshold(const JobDev *__restrict__ jobs, int32_t nj,
-                                                       const int64_t *__restrict__ job_w_base, int64_t total_w,
-                                                       int32_t tiles, const QueryDev *__restrict__ qs, int nbits,
+                                                       const int64_t *__restrict__ job_base, int64_t units,
+                                                       const QueryDev *__restrict__ qs, int nbits,
                                                        uint64_t *__restrict__ rk, uint32_t *__restrict__ rv,
                                                        int32_t *__restrict__ nrec, int64_t cap) {
     const int lane = lane_id();
-    const int64_t stride = (int64_t)gridDim.x * BLK * tiles;
-    for (int64_t x0 = ((int64_t)blockIdx.x * WPB + wave_id()) * 64 * tiles; x0 < total_w; x0 += stride) {
-        const int32_t j = owner_of(job_w_base, nj, x0);
+    for (int64_t u = (int64_t)blockIdx.x * WPB + wave_id(); u < units; u += (int64_t)gridDim.x * WPB) {
+        const int32_t j = owner_of(job_base, nj, u);
         const JobDev &J = jobs[j];
-        const int64_t tile0 = (x0 - job_w_base[j]) >> 6, left = (((int64_t)J.m + 63) >> 6) - tile0;
+        const int64_t first = u - job_base[j], step = job_base[j + 1] - job_base[j], all = ((int64_t)J.m + 63) >> 6;
         unsigned long long *tmask = global_ptr(J.tmask);
-        const int32_t nt = left < tiles ? (int32_t)(left < 0 ? 0 : left) : tiles;
-        const unsigned long long word = lane < nt ? tmask[tile0 + lane] : 0ull;
+        const int32_t nt = (int32_t)((all - first + step - 1) / step); // 1 to 4
+        const unsigned long long word = lane < nt ? tmask[first + lane * step] : 0ull;
         // edges no test added to certify nothing, and their counters are clear
         unsigned long long todo = J.zero_never ? __ballot(word != 0ull) : (1ull << nt) - 1ull;
         if (!todo) continue;
-        QueryLanes L{};
-        L.qs = qs;
-        L.end = J.q1;
-        L.load(J.q0);
         for (; todo; todo &= todo - 1) {
             const int ti = __builtin_ctzll(todo);
-            const int64_t tile = tile0 + ti, e = (tile << 6) + lane;
+            const int64_t tile = first + ti * step, e = (tile << 6) + lane;
             const unsigned long long tm = __shfl(word, ti);
             const bool in = e < J.m;
             int32_t s = 0, dir = 0, du = 0, da = 0, tc = 0;
@@ -352,36 +328,40 @@ __global__ __launch_bounds__(BLK) void k_job_threshold(const JobDev *__restrict_
             uint4 *hrow = reinterpret_cast<uint4 *>(global_ptr(J.hist) + hist_at(tile << 6, 0, J.nls)) + lane;
             uint32_t acc = 0;
             int32_t qi = J.q0;
-            QueryDev Q = L.at(qi);
+            QueryDev Q = next_query(qs, qi, J.q1);
             const uint4 zero4 = make_uint4(0, 0, 0, 0);
-            uint4 next = touched ? hrow[0] : zero4;
-            for (int32_t l0 = 0; l0 < J.nl; l0 += 4) {
-                const uint4 cur = next;
-                if (touched && l0 + 4 < J.nl) next = hrow[((l0 >> 2) + 1) * 64]; // one block ahead
-                uint32_t hv[4] = {cur.x, cur.y, cur.z, cur.w};
-    #pragma unroll
-                for (int jj = 0; jj < 4; jj++) {
-                    const int32_t l = l0 + jj;
-                    if (l >= J.nl) break;
-                    acc += hv[jj];
-                    hv[jj] = acc;
-                    while (Q.level == l) {
-                        // |U| >= 0: an edge's endpoints have degree >= 1
-                        const uint32_t U = (uint32_t)(Q.universe == FOLTY_UNIVERSE_DST   ? du
-                                                      : Q.universe == FOLTY_UNIVERSE_SRC ? da
-                                                                                         : tc) -
-                                           (uint32_t)Q.excl;
-                        const bool cert = in && (touched || !J.zero_never) && (uint64_t)acc * Q.den >= (uint64_t)Q.num * U;
-                        if (__ballot(cert))
-                            wave_run_records(run, in, cert, ((uint64_t)Q.q << (2 * nbits)) | ab, rk, rv, nrec, cap);
-                        Q = L.at(++qi);
+            for (int32_t b0 = 0; 4 * b0 < J.nl; b0 += 4) {
+                uint4 h[4]; // 16 levels' reads go together
+#pragma unroll
+                for (int i = 0; i < 4; i++) h[i] = touched && 4 * (b0 + i) < J.nl ? hrow[(b0 + i) * 64] : zero4;
+#pragma unroll
+                for (int i = 0; i < 4; i++) {
+                    uint32_t hv[4] = {h[i].x, h[i].y, h[i].z, h[i].w};
+#pragma unroll
+                    for (int jj = 0; jj < 4; jj++) {
+                        const int32_t l = 4 * (b0 + i) + jj;
+                        if (l >= J.nl) break;
+                        acc += hv[jj];
+                        hv[jj] = acc;
+                        while (Q.level == l) {
+                            // |U| >= 0: an edge's endpoints have degree >= 1
+                            const uint32_t U = (uint32_t)(Q.universe == FOLTY_UNIVERSE_DST   ? du
+                                                          : Q.universe == FOLTY_UNIVERSE_SRC ? da
+                                                                                             : tc) -
+                                               (uint32_t)Q.excl;
+                            const bool cert =
+                                in && (touched || !J.zero_never) && (uint64_t)acc * Q.den >= (uint64_t)Q.num * U;
+                            if (__ballot(cert))
+                                wave_run_records(run, in, cert, ((uint64_t)Q.q << (2 * nbits)) | ab, rk, rv, nrec, cap);
+                            Q = next_query(qs, ++qi, J.q1);
+                        }
                     }
-                }
-                // per-edge counts read back: the running sums stay; otherwise the
-                // tile is left cleared for the next run
-                if (touched) {
-                    if (J.keep_prefix) hrow[(l0 >> 2) * 64] = make_uint4(hv[0], hv[1], hv[2], hv[3]);
-                    else if (J.reset) hrow[(l0 >> 2) * 64] = zero4;
+                    // per-edge counts read back: the running sums stay; otherwise the
+                    // tile is left cleared for the next run
+                    if (touched && 4 * (b0 + i) < J.nl) {
+                        if (J.keep_prefix) hrow[(b0 + i) * 64] = make_uint4(hv[0], hv[1], hv[2], hv[3]);
+                        else if (J.reset) hrow[(b0 + i) * 64] = zero4;
+                    }
                 }
             }
             if (tm && J.reset && lane == 0) tmask[tile] = 0ull;
@@ -512,16 +492,14 @@ struct Plan {
     };
     std::vector<Job> jobs;
     std::vector<int32_t> qjob, qlevel;
-    std::vector<int64_t> job_w_base, unit_base;
+    std::vector<int64_t> job_base, unit_base; // wavefronts of the threshold step before each job; units before each group
     int32_t ngroups = 0;
     int64_t items = 0, units = 0, total_w = 0, rec_cap = 0; // items: over the jobs; units: over the groups
-    int64_t thr_w = 0;     // total_w with the jobs padded to whole wavefronts of the threshold step
-    int32_t thr_tiles = 1; // its tiles per wavefront
     int nbits = 0;
     CandBuf cand{};
     int64_t chunks = 0, heavy_cap = 1;
     // device memory
-    DevBuf d_jobs, d_job_w_base, d_queries, d_groups, d_gjobs, d_unit_base;
+    DevBuf d_jobs, d_job_base, d_queries, d_groups, d_gjobs, d_unit_base;
     std::vector<DevBuf> hist, tmask, lv;
     DevBuf sv, svn, tag, heavy, scal;
     bool dirty = true; // some histogram may hold counts (fresh, tuned, or a run did not finish)
@@ -561,7 +539,7 @@ Plan::~Plan() {
         d_groups.release();
         d_gjobs.release();
         d_unit_base.release();
-        d_job_w_base.release();
+        d_job_base.release();
         d_queries.release();
         nrec.release();
         keys.release();
@@ -612,9 +590,9 @@ static void enqueue_compute(Plan &P, hipStream_t s) {
         FOLTY_LAUNCHED();
     }
     enqueue_tests(P, P.ipt, P.tblocks, s);
-    if (P.thr_w > 0) {
-        k_job_threshold<<<grid_for(P.thr_w, (int64_t)BLK * P.thr_tiles, 8192), BLK, 0, s>>>(
-            P.d_jobs.as<JobDev>(), nj, P.d_job_w_base.as<int64_t>(), P.thr_w, P.thr_tiles, P.d_queries.as<QueryDev>(),
+    if (P.job_base[nj] > 0) {
+        k_job_threshold<<<grid_for(P.job_base[nj], WPB, 8192), BLK, 0, s>>>(
+            P.d_jobs.as<JobDev>(), nj, P.d_job_base.as<int64_t>(), P.job_base[nj], P.d_queries.as<QueryDev>(),
             P.nbits, P.keys.as<uint64_t>(), P.vals.as<uint32_t>(), P.nrec.as<int32_t>(),
             P.rec_cap);
         FOLTY_LAUNCHED();
@@ -780,18 +758,16 @@ Plan *plan_create(Graph *const *gs, int ng, const folty_query *qs, const int32_t
     P->tmask.resize(nj);
     P->lv.resize(nj);
     std::vector<JobDev> jd(nj);
-    P->job_w_base.assign(nj + 1, 0);
+    P->job_base.assign(nj + 1, 0);
     for (int j = 0; j < nj; j++) {
         P->items += P->graphs[P->jobs[j].graph]->ix.NI;
         P->total_w += ((int64_t)P->graphs[P->jobs[j].graph]->ix.m + 63) & ~63ll;
     }
-    // tiles per wavefront of the threshold step: up to 16 once that leaves 16,384
-    // wavefronts; each job's edges start on a wavefront's first tile
-    P->thr_tiles = (int32_t)std::max<int64_t>(1, std::min<int64_t>(16, P->total_w / 64 / 16384));
-    const int64_t slice = 64 * (int64_t)P->thr_tiles;
+    // wavefronts of the threshold step: a tile each, or up to 4 tiles once that
+    // leaves 16,384 wavefronts
+    const int64_t tiles = std::max<int64_t>(1, std::min<int64_t>(4, P->total_w / 64 / 16384));
     for (int j = 0; j < nj; j++)
-        P->job_w_base[j + 1] = P->job_w_base[j] + (P->graphs[P->jobs[j].graph]->ix.m + slice - 1) / slice * slice;
-    P->thr_w = P->job_w_base[nj];
+        P->job_base[j + 1] = P->job_base[j] + (((int64_t)P->graphs[P->jobs[j].graph]->ix.m + 63) / 64 + tiles - 1) / tiles;
     // the plan's queries grouped by job, each job's by level
     std::vector<int32_t> jq(nq);
     for (int q = 0; q < nq; q++) jq[q] = q;
@@ -920,10 +896,10 @@ Plan *plan_create(Graph *const *gs, int ng, const folty_query *qs, const int32_t
     if (bit_length((uint64_t)std::max(1, nq)) + 2 * P->nbits > 64)
         fail(FOLTY_EOVERFLOW, "too many queries for one plan at this graph size");
     P->d_jobs.ensure(sizeof(JobDev) * (size_t)std::max(1, nj));
-    P->d_job_w_base.ensure(8 * ((size_t)nj + 1));
+    P->d_job_base.ensure(8 * ((size_t)nj + 1));
     P->d_queries.ensure(sizeof(QueryDev) * (size_t)std::max(1, nq));
     if (nj) FOLTY_HIP(hipMemcpyAsync(P->d_jobs.p, jd.data(), sizeof(JobDev) * nj, hipMemcpyHostToDevice, s));
-    FOLTY_HIP(hipMemcpyAsync(P->d_job_w_base.p, P->job_w_base.data(), 8 * (nj + 1), hipMemcpyHostToDevice, s));
+    FOLTY_HIP(hipMemcpyAsync(P->d_job_base.p, P->job_base.data(), 8 * (nj + 1), hipMemcpyHostToDevice, s));
     if (nq) {
         FOLTY_HIP(hipMemcpyAsync(P->d_queries.p, qd.data(), sizeof(QueryDev) * nq, hipMemcpyHostToDevice, s));
     }
