@@ -35,7 +35,7 @@ VALU_PEAK_WAVE_INSTS = 256 * 4 * 2.4e9 / 4
 # the query's dominant kernel, the sources it is compiled from, and the committed
 # counter summary (FETCH_SIZE / WRITE_SIZE per dispatch and the copy-kernel
 # calibration, SQ_INSTS_VALU) that gives its measured HBM traffic and issue rate
-ROOF_KERNEL = "k_tri_enum<FilterSink<0, 0, false> >"
+ROOF_KERNEL = "k_tri_enum<FilterSink<0, FILTER_COUNT> >"
 ROOF_SOURCES = ("paper_2507_17215_amd/csrc/tri_device.h", "paper_2507_17215_amd/csrc/query.hip")
 TRAFFIC_SUMMARY = "profiles/k_tri_enum_filter_large_70M_pmc.md"
 COPY_PROBE_BYTES = 1 << 30
@@ -119,12 +119,12 @@ def cpu_model():
 
 
 def profile_queries(folty, synth, n, src, dst, tt, theta):
-    """A fixed sequence for profilers, in order: on a fresh index, one day and one
-    year with predicate 0 (two filter passes each; the one-year query's second
-    pass re-enumerates most triangles, so later wide windows filter in one
-    pass), then one year with predicates 0 and 3 (one pass), the smaller-side
-    evaluation at one year, and the exists-exists-exists query at one year
-    (counting only, then with temporal triangles, per-edge counts and listing)."""
+    """A fixed sequence for profilers, in order: on a fresh index, one day (the first
+    query, which also counts the triangles) and one year with predicate 0, one year
+    again, one year with predicate 3, the smaller-side evaluation at one year, and
+    the exists-exists-exists query at one year (counting only, then with temporal
+    triangles, per-edge counts and listing).  All filter in two passes: at one year
+    1 triangle in 36 is kept, and the switch to one pass comes at 1 in 12."""
     Y = synth.YEAR_S
     G = folty.Graph(n, src, dst, tt).build()
     seq = []

@@ -14,7 +14,8 @@
 //       sigma_max factor).  A (triangle, directed list) pair is a run of tests.
 //       A run is skipped when the time ranges of its three lists already rule
 //       out t <= t2 <= t3 <= t + delta (a necessary condition, so no result
-//       changes).  The surviving tests are cut into equal chunks over the grid.
+//       changes).  The tests left are spread over the lanes of the wavefront
+//       that holds their triangles, or in pieces over the chip.
 //  a.7  threshold (paper, Algorithm ExistExistForAll, final loop) with the exact
 //       rational theta, then per-pair certificate counts by a wavefront
 //       segmented reduction and a ballot/prefix compaction of the pairs.
