@@ -152,8 +152,8 @@ __device__ inline void triad_any(const TriadOut &o, const int64_t *__restrict__ 
     }
 }
 
-// The triangles' runs, scheduled as the count's (k_tests_light, a few
-// tests of a run per lane; then the pieces of triangles with many tests); total[0] += temporal triangles,
+// The triangles' runs, scheduled as the count's (k_tests_light, a run
+// or a few tests of one per lane; then the pieces of triangles with many tests); total[0] += temporal triangles,
 // total[1] = 1 on a 64-bit overflow.
 template <int VAR, bool INST> struct TriadRunner {
     using Lds = TriadLds;
@@ -168,10 +168,11 @@ template <int VAR, bool INST> struct TriadRunner {
     bool ovf = false;
     __device__ inline uint32_t live(const TriLists &L) const { return tri_live<VAR>(L, dq); }
     __device__ inline int64_t work(const TriLists &L) const { return tri_work<VAR, false>(L, dq); }
-    // A light triangle's items are pieces of its runs: a whole run of 64 tests is a
-    // chain of some hundred dependent reads, which the slowest lane's wavefront
-    // waits for.
+    // A light triangle's items are its runs, which stop at the first edge that closes
+    // a triangle; when all are counted, pieces of them: a whole run of 64 tests is then
+    // a chain of some hundred dependent reads, which its wavefront waits for.
     __device__ inline int64_t units(const Lds &F, int si, int64_t) const {
+        if (!INST) return __popc(F.live[si]);
         int64_t c = 0;
         for (uint32_t live = F.live[si]; live; live &= live - 1)
             c += (F.n[__ffs((int)live) - 1][si] + (int32_t)PIECE_TESTS - 1) / (int32_t)PIECE_TESTS;
@@ -190,10 +191,10 @@ template <int VAR, bool INST> struct TriadRunner {
         int32_t first = 0, cnt = 0;
         for (uint32_t live = on ? F.live[si] : 0u; live; live &= live - 1) {
             k = __ffs((int)live) - 1;
-            const int32_t n1 = F.n[k][si], c = (n1 + (int32_t)PIECE_TESTS - 1) / (int32_t)PIECE_TESTS;
+            const int32_t n1 = F.n[k][si], piece = INST ? (int32_t)PIECE_TESTS : n1, c = INST ? (n1 + piece - 1) / piece : 1;
             if (r < c) {
-                first = (int32_t)(r * PIECE_TESTS);
-                cnt = n1 - first < (int32_t)PIECE_TESTS ? n1 - first : (int32_t)PIECE_TESTS;
+                first = (int32_t)r * piece;
+                cnt = n1 - first < piece ? n1 - first : piece;
                 break;
             }
             r -= c;
