@@ -419,8 +419,8 @@ class Graph:
               exclude_other=False, counts=True, workspace: Workspace | None = None,
               smaller_side=False, one_pass=False) -> Result:
         """The exists-exists-forall query; smaller_side evaluates each run from the
-        shorter of E_{a,b} and L2 (in-neighbour intervals), one_pass filters in one
-        enumeration pass (per-item triangle slots); results are identical."""
+        shorter of E_{a,b} and L2 (in-neighbour intervals), one_pass tests whole
+        triangles only, not known edges first; results are identical."""
         q = make_query(delta, theta, variant, universe, exclude_other, counts, smaller_side, one_pass)
         out = ctypes.c_void_p()
         lib = load_library()
