@@ -127,16 +127,16 @@ size_t exclusive_scan_i32(void *tmp, size_t tb, const int32_t *in, int32_t *out,
 }
 
 namespace {
-// 1 where a new (lo, hi) pair starts in the sorted grouping keys
+// 1 where a new (lo, hi) pair after the first starts in the sorted grouping keys
 struct PairStart {
     const uint64_t *key;
     int shift;
     uint64_t mask; // of the shifted pair
-    __device__ int32_t operator()(int64_t k) const { return k == 0 || ((key[k] ^ key[k - 1]) >> shift & mask) != 0; }
+    __device__ int32_t operator()(int64_t k) const { return k > 0 && ((key[k] ^ key[k - 1]) >> shift & mask) != 0; }
 };
 } // namespace
 
-// out[k] = 1 + the index of the static pair of sorted key k: an inclusive scan
+// out[k] = the index of the static pair of sorted key k: an inclusive scan
 // of pair starts computed from the keys as the scan reads them
 size_t inclusive_scan_pair_starts(void *tmp, size_t tb, const uint64_t *key, int shift, int bits, int32_t *out,
                                   int64_t n,
