@@ -200,6 +200,7 @@ template <int VAR> __device__ inline uint32_t tri_live(const TriLists &T, uint32
            (uint32_t)run_lists<VAR, 0, 2>(T, dq, a, b, c) << 2 | (uint32_t)run_lists<VAR, 2, 0>(T, dq, a, b, c) << 3 |
            (uint32_t)run_lists<VAR, 1, 2>(T, dq, a, b, c) << 4 | (uint32_t)run_lists<VAR, 2, 1>(T, dq, a, b, c) << 5;
 }
+// a predicate code read at run time (one per job in a batch)
 __device__ inline uint32_t tri_live_rt(int variant, const TriLists &T, uint32_t dq) {
     switch (variant) {
     case 0: return tri_live<0>(T, dq);
@@ -210,20 +211,6 @@ __device__ inline uint32_t tri_live_rt(int variant, const TriLists &T, uint32_t 
     case 5: return tri_live<5>(T, dq);
     case 6: return tri_live<6>(T, dq);
     default: return tri_live<7>(T, dq);
-    }
-}
-
-// runtime predicate code (one code per job in a batch)
-__device__ inline int64_t tri_work_rt(int variant, const TriLists &T, uint32_t dq) {
-    switch (variant) {
-    case 0: return tri_work<0>(T, dq);
-    case 1: return tri_work<1>(T, dq);
-    case 2: return tri_work<2>(T, dq);
-    case 3: return tri_work<3>(T, dq);
-    case 4: return tri_work<4>(T, dq);
-    case 5: return tri_work<5>(T, dq);
-    case 6: return tri_work<6>(T, dq);
-    default: return tri_work<7>(T, dq);
     }
 }
 
