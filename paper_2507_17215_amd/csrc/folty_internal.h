@@ -303,7 +303,9 @@ struct Index {
     bool tcnt_ready = false;
     double build_ms = 0;
     int32_t tshift = 0; // timestamps >> tshift fit 32 bits (0 for t < 2^32)
-    int32_t rshift = 0; // timestamps >> rshift fit 14 bits (the ranges in erng)
+    // the ranges in erng: (timestamps - (rbase << tshift)) >> rshift, held to 14 bits
+    int32_t rshift = 0;
+    uint32_t rbase = 0;
 
     DevBuf ts;       // int64[m]
     DevBuf perm;     // int32[m]  input position of each sorted edge
@@ -320,7 +322,7 @@ struct Index {
     DevBuf oadj;     // int32[S]  heads (new ids)
     DevBuf oeid;     // uint32[S] static edge id | direction bit
     DevBuf rec;      // EdgeRec[S]
-    DevBuf erng;     // uint2[S]  first and last timestamp >> rshift of each oriented edge's two lists
+    DevBuf erng;     // uint2[S]  first and last timestamp of each oriented edge's two lists, in 14 bits
                      //           (tri_device.h, ranges)
     DevBuf otail;    // int32[S]  tail of each oriented edge (new id; released after the build)
     DevBuf seg;      // int4[G]   probe segments grouped by owner (see EnumItem)
@@ -374,6 +376,7 @@ struct Graph {
     const int64_t *in_t = nullptr;
     bool sorted_by_time = false;
     int64_t tmax = 0;
+    int64_t bulk_from = 0, bulk_to = 0; // most timestamps lie between them
     Index ix;
     Workspace ws;          // default workspace for the synchronous API
     std::mutex lazy_mu;    // guards index parts computed on first use

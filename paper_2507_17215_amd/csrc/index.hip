@@ -47,6 +47,7 @@ struct ValOut {
     unsigned long long loops;
     unsigned long long tmax;
     unsigned long long descents;
+    int64_t least, bulk_lo, bulk_hi; // of the sampled timestamps (k_init_val)
 };
 
 // VU edges per thread and step, each a coalesced load of its own, all in flight
@@ -114,7 +115,24 @@ __global__ void k_validate(const int32_t *__restrict__ src, const int32_t *__res
     if (bad != ~0ull) atomicMin(&out->first_bad, bad);
 }
 
-__global__ void k_init_val(ValOut *o) {
+// Clears the validation's totals and finds where most timestamps lie: between the
+// order statistics BULK_CUT from either end of BULK_SAMPLE timestamps taken at even
+// steps.  The filter's time ranges have 14 bits, and their unit follows from this
+// span: from 0 to the last timestamp it would be 36 hours for Unix seconds, and
+// a single stray timestamp would widen it as much.
+constexpr int BULK_SAMPLE = 256, BULK_CUT = 4;
+__global__ __launch_bounds__(BULK_SAMPLE) void k_init_val(const int64_t *__restrict__ t, int64_t m, ValOut *o) {
+    __shared__ int64_t s_t[BULK_SAMPLE];
+    const int i = threadIdx.x;
+    const int64_t x = m > 0 ? t[(int64_t)i * m / BULK_SAMPLE] : 0;
+    s_t[i] = x;
+    __syncthreads();
+    int r = 0;
+    for (int j = 0; j < BULK_SAMPLE; j++) r += s_t[j] < x || (s_t[j] == x && j < i);
+    if (r == 0) o->least = x;
+    if (r == BULK_CUT) o->bulk_lo = x;
+    if (r == BULK_SAMPLE - 1 - BULK_CUT) o->bulk_hi = x;
+    if (i > 0) return;
     o->first_bad = ~0ull;
     o->loops = 0;
     o->tmax = 0;
@@ -541,7 +559,7 @@ void load_graph(Graph *g, int32_t n, int64_t m, const int32_t *src, const int32_
     }
     DevBuf vo;
     vo.ensure(sizeof(ValOut));
-    k_init_val<<<1, 1, 0, s>>>(vo.as<ValOut>());
+    k_init_val<<<1, BULK_SAMPLE, 0, s>>>(g->in_t, m, vo.as<ValOut>());
     FOLTY_LAUNCHED();
     if (m > 0) {
         // 16 edges per thread or more, and at most 768 blocks: more of them gain less
@@ -559,6 +577,10 @@ void load_graph(Graph *g, int32_t n, int64_t m, const int32_t *src, const int32_
              h.first_bad, n);
     g->ix.self_loops = (int64_t)h.loops;
     g->tmax = (int64_t)h.tmax;
+    // widened by a part of the span, but not past what was seen
+    const int64_t past = (h.bulk_hi - h.bulk_lo) >> 5;
+    g->bulk_from = std::max(h.least, h.bulk_lo - past);
+    g->bulk_to = std::min(g->tmax, h.bulk_hi + past);
     g->sorted_by_time = h.descents == 0;
 }
 
@@ -829,7 +851,9 @@ void build_index(Graph *g, const folty_build_opts *opts) {
     }
     // ---- oriented-edge records and triangles per lowest vertex ------------------------
     ix.tshift = std::max(0, bit_length((uint64_t)g->tmax) - 32);
-    ix.rshift = std::max(0, bit_length((uint64_t)g->tmax) - 14); // RNG_BITS
+    // the filter's ranges: 14 bits (RNG_BITS) over the span that holds most timestamps
+    ix.rshift = std::max(ix.tshift, bit_length((uint64_t)(g->bulk_to - g->bulk_from)) - 14);
+    ix.rbase = (uint32_t)(g->bulk_from >> ix.tshift);
     ix.one_pass_from.store(INT64_MAX, std::memory_order_relaxed);
     index_triangles(ix, o.cache_triangles != 0, cub, s);
     FOLTY_HIP(hipEventRecord(e1, s));

@@ -55,9 +55,10 @@ __global__ void k_static_recs(const int32_t *__restrict__ soff, const int32_t *_
 }
 
 // Oriented edge p (static edge e, tail lo when bit 31 of its id is set): one
-// 32-byte read of e's record, lists swapped when the tail is hi.
+// 32-byte read of e's record, lists swapped when the tail is hi.  shift: the
+// ranges' shift beyond the records' own.
 __global__ void k_edge_recs(const uint32_t *__restrict__ oeid, const EdgeRec *__restrict__ srec, int32_t S,
-                            int32_t tshift, int32_t rshift, EdgeRec *__restrict__ rec,
+                            int32_t shift, uint32_t rbase, EdgeRec *__restrict__ rec,
                             uint2 *__restrict__ erng) {
     int64_t p = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (p >= S) return;
@@ -69,10 +70,8 @@ __global__ void k_edge_recs(const uint32_t *__restrict__ oeid, const EdgeRec *__
         r.bs = q.fs, r.bn = q.fn, r.blo = q.flo, r.bhi = q.fhi;
     }
     rec[p] = r;
-    // the record's timestamps are shifted by tshift (<= rshift) already
-    const int32_t d = rshift - tshift;
-    erng[p] = make_uint2(r.fn ? rng_pack(r.flo >> d, r.fhi >> d) : RNG_EMPTY,
-                         r.bn ? rng_pack(r.blo >> d, r.bhi >> d) : RNG_EMPTY);
+    erng[p] = make_uint2(r.fn ? rng_pack(rng_code(r.flo, rbase, shift), rng_code(r.fhi, rbase, shift)) : RNG_EMPTY,
+                         r.bn ? rng_pack(rng_code(r.blo, rbase, shift), rng_code(r.bhi, rbase, shift)) : RNG_EMPTY);
 }
 
 // Probe segments: for the oriented edge (u, v) at position p, the candidates
@@ -786,7 +785,7 @@ void index_triangles(Index &ix, bool cache, DevBuf &cub, hipStream_t s) {
         k_static_recs<<<grid_for(S, BLK), BLK, 0, s>>>(ix.soff.as<int32_t>(), ix.smid.as<int32_t>(),
                                                        ix.ts.as<int64_t>(), S, ix.tshift, srec.as<EdgeRec>());
         k_edge_recs<<<grid_for(S, BLK), BLK, 0, s>>>(ix.oeid.as<uint32_t>(), srec.as<EdgeRec>(), S,
-                                                     ix.tshift, ix.rshift, ix.rec.as<EdgeRec>(),
+                                                     ix.rshift - ix.tshift, ix.rbase, ix.rec.as<EdgeRec>(),
                                                      ix.erng.as<uint2>());
         FOLTY_LAUNCHED();
     }

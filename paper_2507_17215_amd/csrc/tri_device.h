@@ -460,11 +460,21 @@ __host__ __device__ inline int64_t range_slack(int64_t dmax, int32_t shift) {
 
 // The ranges of an oriented edge's two lists (Index::erng), tail to head in x and
 // head to tail in y: per list one pair of 16-bit numbers (-first, last) in the
-// low and high half, timestamps >> rshift (RNG_BITS bits); an empty list is
-// (-32768, -32768).  In this form the tests below are packed additions whose
-// signs decide, and an empty list fails every one of them.
+// low and high half, timestamps in units of 2^rshift from a base (RNG_BITS bits); an
+// empty list is (-32768, -32768).  In this form the tests below are packed additions
+// whose signs decide, and an empty list fails every one of them.
 constexpr int RNG_BITS = 14;
 constexpr uint32_t RNG_EMPTY = 0x80008000u;
+// A record's timestamp x in those units.  Timestamps before the base or past the
+// last unit count as the first or last one: that keeps their order and makes no two
+// lie further apart, so what the tests drop has no window, wherever the base lies.
+// Base and unit follow the span of most timestamps (10M edges in one day, times from
+// 0 and from 1.3e9, a window of 60 s: 0.21 and 0.78 ms when the unit followed the
+// largest timestamp, now 0.21 and 0.21).
+__host__ __device__ inline uint32_t rng_code(uint32_t x, uint32_t base, int32_t shift) {
+    const uint32_t c = (x > base ? x - base : 0u) >> shift, most = (1u << RNG_BITS) - 1;
+    return c < most ? c : most;
+}
 typedef short rng_t __attribute__((ext_vector_type(2)));
 __host__ __device__ inline uint32_t rng_pack(uint32_t first, uint32_t last) {
     return (uint32_t)(uint16_t)(-(int32_t)first) | last << 16;

@@ -268,3 +268,67 @@ def test_pair_sorts_at_their_size_limits(pairs):
     r = folty.Graph(n, (p // n).astype(np.int32), (p % n).astype(np.int32), np.arange(p.size)).build().query(5, (0, 1), 0)
     assert np.array_equal(r.pair_u, key // n) and np.array_equal(r.pair_v, key % n)
     assert np.array_equal(r.n_cert, 1 + (np.arange(pairs) < pairs // 3))
+
+
+# ---------------------------------------------------------------------------
+# the filter's time ranges: 14 bits over the span that holds most timestamps
+# ---------------------------------------------------------------------------
+def squeezed(g, span, offset):
+    t = g.t.astype(np.int64)
+    return synth.TemporalGraph(n=g.n, src=g.src, dst=g.dst, t=t * span // (int(t.max()) + 1) + offset, meta=dict(g.meta))
+
+
+@pytest.mark.parametrize("span, delta", [(86_400, 60), (1_000_000, 3600), (YEAR, 86_400)])
+def test_filter_keeps_the_same_wherever_times_start(span, delta):
+    """stats.tests counts the tests of the triangles that the filter kept: the same graph
+    keeps the same ones from 0, from Unix seconds and from the last 32-bit second, and
+    about as many (4 of 256 sampled timestamps may be strays) with stray edges at 0."""
+    base = synth.tiny(seed=11)
+    kept = []
+    for offset in (0, 1_300_000_000, (1 << 32) - 1 - span):
+        g = squeezed(base, span, offset)
+        o = Oracle(g.n, g.src, g.dst, g.t)
+        G = folty.Graph(g.n, g.src, g.dst, g.t).build()
+        kept.append([G.query(delta, (1, 4), v).stats["tests"] for v in (0, 6)])
+        for v in range(8):
+            say("late times", span, offset, v)
+            assert_same(G.query(delta, (1, 4), v), o.query(delta, 1, 4, v))
+    say("kept", kept)
+    assert kept[1] == kept[0] and kept[2] == kept[0]
+    # edges between two vertices of their own, at time 0
+    g = squeezed(base, span, 1_300_000_000)
+    a = np.full(20, g.n, np.int32)
+    strays = synth.TemporalGraph(n=g.n + 2, src=np.concatenate([a, g.src]), dst=np.concatenate([a + 1, g.dst]),
+                                 t=np.concatenate([np.zeros(20, np.int64), g.t]))
+    o = Oracle(strays.n, strays.src, strays.dst, strays.t)
+    G = folty.Graph(strays.n, strays.src, strays.dst, strays.t).build()
+    for v, k in zip((0, 6), kept[0]):
+        say("strays", span, v)
+        r = G.query(delta, (1, 4), v)
+        assert_same(r, o.query(delta, 1, 4, v))
+        assert abs(r.stats["tests"] - k) <= k // 8 + 64
+
+
+@pytest.mark.parametrize("offset, span, low, high", [
+    (0, 50, 0, 0), (5, 16_383, 0, 0), (5, 16_384, 0, 0), (1_000, 16_385, 1, 1),  # units of one, and the first of two
+    (1 << 31, 90_000, 1, 0), (100, 90_000, 0, 1), (1 << 61, 1 << 40, 1, 0), ((1 << 32) - 40, 80, 0, 1)])
+def test_range_codes_at_their_ends(offset, span, low, high):
+    """Timestamps before the base and past the last unit count as its ends: parity on all
+    predicates with a seventh of the edges moved to 0 and to the largest timestamp."""
+    g = squeezed(synth.bruteforce_size(seed=21), span, offset)
+    t = g.t.copy()
+    if low:
+        t[::14] = 0
+    if high:
+        t[7::14] = (1 << 62) - 1
+    o = Oracle(g.n, g.src, g.dst, t)
+    G = folty.Graph(g.n, g.src, g.dst, t).build()  # no longer in time order
+    deltas = sorted({0, 1, span // 3, span, folty.DELTA_INF})
+    for v in range(8):
+        say("range ends", offset, span, low, high, v)
+        for d in deltas:
+            assert_same(G.query(d, (1, 4), v), o.query(d, 1, 4, v))
+    plan = folty.Plan([G], [(0, dict(delta=d, theta=(1, 4), variant=v)) for d in deltas for v in (0, 5)])
+    for r, (d, v) in zip(plan.run(), [(d, v) for d in deltas for v in (0, 5)]):
+        assert_same(r, o.query(d, 1, 4, v))
+    plan.close()
