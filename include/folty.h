@@ -460,11 +460,16 @@ int folty_result_counts(folty_result *r, int64_t *n_certificates, const uint32_t
  * The query of folty_run_fol_query for callers that cannot allocate device
  * memory: code under HIP graph capture, tight serving loops, harnesses that
  * forbid allocation.  It calls no hipMalloc or hipFree and no allocating library
- * routine.  Its scratch (per-edge counts, survivors, per-pair certificate counts,
- * pair keys, sort and scan scratch) is a fixed device array of
+ * routine.  Its scratch (per-edge counts, the triangles a filter keeps, per-pair
+ * certificate counts, pair keys, sort and scan scratch) is a fixed device array of
  * FOLTY_NOALLOC_SCRATCH_BYTES that every device the library runs on holds until
  * the process ends; a query needing more fails with FOLTY_ENOMEM and a message
  * giving the size.  That is enough for graphs of about a million temporal edges.
+ * A graph is refused in the same way, for every window, when 4 m + 32 S + 36 R
+ * bytes exceed the scratch: m edges, S static edges, R the vertices with an edge to
+ * one of no larger out-degree plus those with an edge from one of smaller out-degree
+ * (folty_graph_vertex_array 3).  Triangles that do not fit beside the counts are
+ * tested in parts.
  *   g, q            as for folty_run_fol_query; FOLTY_QUERY_NO_COUNTS is ignored
  *                   (edge_count decides), and the universe N(a) & N(b) needs the
  *                   graph's per-edge triangle counts to exist already (built by a

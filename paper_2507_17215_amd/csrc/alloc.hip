@@ -70,6 +70,10 @@ const AllocHook *current_hook() { return t_arena ? nullptr : t_hook; }
 ArenaScope::ArenaScope(void *b, size_t c) : base(static_cast<char *>(b)), cap(c), prev(t_arena) { t_arena = this; }
 ArenaScope::~ArenaScope() { t_arena = prev; }
 int64_t arena_left() { return t_arena ? (int64_t)(t_arena->cap - t_arena->off) : -1; }
+size_t arena_mark() { return t_arena ? t_arena->off : 0; }
+void arena_rewind(size_t mark) {
+    if (t_arena) t_arena->off = mark;
+}
 
 void *dev_alloc(size_t bytes, size_t *got) {
     if (ArenaScope *a = t_arena) {

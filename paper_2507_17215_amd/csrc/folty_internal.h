@@ -58,6 +58,10 @@ size_t dev_trim();   // give every cached block back to the driver; returns byte
 size_t dev_trim_to(size_t keep); // give back cached blocks, largest first, until at most keep bytes stay
 size_t dev_cached(); // bytes held in the cache
 int64_t arena_left(); // bytes the thread's ArenaScope has left, or -1 without one
+// what an ArenaScope handed out since the mark is free again (its buffers have been
+// forgotten, and the stream orders its next use behind this one)
+size_t arena_mark();
+void arena_rewind(size_t mark);
 void dev_forget_stream(hipStream_t s); // call before destroying a stream blocks were freed on
 // pinned host blocks for large result arrays (alloc.hip); host_alloc returns
 // nullptr when pinned memory is not available, host_free false for a pointer

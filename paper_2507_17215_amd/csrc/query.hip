@@ -438,15 +438,69 @@ namespace {
 // Up to this many chunks (50 MB) are allocated whatever the window keeps, so that
 // no pass has to be repeated and the host reads nothing back in between.
 constexpr int64_t SAFE_CHUNKS = 1 << 16;
-constexpr unsigned ARENA_ENUM_BLOCKS = 1024; // with a fixed scratch: fewer partly filled chunks
-// and room for at least this many bytes per vertex, so that which graphs fit the
-// scratch does not hang on how many triangles a window keeps
-constexpr int64_t ARENA_VERTEX_BYTES = 20;
 
 // chunks allocated at first for a graph of at most `triangles` triangles
 int64_t first_chunks(int64_t triangles, int64_t waves) {
     const int64_t most = most_chunks(triangles, waves);
     return most <= SAFE_CHUNKS ? most : std::max<int64_t>(SAFE_CHUNKS, most / 8);
+}
+
+// What a filter pass goes over: the index's enumeration items, or groups of 64
+// cached triangles.
+int64_t filter_units(const Index &ix) { return ix.tri_cached ? (ix.T.load() + 63) / 64 : ix.NI; }
+
+// `chunks` of them (or up to one per region more) in the workspace
+CandBuf make_chunks(Workspace &ws, unsigned grid, int64_t chunks) {
+    CandBuf B{};
+    B.regions = (int32_t)std::min<unsigned>(MAX_REGIONS, grid);
+    B.per_region = (int32_t)((chunks + B.regions - 1) / B.regions);
+    const size_t total = (size_t)B.regions * (size_t)B.per_region;
+    ws.sv.ensure((CHUNK_BYTES - 4) * total);
+    ws.svn.ensure(4 * total);
+    unsigned long long *scal = ws.scal.as<unsigned long long>();
+    B.sv = ws.sv.as<int32_t>();
+    B.cnt = ws.svn.as<int32_t>();
+    B.ctr = reinterpret_cast<uint32_t *>(scal + SCAL_REGIONS);
+    B.dropped = reinterpret_cast<uint32_t *>(scal + SCAL_DROPPED);
+    ws.kept_chunks = (int64_t)total;
+    return B;
+}
+
+// The filter over units [u0, u0 + nu), which appends to B; T: the triangles, -1 if
+// they are counted by this pass.
+void launch_filter(const Index &ix, int variant, int64_t dmax, const Workspace &ws, const CandBuf &B, int64_t T,
+                   bool one_pass, unsigned grid, int64_t u0, int64_t nu, hipStream_t s) {
+    auto run = [&](auto V, auto M) {
+        FilterSink<decltype(V)::value, decltype(M)::value> sink{};
+        sink.rng = ix.erng.as<uint2>();
+        sink.dq = rng_slack(dmax, ix.rshift);
+        sink.out = B;
+        sink.scal = ws.scal.as<unsigned long long>();
+        if (ix.tri_cached) {
+            k_filter_cached<<<grid, BLK, 0, s>>>(ix.tri.as<int32_t>() + 192 * u0, std::min(T - 64 * u0, 64 * nu), sink);
+        } else {
+            EnumGraph G = enum_graph(ix);
+            G.item += u0;
+            k_tri_enum<<<grid, BLK, 0, s>>>(G, (int32_t)nu, sink);
+        }
+        FOLTY_LAUNCHED();
+    };
+    dispatch_variant(variant, [&](auto V) {
+        if (T < 0) run(V, std::integral_constant<FilterMode, FILTER_COUNT>{});
+        else if (one_pass) run(V, std::integral_constant<FilterMode, FILTER_WIDE>{});
+        else run(V, std::integral_constant<FilterMode, FILTER_NARROW>{});
+    });
+}
+
+// the chunks are free again; the other scalars stay
+__global__ void k_chunks_reset(unsigned long long *__restrict__ scal) {
+    const int i = threadIdx.x;
+    if (i < MAX_REGIONS) scal[SCAL_REGIONS + i * REGION_WORDS + REGION_CHUNKS] = 0;
+    if (i == 0) scal[SCAL_DROPPED] = scal[SCAL_HEAVY] = 0;
+}
+void reset_chunks(Workspace &ws, hipStream_t s) {
+    k_chunks_reset<<<1, MAX_REGIONS, 0, s>>>(ws.scal.as<unsigned long long>());
+    FOLTY_LAUNCHED();
 }
 
 } // namespace
@@ -457,48 +511,17 @@ int64_t first_chunks(int64_t triangles, int64_t waves) {
 // When the chunks do not suffice, they grow to what the pass would have needed
 // and it is repeated.  The scalars have been cleared.
 CandBuf filter_triangles(Index &ix, int variant, int64_t dmax, Workspace &ws, hipStream_t s, bool one_pass) {
-    const int64_t arena = arena_left();
     int64_t T = ix.T.load();
-    const bool cached = ix.tri_cached;
-    const int64_t units = cached ? (T + 63) / 64 : ix.NI;
-    unsigned grid = enum_grid((int32_t)std::min<int64_t>(units, INT32_MAX));
-    if (arena >= 0) grid = std::min(grid, ARENA_ENUM_BLOCKS);
+    const int64_t units = filter_units(ix);
+    const unsigned grid = enum_grid((int32_t)std::min<int64_t>(units, INT32_MAX));
     const int64_t waves = std::min<int64_t>((int64_t)grid * WPB, units);
     const int64_t most = most_chunks(T >= 0 ? T : ix.probes, waves);
-    int64_t chunks = first_chunks(T >= 0 ? T : ix.probes, waves);
-    if (arena < 0) chunks = std::min<int64_t>(most, std::max<int64_t>(chunks, (int64_t)ws.sv.bytes / (CHUNK_BYTES - 4)));
-    else if (chunks * CHUNK_BYTES > arena / 4) chunks = 0; // counted first, then made to fit
-    CandBuf B{};
+    int64_t chunks = std::min<int64_t>(most, std::max<int64_t>(first_chunks(T >= 0 ? T : ix.probes, waves),
+                                                               (int64_t)ws.sv.bytes / (CHUNK_BYTES - 4)));
     for (;;) {
-        const bool sure = chunks >= most;
-        B.regions = (int32_t)std::min<unsigned>(MAX_REGIONS, grid);
-        B.per_region = (int32_t)((chunks + B.regions - 1) / B.regions);
-        const size_t total = (size_t)B.regions * (size_t)B.per_region;
-        ws.sv.ensure((CHUNK_BYTES - 4) * total);
-        ws.svn.ensure(4 * total);
-        unsigned long long *scal = ws.scal.as<unsigned long long>();
-        B.sv = ws.sv.as<int32_t>();
-        B.cnt = ws.svn.as<int32_t>();
-        B.ctr = reinterpret_cast<uint32_t *>(scal + SCAL_REGIONS);
-        B.dropped = reinterpret_cast<uint32_t *>(scal + SCAL_DROPPED);
-        auto run = [&](auto V, auto M) {
-            FilterSink<decltype(V)::value, decltype(M)::value> sink{};
-            sink.rng = ix.erng.as<uint2>();
-            sink.dq = rng_slack(dmax, ix.rshift);
-            sink.out = B;
-            sink.scal = scal;
-            if (cached) k_filter_cached<<<grid, BLK, 0, s>>>(ix.tri.as<int32_t>(), T, sink);
-            else
-                k_tri_enum<<<grid, BLK, 0, s>>>(enum_graph(ix), ix.NI, sink);
-            FOLTY_LAUNCHED();
-        };
-        dispatch_variant(variant, [&](auto V) {
-            if (T < 0) run(V, std::integral_constant<FilterMode, FILTER_COUNT>{});
-            else if (one_pass) run(V, std::integral_constant<FilterMode, FILTER_WIDE>{});
-            else run(V, std::integral_constant<FilterMode, FILTER_NARROW>{});
-        });
-        ws.kept_chunks = (int64_t)total;
-        if (sure) return B;
+        const CandBuf B = make_chunks(ws, grid, chunks);
+        launch_filter(ix, variant, dmax, ws, B, T, one_pass, grid, 0, units, s);
+        if (chunks >= most) return B;
         read_scalars(ws, s, false);
         FOLTY_HIP(hipStreamSynchronize(s));
         const unsigned long long *h = ws.host.as<unsigned long long>();
@@ -511,11 +534,70 @@ CandBuf filter_triangles(Index &ix, int variant, int64_t dmax, Workspace &ws, hi
             ix.T = T;
         }
         chunks = taken + (int64_t)dropped;
-        if (arena >= 0) chunks = std::max<int64_t>(chunks, ARENA_VERTEX_BYTES * (int64_t)ix.n / CHUNK_BYTES);
-        k_fill<unsigned long long><<<1, BLK, 0, s>>>(scal + SCAL_DROPPED, 0ull, SCAL_WORDS - SCAL_DROPPED);
-        FOLTY_LAUNCHED();
+        reset_chunks(ws, s);
     }
 }
+
+namespace {
+
+// The filter and the tests with a fixed scratch: chunks take what is left of it,
+// and when they do not suffice the units are gone over in parts (the tests add up
+// in the per-edge counts, so any split gives the same), each half as long as what
+// did not fit or less.  Afterwards the chunks' part of the scratch is free again.
+constexpr unsigned ARENA_ENUM_BLOCKS = 1024; // fewer partly filled chunks
+template <class Tests>
+void filter_in_arena(Index &ix, const folty_query &q, Workspace &ws, hipStream_t s, bool one_pass, const Tests &tests) {
+    int64_t T = ix.T.load();
+    const int64_t units = filter_units(ix);
+    const size_t mark = arena_mark();
+    auto free_chunks = [&] {
+        ws.sv.forget();
+        ws.svn.forget();
+        ws.pieces.forget();
+        arena_rewind(mark);
+        reset_chunks(ws, s);
+    };
+    for (int64_t u0 = 0, step = units; u0 < units;) {
+        const int64_t nu = std::min(step, units - u0), left = arena_left();
+        // the list of heavy triangles takes what the chunks leave
+        const int64_t room = (left - std::max<int64_t>(left / 16, 1024)) / CHUNK_BYTES;
+        // half of the chunks may be partly filled, one by each wavefront
+        const unsigned grid = (unsigned)std::max<int64_t>(
+            1, std::min({(int64_t)enum_grid((int32_t)std::min<int64_t>(nu, INT32_MAX)), (int64_t)ARENA_ENUM_BLOCKS,
+                         room / (2 * WPB)}));
+        const int64_t most = most_chunks(T >= 0 ? T : ix.probes, std::min<int64_t>((int64_t)grid * WPB, nu));
+        // make_chunks gives every region as many
+        const int64_t chunks = std::min(most, room + 1 - std::min<int64_t>(MAX_REGIONS, grid));
+        if (chunks < most && chunks < 1)
+            fail(FOLTY_ENOMEM, "this call needs more than its fixed device scratch: %lld bytes are left for triangles",
+                 (long long)left);
+        const CandBuf B = make_chunks(ws, grid, chunks);
+        launch_filter(ix, q.variant, q.delta, ws, B, T, one_pass, grid, u0, nu, s);
+        if (chunks < most) {
+            read_scalars(ws, s, false);
+            FOLTY_HIP(hipStreamSynchronize(s));
+            if (T < 0) { // the first part is all of it
+                T = region_sum(ws, REGION_HITS);
+                ix.T = T;
+            }
+            const uint32_t dropped = (uint32_t)ws.host.as<unsigned long long>()[SCAL_DROPPED];
+            if (dropped) {
+                const int64_t need = chunks_taken(ws, B) + dropped;
+                if (nu == 1)
+                    fail(FOLTY_ENOMEM, "this call needs more than its fixed device scratch: %lld bytes for one part of "
+                         "the triangles, %lld left", (long long)(need * CHUNK_BYTES), (long long)left);
+                step = std::max<int64_t>(1, std::min(nu / 2, nu * chunks / (2 * need)));
+                free_chunks();
+                continue;
+            }
+        }
+        if (ws.kept_chunks > 0) tests(B);
+        free_chunks();
+        u0 += nu;
+    }
+}
+
+} // namespace
 
 // After the query's scalars are on the host: the number of triangles on the first
 // query, the filter's passes, and the switch to one pass for later queries.
@@ -990,34 +1072,106 @@ static const uint32_t *query_counts(Graph *g, const folty_query &q, Workspace &w
     FOLTY_HIP(hipEventRecord(ws.ev[0], s));
     clear_query(ix, ws, true, s);
     uint32_t *count = ws.count.as<uint32_t>();
-    FOLTY_HIP(hipEventRecord(ws.ev[4], s));
     if (ix.NI > 0) {
         const bool ss = (q.flags & FOLTY_QUERY_SMALLER_SIDE) != 0;
-        const CandBuf B = filter_triangles(ix, q.variant, q.delta, ws, s, *one_pass);
-        FOLTY_HIP(hipEventRecord(ws.ev[5], s));
-        if (ws.kept_chunks > 0) {
-            if (ss) {
-                // runs with a shorter L2 mark edge ranges in diff; its prefix sum is added at the end
-                ws.diff.ensure(4 * (2 * (size_t)ix.m + 1));
-                int32_t *diff = ws.diff.as<int32_t>(), *ps = diff + ix.m + 1;
-                k_fill<int32_t><<<grid_for(ix.m + 1, BLK, PERSIST_BLOCKS), BLK, 0, s>>>(diff, 0, ix.m + 1);
-                FOLTY_LAUNCHED();
-                DirectOp op{q.delta, count, diff};
-                launch_temporal<true>(ix, q.variant, q.delta, ws, B, op, s);
-                size_t need = inclusive_scan_i32(nullptr, 0, diff, ps, ix.m, s);
-                ws.cub.ensure(need);
-                inclusive_scan_i32(ws.cub.p, need, diff, ps, ix.m, s);
-                k_add_counts<<<grid_for(ix.m, BLK, PERSIST_BLOCKS), BLK, 0, s>>>(ps, ix.m, count);
-                FOLTY_LAUNCHED();
-            } else {
-                launch_temporal<false>(ix, q.variant, q.delta, ws, B, DirectOp{q.delta, count, nullptr}, s);
-            }
+        int32_t *diff = nullptr;
+        if (ss) {
+            // runs with a shorter L2 mark edge ranges in diff; its prefix sum is added at the end
+            ws.diff.ensure(4 * (2 * (size_t)ix.m + 1));
+            diff = ws.diff.as<int32_t>();
+            k_fill<int32_t><<<grid_for(ix.m + 1, BLK, PERSIST_BLOCKS), BLK, 0, s>>>(diff, 0, ix.m + 1);
+            FOLTY_LAUNCHED();
+        }
+        auto tests = [&](const CandBuf &B) {
+            if (ss) launch_temporal<true>(ix, q.variant, q.delta, ws, B, DirectOp{q.delta, count, diff}, s);
+            else launch_temporal<false>(ix, q.variant, q.delta, ws, B, DirectOp{q.delta, count, nullptr}, s);
+        };
+        FOLTY_HIP(hipEventRecord(ws.ev[4], s));
+        if (arena_left() >= 0) {
+            filter_in_arena(ix, q, ws, s, *one_pass, tests);
+            FOLTY_HIP(hipEventRecord(ws.ev[5], s));
+        } else {
+            const CandBuf B = filter_triangles(ix, q.variant, q.delta, ws, s, *one_pass);
+            FOLTY_HIP(hipEventRecord(ws.ev[5], s));
+            if (ws.kept_chunks > 0) tests(B);
+        }
+        if (ss) {
+            int32_t *ps = diff + ix.m + 1;
+            size_t need = inclusive_scan_i32(nullptr, 0, diff, ps, ix.m, s);
+            ws.cub.ensure(need);
+            inclusive_scan_i32(ws.cub.p, need, diff, ps, ix.m, s);
+            k_add_counts<<<grid_for(ix.m, BLK, PERSIST_BLOCKS), BLK, 0, s>>>(ps, ix.m, count);
+            FOLTY_LAUNCHED();
         }
     } else {
+        FOLTY_HIP(hipEventRecord(ws.ev[4], s));
         FOLTY_HIP(hipEventRecord(ws.ev[5], s));
     }
     FOLTY_HIP(hipEventRecord(ws.ev[2], s));
     return count;
+}
+
+// Rows of the oriented graph by the edges (u, v) that meet them: out[0] += rows u with
+// an edge to a row v that is no longer; a bit is set per row v with an edge from a
+// shorter row u.
+__global__ __launch_bounds__(BLK) void k_row_sides(const int32_t *__restrict__ ooff, const int32_t *__restrict__ oadj,
+                                                   int32_t n, uint32_t *__restrict__ bits,
+                                                   unsigned long long *__restrict__ out) {
+    unsigned long long c = 0;
+    for (int64_t u = (int64_t)blockIdx.x * BLK + threadIdx.x; u < n; u += (int64_t)gridDim.x * BLK) {
+        const int32_t b = ooff[u], e = ooff[u + 1];
+        bool any = false;
+        for (int32_t p = b; p < e; p++) {
+            const int32_t v = oadj[p];
+            if (ooff[v + 1] - ooff[v] <= e - b) any = true;
+            else if (bits) atomicOr(&bits[v >> 5], 1u << (v & 31));
+        }
+        c += any;
+    }
+    for (int o = 32; o > 0; o >>= 1) c += __shfl_xor(c, o);
+    if (lane_id() == 0 && c) atomicAdd(out, c);
+}
+__global__ __launch_bounds__(BLK) void k_count_bits(const uint32_t *__restrict__ bits, int64_t words,
+                                                    unsigned long long *__restrict__ out) {
+    unsigned long long c = 0;
+    for (int64_t i = (int64_t)blockIdx.x * BLK + threadIdx.x; i < words; i += (int64_t)gridDim.x * BLK)
+        c += __popc(bits[i]);
+    for (int o = 32; o > 0; o >>= 1) c += __shfl_xor(c, o);
+    if (lane_id() == 0 && c) atomicAdd(out, c);
+}
+
+// The graphs that a fixed scratch takes are a matter of their sizes alone, the same
+// for every window (folty.h): 4 bytes per edge, 32 per static edge and 36 per side of
+// a row have to fit.  That is a promise, and more than the buffers need: the sides
+// are counted only for graphs near the limit.
+static void check_scratch(const Index &ix, Workspace &ws, hipStream_t s) {
+    const int64_t cap = arena_left(), edges = 4 * (int64_t)ix.m + 32 * (int64_t)ix.S;
+    int64_t need = edges;
+    if (edges <= cap && edges + 36 * (int64_t)ix.S > cap) { // at least one edge to a side
+        ws.scal.ensure(SCAL_ALL_BYTES);
+        ws.host.ensure(SCAL_ALL_BYTES);
+        unsigned long long *out = ws.scal.as<unsigned long long>();
+        k_fill<unsigned long long><<<1, 1, 0, s>>>(out, 0ull, 1);
+        const size_t mark = arena_mark();
+        const int64_t words = ((int64_t)ix.n + 31) / 32;
+        DevBuf bits;
+        if (4 * words + 256 <= arena_left()) {
+            bits.ensure(4 * (size_t)words);
+            k_fill<uint32_t><<<grid_for(words, BLK, 1024), BLK, 0, s>>>(bits.as<uint32_t>(), 0u, words);
+        }
+        k_row_sides<<<grid_for(ix.n, BLK, 256), BLK, 0, s>>>(ix.ooff.as<int32_t>(), ix.oadj.as<int32_t>(), ix.n,
+                                                             bits.as<uint32_t>(), out);
+        if (bits.p) k_count_bits<<<grid_for(words, BLK, 256), BLK, 0, s>>>(bits.as<uint32_t>(), words, out);
+        FOLTY_LAUNCHED();
+        bits.forget();
+        arena_rewind(mark);
+        FOLTY_HIP(hipMemcpyAsync(ws.host.p, out, 8, hipMemcpyDeviceToHost, s));
+        FOLTY_HIP(hipStreamSynchronize(s));
+        need += 36 * *ws.host.as<int64_t>();
+    }
+    if (need > cap)
+        fail(FOLTY_ENOMEM, "this call needs more than the %lld bytes of its fixed device scratch (%lld)", (long long)cap,
+             (long long)need);
 }
 
 void run_query_into(Graph *g, const folty_query &q, Workspace &ws, int32_t *pair_u, int32_t *pair_v,
@@ -1035,6 +1189,7 @@ void run_query_into(Graph *g, const folty_query &q, Workspace &ws, int32_t *pair
         fail(FOLTY_EINVAL, "FOLTY_QUERY_ONE_PASS needs the graph's per-item triangle offsets, which this call does "
                            "not build: run one query with that flag through folty_run_fol_query first");
     hipStream_t s = g->stream;
+    if (arena_left() >= 0) check_scratch(ix, ws, s);
     bool one_pass = false;
     const uint32_t *count = query_counts(g, q, ws, s, &one_pass);
     threshold_pairs(g, q, count, ws, s, false);

@@ -71,3 +71,52 @@ def test_noalloc_pair_capacity_and_scratch_limit():
     assert "scratch" in str(ei.value)
     # the scratch is still fine for the next call
     same_as_query(G, 10**6, (1, 4), 3)
+
+
+def spread_ids(n, ids, m, seed):
+    """m edges between ids of n vertices, the others without any."""
+    rng = np.random.default_rng(seed)
+    label = rng.choice(n, ids, replace=False).astype(np.int32)
+    return label[rng.integers(0, ids, m)], label[rng.integers(0, ids, m)], np.sort(rng.integers(0, 10**6, m))
+
+
+def test_noalloc_takes_few_edges_on_many_ids():
+    """The scratch is shared by what the edges need, whatever the number of vertices:
+    the first call on the index, which counts its triangles, and later ones."""
+    src, dst, t = spread_ids(4_000_000, 20_000, 500_000, 45)
+    G = folty.Graph(4_000_000, src, dst, t).build()
+    say("many ids, first call")
+    out = outputs(G, G.m)
+    got = G.query_noalloc(10**6, (1, 100), 0, **out)
+    want = G.query(10**6, (1, 100), 0)
+    assert got["n_pairs"] == want.pair_u.size and got["n_certificates"] == want.n_certificates
+    assert np.array_equal(got["edge_count"].cpu().numpy().view(np.uint32), want.counts())
+    for delta, variant in ((10**6, 0), (20_000, 6)):
+        say("many ids", delta, variant)
+        got = same_as_query(G, delta, (1, 100), variant)
+        assert got["n_pairs"] > 0
+
+
+@pytest.mark.parametrize("cached", [False, True])
+def test_noalloc_tests_triangles_in_parts(cached):
+    """All triangles of a 400-vertex clique (10.6 million, 127 MB as a list) are kept:
+    several times the scratch, so they are tested in parts, on a fresh index (which
+    counts them) and later ones, from items and from the cached list."""
+    k = 400
+    a, b = np.triu_indices(k, 1)
+    rng = np.random.default_rng(46)
+    flip = rng.random(a.size) < 0.5
+    src = np.where(flip, b, a).astype(np.int32)
+    dst = np.where(flip, a, b).astype(np.int32)
+    t = np.sort(rng.integers(0, 10**6, a.size))
+    G = folty.Graph(k, src, dst, t).build(cache_triangles=cached)
+    H = folty.Graph(k, src, dst, t).build(cache_triangles=cached)  # queried without a prior count
+    for delta, variant, side in ((10**6, 0, False), (10**6, 5, False), (10**6, 0, True)):
+        say("clique in parts", cached, delta, variant, side)
+        same_as_query(G, delta, (1, 4), variant, smaller_side=side)
+        want = G.query(delta, (1, 4), variant)
+        out = outputs(H, want.pair_u.size + 1)
+        got = H.query_noalloc(delta, (1, 4), variant, smaller_side=side, **out)
+        assert got["n_certificates"] == want.n_certificates
+        assert np.array_equal(got["edge_count"].cpu().numpy().view(np.uint32), want.counts())
+    assert H.stats()["triangles"] == k * (k - 1) * (k - 2) // 6
