@@ -439,10 +439,18 @@ namespace {
 // no pass has to be repeated and the host reads nothing back in between.
 constexpr int64_t SAFE_CHUNKS = 1 << 16;
 
-// chunks allocated at first for a graph of at most `triangles` triangles
-int64_t first_chunks(int64_t triangles, int64_t waves) {
-    const int64_t most = most_chunks(triangles, waves);
-    return most <= SAFE_CHUNKS ? most : std::max<int64_t>(SAFE_CHUNKS, most / 8);
+// chunks allocated at first for a graph of at most `triangles` triangles, in a
+// workspace that has some: more than the safe ones only out of plenty, so that the
+// rest of the query has room, and otherwise none (the pass then counts what it needs)
+int64_t first_chunks(int64_t triangles, int64_t waves, const Workspace &ws) {
+    const int64_t most = most_chunks(triangles, waves), have = (int64_t)ws.sv.bytes / (CHUNK_BYTES - 4);
+    const int64_t chunks = std::min(most, std::max({SAFE_CHUNKS, most / 8, have}));
+    if (chunks > SAFE_CHUNKS && chunks > have) {
+        size_t fr = 0, tot = 0;
+        FOLTY_HIP(hipMemGetInfo(&fr, &tot));
+        if (chunks * CHUNK_BYTES > (int64_t)((fr + dev_cached()) / 4)) return have;
+    }
+    return chunks;
 }
 
 // What a filter pass goes over: the index's enumeration items, or groups of 64
@@ -508,18 +516,25 @@ void reset_chunks(Workspace &ws, hipStream_t s) {
 // a.5 for one predicate code and window bound: one pass over the enumeration
 // items (or the cached triangles) appends the triangles it keeps to the
 // workspace's chunks.  The first pass over an index also counts its triangles.
-// When the chunks do not suffice, they grow to what the pass would have needed
-// and it is repeated.  The scalars have been cleared.
+// When the chunks do not suffice, or there is no memory for the first of them, they
+// grow to what the pass would have needed and it is repeated.  The scalars have
+// been cleared.
 CandBuf filter_triangles(Index &ix, int variant, int64_t dmax, Workspace &ws, hipStream_t s, bool one_pass) {
     int64_t T = ix.T.load();
     const int64_t units = filter_units(ix);
     const unsigned grid = enum_grid((int32_t)std::min<int64_t>(units, INT32_MAX));
     const int64_t waves = std::min<int64_t>((int64_t)grid * WPB, units);
     const int64_t most = most_chunks(T >= 0 ? T : ix.probes, waves);
-    int64_t chunks = std::min<int64_t>(most, std::max<int64_t>(first_chunks(T >= 0 ? T : ix.probes, waves),
-                                                               (int64_t)ws.sv.bytes / (CHUNK_BYTES - 4)));
-    for (;;) {
-        const CandBuf B = make_chunks(ws, grid, chunks);
+    int64_t chunks = first_chunks(T >= 0 ? T : ix.probes, waves, ws);
+    for (bool counted = false;; counted = true) {
+        CandBuf B;
+        try {
+            B = make_chunks(ws, grid, chunks);
+        } catch (const Error &e) {
+            if (e.code != FOLTY_ENOMEM || counted) throw;
+            chunks = 0;
+            B = make_chunks(ws, grid, 0);
+        }
         launch_filter(ix, variant, dmax, ws, B, T, one_pass, grid, 0, units, s);
         if (chunks >= most) return B;
         read_scalars(ws, s, false);

@@ -332,3 +332,36 @@ def test_range_codes_at_their_ends(offset, span, low, high):
     for r, (d, v) in zip(plan.run(), [(d, v) for d in deltas for v in (0, 5)]):
         assert_same(r, o.query(d, 1, 4, v))
     plan.close()
+
+
+def cliques(count, size, span, seed):
+    rng = np.random.default_rng(seed)
+    a, b = np.triu_indices(size, 1)
+    src = np.concatenate([a + c * size for c in range(count)]).astype(np.int32)
+    dst = np.concatenate([b + c * size for c in range(count)]).astype(np.int32)
+    return synth.TemporalGraph(n=count * size, src=src, dst=dst, t=np.sort(rng.integers(0, span, src.size)))
+
+
+def test_filter_counts_first_when_memory_is_short():
+    """An eighth of 1.02 billion triangles is 1.5 GB of chunks: with 1.2 GB of device
+    memory free the filter counts what its window keeps and allocates that."""
+    import torch
+    g = cliques(12, 800, 10**7, 61)
+    G = folty.Graph(g.n, g.src, g.dst, g.t).build()
+    assert G.stats()["triangles"] == 12 * (800 * 799 * 798 // 6)
+    ws = folty.Workspace()
+    folty.release_cached_memory()
+    torch.cuda.synchronize()
+    fill = []
+    for _ in range(3):
+        k = torch.cuda.mem_get_info()[0] - (1200 << 20)
+        if k > 0:
+            fill.append(torch.empty(k, dtype=torch.uint8, device="cuda:0"))
+    say("short of memory:", torch.cuda.mem_get_info()[0])
+    r = G.query(10_000, (1, 1000), 0, counts=False, workspace=ws)
+    del fill
+    torch.cuda.empty_cache()
+    want = G.query(10_000, (1, 1000), 0, counts=False)
+    assert r.pair_u.size > 0 and r.pairs() == want.pairs() and r.stats["tests"] == want.stats["tests"]
+    ws.close()
+    folty.release_cached_memory()
