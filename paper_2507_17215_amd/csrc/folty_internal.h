@@ -347,6 +347,8 @@ struct Workspace {
     DevBuf svn;     // int32[] slots filled of each chunk
     DevBuf pieces;  // Heavy[]     the temporal step's triangles with many tests
     int64_t kept_chunks = 0;        // chunks the last filter took, or an upper bound
+    int64_t kept_most = 0;          // triangles it kept, or an upper bound
+    bool bounded = false;           // its buffers stay within query_footprint (graphs whose triangles are known)
     int32_t filter_passes = 0;      // passes of the last filter over its triangles
     DevBuf ncert;   // uint32[2S]
     DevBuf pairs_k; // uint64[2S]

@@ -471,8 +471,15 @@ CandBuf make_chunks(Workspace &ws, unsigned grid, int64_t chunks) {
     B.ctr = reinterpret_cast<uint32_t *>(scal + SCAL_REGIONS);
     B.dropped = reinterpret_cast<uint32_t *>(scal + SCAL_DROPPED);
     ws.kept_chunks = (int64_t)total;
+    ws.kept_most = 64 * (int64_t)total;
     return B;
 }
+
+// Wavefronts of a bounded workspace's filter when all that it keeps is much: their
+// partly filled chunks take at most 36 bytes per item then, and all chunks together
+// at most bounded_chunks.
+int64_t bounded_waves(const Index &ix) { return std::max<int64_t>(WPB, 36 * (int64_t)ix.NI / CHUNK_BYTES); }
+int64_t bounded_chunks(const Index &ix, int64_t T) { return T / 64 + bounded_waves(ix); }
 
 // The filter over units [u0, u0 + nu), which appends to B; T: the triangles, -1 if
 // they are counted by this pass.
@@ -522,10 +529,15 @@ void reset_chunks(Workspace &ws, hipStream_t s) {
 CandBuf filter_triangles(Index &ix, int variant, int64_t dmax, Workspace &ws, hipStream_t s, bool one_pass) {
     int64_t T = ix.T.load();
     const int64_t units = filter_units(ix);
-    const unsigned grid = enum_grid((int32_t)std::min<int64_t>(units, INT32_MAX));
+    unsigned grid = enum_grid((int32_t)std::min<int64_t>(units, INT32_MAX));
     const int64_t waves = std::min<int64_t>((int64_t)grid * WPB, units);
-    const int64_t most = most_chunks(T >= 0 ? T : ix.probes, waves);
+    int64_t most = most_chunks(T >= 0 ? T : ix.probes, waves);
     int64_t chunks = first_chunks(T >= 0 ? T : ix.probes, waves, ws);
+    // a bounded workspace takes no more than query_footprint says, or keeps what it has
+    const int64_t bound = !ws.bounded || T < 0
+                              ? INT64_MAX
+                              : std::max(bounded_chunks(ix, T), (int64_t)ws.sv.bytes / (CHUNK_BYTES - 4));
+    chunks = std::min(chunks, bound);
     for (bool counted = false;; counted = true) {
         CandBuf B;
         try {
@@ -535,6 +547,7 @@ CandBuf filter_triangles(Index &ix, int variant, int64_t dmax, Workspace &ws, hi
             chunks = 0;
             B = make_chunks(ws, grid, 0);
         }
+        if (T >= 0) ws.kept_most = std::min(ws.kept_most, T);
         launch_filter(ix, variant, dmax, ws, B, T, one_pass, grid, 0, units, s);
         if (chunks >= most) return B;
         read_scalars(ws, s, false);
@@ -543,12 +556,17 @@ CandBuf filter_triangles(Index &ix, int variant, int64_t dmax, Workspace &ws, hi
         const int64_t taken = chunks_taken(ws, B);
         const uint32_t dropped = (uint32_t)h[SCAL_DROPPED];
         ws.kept_chunks = taken;
+        ws.kept_most = std::min(ws.kept_most, 64 * taken);
         if (dropped == 0) return B;
         if (T < 0) {
             T = region_sum(ws, REGION_HITS);
             ix.T = T;
         }
         chunks = taken + (int64_t)dropped;
+        if (chunks > bound) { // fewer wavefronts, and then every triangle fits
+            grid = (unsigned)(bounded_waves(ix) / WPB);
+            most = chunks = most_chunks(T, (int64_t)grid * WPB);
+        }
         reset_chunks(ws, s);
     }
 }
@@ -1264,17 +1282,16 @@ static Result *run_query_impl(Graph *g, const folty_query &q, Workspace &ws, hip
     return res.release();
 }
 
-// Device bytes one single query takes beyond the resident index: per-edge
-// counts, the chunks of the triangles its filter keeps, the smaller-side difference array, per-pair certificate counts,
-// pair keys and their sorted copies, sort and scan scratch, and the per-edge
-// counts handed back.
+// Device bytes one single query in a bounded workspace takes beyond the resident
+// index: per-edge counts, the chunks of the triangles its filter keeps, the
+// smaller-side difference array, per-pair certificate counts, pair keys and their
+// sorted copies, sort and scan scratch, and the per-edge counts handed back.
 int64_t query_footprint(const Graph *g, const folty_query &q) {
     const Index &ix = g->ix;
     const int64_t T = std::max<int64_t>(0, ix.T.load());
     // counts; the filter's chunks (every triangle kept); heavy triangles; pair step
-    const int64_t chunks = most_chunks(T, std::min<int64_t>((int64_t)ENUM_BLOCKS * WPB, ix.NI)) + MAX_REGIONS;
-    int64_t b = 4 * (int64_t)ix.m + CHUNK_BYTES * chunks + (int64_t)sizeof(Heavy) * heavy_slots(64 * chunks) +
-                56 * (int64_t)ix.S + (int64_t)SCAL_BYTES;
+    int64_t b = 4 * (int64_t)ix.m + CHUNK_BYTES * bounded_chunks(ix, T) +
+                (int64_t)sizeof(Heavy) * heavy_slots(T) + 56 * (int64_t)ix.S;
     if (q.flags & FOLTY_QUERY_SMALLER_SIDE) b += 8 * (int64_t)ix.m + 4;
     if (!(q.flags & FOLTY_QUERY_NO_COUNTS)) b += 4 * ix.m_input;
     // the library scratch the query's sorts and scans ask for (sizes only)
@@ -1283,6 +1300,7 @@ int64_t query_footprint(const Graph *g, const folty_query &q) {
                                                         2 * pair_bits(ix.n), nullptr),
                                      inclusive_scan_i32(nullptr, 0, nullptr, nullptr, ix.m, nullptr),
                                      exclusive_scan_i32(nullptr, 0, nullptr, nullptr, ix.n, nullptr)});
+    // scalars, and what allocations are rounded up by
     return b + (int64_t)scratch + (1 << 20);
 }
 

@@ -76,7 +76,12 @@ void Server::worker_main(int me) {
     if (hipSetDevice(device) != hipSuccess) return;
     hipStream_t s = nullptr;
     if (hipStreamCreateWithFlags(&s, hipStreamNonBlocking) != hipSuccess) return;
-    std::unique_ptr<Workspace> ws(new Workspace());
+    std::unique_ptr<Workspace> ws;
+    auto new_workspace = [&] {
+        ws.reset(new Workspace());
+        ws->bounded = true; // admission goes by query_footprint
+    };
+    new_workspace();
     auto set_kept = [&](int64_t b) { // caller holds mu
         kept_total += b - kept[me];
         kept[me] = b;
@@ -132,7 +137,7 @@ void Server::worker_main(int me) {
         if (give_back) {
             {
                 StreamScope sc(s);
-                ws.reset(new Workspace());
+                new_workspace();
             }
             trim_if_over();
             cv_work.notify_all();

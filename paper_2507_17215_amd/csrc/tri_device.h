@@ -1553,7 +1553,7 @@ template <class R>
 void launch_tests(Workspace &ws, const CandBuf &B, const R &runner, int64_t chunks, hipStream_t s) {
     // any capacity gives the same result: a fixed scratch takes the smallest, or what it has left
     const int64_t left = arena_left();
-    const int64_t cap = left < 0 ? heavy_slots(64 * chunks)
+    const int64_t cap = left < 0 ? heavy_slots(ws.kept_most)
                                  : std::max<int64_t>(1, std::min(heavy_slots(0), (left - 256) / (int64_t)sizeof(Heavy)));
     ws.pieces.ensure(sizeof(Heavy) * (size_t)cap);
     unsigned long long *np = ws.scal.as<unsigned long long>() + SCAL_HEAVY;

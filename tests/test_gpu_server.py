@@ -176,3 +176,32 @@ def test_poll_and_ticket_errors():
     with pytest.raises(folty.FoltyError):
         srv.wait(12345)
     srv.close()
+
+
+def test_estimate_counts_items_not_wavefronts():
+    """What a request is charged: 12 bytes per triangle and a sixteenth, 36 per item (a
+    wavefront's partly filled chunk of 772 bytes would be 39 MB on this graph), the list
+    of heavy triangles, and the per-edge and per-pair arrays with the sort's scratch (12
+    bytes and a little per pair).  A window that keeps everything stays within it."""
+    import re
+    g = synth.c1_family(10_000_000, seed=35)
+    G = folty.Graph(g.n, g.src, g.dst, g.t).build()
+    want = G.query(folty.DELTA_INF, (1, 4), 0, counts=False)
+    st = G.stats()
+    m, S, T, NI = st["m"], st["static_edges"], st["triangles"], st["enum_items"]
+    tiny = folty.Server(workers=1, hbm_budget_bytes=1000)
+    with pytest.raises(folty.FoltyError) as ei:
+        tiny.submit(G, delta=folty.DELTA_INF, counts=False)
+    tiny.close()
+    need = int(re.search(r"needs (\d+) bytes", str(ei.value)).group(1))
+    say("estimate", need, "m S T NI", m, S, T, NI)
+    most = 4 * m + 56 * S + 13 * 2 * S + 12 * T + T // 16 + 36 * NI + 16 * max(T + 1, 65_536) + (4 << 20)
+    assert need <= most
+    assert 772 * NI > 2 * (most - need) + (16 << 20)  # a chunk per item would not pass
+    srv = folty.Server(workers=1, hbm_budget_bytes=need)
+    for _ in range(2):
+        r = srv.wait(srv.submit(G, delta=folty.DELTA_INF, theta=(1, 4), counts=False))
+        assert r.pairs() == want.pairs() and r.stats["tests"] == want.stats["tests"]
+        info = srv.info()
+        assert info["kept_bytes"] <= need and info["peak_in_use_bytes"] <= need
+    srv.close()
