@@ -475,7 +475,8 @@ int folty_result_counts(folty_result *r, int64_t *n_certificates, const uint32_t
  *                   (edge_count decides), and the universe N(a) & N(b) needs the
  *                   graph's per-edge triangle counts to exist already (built by a
  *                   folty_run_fol_query with that universe), else FOLTY_EINVAL;
- *                   so does FOLTY_QUERY_ONE_PASS the per-item triangle offsets.
+ *                   so does FOLTY_QUERY_ONE_PASS a count of the triangles (made
+ *                   by a query with that flag, a plan or the server).
  *   pair_u, pair_v, n_cert  device arrays of pair_cap entries (caller-owned):
  *                   the solution pairs sorted by (u, v) and their certificate
  *                   counts.  More than pair_cap pairs: FOLTY_EOVERFLOW, with

@@ -282,10 +282,10 @@ struct Index {
     int32_t S = 0;           // static edges
     int64_t P = 0;           // non-empty directed lists
     int64_t sigma_max = 0;
-    std::atomic<int64_t> T{-1}; // static triangles (-1 until a query or ensure_tri_base counted them)
-    // tri_base holds per-item triangle offsets; stored (release) after tri_base and
-    // T are final, so a reader that loads it (acquire) sees them
-    std::atomic<bool> tri_base_ready{false};
+    std::atomic<int64_t> T{-1}; // static triangles (-1 until a query or ensure_triangles counted them)
+    // something needed them beforehand: the allocation-free call takes
+    // FOLTY_QUERY_ONE_PASS from then on
+    std::atomic<bool> triangles_asked{false};
     // single queries of delta >= this filter in one pass (INT64_MAX: none, until
     // a query kept one triangle in 12)
     std::atomic<int64_t> one_pass_from{INT64_MAX};
@@ -333,7 +333,6 @@ struct Index {
     DevBuf srng;     // uint2[G]  the ranges of each probe segment's edge
     DevBuf owner;    // int32[G]  the owner of each probe segment
     DevBuf item;     // EnumItem[NI]
-    DevBuf tri_base; // int64[NI+1]
     DevBuf tcnt;     // int32[S]  triangles on each static edge = |N(lo) & N(hi)| (computed on first use)
     DevBuf tri;      // int32[3T] cached triangle list (optional): oriented edges (u,v), (u,w), (v,w)
 
@@ -478,8 +477,7 @@ void server_info(Server *s, folty_server_info *info);
 void server_destroy(Server *s);
 // oriented-edge records, triangle counts per lowest vertex, optional triangle cache
 void index_triangles(Index &ix, bool cache, DevBuf &cub, hipStream_t s);
-void ensure_tri_base(Index &ix, hipStream_t s); // caller holds Graph::lazy_mu once the graph is shared
-void ensure_triangles(Graph *g);                 // ensure_tri_base on the graph's stream, under lazy_mu
+void ensure_triangles(Graph *g); // counts the triangles unless they are known, under lazy_mu
 // library-primitive wrappers (rocPRIM), all on `stream`
 size_t sort_pairs_u64_i32(void *tmp, size_t tmp_bytes, const uint64_t *kin, uint64_t *kout,
                           const int32_t *vin, int32_t *vout, int64_t n, int end_bit,

@@ -889,6 +889,8 @@ template <class Sink> static void enumerate_all(const Index &ix, const Sink &sin
     FOLTY_LAUNCHED();
 }
 
+static void count_triangles(Index &ix, DevBuf &base, hipStream_t s);
+
 void index_triangles(Index &ix, bool cache, DevBuf &cub, hipStream_t s) {
     const int32_t n = ix.n, S = ix.S;
     ix.rec.ensure(sizeof(EdgeRec) * ((size_t)S + 1));
@@ -981,17 +983,18 @@ void index_triangles(Index &ix, bool cache, DevBuf &cub, hipStream_t s) {
     ix.NI = ni;
     ix.G = ng;
     ix.probes = probes;
-    // triangle slots per item are made on first use (plans, the server's memory
-    // estimate, the cached list): a single query counts its survivors itself
+    // counted by the first query, or by what needs them before (plans, the server's
+    // memory estimate, the cached list)
     ix.T = -1;
-    ix.tri_base_ready.store(false, std::memory_order_release);
+    ix.triangles_asked.store(cache, std::memory_order_release);
     ix.tri_cached = false;
     ix.tri.release();
     if (cache) {
-        ensure_tri_base(ix, s);
+        DevBuf base;
+        count_triangles(ix, base, s);
         if (ix.T > 0) {
             ix.tri.ensure(12 * (size_t)ix.T);
-            CacheSink sink{ix.tri_base.as<int64_t>(), ix.tri.as<int32_t>(), 0};
+            CacheSink sink{base.as<int64_t>(), ix.tri.as<int32_t>(), 0};
             enumerate_all(ix, sink, s);
             FOLTY_LAUNCHED();
             ix.tri_cached = true;
@@ -1000,46 +1003,36 @@ void index_triangles(Index &ix, bool cache, DevBuf &cub, hipStream_t s) {
 }
 
 
-// per-item triangle offsets from per-item triangle counts tri_it[0, NI) (the
-// counting filter's, or a CountSink pass); tri_it[NI] is set to 0 here
-static void tri_base_from_counts(Index &ix, int32_t *tri_it, hipStream_t s) {
+// counts the triangles (ix.T); base: int64[NI + 1], each item's first slot in a list of them all
+static void count_triangles(Index &ix, DevBuf &base, hipStream_t s) {
     const int32_t ni = ix.NI;
-    ix.tri_base.ensure(8 * ((size_t)ni + 1));
-    DevBuf cub;
-    k_fill<int32_t><<<1, 1, 0, s>>>(tri_it + ni, 0, 1);
+    DevBuf tri_it, cub;
+    tri_it.ensure(4 * ((size_t)ni + 1));
+    base.ensure(8 * ((size_t)ni + 1));
+    if (ni > 0) enumerate_all(ix, CountSink{tri_it.as<int32_t>(), 0}, s);
+    k_fill<int32_t><<<1, 1, 0, s>>>(tri_it.as<int32_t>() + ni, 0, 1);
     FOLTY_LAUNCHED();
-    size_t need = exclusive_scan_i32_to_i64(nullptr, 0, tri_it, ix.tri_base.as<int64_t>(), (int64_t)ni + 1, s);
+    size_t need = exclusive_scan_i32_to_i64(nullptr, 0, tri_it.as<int32_t>(), base.as<int64_t>(), (int64_t)ni + 1, s);
     cub.ensure(need);
-    exclusive_scan_i32_to_i64(cub.p, need, tri_it, ix.tri_base.as<int64_t>(), (int64_t)ni + 1, s);
+    exclusive_scan_i32_to_i64(cub.p, need, tri_it.as<int32_t>(), base.as<int64_t>(), (int64_t)ni + 1, s);
     int64_t T = 0;
-    FOLTY_HIP(hipMemcpyAsync(&T, ix.tri_base.as<int64_t>() + ni, 8, hipMemcpyDeviceToHost, s));
+    FOLTY_HIP(hipMemcpyAsync(&T, base.as<int64_t>() + ni, 8, hipMemcpyDeviceToHost, s));
     FOLTY_HIP(hipStreamSynchronize(s));
     ix.T = T;
-    ix.tri_base_ready.store(true, std::memory_order_release);
-}
-
-// triangles of each enumeration item, their exclusive offsets (the slots of a
-// one-pass filter and of the cached list) and the triangle count
-void ensure_tri_base(Index &ix, hipStream_t s) {
-    if (ix.tri_base_ready.load(std::memory_order_acquire)) return;
-    const int32_t ni = ix.NI;
-    DevBuf tri_it;
-    tri_it.ensure(4 * ((size_t)ni + 1));
-    if (ni > 0) {
-        CountSink cs{tri_it.as<int32_t>(), 0};
-        enumerate_all(ix, cs, s);
-        FOLTY_LAUNCHED();
-    }
-    tri_base_from_counts(ix, tri_it.as<int32_t>(), s);
 }
 
 void ensure_triangles(Graph *g) {
     std::lock_guard<std::mutex> lk(g->lazy_mu);
-    if (g->ix.tri_base_ready.load(std::memory_order_acquire) || !g->ix.built) return;
-    FOLTY_HIP(hipSetDevice(g->device));
-    StreamScope sc(g->stream);
-    HookScope hs(&g->hook);
-    ensure_tri_base(g->ix, g->stream);
+    Index &ix = g->ix;
+    if (!ix.built) return;
+    if (ix.T.load() < 0) {
+        FOLTY_HIP(hipSetDevice(g->device));
+        StreamScope sc(g->stream);
+        HookScope hs(&g->hook);
+        DevBuf base;
+        count_triangles(ix, base, g->stream);
+    }
+    ix.triangles_asked.store(true, std::memory_order_release);
 }
 
 void ensure_tcnt(Index &ix, hipStream_t s) {
@@ -1218,9 +1211,9 @@ void run_query_into(Graph *g, const folty_query &q, Workspace &ws, int32_t *pair
     if (q.universe == FOLTY_UNIVERSE_COMMON && !ix.tcnt_ready)
         fail(FOLTY_EINVAL, "the universe N(a) & N(b) needs the graph's per-edge triangle counts, which this call "
                            "does not build: run one query with that universe through folty_run_fol_query first");
-    if ((q.flags & FOLTY_QUERY_ONE_PASS) && !ix.tri_base_ready.load(std::memory_order_acquire))
-        fail(FOLTY_EINVAL, "FOLTY_QUERY_ONE_PASS needs the graph's per-item triangle offsets, which this call does "
-                           "not build: run one query with that flag through folty_run_fol_query first");
+    if ((q.flags & FOLTY_QUERY_ONE_PASS) && !ix.triangles_asked.load(std::memory_order_acquire))
+        fail(FOLTY_EINVAL, "FOLTY_QUERY_ONE_PASS needs the graph's triangles, which this call does not count "
+                           "beforehand: run one query with that flag through folty_run_fol_query first");
     hipStream_t s = g->stream;
     if (arena_left() >= 0) check_scratch(ix, ws, s);
     bool one_pass = false;

@@ -365,3 +365,25 @@ def test_filter_counts_first_when_memory_is_short():
     assert r.pair_u.size > 0 and r.pairs() == want.pairs() and r.stats["tests"] == want.stats["tests"]
     ws.close()
     folty.release_cached_memory()
+
+
+def test_triangles_known_are_not_counted_again():
+    """After a query the triangle count is known: a one-pass query, a plan and a server
+    request use it (nothing is added to the index), with the results of a graph on
+    which they come first."""
+    g = synth.tiny(seed=12)
+    G = folty.Graph(g.n, g.src, g.dst, g.t).build()
+    fresh = folty.Graph(g.n, g.src, g.dst, g.t).build()
+    G.query(10**6, (1, 4), 0)
+    before = G.device_bytes()
+    for d, v in ((10**6, 0), (3600, 3)):
+        want = fresh.query(d, (1, 4), v, one_pass=True)
+        got = G.query(d, (1, 4), v, one_pass=True)
+        assert got.pairs() == want.pairs() and got.stats["triangles"] == want.stats["triangles"] > 0
+    plan = folty.Plan([G], [(0, dict(delta=10**6, theta=(1, 4), variant=0))])
+    assert plan.run()[0].pairs() == G.query(10**6, (1, 4), 0).pairs()
+    plan.close()
+    srv = folty.Server(workers=1)
+    assert srv.wait(srv.submit(G, delta=10**6, theta=(1, 4))).pairs() == G.query(10**6, (1, 4), 0).pairs()
+    srv.close()
+    assert G.device_bytes() == before
