@@ -1022,7 +1022,7 @@ void plan_run(Plan *P, Result **outs) {
         Result *r = res[q].get();
         const Graph *g = P->graphs[P->qgraph[q]];
         fill_stats_from_index(g->ix, &r->stats);
-        r->stats.filter_passes = 1; // plans enumerate once for all their queries
+        r->stats.filter_passes = g->ix.NI > 0 ? 2 : 0; // known edges, then triangles (FILTER_NARROW)
         r->stats.n_pairs = (int64_t)r->u.size();
         r->stats.n_certificates = r->n_certificates;
         r->stats.query_ms = P->last_ms / std::max(1, nq);

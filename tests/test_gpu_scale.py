@@ -387,3 +387,18 @@ def test_triangles_known_are_not_counted_again():
     assert srv.wait(srv.submit(G, delta=10**6, theta=(1, 4))).pairs() == G.query(10**6, (1, 4), 0).pairs()
     srv.close()
     assert G.device_bytes() == before
+
+
+def test_plan_results_state_the_filter_passes():
+    """Known edges first, then triangles, as in a single query of a fresh graph; none
+    without closing probes (a path)."""
+    g = synth.tiny(seed=13)
+    G = folty.Graph(g.n, g.src, g.dst, g.t).build()
+    ids = np.arange(9, dtype=np.int32)
+    P = folty.Graph(10, ids, ids + 1, np.arange(9, dtype=np.int64)).build()
+    plan = folty.Plan([G, P], [(0, dict(delta=10**6, theta=(1, 4))), (1, dict(delta=5, theta=(1, 4)))])
+    for _ in range(2):
+        assert [r.stats["filter_passes"] for r in plan.run()] == [2, 0]
+    plan.close()
+    assert G.query(3600, (1, 4), 0).stats["filter_passes"] == 2
+    assert P.query(5, (1, 4), 0).stats["filter_passes"] == 0
