@@ -6,7 +6,7 @@
 // still use it carries an event recorded on that stream; a reuse on another
 // stream waits for that event first, a reuse on the same stream is ordered by
 // the stream itself.  Every public call synchronises its stream before it
-// returns, so blocks freed outside any call are idle.
+// returns, also with an error (StreamScope), so blocks freed outside any call are idle.
 #include <exception>
 #include <map>
 #include <mutex>
@@ -59,8 +59,11 @@ void drop_block(Block &b) {
 
 } // namespace
 
-StreamScope::StreamScope(hipStream_t s) : prev(t_stream) { t_stream = s; }
-StreamScope::~StreamScope() { t_stream = prev; }
+StreamScope::StreamScope(hipStream_t s) : prev(t_stream), unwinding(std::uncaught_exceptions()) { t_stream = s; }
+StreamScope::~StreamScope() {
+    if (std::uncaught_exceptions() > unwinding && t_stream) (void)hipStreamSynchronize(t_stream);
+    t_stream = prev;
+}
 
 HookScope::HookScope(const AllocHook *h) : prev(t_hook) { t_hook = h && h->set() ? h : nullptr; }
 HookScope::~HookScope() { t_hook = prev; }

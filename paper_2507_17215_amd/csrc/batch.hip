@@ -977,6 +977,7 @@ void plan_run(Plan *P, Result **outs) {
     HostVec<uint64_t> keys(npairs);
     HostVec<uint32_t> vals(npairs);
     if (npairs > 0) {
+        StreamScope copies(s); // an error waits for the copies into them before they go
         P->keys2.ensure(8 * (size_t)npairs);
         P->vals2.ensure(4 * (size_t)npairs);
         int kb = bit_length((uint64_t)std::max(1, nq)) + 2 * P->nbits;

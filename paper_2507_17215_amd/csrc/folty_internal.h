@@ -46,9 +46,12 @@ void set_last_error(const char *msg);
 // ---------------------------------------------------------------------------
 // device memory: a caching allocator (alloc.hip) and a growable buffer on it
 // ---------------------------------------------------------------------------
-// The stream that buffers allocated or freed on this thread are used with.
+// The stream that buffers allocated or freed on this thread are used with.  A scope
+// left by an exception waits for its stream: what the failed call started may still
+// write to buffers that are given back after it.
 struct StreamScope {
     hipStream_t prev;
+    int unwinding; // exceptions in flight when the scope began
     explicit StreamScope(hipStream_t s);
     ~StreamScope();
 };

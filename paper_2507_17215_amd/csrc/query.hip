@@ -1253,6 +1253,7 @@ static Result *run_query_impl(Graph *g, const folty_query &q, Workspace &ws, hip
         FOLTY_HIP(hipStreamSynchronize(s));
     }
     std::unique_ptr<Result> res(new Result());
+    StreamScope sc(s); // an error waits for the copies into res before res goes
     bool one_pass = false;
     const uint32_t *count = query_counts(g, q, ws, s, &one_pass);
     const int32_t *first = finish_query(g, q, count, ws, res.get(), s, vq && vq->inner == FOLTY_INNER_EXISTS);

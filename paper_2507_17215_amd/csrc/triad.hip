@@ -413,6 +413,7 @@ Result *run_triad_query(Graph *g, const folty_triad_query &q, Workspace &ws) {
     const bool edge = (q.flags & FOLTY_TRIAD_EDGE_INSTANCES) != 0;
     const bool inst = edge || (q.flags & FOLTY_TRIAD_INSTANCES) != 0;
     std::unique_ptr<Result> res(new Result());
+    StreamScope sc(s); // an error waits for the copies into res before res goes
     res->triad = true;
     res->device = g->device;
     ws.ensure_events();

@@ -402,3 +402,39 @@ def test_plan_results_state_the_filter_passes():
     plan.close()
     assert G.query(3600, (1, 4), 0).stats["filter_passes"] == 2
     assert P.query(5, (1, 4), 0).stats["filter_passes"] == 0
+
+
+def test_a_failed_call_waits_for_its_stream():
+    """Buffers of a failed call go back to pools that other streams take from: the call
+    returns its error only when its stream is idle (40 products are queued on it here
+    before a query whose first allocation fails), and the same query answers after."""
+    import ctypes
+    import torch
+    g = synth.tiny(seed=14)
+    stream = torch.cuda.Stream()
+    G = folty.Graph(g.n, g.src, g.dst, g.t, stream=stream.cuda_stream)
+    dev, refuse = torch.cuda.current_device(), []
+
+    def alloc(nbytes, st, ctx):
+        return None if refuse else torch.cuda.caching_allocator_alloc(int(nbytes), dev, int(st or 0))
+
+    opts = folty.BuildOpts(0, 0, 0, folty.ALLOC_FN(alloc),
+                           folty.FREE_FN(lambda p, nbytes, st, ctx: torch.cuda.caching_allocator_delete(p)), None)
+    assert folty.load_library().folty_build_index(G._h, ctypes.byref(opts)) == folty.OK
+    G.query(10**6, (1, 4), 0)
+    a = torch.ones(8192, 8192, device="cuda:0", dtype=torch.bfloat16)
+    torch.cuda.synchronize()
+    with torch.cuda.stream(stream):
+        for _ in range(40):
+            a @ a
+    refuse.append(1)
+    # N(a) & N(b): the per-edge triangle counts are made on first use, in the caller's memory
+    with pytest.raises(folty.FoltyError) as ei:
+        G.query(10**6, (1, 4), 0, folty.UNIVERSE_COMMON)
+    idle = stream.query()
+    say("failed query", ei.value.code, idle)
+    assert ei.value.code == folty.ENOMEM and idle
+    refuse.clear()
+    o = Oracle(g.n, g.src, g.dst, g.t)
+    assert_same(G.query(10**6, (1, 4), 0, folty.UNIVERSE_COMMON), o.query(10**6, 1, 4, 0, folty.UNIVERSE_COMMON))
+    G.close()
