@@ -565,7 +565,8 @@ static void clear_hist(Plan &P, int j, hipStream_t s) {
 static void enqueue_tests(Plan &P, int ipt, int blocks, hipStream_t s) {
     if (P.chunks <= 0) return;
     unsigned long long *scal = P.scal.as<unsigned long long>();
-    const unsigned lb = (unsigned)std::max<int64_t>(1, std::min<int64_t>((P.chunks + WPB - 1) / WPB, blocks));
+    const unsigned lb = (unsigned)std::max<int64_t>(
+        1, std::min({(P.chunks + WPB - 1) / WPB, (int64_t)blocks, MOST_TEST_BLOCKS}));
     k_plan_light<<<lb, BLK, 0, s>>>(P.cand, P.d_groups.as<GroupDev>(), P.d_gjobs.as<int32_t>(), P.d_jobs.as<JobDev>(),
                                     P.heavy.as<Heavy>(), scal + SCAL_HEAVY, P.heavy_cap, ipt, scal);
     const unsigned pb = (unsigned)std::max<int64_t>(1, std::min<int64_t>(P.chunks * 16, PIECE_BLOCKS));

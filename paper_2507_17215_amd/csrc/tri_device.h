@@ -1295,7 +1295,7 @@ template <int VAR, class Op, bool SS> struct CountRunner {
 // one.  `full` is set once this wavefront's atomic returned an entry count of cap
 // or more, after which it lists nothing: each wavefront adds at most 64 entries
 // past cap, so the entry count stays below cap + 64 x (the grid's wavefronts),
-// far below 2^24.
+// below 2^24 (the static assertion at MOST_TEST_BLOCKS).
 __device__ inline bool defer_heavy(int64_t slot, int64_t np, Heavy *__restrict__ heavy,
                                    unsigned long long *__restrict__ counter, int64_t cap, bool &full) {
     if (full || !__ballot(np > 0)) return false;
@@ -1530,6 +1530,11 @@ constexpr int64_t MAX_HEAVY = 1 << 22; // 64 MB of heavy-survivor entries at mos
 constexpr int64_t MIN_HEAVY = 1 << 16; // room for this many whatever the survivors
 constexpr int64_t LIGHT_BLOCKS = 4096; // a group per wavefront or two; 16,384 blocks mostly started for nothing
 constexpr int64_t PIECE_BLOCKS = 8192;
+// A plan's block count may come from a file: more than this many could take the count
+// of heavy triangles past its 24 bits (and have no use: tried shapes end at 16,384).
+constexpr int64_t MOST_TEST_BLOCKS = 32768;
+static_assert(MAX_HEAVY + 64 * WPB * MOST_TEST_BLOCKS < (int64_t)1 << (64 - HEAVY_SHIFT) && LIGHT_BLOCKS <= MOST_TEST_BLOCKS,
+              "entries of the heavy list's counter");
 
 // the heavy list's capacity limit: MAX_HEAVY, or FOLTY_MAX_HEAVY (>= 1) when set
 inline int64_t max_heavy() {

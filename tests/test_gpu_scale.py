@@ -438,3 +438,37 @@ def test_a_failed_call_waits_for_its_stream():
     o = Oracle(g.n, g.src, g.dst, g.t)
     assert_same(G.query(10**6, (1, 4), 0, folty.UNIVERSE_COMMON), o.query(10**6, 1, 4, 0, folty.UNIVERSE_COMMON))
     G.close()
+
+
+def test_plan_takes_a_tuning_file_with_more_blocks_than_run(tmp_path):
+    """A tuning file may name up to 2^20 blocks; the launch is held to what the heavy
+    list's counter allows, results are the single queries' (a child process: the table
+    lives as long as the process)."""
+    import json
+    import os
+    import subprocess
+    import sys
+    path = tmp_path / "tune.json"
+    path.write_text(json.dumps(dict(arch="gfx950", entries=[
+        dict(tests_log2=a, edges_log2=b, tests_per_chunk=2, blocks=1 << 20, ms=1.0) for a in range(40) for b in range(32)])))
+    code = r"""
+import numpy as np
+from paper_2507_17215_amd import folty
+rng = np.random.default_rng(15)
+n, m = 60, 60_000  # long lists: most triangles have more than 64 tests
+src, dst, t = rng.integers(0, n, m), rng.integers(0, n, m), np.sort(rng.integers(0, 10**6, m))
+G = folty.Graph(n, src.astype(np.int32), dst.astype(np.int32), t).build()
+qs = [dict(delta=d, theta=(1, 4), variant=v) for d in (500, 20_000) for v in (0, 5)]
+plan = folty.Plan([G], [(0, q) for q in qs])
+for _ in range(2):
+    for q, r in zip(qs, plan.run()):
+        w = G.query(**q)
+        assert np.array_equal(r.counts(), w.counts()) and r.pairs() == w.pairs()
+assert plan.info()["temporal_blocks"] == 1 << 20 and plan.info()["tune_source"] == 2, plan.info()
+print("ok")
+"""
+    root = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+    out = subprocess.run([sys.executable, "-c", code], capture_output=True, text=True, timeout=110, cwd=root,
+                         env=dict(os.environ, FOLTY_TUNE_CACHE=str(path)))
+    say("tuning file:", out.stdout.strip(), out.stderr[-1500:])
+    assert out.returncode == 0 and out.stdout.strip() == "ok"
