@@ -1373,16 +1373,18 @@ __device__ inline void spread_units(Lds &F, int32_t incl, bool own, const Flat &
 // time across chunks.  Groups of up to 64 chunks, fewer when that would leave
 // less than GROUPS_WANTED groups (8,192 and 4,096 of them were slower: 1.70 ms
 // against 1.62 at one year, 0.15 against 0.11 for 10M uniform edges); with few
-// chunks each is shared by up to eight wavefronts, since a wavefront's tests are a
-// chain of dependent reads (temporal step, one / two / four / eight wavefronts per
-// chunk: 500 triangles 20 / - / 15 / 14 us, 19,000 in 5,200 chunks 37 / 30 / 47 / 61).
+// chunks each is shared by two or eight wavefronts, since a wavefront's tests are a
+// chain of dependent reads.  Temporal step with one / two / four / eight wavefronts
+// per chunk, us: 165 triangles in 164 chunks 14.8 / 13.6 / 13.3 / 13.4; 1,002 in 828
+// 18.7 / 18.9 / 22.5 / 28.9; 17,400 in 2,050 38.7 / 30.1 / 32.9 / 46.3; 38,600 in
+// 4,640 40.4 / 41.2 / 49.7 / 76.2; 17,800 in 5,120 36.3 / 44.2 / 59.6 / 87.8.
 constexpr int32_t GROUPS_WANTED = 16384;
 __device__ inline int32_t group_chunks(int32_t total) {
     const int32_t k = total / GROUPS_WANTED;
     return k < 1 ? 1 : k > 64 ? 64 : k;
 }
 __device__ inline int32_t chunk_parts(int32_t total) {
-    return total >= GROUPS_WANTED / 4 ? 1 : total >= GROUPS_WANTED / 16 ? 2 : total >= GROUPS_WANTED / 32 ? 4 : 8;
+    return total >= GROUPS_WANTED / 4 ? 1 : total >= GROUPS_WANTED / 32 ? 2 : 8;
 }
 struct GroupLds {
     int32_t incl[64];  // slots of the group's chunks up to this one
@@ -1562,7 +1564,7 @@ void launch_tests(Workspace &ws, const CandBuf &B, const R &runner, int64_t chun
                                  : std::max<int64_t>(1, std::min(heavy_slots(0), (left - 256) / (int64_t)sizeof(Heavy)));
     ws.pieces.ensure(sizeof(Heavy) * (size_t)cap);
     unsigned long long *np = ws.scal.as<unsigned long long>() + SCAL_HEAVY;
-    // up to eight wavefronts per chunk
+    // up to eight wavefronts per chunk (chunk_parts)
     const unsigned lb = (unsigned)std::max<int64_t>(1, std::min<int64_t>((8 * chunks + WPB - 1) / WPB, LIGHT_BLOCKS));
     k_tests_light<<<lb, BLK, 0, s>>>(B, runner, ws.pieces.as<Heavy>(), np, cap, ws.scal.as<unsigned long long>());
     FOLTY_LAUNCHED();
