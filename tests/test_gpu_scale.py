@@ -472,3 +472,53 @@ print("ok")
                          env=dict(os.environ, FOLTY_TUNE_CACHE=str(path)))
     say("tuning file:", out.stdout.strip(), out.stderr[-1500:])
     assert out.returncode == 0 and out.stdout.strip() == "ok"
+
+
+@pytest.mark.parametrize("close, passes", [(1, 2), (2, 1)])
+def test_switch_to_one_pass_at_one_triangle_in_twelve(close, passes):
+    """24 separate triangles, `close` of them within the window: one in 12 kept switches
+    later queries from half of that window on, one in 24 does not."""
+    k = 24
+    a = np.arange(k, dtype=np.int32) * 3
+    gap = np.where(np.arange(k) < close, 10, 5000)
+    src = np.concatenate([a, a, a + 1])
+    dst = np.concatenate([a + 1, a + 2, a + 2])
+    t = np.concatenate([np.zeros(k, np.int64), gap // 2, gap])
+    o = Oracle(3 * k, src, dst, t)
+    G = folty.Graph(3 * k, src, dst, t).build()
+    got = []
+    for delta in (100, 100, 50, 49):
+        r = G.query(delta, (1, 2), 0)
+        assert_same(r, o.query(delta, 1, 2, 0))
+        got.append(r.stats["filter_passes"])
+    assert got == [2, passes, passes, 2]
+
+
+def test_row_table_with_ids_equal_in_their_low_bits():
+    """The row table keeps the low 22 bits of ids: with more vertices than that, entries
+    that agree in them are told apart by the row.  In the random orientation an
+    id's rank does not depend on the edges: a complete graph on the ranks below 64
+    and the ones 2^22 above them has such pairs in every row and among its probes."""
+    n = (1 << 22) + 64
+    e = np.zeros(1, np.int32)
+    rank = folty.Graph(n, e, e + 1, e.astype(np.int64)).build(rank_mode=folty.RANK_RANDOM, rank_seed=9).ranks()
+    ids = np.nonzero((rank < 64) | (rank >= 1 << 22))[0].astype(np.int32)
+    assert ids.size == 128
+    rng = np.random.default_rng(17)
+    i, j = np.triu_indices(128, 1)
+    keep = rng.random(i.size) < 0.7
+    i, j = np.repeat(i[keep], 2), np.repeat(j[keep], 2)
+    flip = rng.random(i.size) < 0.5
+    src, dst = np.where(flip, ids[j], ids[i]), np.where(flip, ids[i], ids[j])
+    t = rng.integers(0, 10_000, src.size)
+    o = Oracle(n, src, dst, t)
+    G = folty.Graph(n, src, dst, t).build(rank_mode=folty.RANK_RANDOM, rank_seed=9)
+    assert np.array_equal(G.ranks(), rank)
+    for delta, v, one in ((300, 0, False), (10_000, 5, False), (10_000, 0, True)):
+        say("equal low bits", delta, v, one)
+        want = o.query(delta, 1, 10, v)
+        assert (want["counts"] > 0).any()
+        assert_same(G.query(delta, (1, 10), v, one_pass=one), want)
+    A = np.zeros((128, 128), np.int64)
+    A[i, j] = A[j, i] = 1
+    assert G.stats()["triangles"] == int((A @ A * A).sum()) // 6
