@@ -504,6 +504,7 @@ struct Plan {
     DevBuf sv, svn, tag, heavy, scal;
     bool dirty = true; // some histogram may hold counts (fresh, tuned, or a run did not finish)
     DevBuf nrec, keys, vals, keys2, vals2;
+    PinnedBuf host; // read-backs
     // launch shape and capture
     int ipt = 4, tblocks = 8192; // tests per piece, blocks of the temporal kernel
     bool tuned = false;
@@ -606,11 +607,10 @@ static void tune(Plan &P) {
     const int nj = (int)P.jobs.size();
     hipStream_t s = P.stream;
     int64_t tests = 0;
-    PinnedBuf hb;
-    hb.ensure(SCAL_BYTES);
-    FOLTY_HIP(hipMemcpyAsync(hb.p, P.scal.p, SCAL_BYTES, hipMemcpyDeviceToHost, s));
+    P.host.ensure(SCAL_BYTES);
+    FOLTY_HIP(hipMemcpyAsync(P.host.p, P.scal.p, SCAL_BYTES, hipMemcpyDeviceToHost, s));
     FOLTY_HIP(hipStreamSynchronize(s));
-    for (int r = 0; r < MAX_REGIONS; r++) tests += hb.as<int64_t>()[SCAL_REGIONS + r * REGION_WORDS + REGION_TESTS];
+    for (int r = 0; r < MAX_REGIONS; r++) tests += P.host.as<int64_t>()[SCAL_REGIONS + r * REGION_WORDS + REGION_TESTS];
     P.last_tests = tests;
     const std::pair<int, int> bucket{log2_ceil(tests), log2_ceil(P.total_w)};
     {
@@ -968,9 +968,10 @@ void plan_run(Plan *P, Result **outs) {
     // read back how many records, then sort the (query, u, v) records; records
     // of one pair from several wavefronts are merged below, and a query's
     // certificates are the sum of its records
-    int32_t npairs = 0;
-    FOLTY_HIP(hipMemcpyAsync(&npairs, P->nrec.p, 4, hipMemcpyDeviceToHost, s));
+    P->host.ensure(4);
+    FOLTY_HIP(hipMemcpyAsync(P->host.p, P->nrec.p, 4, hipMemcpyDeviceToHost, s));
     FOLTY_HIP(hipStreamSynchronize(s));
+    const int32_t npairs = *P->host.as<int32_t>();
     P->dirty = false;
     if (npairs < 0 || npairs > P->rec_cap)
         fail(FOLTY_EDEVICE, "certificate records exceed their bound (%d > %lld)", npairs, (long long)P->rec_cap);

@@ -1015,10 +1015,11 @@ static void count_triangles(Index &ix, DevBuf &base, hipStream_t s) {
     size_t need = exclusive_scan_i32_to_i64(nullptr, 0, tri_it.as<int32_t>(), base.as<int64_t>(), (int64_t)ni + 1, s);
     cub.ensure(need);
     exclusive_scan_i32_to_i64(cub.p, need, tri_it.as<int32_t>(), base.as<int64_t>(), (int64_t)ni + 1, s);
-    int64_t T = 0;
-    FOLTY_HIP(hipMemcpyAsync(&T, base.as<int64_t>() + ni, 8, hipMemcpyDeviceToHost, s));
+    PinnedBuf hb;
+    hb.ensure(8);
+    FOLTY_HIP(hipMemcpyAsync(hb.p, base.as<int64_t>() + ni, 8, hipMemcpyDeviceToHost, s));
     FOLTY_HIP(hipStreamSynchronize(s));
-    ix.T = T;
+    ix.T = *hb.as<int64_t>();
 }
 
 void ensure_triangles(Graph *g) {
