@@ -1102,33 +1102,41 @@ static const uint32_t *query_counts(Graph *g, const folty_query &q, Workspace &w
     if (ix.NI > 0) {
         const bool ss = (q.flags & FOLTY_QUERY_SMALLER_SIDE) != 0;
         int32_t *diff = nullptr;
-        if (ss) {
-            // runs with a shorter L2 mark edge ranges in diff; its prefix sum is added at the end
+        // runs with a shorter L2 mark edge ranges in diff; its prefix sum is added at the end
+        auto clear_marks = [&] {
+            if (!ss) return;
             ws.diff.ensure(4 * (2 * (size_t)ix.m + 1));
             diff = ws.diff.as<int32_t>();
             k_fill<int32_t><<<grid_for(ix.m + 1, BLK, PERSIST_BLOCKS), BLK, 0, s>>>(diff, 0, ix.m + 1);
             FOLTY_LAUNCHED();
-        }
-        auto tests = [&](const CandBuf &B) {
-            if (ss) launch_temporal<true>(ix, q.variant, q.delta, ws, B, DirectOp{q.delta, count, diff}, s);
-            else launch_temporal<false>(ix, q.variant, q.delta, ws, B, DirectOp{q.delta, count, nullptr}, s);
         };
-        FOLTY_HIP(hipEventRecord(ws.ev[4], s));
-        if (arena_left() >= 0) {
-            filter_in_arena(ix, q, ws, s, *one_pass, tests);
-            FOLTY_HIP(hipEventRecord(ws.ev[5], s));
-        } else {
-            const CandBuf B = filter_triangles(ix, q.variant, q.delta, ws, s, *one_pass);
-            FOLTY_HIP(hipEventRecord(ws.ev[5], s));
-            if (ws.kept_chunks > 0) tests(B);
-        }
-        if (ss) {
+        auto add_marks = [&] {
+            if (!ss) return;
             int32_t *ps = diff + ix.m + 1;
             size_t need = inclusive_scan_i32(nullptr, 0, diff, ps, ix.m, s);
             ws.cub.ensure(need);
             inclusive_scan_i32(ws.cub.p, need, diff, ps, ix.m, s);
             k_add_counts<<<grid_for(ix.m, BLK, PERSIST_BLOCKS), BLK, 0, s>>>(ps, ix.m, count);
             FOLTY_LAUNCHED();
+        };
+        auto tests = [&](const CandBuf &B) {
+            if (ss) launch_temporal<true>(ix, q.variant, q.delta, ws, B, DirectOp{q.delta, count, diff}, s);
+            else launch_temporal<false>(ix, q.variant, q.delta, ws, B, DirectOp{q.delta, count, nullptr}, s);
+        };
+        FOLTY_HIP(hipEventRecord(ws.ev[4], s));
+        if (arena_left() >= 0) {
+            clear_marks();
+            filter_in_arena(ix, q, ws, s, *one_pass, tests);
+            FOLTY_HIP(hipEventRecord(ws.ev[5], s));
+            add_marks();
+        } else {
+            const CandBuf B = filter_triangles(ix, q.variant, q.delta, ws, s, *one_pass);
+            FOLTY_HIP(hipEventRecord(ws.ev[5], s));
+            if (ws.kept_chunks > 0) {
+                clear_marks();
+                tests(B);
+                add_marks();
+            }
         }
     } else {
         FOLTY_HIP(hipEventRecord(ws.ev[4], s));
