@@ -233,8 +233,9 @@ int folty_build_index(folty_graph *g, const folty_build_opts *opts);
  * The filter of a query enumerates the graph's triangles once and appends those
  * that can have a run to chunks in the workspace (12 bytes each).  When the chunks
  * do not suffice (they start at an eighth of what every triangle would take, at
- * least 50 MB, or at none when that is more than a quarter of the free device
- * memory) they grow to what the pass needed and it is repeated.  After a
+ * least 50 MB, or at all of it beside a cached list; at none when that is more than
+ * a quarter of the free device memory) they grow to what the pass needed and it is
+ * repeated.  After a
  * query that kept at least one triangle in 12, later queries on the graph whose
  * delta is at least half of that query's test whole triangles only
  * (FOLTY_QUERY_ONE_PASS asks for that on any query).  The choice depends only on

@@ -522,3 +522,20 @@ def test_row_table_with_ids_equal_in_their_low_bits():
     A = np.zeros((128, 128), np.int64)
     A[i, j] = A[j, i] = 1
     assert G.stats()["triangles"] == int((A @ A * A).sum()) // 6
+
+
+@pytest.mark.parametrize("delta", [folty.DELTA_INF, 100])
+def test_cached_list_takes_its_chunks_at_once(delta):
+    """A cached list of 10.6 million triangles (165,000 chunks, past the 65,536 that are
+    always allocated): everything kept by the first query, and next to nothing."""
+    g = cliques(1, 400, 10**6, 62)
+    G = folty.Graph(g.n, g.src, g.dst, g.t).build(cache_triangles=True)
+    H = folty.Graph(g.n, g.src, g.dst, g.t).build()
+    for v in (0, 5):
+        say("cached list", delta, v)
+        got, want = G.query(delta, (1, 400), v), H.query(delta, (1, 400), v)
+        assert np.array_equal(got.counts(), want.counts()) and got.pairs() == want.pairs()
+        assert got.stats["tests"] == want.stats["tests"]
+        a, b = G.triad_query(delta, v, triples=False), H.triad_query(delta, v, triples=False)
+        assert a.triads()["n_instances"] == b.triads()["n_instances"]
+        assert a.triads()["n_solutions"] == b.triads()["n_solutions"]
