@@ -145,8 +145,9 @@ typedef struct {
  * window): then queries of at least half of that window look every probe up
  * and test whole triangles only, by themselves.  Results are identical either
  * way.  The graph's triangles are counted first if they have not been.  Single and
- * vertex queries (plans always use two passes; exists-exists-exists queries
- * follow the graph's switch). */
+ * vertex queries (plans use two passes unless the largest window on each of their
+ * graphs spans its timestamps; exists-exists-exists queries follow the graph's
+ * switch). */
 #define FOLTY_QUERY_ONE_PASS 4u
 
 /* Sizes and timings of a graph's index (folty_graph_stats) or of one query

@@ -89,12 +89,16 @@ struct GroupDev {
 };
 
 // Wavefront per unit: an enumeration item of its group, or 64 cached triangles.
+// FILTER_WIDE when every group's largest window spans its timestamps: no pair of
+// non-empty lists is further apart, so testing known edges first drops nothing (a
+// 10M-edge graph of communities with 49M triangles, no window: 1.43 -> 0.78 ms).
+template <FilterMode MODE>
 __global__ __launch_bounds__(BLK) __attribute__((amdgpu_waves_per_eu(4))) void k_multi_filter(
     const GroupDev *__restrict__ groups, int32_t ngr, const int64_t *__restrict__ unit_base, int64_t units,
     CandBuf out) {
     __shared__ EnumLds lds[WPB];
     const int w = wave_id();
-    FilterSink<-1, FILTER_NARROW> sink{};
+    FilterSink<-1, MODE> sink{};
     sink.out = out;
     int32_t last = -1;
     EnumGraph E{};
@@ -498,6 +502,7 @@ struct Plan {
     int nbits = 0;
     CandBuf cand{};
     int64_t chunks = 0, heavy_cap = 1;
+    bool wide = false; // the filter tests whole triangles only (k_multi_filter)
     // device memory
     DevBuf d_jobs, d_job_base, d_queries, d_groups, d_gjobs, d_unit_base;
     std::vector<DevBuf> hist, tmask, lv;
@@ -587,8 +592,8 @@ static void enqueue_compute(Plan &P, hipStream_t s) {
     FOLTY_LAUNCHED();
     if (P.units > 0) {
         const unsigned g = (unsigned)std::max<int64_t>(1, std::min<int64_t>((P.units + WPB - 1) / WPB, ENUM_BLOCKS));
-        k_multi_filter<<<g, BLK, 0, s>>>(P.d_groups.as<GroupDev>(), P.ngroups, P.d_unit_base.as<int64_t>(), P.units,
-                                         P.cand);
+        (P.wide ? k_multi_filter<FILTER_WIDE> : k_multi_filter<FILTER_NARROW>)<<<g, BLK, 0, s>>>(
+            P.d_groups.as<GroupDev>(), P.ngroups, P.d_unit_base.as<int64_t>(), P.units, P.cand);
         FOLTY_LAUNCHED();
     }
     enqueue_tests(P, P.ipt, P.tblocks, s);
@@ -844,6 +849,7 @@ Plan *plan_create(Graph *const *gs, int ng, const folty_query *qs, const int32_t
         G.T = T;
         G.rng = ix.erng.as<uint2>();
         G.dq = rng_slack(dmax, ix.rshift);
+        P->wide = (gd.empty() || P->wide) && G.dq == rng_slack(INT64_MAX, ix.rshift);
         gd.push_back(G);
         P->unit_base.push_back(P->unit_base.back() + (G.tri ? (T + 63) / 64 : ix.NI));
         P->chunks += plan_chunks(ix, T);
@@ -1025,7 +1031,7 @@ void plan_run(Plan *P, Result **outs) {
         Result *r = res[q].get();
         const Graph *g = P->graphs[P->qgraph[q]];
         fill_stats_from_index(g->ix, &r->stats);
-        r->stats.filter_passes = g->ix.NI > 0 ? 2 : 0; // known edges, then triangles (FILTER_NARROW)
+        r->stats.filter_passes = g->ix.NI == 0 ? 0 : P->wide ? 1 : 2;
         r->stats.n_pairs = (int64_t)r->u.size();
         r->stats.n_certificates = r->n_certificates;
         r->stats.query_ms = P->last_ms / std::max(1, nq);

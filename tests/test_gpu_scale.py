@@ -391,7 +391,8 @@ def test_triangles_known_are_not_counted_again():
 
 def test_plan_results_state_the_filter_passes():
     """Known edges first, then triangles, as in a single query of a fresh graph; none
-    without closing probes (a path)."""
+    without closing probes (a path).  Triangles alone when each graph's largest window
+    spans its timestamps, with the results of single queries."""
     g = synth.tiny(seed=13)
     G = folty.Graph(g.n, g.src, g.dst, g.t).build()
     ids = np.arange(9, dtype=np.int32)
@@ -402,6 +403,19 @@ def test_plan_results_state_the_filter_passes():
     plan.close()
     assert G.query(3600, (1, 4), 0).stats["filter_passes"] == 2
     assert P.query(5, (1, 4), 0).stats["filter_passes"] == 0
+    g2 = synth.bruteforce_size(seed=16)
+    G2 = folty.Graph(g2.n, g2.src, g2.dst, g2.t).build(cache_triangles=True)
+    for last, passes in ((folty.DELTA_INF, 1), (3600, 2)):
+        qs = [(i, dict(delta=d, theta=(1, 4), variant=v)) for v in range(8)
+              for i, d in ((0, folty.DELTA_INF), (0, 3600), (1, 600), (1, last))]
+        plan = folty.Plan([G, G2], qs)
+        for _ in range(2):
+            for (i, q), r in zip(qs, plan.run()):
+                say("plan passes", i, q)
+                w = (G, G2)[i].query(**q)
+                assert r.stats["filter_passes"] == passes
+                assert np.array_equal(r.counts(), w.counts()) and r.pairs() == w.pairs()
+        plan.close()
 
 
 def test_a_failed_call_waits_for_its_stream():
