@@ -525,10 +525,11 @@ void folty_graph_free(folty_graph *g);
 
 /* The library keeps freed device blocks for reuse (allocation and release are
  * slow and a release waits for the whole device), and the pinned host blocks of
- * freed results' large arrays (up to 4 GiB).  This hands every cached device
- * block of the current device, and every cached pinned block, back to the
- * driver; *bytes (if not NULL) receives the amount.  Call it when other code
- * needs the memory. */
+ * freed results' large arrays (up to 4 GiB), small pinned blocks for read-backs (at
+ * most 64 of 32 KiB) and the streams of freed graphs and plans (at most 16 per
+ * device).  This hands every cached device block of the current device, every cached
+ * pinned block and every idle stream back to the driver; *bytes (if not NULL)
+ * receives the amount.  Call it when other code needs the memory. */
 int folty_release_cached_memory(int64_t *bytes);
 
 #ifdef __cplusplus

@@ -248,7 +248,7 @@ constexpr int MAX_REGIONS = 32;
 // thousands of wavefronts or blocks add up is kept per region, on the region's
 // cache line, and summed on the host.
 enum : int {
-    SCAL_THRESHOLD = 0, // [4] the threshold step's
+    SCAL_PAIRS = 2,     // the threshold step's pairs (32 bits)
     SCAL_TRIAD = 4,     // [3] the exists-exists-exists totals: triangles, overflow, solutions
     SCAL_HEAVY = 11,    // heavy triangles and pieces
     SCAL_DROPPED = 12,  // chunks dropped (32 bits)
@@ -361,7 +361,7 @@ struct Workspace {
     DevBuf cub;     // library scan/sort temporaries
     DevBuf vtmp;    // vertex queries: per-vertex counts, flags, offsets, output
     DevBuf diff;    // int32[2m+1] interval marks of the smaller-side evaluation and their prefix sum
-    DevBuf tflag;   // exists-exists-exists: uint32[(survivor slots + 3) / 4] solution bits
+    DevBuf tflag;   // exists-exists-exists: solution bits, a byte per slot of the chunks
     DevBuf tinst;   // exists-exists-exists: uint64[m_input] temporal triangles per first edge, input order
     PinnedBuf host;
     hipEvent_t ev[8] = {};
@@ -491,14 +491,12 @@ size_t sort_pairs_u64_u32(void *tmp, size_t tmp_bytes, const uint64_t *kin, uint
 size_t sort_pairs_u32_i32(void *tmp, size_t tmp_bytes, const uint32_t *kin, uint32_t *kout,
                           const int32_t *vin, int32_t *vout, int64_t n, int end_bit,
                           hipStream_t stream);
-size_t exclusive_scan_i64(void *tmp, size_t tmp_bytes, const int64_t *in, int64_t *out, int64_t n,
-                          hipStream_t stream);
 size_t exclusive_scan_i32_to_i64(void *tmp, size_t tmp_bytes, const int32_t *in, int64_t *out,
                                  int64_t n, hipStream_t stream);
 size_t inclusive_scan_i32(void *tmp, size_t tmp_bytes, const int32_t *in, int32_t *out, int64_t n,
                           hipStream_t stream);
-// out[k] = 1 + the index of the static pair of sorted key k: the `bits` bits from
-// bit `shift` on
+// out[k] = the index of the static pair of sorted key k: the `bits` bits from bit
+// `shift` on
 size_t inclusive_scan_pair_starts(void *tmp, size_t tb, const uint64_t *key, int shift, int bits, int32_t *out,
                                   int64_t n, hipStream_t s);
 size_t exclusive_scan_i32(void *tmp, size_t tmp_bytes, const int32_t *in, int32_t *out, int64_t n,

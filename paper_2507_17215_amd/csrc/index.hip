@@ -23,25 +23,6 @@ constexpr int BLK = 256;
 
 __device__ inline int lane_id() { return __lane_id(); }
 
-// make this wavefront's LDS writes visible to all of its lanes
-__device__ inline void wave_sync() {
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-    __builtin_amdgcn_wave_barrier();
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-}
-
-// wave-aggregated append: one atomic per wave, slots in lane order
-__device__ inline int32_t wave_append(int32_t *counter, bool pred) {
-    unsigned long long mask = __ballot(pred);
-    if (!mask) return -1;
-    int lane = lane_id();
-    int leader = __ffsll((long long)mask) - 1;
-    int32_t base = 0;
-    if (lane == leader) base = atomicAdd(counter, (int32_t)__popcll(mask));
-    base = __shfl(base, leader);
-    return pred ? base + (int32_t)__popcll(mask & ((1ull << lane) - 1ull)) : -1;
-}
-
 struct ValOut {
     unsigned long long first_bad;
     unsigned long long loops;

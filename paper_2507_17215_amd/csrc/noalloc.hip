@@ -1,8 +1,8 @@
 // The single query for callers that cannot allocate device memory (code under
 // HIP graph capture, tight serving loops, harnesses that forbid allocation).
 //
-// Every scratch buffer of the query (per-edge counts, survivors and their
-// offsets, per-pair certificate counts, pair keys, sort and scan scratch) is
+// Every scratch buffer of the query (per-edge counts, the triangles its filter
+// keeps, per-pair certificate counts, pair keys, sort and scan scratch) is
 // carved from `scratch`, a fixed device array of FOLTY_NOALLOC_SCRATCH_BYTES
 // that each device the library runs on holds until the process ends.  Its
 // device address comes from hipGetSymbolAddress, once per device, with that

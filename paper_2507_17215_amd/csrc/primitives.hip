@@ -113,10 +113,6 @@ size_t sort_pairs_u32_i32(void *tmp, size_t tb, const uint32_t *kin, uint32_t *k
     return sort_pairs(tmp, tb, kin, kout, vin, vout, n, end_bit, s);
 }
 
-size_t exclusive_scan_i64(void *tmp, size_t tb, const int64_t *in, int64_t *out, int64_t n, hipStream_t s) {
-    return scan_exclusive(tmp, tb, in, out, n, s);
-}
-
 size_t exclusive_scan_i32_to_i64(void *tmp, size_t tb, const int32_t *in, int64_t *out, int64_t n,
                                  hipStream_t s) {
     return scan_exclusive(tmp, tb, in, out, n, s);

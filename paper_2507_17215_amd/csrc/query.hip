@@ -666,7 +666,7 @@ bool use_one_pass(Graph *g, const folty_query &q) {
 
 namespace {
 
-// per-edge counts of the survivors' runs (a.6)
+// per-edge counts of the kept triangles' runs (a.6)
 template <bool SS>
 void launch_temporal(const Index &ix, int variant, int64_t dmax, Workspace &ws, const CandBuf &B, const DirectOp &op,
                      hipStream_t s) {
@@ -766,7 +766,7 @@ void threshold_pairs(const Graph *g, const folty_query &q, const uint32_t *count
                            hipStream_t s, bool any) {
     const Index &ix = g->ix;
     const int32_t S = ix.S, m = ix.m;
-    int32_t *np = ws.scal.as<int32_t>() + 4;
+    int32_t *np = reinterpret_cast<int32_t *>(ws.scal.as<unsigned long long>() + SCAL_PAIRS);
     if (m > 0) {
         ThreshArgs A;
         A.count = count;
@@ -803,7 +803,7 @@ void threshold_pairs(const Graph *g, const folty_query &q, const uint32_t *count
 // |Sol| and the number of pairs, from the scalars on the host
 PairCounts pair_counts(const Workspace &ws) {
     int32_t npairs;
-    memcpy(&npairs, ws.host.as<char>() + 16, 4);
+    memcpy(&npairs, ws.host.as<unsigned long long>() + SCAL_PAIRS, 4);
     return PairCounts{region_sum(ws, REGION_CERTS), npairs};
 }
 
@@ -910,7 +910,7 @@ void index_triangles(Index &ix, bool cache, DevBuf &cub, hipStream_t s) {
                                                      ix.erng.as<uint2>());
         FOLTY_LAUNCHED();
     }
-    // probe segments grouped by (owner, mode), their probe prefix, and items
+    // probe segments grouped by owner, their probe prefix, and items
     ix.seg.ensure(sizeof(int4) * ((size_t)S + 1));
     ix.srng.ensure(sizeof(uint2) * ((size_t)S + 1));
     ix.owner.ensure(4 * ((size_t)S + 1));

@@ -1045,9 +1045,9 @@ __global__ __launch_bounds__(BLK) void k_filter_cached(const int32_t *__restrict
 // triangle by a search over 64 prefix sums and its run by the triangle's bits,
 // and all lanes run one copy of the test whatever their run or predicate.
 // (A copy per run, six in turn with part of the lanes each, took 2.2 ms where
-// this takes 1.5 ms: 36.6M tests of the 70M-edge graph at one year.)  The
+// this takes 1.6 ms: 36.6M tests of the 70M-edge graph at one year.)  The
 // per-edge counts take two tests per lane at a time (their first reads go together:
-// 545,000 tests in 12,000 chunks 0.11 -> 0.07 ms), so neighbouring lanes take
+// 686,000 tests of 10M uniform edges 0.127 -> 0.079 ms), so neighbouring lanes take
 // neighbouring tests of one run and their loads coalesce; the exists-exists-exists
 // counting, whose window bookkeeping the tests of a run share, takes a few of them
 // per lane.
@@ -1062,8 +1062,8 @@ __global__ __launch_bounds__(BLK) void k_filter_cached(const int32_t *__restrict
 // enough for four to eight wavefronts per SIMD.
 // 70M-edge graph, one year (14.1M triangles, 36.6M tests) and a graph of
 // 5,000-edge lists closed by short ones (2.9M triangles, 106M tests), both kernels:
-// light limit 32 / 64 / 128 with pieces of 4: 1.67, 1.62, 1.58 and 1.13, 1.14, 1.10 ms;
-// limit 64 with pieces of 2 / 8: 1.60, 1.71 and 1.22, 1.68 ms.
+// light limit 32 / 64 / 128 with pieces of 4: 1.60, 1.58, 1.56 and 1.12, 1.10, 1.11 ms;
+// limit 64 with pieces of 2 / 8: 1.53, 1.67 and 1.19, 1.68 ms.
 constexpr int64_t LIGHT_TESTS = 64;
 constexpr int64_t PIECE_TESTS = 4;
 
@@ -1371,8 +1371,9 @@ __device__ inline void spread_units(Lds &F, int32_t incl, bool own, const Flat &
 // A wavefront's group of chunks as a dense sequence of slots: narrow windows
 // leave most chunks with an entry or two, and their triangles are taken 64 at a
 // time across chunks.  Groups of up to 64 chunks, fewer when that would leave
-// less than GROUPS_WANTED groups (8,192 and 4,096 of them were slower: 1.70 ms
-// against 1.62 at one year, 0.15 against 0.11 for 10M uniform edges); with few
+// less than GROUPS_WANTED groups (8,192 and 4,096 of them: 1.69 and 1.94 ms against
+// 1.58 on the 70M-edge graph at one year, 0.079 and 0.097 against 0.079 for 10M uniform
+// edges, but 0.061 and 0.056 against 0.084 for 10M renewal edges at 4 weeks); with few
 // chunks each is shared by two or eight wavefronts, since a wavefront's tests are a
 // chain of dependent reads.  Temporal step with one / two / four / eight wavefronts
 // per chunk, us: 165 triangles in 164 chunks 14.8 / 13.6 / 13.3 / 13.4; 1,002 in 828
@@ -1528,8 +1529,8 @@ __global__ __launch_bounds__(BLK) void k_tests_pieces(const Heavy *__restrict__ 
     runner.finish();
 }
 
-constexpr int64_t MAX_HEAVY = 1 << 22; // 64 MB of heavy-survivor entries at most
-constexpr int64_t MIN_HEAVY = 1 << 16; // room for this many whatever the survivors
+constexpr int64_t MAX_HEAVY = 1 << 22; // 64 MB of entries at most
+constexpr int64_t MIN_HEAVY = 1 << 16; // room for this many however few triangles are kept
 constexpr int64_t LIGHT_BLOCKS = 4096; // a group per wavefront or two; 16,384 blocks mostly started for nothing
 constexpr int64_t PIECE_BLOCKS = 8192;
 // A plan's block count may come from a file: more than this many could take the count

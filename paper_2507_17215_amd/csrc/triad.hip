@@ -4,8 +4,8 @@
 //
 // It shares the index and the time-range filter of the exists-exists-forall
 // query: the filter keeps the static triangles with a run (triangle, directed
-// list E_{a,b}) whose three lists can hold t <= t2 <= t3 <= t + delta, and the
-// runs' temporal edges are cut into equal chunks over the grid.  Per chunk:
+// list E_{a,b}) whose three lists can hold t <= t2 <= t3 <= t + delta, and a lane
+// takes a run or a piece of one:
 //   - solutions: the first-entry search of Theorems 3.1 and 3.2 per edge of
 //     E_{a,b}, stopping at the first edge with a triangle, sets the run's bit;
 //     a run is the ordered triple (a, b, w), so the set bits are the solutions;
@@ -14,10 +14,10 @@
 //     and f(j) the first entry of L3 at or after L2[j], the edge closes
 //     sum_{j in [lo, hi)} (h3 - f(j)) = (hi - lo) h3 - (F(hi) - F(lo)) pairs,
 //     F the running sum of f.  lo, hi, h3 and the two search cursors for f only
-//     move forward over a chunk's time-sorted edges, so a chunk costs its edges
-//     plus the entries its windows pass, each with a search from the cursor.
-// The set bits are then counted item by item over the survivor slots only, and
-// listed as (a, b, w) in original ids, sorted by two stable radix sorts (w, then
+//     move forward over a piece's time-sorted edges, so a piece costs its edges
+//     plus the entries its windows pass, each with a search (range_sum).
+// The set bits are then counted chunk by chunk over the kept triangles, and listed
+// as (a, b, w) in original ids, sorted by two stable radix sorts (w, then
 // the pair key a n + b).
 #include <algorithm>
 #include <cstring>
