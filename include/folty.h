@@ -236,9 +236,8 @@ int folty_build_index(folty_graph *g, const folty_build_opts *opts);
  * do not suffice (they start at an eighth of what every triangle would take, at
  * least 50 MB, or at all of it beside a cached list; at none when that is more than
  * a quarter of the free device memory) they grow to what the pass needed and it is
- * repeated.  After a
- * query that kept at least one triangle in 12, later queries on the graph whose
- * delta is at least half of that query's test whole triangles only
+ * repeated.  After a query that kept at least one triangle in 12, later queries on
+ * the graph whose delta is at least half of that query's test whole triangles only
  * (FOLTY_QUERY_ONE_PASS asks for that on any query).  The choice depends only on
  * the graph and the queries run before.
  *
@@ -469,8 +468,9 @@ int folty_result_counts(folty_result *r, int64_t *n_certificates, const uint32_t
  * the process ends; a query needing more fails with FOLTY_ENOMEM and a message
  * giving the size.  That is enough for graphs of about a million temporal edges.
  * A graph is refused in the same way, for every window, when 4 m + 32 S + 36 R
- * bytes exceed the scratch: m edges, S static edges, R the vertices with an edge to
- * one of no larger out-degree plus those with an edge from one of smaller out-degree
+ * bytes exceed the scratch: m edges, S static edges, R = the vertices u of some
+ * oriented edge (u, v) with out-degree(v) <= out-degree(u), plus the vertices v of
+ * some oriented edge (u, v) with out-degree(u) < out-degree(v)
  * (folty_graph_vertex_array 3).  Triangles that do not fit beside the counts are
  * tested in parts.
  *   g, q            as for folty_run_fol_query; FOLTY_QUERY_NO_COUNTS is ignored

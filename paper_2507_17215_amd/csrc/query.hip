@@ -450,7 +450,10 @@ int64_t first_chunks(int64_t triangles, int64_t waves, bool cached, const Worksp
     const int64_t chunks = std::min(most, std::max({SAFE_CHUNKS, cached ? most : most / 8, have}));
     if (chunks > SAFE_CHUNKS && chunks > have) {
         size_t fr = 0, tot = 0;
-        FOLTY_HIP(hipMemGetInfo(&fr, &tot));
+        if (hipMemGetInfo(&fr, &tot) != hipSuccess) {
+            (void)hipGetLastError();
+            fr = 0;
+        }
         if (chunks * CHUNK_BYTES > (int64_t)((fr + dev_cached()) / 4)) return have;
     }
     return chunks;
