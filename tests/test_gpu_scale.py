@@ -282,7 +282,7 @@ def squeezed(g, span, offset):
 def test_filter_keeps_the_same_wherever_times_start(span, delta):
     """stats.tests counts the tests of the triangles that the filter kept: the same graph
     keeps the same ones from 0, from Unix seconds and from the last 32-bit second, and
-    about as many (4 of 256 sampled timestamps may be strays) with stray edges at 0."""
+    about as many (2 of 64 sampled timestamps may be strays) with stray edges at 0."""
     base = synth.tiny(seed=11)
     kept = []
     for offset in (0, 1_300_000_000, (1 << 32) - 1 - span):
